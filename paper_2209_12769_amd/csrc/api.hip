@@ -334,6 +334,8 @@ dc_status do_simulate(dc_ctx* ctx, int32_t n_cand, const BatchView& in, const fl
   a.out_rowptr = in.out_rowptr;
   a.out_col = in.out_col;
   a.in_rowptr = in.in_rowptr;
+  a.in_col = in.in_col;
+  a.max_module_nodes = ctx->max_gn;
   a.op_time = op_time;
   a.ar_size = ar_size;
   a.ar_c = ar_c;
@@ -343,6 +345,7 @@ dc_status do_simulate(dc_ctx* ctx, int32_t n_cand, const BatchView& in, const fl
   a.scratch = ctx->sim_scratch;
   a.scratch_stride = ctx->sim_stride;
   a.n_slices = ctx->sim_slices;
+  a.n_cu = ctx->n_cu;
   a.status = ctx->status;
   if (ctx->prof.on) ctx->prof.begin(kFamSimulate, s);
   hipError_t e = launch_simulate(a, s);

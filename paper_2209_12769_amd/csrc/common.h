@@ -183,14 +183,17 @@ struct SimArgs {
   const int* out_rowptr;
   const int* out_col;
   const int* in_rowptr;
+  const int* in_col;
+  int max_module_nodes;     // no module of the batch is expected to have more nodes (those that do are still simulated)
   const float* op_time;     // [Ntot] execution time of computation nodes
   const float* ar_size;     // [Ntot] tensor size of all-reduce nodes, negative for computation nodes
   float ar_c, ar_d;         // T = ar_c * size + ar_d
   float* cost;              // [n_cand]
-  int lds_bytes;            // LDS per wave for modules walked on chip
-  char* scratch;            // slices of global memory for the others
+  int lds_bytes;            // LDS per wave of the general walk
+  char* scratch;            // slices of global memory for the modules that do not fit it
   size_t scratch_stride;
   int n_slices;
+  int n_cu;
   int* status;
 };
 size_t simulate_scratch_bytes(long long max_graph_nodes, long long max_graph_edges, int n_slices);
@@ -330,14 +333,33 @@ __device__ __forceinline__ void bf16_pair_add(float& lo, float& hi, unsigned x, 
   hi = __builtin_amdgcn_fdot2_f32_bf16(v, __builtin_bit_cast(bf16x2_t, one << 16), hi, false);
 }
 
+// Moves between lanes inside the vector ALU (DPP): the value of the lane `kCtrl` names, or `idle` where there is none
+// or the row of 16 lanes is not in kRows.  row_shr:n = 0x110 + n, row_bcast:15 = 0x142, row_bcast:31 = 0x143.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int dpp(int idle, int x) {
+  return __builtin_amdgcn_update_dpp(idle, x, kCtrl, kRows, 0xF, false);
+}
+// Inclusive scan over the wave: inside each row of 16 lanes, then the rows' ends to the rows behind them.  Six
+// vector instructions; through LDS (ds_bpermute) each of the six steps is a round trip of some 60 cycles.
 __device__ __forceinline__ int wave_incl_scan(int x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
+  x += dpp<0x111, 0xF>(0, x);
+  x += dpp<0x112, 0xF>(0, x);
+  x += dpp<0x114, 0xF>(0, x);
+  x += dpp<0x118, 0xF>(0, x);
+  x += dpp<0x142, 0xA>(0, x);
+  x += dpp<0x143, 0xC>(0, x);
   return x;
+}
+// Smallest value of the wave, in every lane.
+__device__ __forceinline__ int wave_min(int x) {
+  constexpr int kIdle = 0x7FFFFFFF;
+  x = min(x, dpp<0x111, 0xF>(kIdle, x));
+  x = min(x, dpp<0x112, 0xF>(kIdle, x));
+  x = min(x, dpp<0x114, 0xF>(kIdle, x));
+  x = min(x, dpp<0x118, 0xF>(kIdle, x));
+  x = min(x, dpp<0x142, 0xA>(kIdle, x));
+  x = min(x, dpp<0x143, 0xC>(kIdle, x));
+  return __builtin_amdgcn_readlane(x, 63);
 }
 
 // Exclusive scan of in[0..n) into out[0..n) (may alias) by the whole workgroup;

@@ -11,13 +11,18 @@
 // next op is taken, ties in ascending index; successors are released in ascending index;
 // a module whose graph has a cycle (an invalid fusion) costs +infinity.
 //
-// The walk over one module is a serial chain, so the batch supplies the parallelism: one
-// wave per candidate, with the whole module (successor lists, durations, dependency
-// counters, ready times, both queues) in LDS; the lanes release the successors of the
-// current node together (lists are duplicate free, so no two lanes touch one node) and
-// append the newly ready ones in lane order = ascending index.  Modules too large for LDS
-// keep the same arrays in a slice of global memory.  Times are fp64, added in the order
-// the rules fix, so the result does not depend on the implementation.
+// Times are fp64, added in the order the rules fix, so the result does not depend on the
+// implementation.
+//
+//   simulate_order_kernel    modules whose execution times are not negative and whose all-reduces
+//                            have no successors, i.e. every module that comes of profiled data: the
+//                            order of the nodes does not depend on the times there and is found by
+//                            all nodes at once; the times are added along it
+//   simulate_general_kernel  the others: one wave walks the module node by node, with its arrays in
+//                            LDS or in a slice of global memory; the lanes release the successors
+//                            of the current node together (lists are duplicate free, so no two
+//                            lanes touch one node) and append the newly ready ones in lane order =
+//                            ascending index
 #include <math.h>
 
 #include <mutex>
@@ -27,7 +32,7 @@
 namespace dc {
 namespace {
 
-// The arrays of a module in global memory ...
+// The arrays of a module of the general kernel in global memory ...
 __host__ __device__ inline size_t sim_bytes(long long G, long long E) {
   // ready[G] f64 | val[G] f32 | dep[G] i32 | queue[G] i32 | rp[G+1] i32 | ci[E] u16 (padded to 8 bytes)
   return (size_t)G * (8 + 4 + 4 + 4) + (size_t)(G + 1) * 4 + (((size_t)E * 2 + 7) & ~(size_t)7) + 8;
@@ -53,7 +58,419 @@ struct SimTypes<true> {           // LDS
   static constexpr int kAr = 1 << 15;
 };
 
+// Modules the first kernel leaves to the second carry this pattern in their cost: a NaN that no arithmetic gives.
+constexpr unsigned kLeft = 0x7FC5A11Du;
+
 extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
+
+// ---------------------------------------------------------------------------------------------------
+// The order of a module by iteration, its times along the order.
+//
+// With execution times that are not negative the device's clock never runs backwards, so an op never waits for its
+// predecessors (they ran before it) and starts when the device is free; an all-reduce without successors holds
+// nothing up.  The order of the ops is then a matter of the graph alone: an op enters the queue when its last
+// predecessor ends, so the ops stand in the order of (place of the last predecessor, index), where the place of an op
+// is its rank in that same order.  The kernel solves this by iteration: from any places it computes every op's key =
+// the largest place among its predecessors, sorts by (key, index) and takes the ranks as the new places, until
+// nothing changes.  A fixed point in which every key lies before its op's place is the order of the queue: by
+// induction over the places, the first k ops are the queue's, and the next one is the smallest (key, index) among the
+// ops whose predecessors are all among them.  For the same reason the places before the first one that changed or
+// holds a key not before it are right from then on and grow by one a round at the least; where no op outside them has
+// all its predecessors among them, the module has a cycle.
+//
+// One iteration is parallel over all nodes, where the walk that this replaces took the nodes one after another at
+// four dependent LDS round trips each (about 1000 cycles a node).  The number of iterations is the depth to which
+// neighbouring chains interleave, not the length of the module: from the index order as the first guess 4 to 7 on the
+// contracted modules of a 24-block transformer (1.4 k nodes, 1.3 k of them one after another), 13 on the unfused
+// module (6.6 k nodes), 20 on power-law graphs.  What takes kMostRounds is left to the general kernel.
+//
+// A thread owns NPT nodes and keeps their predecessors (three or four each; what longer lists hold beyond three lies
+// in LDS, or is read from memory again once that is full) and keys in registers; LDS holds the places, the counters of
+// the sort and the order: 8 bytes per node with the longer lists.  The sort is a
+// counting sort by key (16-bit counters, two to a word); equal keys are the few ops that one op releases, and an op
+// finds its rank among them by comparing with each.  Sources keep their places throughout.
+//
+// The times: the device's clock is a running sum over the ops, the channel's a chain of maximum and sum over the
+// all-reduces, which are sorted by (place of the last predecessor, index) in the same way and taken by one wave.
+//
+// What bounds it: LDS round trips between some six barriers a round (about 15 k cycles a round with 1024 threads and
+// 6.6 k nodes, 12 rounds, and 60 k for the times; 64 or 256 threads for small modules: 9 k a round).  Measured, walk
+// before -> now: 4096 contracted modules of 1.4 k nodes 2.48 -> 0.23 ms, 1000 nearly unfused ones of 6.5 k nodes
+// (walked in global memory before) 6.02 -> 0.59 ms, 16 modules of 0.7 k nodes 0.27 -> 0.03 ms.  Workgroups of 512
+// threads with sixteen nodes each, two per CU, take the same time as 1024 with eight.
+// ---------------------------------------------------------------------------------------------------
+constexpr int kMostRounds = 256;
+constexpr int kNone = 0x7FFFFFFF;
+
+__device__ __forceinline__ int lane_of(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
+__device__ __forceinline__ double lane_of(double x, int l) {
+  const long long b = __double_as_longlong(x);
+  const unsigned lo = (unsigned)lane_of((int)b, l), hi = (unsigned)lane_of((int)(b >> 32), l);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <int T, int NPT>
+struct OrderLds {
+  static constexpr int kCap = T * NPT;
+  static constexpr int kPlace = 0;                                   // u16 [kCap + 1]: place + 1; entry kCap is 0
+  static constexpr int kOrder = (2 * (kCap + 1) + 15) & ~15;         // u16 [kCap]
+  static constexpr int kCount = kOrder + ((2 * kCap + 15) & ~15);    // u16 [kCap + 2]: counters by key, then starts
+  static constexpr int kExtra = kCount + ((2 * (kCap + 2) + 15) & ~15);   // u16 [kCap]: predecessors of longer lists
+  static constexpr int kSums = kExtra + ((2 * kCap + 15) & ~15);     // f64 [max(T, 128)]: see the times
+  static constexpr int kValue = kCount;                              // f32 [kCap]: times along the order, at last
+  static_assert(kSums - kValue >= 4 * kCap, "the times take the place of the counters and the longer lists");
+  static constexpr int kBytes = kSums + 8 * (T > 128 ? T : 128);
+};
+
+// Exclusive scan of the counters of keys 1 .. n (16 bits each, at words [0, words)) in place, starting from `base`;
+// counter 0 becomes `base`.  Ends with a barrier.
+template <int T>
+__device__ __forceinline__ void scan_counts(unsigned* words_, int words, int base, int* wsum) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int K = (words + T - 1) / T;
+  const int lo = min(t * K, words), hi = min(lo + K, words);
+  int s = 0;
+  for (int i = lo; i < hi; ++i) s += (int)(words_[i] & 0xFFFFu) + (int)(words_[i] >> 16);
+  const int inc = wave_incl_scan(s);
+  int run = base + inc - s;
+  if constexpr (T > 64) {
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) {
+      const int x = wsum[w];
+      run += w < wave ? x : 0;
+    }
+  }
+  for (int i = lo; i < hi; ++i) {
+    const unsigned x = words_[i];
+    const int mid = run + (int)(x & 0xFFFFu);
+    words_[i] = (unsigned)run | (unsigned)mid << 16;
+    run = mid + (int)(x >> 16);
+  }
+  __syncthreads();
+}
+
+template <int T, int NPT>
+__global__ __launch_bounds__(T) void simulate_order_kernel(
+    const int* __restrict__ node_off, const int* __restrict__ out_rp, const int* __restrict__ in_rp,
+    const int* __restrict__ in_ci, const float* __restrict__ op_time, const float* __restrict__ ar_size, int C,
+    float ar_c, float ar_d, float* __restrict__ cost, int fewest, int last, const int* __restrict__ status) {
+  // the modules of `fewest` to T * NPT nodes; the last class to be launched leaves the larger ones to the general kernel
+  typedef OrderLds<T, NPT> Lds;
+  constexpr int kCap = Lds::kCap, kWaves = T / 64;
+  __shared__ int wsum[kWaves], sh_min[2][2], sh_src[NPT][kWaves], n_extra;
+  unsigned short* place = reinterpret_cast<unsigned short*>(dc_sim_smem + Lds::kPlace);
+  unsigned* count2 = reinterpret_cast<unsigned*>(dc_sim_smem + Lds::kCount);
+  unsigned short* count = reinterpret_cast<unsigned short*>(dc_sim_smem + Lds::kCount);
+  unsigned short* order = reinterpret_cast<unsigned short*>(dc_sim_smem + Lds::kOrder);
+  unsigned short* extra = reinterpret_cast<unsigned short*>(dc_sim_smem + Lds::kExtra);
+  float* value = reinterpret_cast<float*>(dc_sim_smem + Lds::kValue);
+  double* sums = reinterpret_cast<double*>(dc_sim_smem + Lds::kSums);
+  if (status[0] != 0) return;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  for (int c = blockIdx.x; c < C; c += gridDim.x) {
+    const int n0 = node_off[c], G = node_off[c + 1] - n0;
+    if (G < fewest) continue;
+    if (G > kCap) {
+      if (last && t == 0) cost[c] = __uint_as_float(kLeft);
+      continue;
+    }
+    if (t == 0) n_extra = 0;
+    __syncthreads();
+    // ---- the thread's nodes t, t + T, ...: predecessors, kind
+    unsigned p01[NPT], p23[NPT];
+    unsigned is_op = 0, is_ar = 0, is_src = 0, more = 0, far = 0;   // bit i: node t + i * T
+    bool plain = true;
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const int v = t + i * T;
+      p01[i] = p23[i] = (unsigned)kCap * 0x10001u;
+      if (v < G) {
+        const int a = in_rp[n0 + v], d = in_rp[n0 + v + 1] - a;
+        const bool ar = ar_size[n0 + v] >= 0.0f;
+        plain &= ar ? out_rp[n0 + v + 1] == out_rp[n0 + v] : op_time[n0 + v] >= 0.0f;      // a NaN is neither
+        const unsigned x0 = d > 0 ? in_ci[a] - n0 : kCap, x1 = d > 1 ? in_ci[a + 1] - n0 : kCap;
+        const unsigned x2 = d > 2 ? in_ci[a + 2] - n0 : kCap;
+        unsigned x3 = d > 3 ? in_ci[a + 3] - n0 : kCap;
+        if (d > 4) {                                           // the others follow each other in LDS, kCap ends them
+          const int at = atomicAdd(&n_extra, d - 2);
+          if (at + d - 2 <= kCap) {
+            extra[at] = (unsigned short)x3;
+            for (int k = 4; k < d; ++k) extra[at + k - 3] = (unsigned short)(in_ci[a + k] - n0);
+            extra[at + d - 3] = (unsigned short)kCap;
+            x3 = (unsigned)at;
+            more |= 1u << i;
+          } else {
+            far |= 1u << i;
+          }
+        }
+        p01[i] = x0 | x1 << 16;
+        p23[i] = x2 | x3 << 16;
+        is_ar |= (unsigned)ar << i;
+        is_op |= (unsigned)!ar << i;
+        is_src |= (unsigned)(!ar && d == 0) << i;
+        place[v] = (unsigned short)(v + 1);                  // the first guess: the index order
+      }
+    }
+    if (t == 0) place[kCap] = 0;
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const unsigned long long m = __ballot((is_src >> i) & 1u);
+      if (lane == 0) sh_src[i][wave] = __popcll(m);
+    }
+    if (t == 0) sh_min[0][0] = sh_min[0][1] = kNone;
+    if (__syncthreads_or(!plain)) {
+      if (t == 0) cost[c] = __uint_as_float(kLeft);
+      continue;
+    }
+    // sources stand first, in index order
+    int n_src = 0;
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const unsigned long long m = __ballot((is_src >> i) & 1u);
+      int before = n_src;
+      for (int w = 0; w < kWaves; ++w) {
+        const int k = sh_src[i][w];
+        if (w < wave) before += k;
+        n_src += k;
+      }
+      if ((is_src >> i) & 1u) place[t + i * T] = (unsigned short)(before + __popcll(m & ((1ull << lane) - 1ull)) + 1);
+    }
+    const int words = (G + 3) >> 1;                          // counters of keys 0 .. G and one more start
+
+    // key of node i: the largest place + 1 among its predecessors
+    auto key_of = [&](int i) {
+      // (kept from being taken out of the loop of rounds: unpacked, the predecessors would take four registers a node)
+      asm volatile("" : "+v"(p01[i]), "+v"(p23[i]));
+      int k = max(max((int)place[p01[i] & 0xFFFFu], (int)place[p01[i] >> 16]), (int)place[p23[i] & 0xFFFFu]);
+      if ((more >> i) & 1u) {
+        for (int at = p23[i] >> 16, u = extra[at]; u != kCap; u = extra[++at]) k = max(k, (int)place[u]);
+      } else {
+        k = max(k, (int)place[p23[i] >> 16]);
+      }
+      if ((far >> i) & 1u) {
+        int v = n0 + t + i * T;
+        asm volatile("" : "+v"(v));
+        for (int e = in_rp[v] + 4; e < in_rp[v + 1]; ++e) k = max(k, (int)place[in_ci[e] - n0]);
+      }
+      return k;
+    };
+    // Sorts the nodes of the mask by (key, index), ranks counted from `base`; order[off + base] and the places behind
+    // it serve as scratch.  ka[i]: key of the thread's node i, and above it its turn among those of the same key.
+    unsigned ka[NPT];
+    auto sort = [&](unsigned mask, int base, int off) {
+      for (int i = t; i < words; i += T) count2[i] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NPT; ++i)
+        if ((mask >> i) & 1u) {
+          const int key = key_of(i), sh = (key & 1) << 4;
+          ka[i] = (unsigned)key | ((atomicAdd(&count2[key >> 1], 1u << sh) >> sh) << 16);
+        }
+      __syncthreads();
+      scan_counts<T>(count2, words, base, wsum);
+#pragma unroll
+      for (int i = 0; i < NPT; ++i)
+        if ((mask >> i) & 1u) order[off + count[ka[i] & 0xFFFFu] + (ka[i] >> 16)] = (unsigned short)(t + i * T);
+      __syncthreads();
+    };
+    auto rank_of = [&](int i, int off) {
+      const int s = count[ka[i] & 0xFFFFu], e = count[(ka[i] & 0xFFFFu) + 1];
+      int r = s;
+      if (e - s > 1)
+        for (int k = s; k < e; ++k) r += (int)order[off + k] < t + i * T;
+      return r;
+    };
+
+    // ---- the order of the ops
+    const unsigned mask = is_op & ~is_src;
+    int round = 0, state = 0;                                // 1: the order is found, 2: a cycle
+    for (; round < kMostRounds && state == 0; ++round) {
+      sort(mask, n_src, 0);
+      int changed = kNone, ahead = kNone;
+#pragma unroll
+      for (int i = 0; i < NPT; ++i)
+        if ((mask >> i) & 1u) {
+          const int rank = rank_of(i, 0);
+          if ((int)place[t + i * T] != rank + 1) {
+            changed = min(changed, rank);
+            place[t + i * T] = (unsigned short)(rank + 1);
+          }
+          if ((int)(ka[i] & 0xFFFFu) > rank) ahead = min(ahead, rank);
+        }
+      int* mn = sh_min[round & 1];
+      changed = wave_min(changed);
+      ahead = wave_min(ahead);
+      if (lane == 0 && changed != kNone) atomicMin(&mn[0], changed);
+      if (lane == 0 && ahead != kNone) atomicMin(&mn[1], ahead);
+      if (t == 0) sh_min[(round & 1) ^ 1][0] = sh_min[(round & 1) ^ 1][1] = kNone;
+      __syncthreads();
+      const int right = min(mn[0], mn[1]);                   // so many places are the queue's
+      if (right == kNone) state = 1;
+      else if ((int)count[right + 1] == right) state = 2;    // no other op has all its predecessors among them
+      __syncthreads();
+    }
+    if (state != 1) {
+      if (t == 0) cost[c] = state == 2 ? INFINITY : __uint_as_float(kLeft);
+      __syncthreads();
+      continue;
+    }
+    // ---- the all-reduces by (place of the last predecessor, index), behind the ops
+    unsigned n_of = 0;
+    for (int i = 0; i < NPT; ++i) n_of += (is_op >> i) & 1u;
+    const int lane_sum = wave_incl_scan((int)n_of);
+    if (lane == 63) wsum[wave] = lane_sum;
+    __syncthreads();
+    int n_op = 0;
+    for (int w = 0; w < kWaves; ++w) n_op += wsum[w];
+    const int n_ar = G - n_op;
+    __syncthreads();
+    if (n_ar > 0) {
+      sort(is_ar, 0, n_op);
+#pragma unroll
+      for (int i = 0; i < NPT; ++i)
+        if ((is_ar >> i) & 1u) ka[i] = (unsigned)rank_of(i, n_op) << 16 | (ka[i] & 0xFFFFu);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NPT; ++i)
+        if ((is_ar >> i) & 1u) {
+          order[n_op + (ka[i] >> 16)] = (unsigned short)(t + i * T);
+          place[t + i * T] = (unsigned short)ka[i];
+        }
+    }
+    __syncthreads();
+    // execution times and tensor sizes in that order
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const int v = t + i * T;
+      if ((is_op >> i) & 1u) value[place[v] - 1] = op_time[n0 + v];
+      if ((is_ar >> i) & 1u) value[n_op + (ka[i] >> 16)] = ar_size[n0 + v];
+    }
+    if (t == 0) sh_min[0][0] = sh_min[0][1] = kNone;
+    __syncthreads();
+    // ---- the times.  fp64 sums of fp32 values are exact, and so the same in any order, as long as no sum reaches 2^53
+    // of the smallest value's last place: with the exponents' range known the clock at every op is a parallel scan,
+    // and the serial chain is left for values that differ too much (or are infinite).
+    double own = 0.0;                                        // the thread's NPT ops in the order
+    {
+      int lo = kNone, hi = kNone;                            // smallest exponent, 255 - largest
+#pragma unroll
+      for (int k = 0; k < NPT; ++k) {
+        const int q = t * NPT + k;
+        const float x = q < n_op ? value[q] : 0.f;
+        const int ex = max((int)(__float_as_uint(x) >> 23 & 0xFFu), 1);
+        if (x != 0.f) {
+          lo = min(lo, ex);
+          hi = min(hi, 255 - ex);
+        }
+        own += (double)x;
+      }
+      lo = wave_min(lo);
+      hi = wave_min(hi);
+      if (lane == 0 && lo != kNone) {
+        atomicMin(&sh_min[0][0], lo);
+        atomicMin(&sh_min[0][1], hi);
+      }
+    }
+    double before = own;                                     // sum of the lanes up to this one
+    for (int o = 1; o < 64; o <<= 1) {
+      const double y = __shfl_up(before, o, 64);
+      if (lane >= o) before += y;
+    }
+    if (lane == 63) sums[wave] = before;
+    __syncthreads();
+    const int lo = sh_min[0][0], hi = sh_min[0][1];
+    const bool exact = lo == kNone || ((255 - hi) - lo + 24 + (32 - __clz(n_op)) <= 53 && hi > 0);
+    double total = 0.0;
+    for (int w = 0; w < kWaves; ++w) {
+      const double x = sums[w];
+      if (w < wave) before += x;
+      total += x;
+    }
+    __syncthreads();
+    if (exact) sums[t] = before - own;                       // the clock when the thread's first op begins
+    __syncthreads();
+    if (wave == 0) {
+      double chan = 0.0;
+      int e = 0;                                             // the next all-reduce; lane l holds number e0 + l
+      int e0 = 0, by = 0;
+      double run = 0.0;
+      auto load_ar = [&]() {
+        e0 = e;
+        const bool ok = e0 + lane < n_ar;
+        by = ok ? (int)place[order[n_op + e0 + lane]] : kNone;
+        run = (double)ar_c * (double)(ok ? value[n_op + e0 + lane] : 0.f) + (double)ar_d;
+      };
+      // the channel's turn for n all-reduces from e on, produced at the lanes' r
+      auto take = [&](double r, int n) {
+        for (int k = e - e0; k < e - e0 + n; ++k) {
+          const double rk = lane_of(r, k);
+          chan = (rk > chan ? rk : chan) + lane_of(run, k);
+        }
+        e += n;
+      };
+      double dev = total;
+      if (exact) {
+        while (e < n_ar) {
+          load_ar();
+          const int b = by == kNone ? 0 : by;
+          double r = sums[min(b / NPT, T - 1)];
+          const int first = b / NPT < T ? b & ~(NPT - 1) : b - NPT;
+#pragma unroll
+          for (int k = 0; k < NPT; ++k) r += first + k < b ? (double)value[first + k] : 0.0;
+          take(r, min(64, n_ar - e0));
+        }
+      } else {
+        double* ends = sums;                                 // the clock after each of 64 ops
+        double* runs = sums + 64;                            // their times
+        auto produce = [&](int done, int first) {            // those produced by the first `done` ops
+          while (e < n_ar) {
+            if (e == e0 + 64) load_ar();
+            const unsigned long long m = __ballot(by <= done) & (~0ull << (e - e0));
+            if (m == 0) break;
+            double r = 0.0;
+            if (by <= done && by > 0 && e0 + lane >= e) r = ends[by - 1 - first];
+            take(r, __popcll(m));
+          }
+        };
+        if (n_ar > 0) load_ar();
+        produce(0, 0);
+        dev = 0.0;                                           // lane 0's is the clock
+        for (int i0 = 0; i0 < n_op; i0 += 64) {
+          runs[lane] = (double)(i0 + lane < n_op ? value[i0 + lane] : 0.f);
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+          if (lane == 0)
+            for (int k = 0; k < 64; ++k) {
+              dev += runs[k];
+              ends[k] = dev;
+            }
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+          produce(min(i0 + 64, n_op), i0);
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        }
+      }
+      if (lane == 0) cost[c] = (float)(dev > chan ? dev : chan);
+    }
+    __syncthreads();
+  }
+}
+
+template <int T, int NPT>
+hipError_t launch_order(const SimArgs& a, int fewest, bool last, hipStream_t s) {
+  static bool attr_done = false;
+  constexpr int bytes = OrderLds<T, NPT>::kBytes;
+  if (!attr_done && bytes > 48 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&simulate_order_kernel<T, NPT>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  const int resident = a.n_cu * (2048 / T > 16 ? 16 : 2048 / T);
+  hipLaunchKernelGGL((simulate_order_kernel<T, NPT>), dim3(a.n_cand < resident ? a.n_cand : resident), dim3(T), bytes, s,
+                     a.node_off, a.out_rowptr, a.in_rowptr, a.in_col, a.op_time, a.ar_size, a.n_cand, a.ar_c, a.ar_d,
+                     a.cost, fewest, (int)last, a.status);
+  return hipGetLastError();
+}
 
 // The workgroup is one wave.  LDS operations of a wave are carried out in issue order, so
 // between a lane's write and another lane's later read only the compiler has to be kept from
@@ -65,27 +482,27 @@ __device__ __forceinline__ void sync_wave() {
 }
 
 template <bool kLds>
-__global__ __launch_bounds__(64) void simulate_kernel(const int* __restrict__ node_off,
-                                                       const int* __restrict__ out_rp, const int* __restrict__ out_ci,
-                                                       const int* __restrict__ in_rp,
-                                                       const float* __restrict__ op_time,
-                                                       const float* __restrict__ ar_size, int C, float ar_c,
-                                                       float ar_d, float* __restrict__ cost, char* gscratch,
-                                                       size_t gstride, int lds_lo, int lds_hi, int* status) {
-  // kLds: this launch walks the modules whose arrays need more than lds_lo and at most lds_hi
-  // bytes (its LDS allocation); !kLds: those that need more than lds_hi, in global memory
+__global__ __launch_bounds__(64) void simulate_general_kernel(const int* __restrict__ node_off,
+                                                               const int* __restrict__ out_rp,
+                                                               const int* __restrict__ out_ci,
+                                                               const int* __restrict__ in_rp,
+                                                               const float* __restrict__ op_time,
+                                                               const float* __restrict__ ar_size, int C, float ar_c,
+                                                               float ar_d, float* __restrict__ cost, char* gscratch,
+                                                               size_t gstride, int lds_bytes, int last, int* status) {
+  // The modules that simulate_order_kernel left.  kLds: those whose arrays fit lds_bytes of LDS; !kLds: the others,
+  // in global memory.  The last of the two to be launched reports a module that fits neither.
   typedef typename SimTypes<kLds>::dep_t dep_t;
   typedef typename SimTypes<kLds>::q_t q_t;
   constexpr int kAr = SimTypes<kLds>::kAr;
   if (status[0] != 0) return;
   const int lane = threadIdx.x;
   for (int c = blockIdx.x; c < C; c += gridDim.x) {
+    if (__float_as_uint(cost[c]) != kLeft) continue;
     const int n0 = node_off[c], G = node_off[c + 1] - n0;
     const int e0 = out_rp[n0], E = out_rp[n0 + G] - e0;
-    const size_t need = sim_lds_bytes(G, E);
-    if (kLds ? (need <= (size_t)lds_lo || need > (size_t)lds_hi) : need <= (size_t)lds_hi) continue;
-    if (!kLds && sim_bytes(G, E) > gstride) {       // larger than any base graph of this context
-      if (lane == 0) {
+    if (kLds ? sim_lds_bytes(G, E) > (size_t)lds_bytes : sim_bytes(G, E) > gstride) {
+      if (last && lane == 0) {                      // larger than any base graph of this context
         set_error(status, (int)DC_ERR_CAPACITY);
         cost[c] = INFINITY;
       }
@@ -192,28 +609,29 @@ size_t simulate_scratch_bytes(long long max_graph_nodes, long long max_graph_edg
 
 hipError_t launch_simulate(const SimArgs& a, hipStream_t s) {
   if (a.n_cand <= 0) return hipSuccess;
-  // Modules are walked on chip in five launches by size class, each with just the LDS its class
-  // needs (10, 6, 4, 3 or 2 waves per CU of 160 KB); a workgroup whose candidate belongs to another
-  // class returns at once.  The rest walk in slices of global memory (a persistent grid).
-  constexpr int kClasses = 5;
-  int classes[kClasses + 1] = {0, 16 * 1024, 26 * 1024 + 512, 40 * 1024, 53 * 1024, a.lds_bytes};
-  for (int k = 1; k < kClasses; ++k) classes[k] = classes[k] < a.lds_bytes ? classes[k] : a.lds_bytes;
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&simulate_kernel<true>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&simulate_general_kernel<true>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  for (int k = 0; k < kClasses; ++k)
-    if (classes[k + 1] > classes[k])
-    hipLaunchKernelGGL(simulate_kernel<true>, dim3(a.n_cand), dim3(64), classes[k + 1], s, a.node_off, a.out_rowptr,
-                       a.out_col, a.in_rowptr, a.op_time, a.ar_size, a.n_cand, a.ar_c, a.ar_d, a.cost, nullptr,
-                       (size_t)0, classes[k], classes[k + 1], a.status);
+  // classes of module size, up to what the largest module of the batch may need
+  const int n = a.max_module_nodes;
+  hipError_t e = launch_order<64, 4>(a, 0, n <= 256, s);
+  if (e == hipSuccess && n > 256) e = launch_order<256, 8>(a, 257, n <= 2048, s);
+  if (e == hipSuccess && n > 2048) e = launch_order<1024, 8>(a, 2049, n <= 8192, s);
+  if (e == hipSuccess && n > 8192) e = launch_order<1024, 16>(a, 8193, true, s);
+  if (e != hipSuccess) return e;
+  // what it left: two modules per CU in LDS, sixteen in global memory
+  const int lds_grid = 2 * a.n_cu;
+  hipLaunchKernelGGL(simulate_general_kernel<true>, dim3(a.n_cand < lds_grid ? a.n_cand : lds_grid), dim3(64), a.lds_bytes, s,
+                     a.node_off, a.out_rowptr, a.out_col, a.in_rowptr, a.op_time, a.ar_size, a.n_cand, a.ar_c, a.ar_d,
+                     a.cost, nullptr, (size_t)0, a.lds_bytes, a.n_slices == 0, a.status);
   if (a.n_slices > 0)
-    hipLaunchKernelGGL(simulate_kernel<false>, dim3(a.n_slices), dim3(64), 0, s, a.node_off, a.out_rowptr, a.out_col,
-                       a.in_rowptr, a.op_time, a.ar_size, a.n_cand, a.ar_c, a.ar_d, a.cost, a.scratch, a.scratch_stride,
-                       0, a.lds_bytes, a.status);
+    hipLaunchKernelGGL(simulate_general_kernel<false>, dim3(a.n_slices), dim3(64), 0, s, a.node_off, a.out_rowptr,
+                       a.out_col, a.in_rowptr, a.op_time, a.ar_size, a.n_cand, a.ar_c, a.ar_d, a.cost, a.scratch,
+                       a.scratch_stride, a.lds_bytes, 1, a.status);
   return hipGetLastError();
 }
 
@@ -304,6 +722,8 @@ extern "C" dc_status dc_simulate_static(const dc_batch* in, int32_t max_module_n
   a.out_rowptr = in->out_rowptr;
   a.out_col = in->out_col;
   a.in_rowptr = in->in_rowptr;
+  a.in_col = in->in_col;
+  a.max_module_nodes = max_module_nodes;
   a.op_time = op_time;
   a.ar_size = ar_size;
   a.ar_c = ar_c;
@@ -313,6 +733,7 @@ extern "C" dc_status dc_simulate_static(const dc_batch* in, int32_t max_module_n
   a.scratch = scratch + kStaticHeaderBytes;
   a.scratch_stride = kStaticSliceBytes;
   a.n_slices = kStaticSlices;
+  a.n_cu = n_cu;
   a.status = status;
   e = launch_simulate(a, s);
   if (e == hipSuccess && dev_status) {

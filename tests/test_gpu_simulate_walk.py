@@ -1,0 +1,94 @@
+"""The two kernels of the simulator at the places where one hands over to the other or changes its layout: costs bit
+for bit equal to the CPU oracle's (both add fp64 times in the order the rules fix)."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2209_12769_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+F = 16
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2209_12769_amd import binding
+    binding.lib()
+    return binding
+
+
+def graph(n, edges):
+    src, dst = (np.array(x, np.int64) for x in zip(*edges)) if edges else (np.zeros(0, np.int64),) * 2
+    rp, ci = wl._csr_from_edges(n, src, dst)
+    return wl.BaseGraph(n, n, rp, ci, np.zeros((n, F), np.float32))
+
+
+def chain(n, extra=()):
+    return graph(n, [(i, i + 1) for i in range(n - 1)] + list(extra))
+
+
+def fan(n):
+    """One op releases n - 2 others, which all precede the last."""
+    return graph(n, [(0, i) for i in range(1, n - 1)] + [(i, n - 1) for i in range(1, n - 1)])
+
+
+def tensors(n_op, n_ar):
+    """A chain of ops whose last one produces n_ar tensors; the first tensor of the list has no predecessor."""
+    return graph(n_op + n_ar, [(i, i + 1) for i in range(n_op - 1)] + [(n_op - 1, n_op + k) for k in range(1, n_ar)])
+
+
+def sources(n):
+    return graph(n + 1, [(i, n) for i in range(n)])
+
+
+# name: (graph, mask of all-reduce nodes as a function of the node number, change of the op times)
+CASES = {
+    **{f"chain{n}": (chain(n), None, None) for n in (1, 2, 63, 64, 65, 128, 129, 200)},
+    **{f"fan{n}": (fan(n), None, None) for n in (10, 65, 66, 67, 129, 130, 400)},
+    **{f"sources{n}": (sources(n), None, None) for n in (15, 16, 17, 64, 65, 127, 128, 200)},
+    **{f"tensors{k}": (tensors(70, k), lambda v: v >= 70, None) for k in (1, 63, 64, 65, 66, 129, 300)},
+    "all_tensors": (graph(70, []), lambda v: v >= 0, None),
+    "no_edges": (graph(300, []), lambda v: v % 7 == 0, None),
+    "tensor_with_successor": (chain(90), lambda v: v % 10 == 5, None),
+    "negative_time": (chain(90, [(3, 50)]), None, lambda t: np.where(np.arange(t.size) == 40, np.float32(-1), t)),
+    "infinite_time": (chain(90), lambda v: v == 89, lambda t: np.where(np.arange(t.size) == 40, np.float32(np.inf), t)),
+    "times_far_apart": (chain(500, [(3, 400)]), lambda v: v % 50 == 49 and v > 450, lambda t: t * np.where(np.arange(t.size) % 3 == 0, 1e6, 1e-6)),
+    "times_at_the_limit": (chain(255), None, lambda t: np.where(np.arange(t.size) == 9, 2.0 ** -20, 1.0 + t)),
+    "times_past_the_limit": (chain(255), None, lambda t: np.where(np.arange(t.size) == 9, 2.0 ** -24 * (1 + t), 1.0 + t)),
+    "zero_times": (fan(100), lambda v: v == 99, lambda t: np.zeros_like(t)),
+    "longest_in_lds": (chain(32000), None, None),
+    "too_long_for_lds": (chain(33500), None, None),
+    "wide_and_long": (wl.random_dag(31, 3000, 0.002, F), lambda v: v % 9 == 8, None),
+}
+
+
+def test_every_layout_gives_the_oracle_s_costs(B):
+    import torch
+    graphs = [c[0] for c in CASES.values()]
+    labels = [np.arange(g.n, dtype=np.int32).reshape(1, -1) for g in graphs]
+    w = wl.custom("walk", wl.ModelSpec(F, 32, 1, "f32"), graphs, labels, seed=1)
+    ref = orc.contract(w, False)
+    rng = wl.Rng(9, 1)
+    op_time, ar_size = [], []
+    for g, ar, change in CASES.values():
+        t = (rng.uniform(g.n) + 0.01).astype(np.float32)
+        is_ar = np.zeros(g.n, bool) if ar is None else np.asarray([ar(v) for v in range(g.n)], bool)
+        op_time.append(t if change is None else change(t).astype(np.float32))
+        ar_size.append(np.where(is_ar, 8 * rng.uniform(g.n), -1.0).astype(np.float32))
+    op_time, ar_size = np.concatenate(op_time), np.concatenate(ar_size)
+    ev = B.evaluator_for(w)
+    nb, eb = sum(g.n for g in graphs), sum(g.e for g in graphs)
+    batch = ev.contract_graphs(ev.to_device(w.cand_graph), ev.to_device(w.cand_off), ev.to_device(w.group_id),
+                               ev.alloc_batch(w.n_cand, nb, nb, eb))
+    t, x = torch.from_numpy(op_time).to(ev.device), torch.from_numpy(ar_size).to(ev.device)
+    for c, d in ((0.25, 0.05), (0.0, 0.0), (3.0, 1.0)):
+        want = orc.simulate(ref, op_time, ar_size, c, d)
+        got = ev.simulate(batch, t, x, c, d).cpu().numpy()
+        assert ev.check() == B.DC_OK
+        for name, a, b in zip(CASES, got, want):
+            assert a == b, (name, c, d, a, b)
+    ev.close()
