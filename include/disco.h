@@ -300,8 +300,8 @@ dc_status dc_last_fused_op_repeats(dc_ctx* ctx, int64_t* n_repeats, void* stream
  *                  member; low 32 bits of the draw), then one of its predecessor ops in the
  *                  current module uniformly (the groups with a dependency into it, same order;
  *                  high 32 bits), and the predecessor joins the op; an op without predecessors
- *                  leaves the module as it is.  Needs 7 bytes of LDS per base node: graphs of
- *                  more than about 23,000 nodes return DC_ERR_UNSUPPORTED.
+ *                  leaves the module as it is.  Needs 6.4 bytes of LDS per base node: graphs of
+ *                  more than about 25,000 nodes return DC_ERR_UNSUPPORTED.
  *   tensor fusion  n times: an all-reduce node a and a side are drawn uniformly; the nearest
  *                  bucket on that side in production order joins a's      (Sec. 4, method (iii))
  * (method (ii) duplicates an op; a labelling cannot express that).  The children of a step are
