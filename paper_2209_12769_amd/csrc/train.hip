@@ -45,7 +45,20 @@ __global__ __launch_bounds__(256) void readout_kernel(const float* __restrict__ 
        idx += (long long)gridDim.x * blockDim.x) {
     const int g = (int)(idx / cpr), ch = (int)(idx - (long long)g * cpr);
     double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    for (int v = node_off[g]; v < node_off[g + 1]; ++v) {
+    const int v1 = node_off[g + 1];
+    int v = node_off[g];
+    // eight rows requested together, added one after another: the chain of a long sample is eight times shorter
+    // (1.8 k rows in 130 samples: 27 -> 8 us)
+    for (; v + 8 <= v1; v += 8) {
+      float4 x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = h4[(size_t)(v + u) * cpr + ch];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        a0 += x[u].x; a1 += x[u].y; a2 += x[u].z; a3 += x[u].w;
+      }
+    }
+    for (; v < v1; ++v) {
       const float4 x = h4[(size_t)v * cpr + ch];
       a0 += x.x; a1 += x.y; a2 += x.z; a3 += x.w;
     }
@@ -495,7 +508,9 @@ __global__ __launch_bounds__(512) void wgrad_dma_kernel(const float* __restrict_
   }
 }
 
-// gW [M*N] and gb [N] = sums of the slabs' partial results, fp64, ascending slab order
+// gW [M*N] and gb [N] = sums of the slabs' partial results, fp64, ascending slab order.  Bound by memory latency: a
+// thread owns one sum, so sixteen of its addends are requested together (one at a time, a round trip per slab, took
+// 33 us for 128 slabs of 49 k entries; 5.6 us now).  S is a multiple of eight.
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ part, long long part_stride,
                                                            int S, long long MN, int N, float* __restrict__ gW,
                                                            float* __restrict__ gb, const int* __restrict__ status) {
@@ -504,7 +519,16 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
        i += (long long)gridDim.x * blockDim.x) {
     double s = 0.0;
-    for (int k = 0; k < S; ++k) s += (double)part[(size_t)k * (size_t)part_stride + i];
+    const float* __restrict__ p = part + i;
+    int k = 0;
+    for (; k + 16 <= S; k += 16, p += 16 * part_stride) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = p[u * part_stride];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s += (double)x[u];
+    }
+    for (; k < S; ++k, p += part_stride) s += (double)*p;
     if (i < MN) gW[i] = (float)s; else gb[i - MN] = (float)s;
   }
 }
