@@ -268,6 +268,7 @@ dc_status do_contract(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_graph, co
   a.slab_stride = ctx->slab_stride;
   a.slab_wgs = ctx->slab_wgs;
   a.lds_limit = ctx->lds_limit;
+  a.n_cu = ctx->n_cu;
   hipError_t e = launch_contract(a, ctx->prof.on ? &ctx->prof : nullptr, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "contraction launch");
   return DC_OK;

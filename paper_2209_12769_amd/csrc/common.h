@@ -87,6 +87,7 @@ struct ContractLaunch {
   size_t slab_stride;
   int slab_wgs;
   int lds_limit;
+  int n_cu;
 };
 hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t s);
 int contract_working_set_bytes(int n_nodes, int n_edges);

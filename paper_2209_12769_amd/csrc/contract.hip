@@ -532,13 +532,14 @@ __global__ __launch_bounds__(1024) void scan_sizes_kernel(int C, const int* Gc, 
 }
 
 
-// Places candidate c's lists at their block-diagonal position and sums features.
+// Places candidate c's lists at their block-diagonal position and sums features.  gridDim.y workgroups share a
+// candidate: they take its list entries and feature items in turn.
 template <bool kBf16>
 __global__ __launch_bounds__(256) void finalize_kernel(BaseGraphs bg, int C, const int* cand_graph,
                                                         const int* cand_off, ContractTmp tmp, BatchView out, int F,
                                                         const int* status) {
   if (status[0] != 0) return;
-  const int c = blockIdx.x, t = threadIdx.x, T = blockDim.x;
+  const int c = blockIdx.x, t = blockIdx.y * blockDim.x + threadIdx.x, T = gridDim.y * blockDim.x;
   const int b = cand_graph[c];
   const int coff = cand_off[c];
   const int nslot = coff + c, eslot = tmp.tmp_eoff[c];
@@ -653,11 +654,17 @@ hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t 
   if (prof) prof->begin(kFamFinalize, s);
   hipLaunchKernelGGL(scan_sizes_kernel, dim3(1), dim3(1024), 0, s, C, a.tmp.Gc, a.tmp.Ec, a.out.node_off,
                      a.out.edge_off, a.out.cap_nodes, a.out.cap_edges, a.status, a.totals);
+  // One workgroup per candidate fills the chip once there are eight of them per CU.  With fewer candidates several
+  // share one, down to one round of 4 x 256 feature items each (7 candidates of 1.4 k groups and F = 64: 111 us with
+  // one workgroup each, 9.8 us with 23).
+  const int rounds = ceil_div(a.max_graph_nodes * (a.F >> 2), 4 * 256);
+  const int want = ceil_div(8 * a.n_cu, C);
+  const dim3 fgrid(C, want < rounds ? want : (rounds > 0 ? rounds : 1));
   if (a.bf16)
-    hipLaunchKernelGGL(finalize_kernel<true>, dim3(C), dim3(256), 0, s, a.bg, C, a.cand_graph, a.cand_off, a.tmp,
+    hipLaunchKernelGGL(finalize_kernel<true>, fgrid, dim3(256), 0, s, a.bg, C, a.cand_graph, a.cand_off, a.tmp,
                        a.out, a.F, a.status);
   else
-    hipLaunchKernelGGL(finalize_kernel<false>, dim3(C), dim3(256), 0, s, a.bg, C, a.cand_graph, a.cand_off, a.tmp,
+    hipLaunchKernelGGL(finalize_kernel<false>, fgrid, dim3(256), 0, s, a.bg, C, a.cand_graph, a.cand_off, a.tmp,
                        a.out, a.F, a.status);
   if (prof) prof->end(s);
   return hipGetLastError();

