@@ -876,7 +876,7 @@ dc_status dc_set_profile(dc_ctx* ctx, const float* op_time, const float* ar_size
     f.fb.node_off = a.take<int>(cap_ops + 1);
     f.fb.edge_off = a.take<int>(cap_ops + 1);
     f.fo_cnode = a.take<int>(cap_ops + 1);
-    f.table = a.take<int>(fused_op_table_entries(cap_ops));
+    f.table = a.take<unsigned long long>(fused_op_table_entries(cap_ops));
     f.dup_of = a.take<int>(k.NB + k.C + 1);
     f.fb.new_id = a.take<int>(k.NB + 1);
     f.fb.out_rowptr = a.take<int>(k.NB + 1);

@@ -217,7 +217,7 @@ struct FusedOpsArgs {
   // scratch, slot cand_off[c] + c with one extra entry per candidate
   int* gfm;                    // per group: rows of fused ops before it (local)
   int* gfk;                    // per group: fused ops before it (local)
-  int* dgo;                    // per member position: edges inside groups before it, successors
+  int* dgo;                    // per row of the candidate: edges inside groups before it, successors
   int* dgi;                    // the same, predecessors
   int* cnt;                    // [3][C+1] fused ops / rows / edges per candidate, scanned in place
   int* totals;                 // {0, rows} {0, fused ops} edges, [5] fused ops that repeat an earlier one
@@ -225,7 +225,7 @@ struct FusedOpsArgs {
   int* fo_cnode;               // contracted node (global) of each fused op
   // Fused ops with the same members in the same base graph have the same subgraph and hence the same
   // estimate: with a table (not null) the estimator runs on the first of each kind only
-  int* table;                  // [table_mask + 1] open addressing, entry = contracted node (global) of that first one, -1 = free
+  unsigned long long* table;   // [table_mask + 1] open addressing, entry = candidate << 32 | group of that first one, all ones = free
   unsigned table_mask;
   int* dup_of;                 // slot cand_off[c] + c, per group: the contracted node (global) it repeats, or -1
   long long cap_ops, cap_rows, cap_edges;

@@ -47,14 +47,14 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
   return z ^ (z >> 31);
 }
 
-// Exclusive scans of a[0..n) and b[0..n) in place by a workgroup of 256 threads, in rounds of 1024 entries: a
-// thread takes four neighbouring entries of each array, so a wave reads and writes whole cache lines (the
-// arrays live in global memory; a contiguous run per thread would touch a line per entry).  One barrier per
-// round (the wave sums alternate between two halves of ws), one at the end.  Returns the totals.
-__device__ __forceinline__ void block_exscan_pair(int* a, int* b, int n, int (&ws)[2][2][4], int& total_a, int& total_b) {
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+// Exclusive scans of a[0..n) and b[0..n) in place by the workgroup (up to 16 waves), in rounds of four neighbouring
+// entries of each array per thread, so a wave reads and writes whole cache lines (the arrays live in global memory; a
+// contiguous run per thread would touch a line per entry).  One barrier per round (the wave sums alternate between
+// two halves of ws), one at the end.  Returns the totals.
+__device__ __forceinline__ void block_exscan_pair(int* a, int* b, int n, int (&ws)[2][2][16], int& total_a, int& total_b) {
+  const int t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6, nw = T >> 6;
   int carry_a = 0, carry_b = 0, par = 0;
-  for (int i0 = 0; i0 < n; i0 += 1024, par ^= 1) {
+  for (int i0 = 0; i0 < n; i0 += 4 * T, par ^= 1) {
     const int i = i0 + 4 * t;
     int xa[4], xb[4];
 #pragma unroll
@@ -70,8 +70,7 @@ __device__ __forceinline__ void block_exscan_pair(int* a, int* b, int n, int (&w
     }
     __syncthreads();
     int before_a = carry_a, before_b = carry_b;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < nw; ++w) {
       const int wa = ws[par][0][w], wb = ws[par][1][w];
       if (w < wave) {
         before_a += wa;
@@ -96,50 +95,61 @@ __device__ __forceinline__ void block_exscan_pair(int* a, int* b, int n, int (&w
   total_b = carry_b;
 }
 
-__global__ __launch_bounds__(256) void fo_clear_table_kernel(int* __restrict__ table, unsigned mask, int* totals) {
+constexpr unsigned long long kFreePlace = ~0ull;
+
+__global__ __launch_bounds__(256) void fo_clear_table_kernel(unsigned long long* __restrict__ table, unsigned mask, int* totals) {
   const size_t n = (size_t)mask + 1;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) table[i] = -1;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) table[i] = kFreePlace;
   if (blockIdx.x == 0 && threadIdx.x == 0) totals[5] = 0;
 }
 
-// The fused op (candidate c, group g: base graph b, members mem[s .. s + n)) against the table: returns the
-// contracted node (global) of an equal fused op entered before, or -1 after entering this one (`me`).
-__device__ __forceinline__ int find_or_enter(const FusedOpsArgs& a, int b, const int* mem, int s, int n, int me) {
+// The fused op (candidate c, group g: base graph b, members mem[s .. s + n), the first eight of them in m) against
+// the table: returns the contracted node (global) of an equal fused op entered before, or -1 after entering this one.
+// A place holds (candidate, group), so that a probe reads its rival's bounds at once instead of searching the
+// candidate that a node number belongs to (twelve dependent loads for 4096 candidates).
+__device__ __forceinline__ int find_or_enter(const FusedOpsArgs& a, int b, const int* mem, int s, int n, const int (&m)[8],
+                                             int c, int g) {
   unsigned long long h = mix64(0x9E3779B97F4A7C15ull + (unsigned)b);
-  for (int i = 0; i < n; ++i) h = mix64(h ^ (unsigned)mem[s + i]);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (i < n) h = mix64(h ^ (unsigned)m[i]);
+  for (int i = 8; i < n; ++i) h = mix64(h ^ (unsigned)mem[s + i]);
+  const unsigned long long me = ((unsigned long long)(unsigned)c << 32) | (unsigned)g;
   unsigned slot = (unsigned)h & a.table_mask;
   for (int probe = 0; probe < kMaxProbes; ++probe) {
     // a place only ever changes from free to taken, so whatever a plain read finds taken is final, and only a
     // place that looks free needs the atomic (thousands of candidates may carry the same fused op)
-    int old = a.table[slot];
-    if (old == -1) old = atomicCAS(&a.table[slot], -1, me);
-    if (old == -1) return -1;
-    int lo = 0, hi = a.n_cand;                 // the candidate of node `old`: the last one that starts at or before it
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (a.c_node_off[mid] <= old) lo = mid; else hi = mid;
-    }
-    if (a.cand_graph[lo] == b) {
-      const int coff2 = a.cand_off[lo];
-      const int* ms2 = a.mstart + coff2 + lo;
-      const int* mem2 = a.members + coff2;
-      const int g2 = old - a.c_node_off[lo];
-      const int s2 = ms2[g2];
-      bool same = ms2[g2 + 1] - s2 == n;
-      for (int i = 0; same && i < n; ++i) same = mem2[s2 + i] == mem[s + i];
-      if (same) return old;
+    unsigned long long old = a.table[slot];
+    if (old == kFreePlace) old = atomicCAS(&a.table[slot], kFreePlace, me);
+    if (old == kFreePlace) return -1;
+    const int c2 = (int)(old >> 32), g2 = (int)(unsigned)old;
+    const int b2 = a.cand_graph[c2], coff2 = a.cand_off[c2], first2 = a.c_node_off[c2];
+    const int* ms2 = a.mstart + coff2 + c2;
+    const int s2 = ms2[g2], e2 = ms2[g2 + 1];
+    if (b2 == b && e2 - s2 == n) {
+      const int* mem2 = a.members + coff2 + s2;
+      bool same = true;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) same &= i >= n || mem2[min(i, n - 1)] == m[i];
+      for (int i = 8; same && i < n; ++i) same = mem2[i] == mem[s + i];
+      if (same) return first2 + g2;
     }
     slot = (slot + 1) & a.table_mask;
   }
   return -1;
 }
 
-__global__ __launch_bounds__(256) void fo_count_kernel(FusedOpsArgs a) {
-  __shared__ int wsum[2][2][4];
+// Per candidate: first its groups, one thread each, then the edges inside those groups that get rows.  Bound by the
+// latency of dependent loads, so the members of a group are read eight at a time and the second part runs over the
+// rows only: in a batch whose candidates share most fused ops hardly any candidate has rows, and counts and scan over
+// all members took most of the time (4096 candidates of 1.4 k groups: this kernel 767 -> 456 us, fo_fill_kernel 421 ->
+// 126 us; 1000 candidates of 6.5 k groups: 256 -> 157 and 58 -> 18 us).
+__global__ __launch_bounds__(1024) void fo_count_kernel(FusedOpsArgs a) {
+  __shared__ int wsum[2][2][16];
   if (a.status[0] != 0) return;
   const int c = blockIdx.x, t = threadIdx.x, T = blockDim.x;
   const int b = a.cand_graph[c];
-  const int coff = a.cand_off[c], N = a.cand_off[c + 1] - coff, nslot = coff + c;
+  const int coff = a.cand_off[c], nslot = coff + c;
   const int G = a.Gc[c], gb = a.bg.gno[b], n0 = a.c_node_off[c];
   const int* ms = a.mstart + nslot;
   const int* mem = a.members + coff;
@@ -150,19 +160,50 @@ __global__ __launch_bounds__(256) void fo_count_kernel(FusedOpsArgs a) {
   int* gfk = a.gfk + nslot;
   int n_repeats = 0;
   for (int g = t; g < G; g += T) {
-    const int s = ms[g], e = ms[g + 1], n = e - s;
+    const int s = ms[g], n = ms[g + 1] - s;      // a group has at least one member
+    int m[8];
+    float x[8];
+    m[0] = mem[s];
+#pragma unroll
+    for (int u = 1; u < 8; ++u) m[u] = m[0];
+    if (__any(n > 1)) {
+#pragma unroll
+      for (int u = 1; u < 4; ++u) m[u] = mem[s + min(u, n - 1)];
+    }
+    if (__any(n > 4)) {
+#pragma unroll
+      for (int u = 4; u < 8; ++u) m[u] = mem[s + min(u, n - 1)];
+    }
+    x[0] = xb[m[0]];
+    const float t0 = tb[m[0]];
+#pragma unroll
+    for (int u = 1; u < 8; ++u) x[u] = x[0];
+    if (__any(n > 1)) {
+#pragma unroll
+      for (int u = 1; u < 4; ++u) x[u] = xb[m[u]];
+    }
+    if (__any(n > 4)) {
+#pragma unroll
+      for (int u = 4; u < 8; ++u) x[u] = xb[m[u]];
+    }
     int n_ar = 0;
     double size = 0.0;
-    for (int m = s; m < e; ++m) {
-      const float x = xb[mem[m]];
-      if (x >= 0.0f) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < n && x[u] >= 0.0f) {
         ++n_ar;
-        size += (double)x;
+        size += (double)x[u];
+      }
+    for (int i = 8; i < n; ++i) {
+      const float y = xb[mem[s + i]];
+      if (y >= 0.0f) {
+        ++n_ar;
+        size += (double)y;
       }
     }
     bool fused = n_ar == 0 && n >= 2;
     if (a.table) {
-      const int first = fused ? find_or_enter(a, b, mem, s, n, n0 + g) : -1;
+      const int first = fused ? find_or_enter(a, b, mem, s, n, m, c, g) : -1;
       a.dup_of[nslot + g] = first;
       if (first >= 0) {
         fused = false;                         // no rows of its own
@@ -174,7 +215,7 @@ __global__ __launch_bounds__(256) void fo_count_kernel(FusedOpsArgs a) {
       ot = 0.0f;
       as = (float)size;
     } else if (n_ar == 0) {
-      ot = n == 1 ? tb[mem[s]] : 0.0f;      // a fused op's time is written by fo_time_kernel / fo_repeat_kernel
+      ot = n == 1 ? t0 : 0.0f;              // a fused op's time is written by fo_time_kernel / fo_repeat_kernel
       as = -1.0f;
     } else {
       ot = INFINITY;
@@ -196,30 +237,34 @@ __global__ __launch_bounds__(256) void fo_count_kernel(FusedOpsArgs a) {
     gfm[G] = Mc;
     gfk[G] = Kc;
   }
-  __syncthreads();
-  // edges inside a group, per member (in member order), both directions
-  const int* rp = a.bg.rowptr + gb + b;
-  const int* ci = a.bg.col + a.bg.geo[b];
-  const int* crp = a.bg.crowptr + gb + b;
-  const int* cci = a.bg.ccol + a.bg.geo[b];
-  int* dgo = a.dgo + nslot;
-  int* dgi = a.dgi + nslot;
-  for (int i = t; i < N; i += T) {
-    const int u = mem[i], g = nid[u];
-    int no = 0, ni = 0;
-    if (gfm[g + 1] != gfm[g]) {
+  int Eo = 0, Ei = 0;
+  if (Mc > 0) {
+    int* dgo = a.dgo + nslot;
+    int* dgi = a.dgi + nslot;
+    __syncthreads();
+    for (int g = t; g < G; g += T) {             // rows of a group: its members in order; for now their place in mem
+      const int r = gfm[g], n = gfm[g + 1] - r;
+      const int s = n > 0 ? ms[g] : 0;
+      for (int j = 0; j < n; ++j) dgo[r + j] = s + j;
+    }
+    __syncthreads();
+    // edges inside a group, per row, both directions
+    const int* rp = a.bg.rowptr + gb + b;
+    const int* ci = a.bg.col + a.bg.geo[b];
+    const int* crp = a.bg.crowptr + gb + b;
+    const int* cci = a.bg.ccol + a.bg.geo[b];
+    for (int r = t; r < Mc; r += T) {
+      const int u = mem[dgo[r]], g = nid[u];
+      int no = 0, ni = 0;
       for (int k = rp[u]; k < rp[u + 1]; ++k) no += nid[ci[k]] == g;
       for (int k = crp[u]; k < crp[u + 1]; ++k) ni += nid[cci[k]] == g;
+      dgo[r] = no;
+      dgi[r] = ni;
     }
-    dgo[i] = no;
-    dgi[i] = ni;
+    __syncthreads();
+    block_exscan_pair(dgo, dgi, Mc, wsum, Eo, Ei);
   }
-  __syncthreads();
-  int Eo, Ei;
-  block_exscan_pair(dgo, dgi, N, wsum, Eo, Ei);
   if (t == 0) {
-    dgo[N] = Eo;
-    dgi[N] = Ei;
     a.cnt[c] = Kc;
     a.cnt[a.n_cand + 1 + c] = Mc;
     a.cnt[2 * (a.n_cand + 1) + c] = Eo;
@@ -269,15 +314,17 @@ __device__ __forceinline__ int rank_in(const int* m, int n, int w) {
   return lo;
 }
 
+// As fo_count_kernel: groups first, then rows; a candidate without rows of its own has nothing to write.
 template <bool kBf16>
-__global__ __launch_bounds__(256) void fo_fill_kernel(FusedOpsArgs a) {
+__global__ __launch_bounds__(1024) void fo_fill_kernel(FusedOpsArgs a) {
   if (a.status[0] != 0) return;
   const int c = blockIdx.x, t = threadIdx.x, T = blockDim.x, C = a.n_cand;
-  const int b = a.cand_graph[c];
-  const int coff = a.cand_off[c], N = a.cand_off[c + 1] - coff, nslot = coff + c;
-  const int G = a.Gc[c], gb = a.bg.gno[b], n0 = a.c_node_off[c];
   const int k0 = a.cnt[c], m0 = a.cnt[C + 1 + c], e0 = a.cnt[2 * (C + 1) + c];
   const int Mc = a.cnt[C + 1 + c + 1] - m0;
+  if (Mc == 0) return;
+  const int b = a.cand_graph[c];
+  const int coff = a.cand_off[c], nslot = coff + c;
+  const int G = a.Gc[c], gb = a.bg.gno[b], n0 = a.c_node_off[c];
   const int* ms = a.mstart + nslot;
   const int* mem = a.members + coff;
   const int* nid = a.new_id + coff;
@@ -286,26 +333,26 @@ __global__ __launch_bounds__(256) void fo_fill_kernel(FusedOpsArgs a) {
   const int* dgo = a.dgo + nslot;
   const int* dgi = a.dgi + nslot;
   for (int g = t; g < G; g += T) {
-    if (gfm[g + 1] == gfm[g]) continue;
-    const int k = k0 + gfk[g];
-    a.fb.node_off[k] = m0 + gfm[g];
-    a.fb.edge_off[k] = e0 + dgo[ms[g]];
+    const int r = gfm[g], n = gfm[g + 1] - r;
+    if (n == 0) continue;
+    const int k = k0 + gfk[g], s = ms[g];
+    a.fb.node_off[k] = m0 + r;
+    a.fb.edge_off[k] = e0 + dgo[r];
     a.fo_cnode[k] = n0 + g;
+    for (int j = 0; j < n; ++j) a.fb.new_id[m0 + r + j] = mem[s + j];
   }
+  __syncthreads();          // fb.new_id of this candidate's rows is complete
   const int* rp = a.bg.rowptr + gb + b;
   const int* ci = a.bg.col + a.bg.geo[b];
   const int* crp = a.bg.crowptr + gb + b;
   const int* cci = a.bg.ccol + a.bg.geo[b];
-  for (int i = t; i < N; i += T) {
-    const int u = mem[i], g = nid[u];
-    if (gfm[g + 1] == gfm[g]) continue;
+  for (int r = t; r < Mc; r += T) {
+    const int u = a.fb.new_id[m0 + r], g = nid[u];
     const int s = ms[g], n = ms[g + 1] - s;
     const int first = m0 + gfm[g];            // row of the group's first member
-    const int row = first + (i - s);
-    a.fb.new_id[row] = u;
-    int ko = e0 + dgo[i], ki = e0 + dgi[i];
-    a.fb.out_rowptr[row] = ko;
-    a.fb.in_rowptr[row] = ki;
+    int ko = e0 + dgo[r], ki = e0 + dgi[r];
+    a.fb.out_rowptr[m0 + r] = ko;
+    a.fb.in_rowptr[m0 + r] = ki;
     for (int k = rp[u]; k < rp[u + 1]; ++k) {
       const int w = ci[k];
       if (nid[w] == g) a.fb.out_col[ko++] = first + rank_in(mem + s, n, w);
@@ -315,7 +362,6 @@ __global__ __launch_bounds__(256) void fo_fill_kernel(FusedOpsArgs a) {
       if (nid[w] == g) a.fb.in_col[ki++] = first + rank_in(mem + s, n, w);
     }
   }
-  __syncthreads();          // fb.new_id of this candidate's rows is complete
   const int q = a.F >> 2;
   const float4* X4 = reinterpret_cast<const float4*>(a.bg.X) + (size_t)gb * q;
   for (int i = t; i < Mc * q; i += T) {
@@ -455,10 +501,12 @@ __global__ __launch_bounds__(256) void fo_repeat_kernel(FusedOpsArgs a) {
 
 }  // namespace
 
-// Places of the table for up to `max_fused_ops` entries: a power of two, at most half full.
+// Places of the table for up to `max_fused_ops` entries: a power of two, at most eight ninths full.  It is cleared in
+// every call, so a larger one costs bandwidth, and real batches fill it to a few per cent.
 size_t fused_op_table_entries(long long max_fused_ops) {
+  const size_t most = max_fused_ops > 0 ? (size_t)max_fused_ops : 1;
   size_t n = 1024;
-  while (n < 2 * (size_t)(max_fused_ops > 0 ? max_fused_ops : 1)) n <<= 1;
+  while (n < most + most / 8) n <<= 1;
   return n;
 }
 
@@ -467,10 +515,13 @@ hipError_t launch_fused_op_extract(const FusedOpsArgs& a, Profiler* prof, hipStr
   if (prof) prof->begin(kFamFusedOps, s);
   if (a.table)
     hipLaunchKernelGGL(fo_clear_table_kernel, dim3(a.n_cu * 8), dim3(256), 0, s, a.table, a.table_mask, a.totals);
-  hipLaunchKernelGGL(fo_count_kernel, dim3(a.n_cand), dim3(256), 0, s, a);
+  // A workgroup per candidate: of eight waves, so that four of them fill a CU; with fewer than two candidates per CU
+  // of sixteen.
+  const dim3 per_cand(a.n_cand < 2 * a.n_cu ? 1024 : 512);
+  hipLaunchKernelGGL(fo_count_kernel, dim3(a.n_cand), per_cand, 0, s, a);
   hipLaunchKernelGGL(fo_scan_kernel, dim3(1), dim3(1024), 0, s, a);
-  if (a.bf16) hipLaunchKernelGGL(fo_fill_kernel<true>, dim3(a.n_cand), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(fo_fill_kernel<false>, dim3(a.n_cand), dim3(256), 0, s, a);
+  if (a.bf16) hipLaunchKernelGGL(fo_fill_kernel<true>, dim3(a.n_cand), per_cand, 0, s, a);
+  else hipLaunchKernelGGL(fo_fill_kernel<false>, dim3(a.n_cand), per_cand, 0, s, a);
   if (prof) prof->end(s);
   return hipGetLastError();
 }
