@@ -100,6 +100,92 @@ __global__ __launch_bounds__(256) void aggregate_kernel(const void* __restrict__
 }
 
 // ---------------------------------------------------------------------------
+// update, fp32, few rows: the same product, one wave per 32 x 32 tile of the output, operands straight from memory
+// ---------------------------------------------------------------------------
+// A 128-row tile keeps one CU's matrix cores busy for 20 us at K = 384 (two MFMAs of 64 cycles per wave and step, two
+// waves per SIMD), whether or not the other 255 CUs have work.  With at most one 32 x 32 tile per SIMD of the chip the
+// product is spread over all of them instead: 5 us of MFMAs each, no LDS and no barriers, operands three chunks of 16 k
+// ahead in registers (a search step's layers of a few hundred
+// rows at K = 384: 20.1 -> 11.6 us).  The products are added in the same order as in the large tiles (k pairs
+// ascending), so a result does not depend on the size of its batch.  Beyond that many tiles the large ones read W and
+// the rows fewer times.
+__device__ __forceinline__ bool few_tiles(int ntot, int H, int most) { return ((ntot + 31) >> 5) * (H >> 5) <= most; }
+
+struct Chunk16 {
+  float4 a[2];      // columns 8 i + 4 lh .. + 3 of the lane's row
+  float b[8];       // the lane's column of W, rows 2 i + lh
+};
+struct Operands32 {
+  const float *A0, *A1, *A2, *W;
+  unsigned arow, wcol;      // the lane's place in the first chunk (few rows: 32 bits), everything else is uniform
+  int d, H, nk;
+};
+__device__ __forceinline__ void fetch16(const Operands32& o, Chunk16& x, int c) {
+  const int k0 = c * 16, seg = k0 / o.d;
+  const float* ap = (seg == 0 ? o.A0 : (seg == 1 ? o.A1 : o.A2)) + (k0 - seg * o.d);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) x.a[i] = *reinterpret_cast<const float4*>(ap + 8 * i + o.arow);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x.b[i] = (o.W + (size_t)(k0 + 2 * i) * o.H)[o.wcol];
+}
+// Lanes 0-31 hold column k in p and k + 1 in q, lanes 32-63 k + 4 and k + 5: afterwards p is the operand of columns
+// (k, k + 1), q that of (k + 4, k + 5).
+__device__ __forceinline__ void halves_to_pairs(float& p, float& q) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+  p = __uint_as_float(r[0]);
+  q = __uint_as_float(r[1]);
+}
+// chunk c from cur, while chunk c + 3 is requested into the set that held chunk c - 1
+__device__ __forceinline__ void step16(const Operands32& o, f32x16& acc, const Chunk16& cur, Chunk16& free, int c) {
+  if (c >= o.nk) return;
+  if (c + 3 < o.nk) fetch16(o, free, c + 3);
+  __builtin_amdgcn_sched_barrier(0);                  // the requests stay ahead of the products
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    float x = cur.a[i].x, y = cur.a[i].y, z = cur.a[i].z, w = cur.a[i].w;
+    halves_to_pairs(x, y);
+    halves_to_pairs(z, w);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, cur.b[4 * i], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(z, cur.b[4 * i + 1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y, cur.b[4 * i + 2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w, cur.b[4 * i + 3], acc, 0, 0, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ void update32_few(const float* __restrict__ A0, const float* __restrict__ A1,
+                                             const float* __restrict__ A2, int d, int nseg, const float* __restrict__ Wf,
+                                             const float* __restrict__ bias, float* __restrict__ out, int H, int ntot) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, nw = blockDim.x >> 6;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int nct = H >> 5, ntiles = ((ntot + 31) >> 5) * nct;
+  // four waves of a workgroup, one per SIMD, before the next four
+  for (int tile = blockIdx.x * 4 + (wave & 3) + (wave >> 2) * 4 * gridDim.x; tile < ntiles; tile += nw * gridDim.x) {
+    const int m0 = (tile / nct) * 32, n0 = (tile % nct) * 32;
+    const Operands32 o{A0, A1, A2, Wf, (unsigned)(min(m0 + l32, ntot - 1) * d + 4 * lh), (unsigned)(n0 + l32 + lh * H), d, H, nseg * d / 16};
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    Chunk16 s0, s1, s2, s3;
+    fetch16(o, s0, 0);
+    if (o.nk > 1) fetch16(o, s1, 1);
+    if (o.nk > 2) fetch16(o, s2, 2);
+    for (int c = 0; c < o.nk; c += 4) {
+      step16(o, acc, s0, s3, c);
+      step16(o, acc, s1, s0, c + 1);
+      step16(o, acc, s2, s1, c + 2);
+      step16(o, acc, s3, s2, c + 3);
+    }
+    const float bj = bias ? bias[n0 + l32] : 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = m0 + 8 * (v >> 2) + 4 * lh + (v & 3);
+      if (row < ntot) out[(size_t)row * H + n0 + l32] = bias ? fmaxf(acc[v] + bj, 0.f) : acc[v];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // update: h' = ReLU([h | h_in | h_out] W + b) on MFMA
 // ---------------------------------------------------------------------------
 // Tile BM x BN per workgroup, WM x WN per wave, K advanced in steps of BK that
@@ -109,10 +195,10 @@ __global__ __launch_bounds__(256) void aggregate_kernel(const void* __restrict__
 //         straight copy and fragment reads are contiguous across lanes.
 //   fp32: A rows padded by one float, B rows padded to an odd multiple of 32.
 template <bool kBf16, int BM, int BN, int BK, int WM, int WN>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void update_kernel(
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_waves_per_eu(kBf16 ? 1 : 4, 8))) void update_kernel(
     const void* __restrict__ A0, const void* __restrict__ A1, const void* __restrict__ A2, int d, int nseg,
     const void* __restrict__ Wl, const float* __restrict__ bias, void* __restrict__ out, int H,
-    const int* __restrict__ node_off, int C, int interleave, const int* __restrict__ status) {
+    const int* __restrict__ node_off, int C, int interleave, int few, const int* __restrict__ status) {
   // nseg = 3: out = ReLU([A0 | A1 | A2] W + bias); nseg = 1 (bias == nullptr): out = A0 W.
   // interleave: the K chunks in the order of the sixteen-wave layer kernel (chunk c of A0, of A1, of A2, then
   // chunk c + 1 ...) instead of segment by segment, so that both add their products in the same order.
@@ -133,6 +219,13 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void update_kernel(
   const int wm = wave / (BN / WN), wn = wave % (BN / WN);
   const int l32 = lane & 31, lh = lane >> 5;
   const int ntot = node_off[C];
+  if constexpr (!kBf16 && BN == 32) {      // the wider tiles of this kernel need the registers for more waves
+    if (few_tiles(ntot, H, few)) {
+      update32_few(static_cast<const float*>(A0), static_cast<const float*>(A1), static_cast<const float*>(A2), d, nseg,
+                   static_cast<const float*>(Wl), bias, static_cast<float*>(out), H, ntot);
+      return;
+    }
+  }
   const int nct = H / BN;
   const int ntiles = ((ntot + BM - 1) / BM) * nct;
 
@@ -249,11 +342,11 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void update_kernel(
 // in memory; MFMA block j of a wave takes columns 2l + j of its 64 (l = lane mod 32), so one 8-byte
 // LDS read feeds both of a lane's B operands and results leave as 8-byte stores.
 template <int BN, int WM>
-__global__ __launch_bounds__(512) void update32_kernel(const float* __restrict__ A0, const float* __restrict__ A1,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) void update32_kernel(const float* __restrict__ A0, const float* __restrict__ A1,
                                                        const float* __restrict__ A2, int d, int nseg,
                                                        const float* __restrict__ Wf, const float* __restrict__ bias,
                                                        float* __restrict__ out, int H,
-                                                       const int* __restrict__ node_off, int C,
+                                                       const int* __restrict__ node_off, int C, int few,
                                                        const int* __restrict__ status) {
   if (status[0] != 0) return;
   constexpr int BM = 128, BK = 16, WN = 64, NT = 512;
@@ -267,6 +360,10 @@ __global__ __launch_bounds__(512) void update32_kernel(const float* __restrict__
   const int wm = wave / (BN / WN), wn = wave % (BN / WN);
   const int l32 = lane & 31, lh = lane >> 5;
   const int ntot = node_off[C];
+  if (few_tiles(ntot, H, few)) {
+    update32_few(A0, A1, A2, d, nseg, Wf, bias, out, H, ntot);
+    return;
+  }
   const int nct = H / BN;
   const int ntiles = ((ntot + BM - 1) / BM) * nct;
   const int K = nseg * d, nk = K / BK;
@@ -369,6 +466,20 @@ __global__ __launch_bounds__(512) void update32_kernel(const float* __restrict__
 // where the last layer's kernel left them (the sum of chunk k for graph c at row k + c: both grow
 // along the rows, so the place is unique).  The same tree on both routes: the same bits.
 // ---------------------------------------------------------------------------
+// s + sum over k of x[k] W[k][j], ascending k.  A chain of fp64 additions over H matrix entries that lie a row apart:
+// 32 of them are requested together, else every few entries cost a round trip to L2 (H is a multiple of 32; 7
+// candidates with H = 256: the kernel 49 -> 17 us).
+__device__ __forceinline__ double head_column(double s, const float* x, const float* __restrict__ W, int H, int j) {
+  for (int k = 0; k < H; k += 32) {
+    float w[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) w[u] = W[(size_t)(k + u) * H + j];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) s += (double)x[k + u] * (double)w[u];
+  }
+  return s;
+}
+
 template <bool kBf16, int kOrder>
 __global__ __launch_bounds__(256) void readout_head_kernel(const void* __restrict__ h, int H,
                                                             const int* __restrict__ node_off, int C,
@@ -475,20 +586,6 @@ __global__ __launch_bounds__(256) void readout_head_kernel(const void* __restric
   __syncthreads();
   const float* W1 = head;
   const float* b1 = W1 + (size_t)H * H;
-// s + sum over k of x[k] W[k][j], ascending k.  A chain of fp64 additions over H matrix entries that lie a row apart:
-// 32 of them are requested together, else every few entries cost a round trip to L2 (H is a multiple of 32; 7
-// candidates with H = 256: the kernel 49 -> 17 us).
-__device__ __forceinline__ double head_column(double s, const float* x, const float* __restrict__ W, int H, int j) {
-  for (int k = 0; k < H; k += 32) {
-    float w[32];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) w[u] = W[(size_t)(k + u) * H + j];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) s += (double)x[k + u] * (double)w[u];
-  }
-  return s;
-}
-
   const float* W2 = b1 + H;
   const float* b2 = W2 + (size_t)H * H;
   const float* w3 = b2 + H;
@@ -518,7 +615,7 @@ void launch_update(const GnnArgs& a, const void* A0, const void* A1, const void*
                    const float* bias, void* out, int interleave, hipStream_t s) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   hipLaunchKernelGGL((update_kernel<kBf16, BM, BN, BK, WM, WN>), dim3(a.n_cu * (kBf16 ? 2 : 4)), dim3(NT), 0, s, A0, A1, A2, d, nseg,
-                     Wl, bias, out, a.H, a.node_off, a.n_cand, interleave, a.status);
+                     Wl, bias, out, a.H, a.node_off, a.n_cand, interleave, 4 * a.n_cu, a.status);
 }
 
 template <bool kBf16, int BK>
@@ -546,11 +643,11 @@ void run_update(const GnnArgs& a, const void* A0, const void* A1, const void* A2
     if (a.H % 256 == 0)
       hipLaunchKernelGGL((update32_kernel<256, 64>), dim3(a.n_cu * 2), dim3(512), 0, s, f0, f1, f2, d, nseg,
                          static_cast<const float*>(Wl), bias, static_cast<float*>(out), a.H, a.node_off, a.n_cand,
-                         a.status);
+                         4 * a.n_cu, a.status);
     else if (a.H % 128 == 0)
       hipLaunchKernelGGL((update32_kernel<128, 32>), dim3(a.n_cu * 2), dim3(512), 0, s, f0, f1, f2, d, nseg,
                          static_cast<const float*>(Wl), bias, static_cast<float*>(out), a.H, a.node_off, a.n_cand,
-                         a.status);
+                         4 * a.n_cu, a.status);
     else
       dispatch_update<false, 16>(a, A0, A1, A2, d, nseg, Wl, bias, out, 0, s);
   }
