@@ -174,7 +174,7 @@ size_t carve(const dc_config& cfg, char* base, dc_ctx* ctx) {
   int* heavy0 = a.take<int>((size_t)k.NN + 128);
   int* heavy1 = a.take<int>((size_t)k.NN + 128);
   int* heavy_cnt = a.take<int>(2 * ((size_t)k.NN / 128 + 2));
-  int* heavy_ctr = a.take<int>(kHeavyCtrInts);
+  int* heavy_ctr = a.take<int>(2 * kHeavyCtrInts);
   int* heavy_off = a.take<int>(2 * ((size_t)k.NN / 128 + 2) + 1);
   unsigned* heavy_list = a.take<unsigned>(2 * ((size_t)k.NN + 128));
   // chunk sums of the readout formed by the last layer (bulk bf16 shapes with uniform coefficients only)

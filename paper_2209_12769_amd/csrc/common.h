@@ -115,7 +115,7 @@ struct GnnArgs {
   int* heavy_cnt = nullptr;             // [2 * tiles] how many of them: entry 2 * tile + direction
   int* heavy_off = nullptr;             // [2 * tiles + 1] exclusive scan of heavy_cnt
   unsigned* heavy_list = nullptr;       // the long rows of all tiles as one list: row number, bit 31 = successors' side
-  int* heavy_ctr = nullptr;             // [kHeavyCtrInts] the pre-pass's work counters, one per XCD (cleared by every launch)
+  int* heavy_ctr = nullptr;             // [2 * kHeavyCtrInts] the pre-pass's work counters, one per XCD, in two sets that launches use in turn
   // the last layer forming the readout's sums itself (bulk bf16 shapes): per chunk of 64 rows and graph one row of
   // H partial sums at row chunk + graph, and per chunk the graph its first row belongs to; 0 / nullptr: not used
   int fuse_readout = 0;
@@ -164,14 +164,15 @@ hipError_t launch_build_desc(const GnnArgs& a, hipStream_t s);
 // readout: the layer leaves the readout's chunk sums in a.ro_part instead of its rows in out (needs
 // launch_chunk_first on the same batch before)
 hipError_t launch_layer256(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
-                           bool readout, Profiler* prof, hipStream_t s);
+                           bool readout, int turn, Profiler* prof, hipStream_t s);
 hipError_t launch_chunk_first(const GnnArgs& a, hipStream_t s);
 // gnn_layer256w.hip: the same layer (five gather slots) with sixteen waves per workgroup; descriptors and
 // pre-pass means as for launch_layer256
+// turn: number of the layer (launches of one pass use the pre-pass's two sets of counters in turn)
 hipError_t launch_build_desc_sorted(const GnnArgs& a, hipStream_t s);
 // Means of the rows with more than five neighbours (listed by launch_build_desc_sorted), written at the rows'
 // own places in a.agg[0] (predecessors) and a.agg[1] (successors); h [rows, d], d = 256 or 64, bf16.
-hipError_t launch_heavy_means(const void* h, int d, const GnnArgs& a, hipStream_t s);
+hipError_t launch_heavy_means(const void* h, int d, const GnnArgs& a, int turn, hipStream_t s);
 hipError_t launch_layer256w(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
                             bool readout, hipStream_t s);
 hipError_t launch_dense256(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,

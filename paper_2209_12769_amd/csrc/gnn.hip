@@ -758,7 +758,7 @@ hipError_t mean_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, const vo
     void* hnext = a.act[l & 1];
     if (a.allow_fused && layer256_supported(d, a.H, a.bf16)) {
       const bool readout = l == a.L - 1 && readout_in_last_layer(a);   // then hnext is not written
-      hipError_t e = launch_layer256(hcur, d, a, Wl, bl, hnext, readout, prof, s);
+      hipError_t e = launch_layer256(hcur, d, a, Wl, bl, hnext, readout, l, prof, s);
       if (e != hipSuccess) return e;
     } else if (a.allow_fused && fused_layer_supported(d, a.H, a.bf16)) {
       if (prof) prof->begin(kFamFused, s);

@@ -751,13 +751,14 @@ __global__ __launch_bounds__(256) void build_desc_sorted_kernel(
 // before this round's barrier; a few hundred thousand entries at most), ...
 constexpr int kScanPer = 8;
 __global__ __launch_bounds__(1024) void heavy_scan_kernel(const int* __restrict__ heavy_cnt, int* __restrict__ heavy_off,
-                                                          const int* __restrict__ node_off, int C,
+                                                          int* __restrict__ ctr, const int* __restrict__ node_off, int C,
                                                           const int* __restrict__ status) {
   __shared__ int wsum[2][16];
   if (status[0] != 0) return;
   const int ntot = node_off[C];
   const int n = 2 * ((ntot + kBM - 1) / kBM);
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (t < 2 * kHeavyCtrInts) ctr[t] = 0;         // the pre-pass's work counters
   auto load = [&](int i, int (&x)[kScanPer]) {   // i is a multiple of 8: whole 16-byte pieces where they lie below n
 #pragma unroll
     for (int q = 0; q < kScanPer; q += 4) {
@@ -849,10 +850,6 @@ __global__ __launch_bounds__(256) void heavy_compact_kernel(const int* __restric
   }
 }
 
-__global__ __launch_bounds__(256) void clear_heavy_ctr_kernel(int* __restrict__ ctr) {
-  if (threadIdx.x < kHeavyCtrInts) ctr[threadIdx.x] = 0;
-}
-
 // Means of the rows with more than kSlots neighbours (the pre-pass), from the list the two kernels above
 // leave.  LPR = d / 8 lanes (16 bytes each) serve a row: they fetch sixteen neighbour ids (eight at d = 64) with
 // one load, hand them round, and keep eight neighbour rows in flight; the rows are added in ascending list order
@@ -875,11 +872,13 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_means_kernel(
     const u16* __restrict__ h, const int* __restrict__ in_rp, const int* __restrict__ in_ci,
     const int* __restrict__ out_rp, const int* __restrict__ out_ci, const unsigned* __restrict__ heavy_list,
     const int* __restrict__ heavy_off, u16* __restrict__ h_in, u16* __restrict__ h_out, int* __restrict__ ctr,
-    const int* __restrict__ node_off, int C, const int* __restrict__ status) {
+    int* __restrict__ other_ctr, const int* __restrict__ node_off, int C, const int* __restrict__ status) {
   constexpr int NSG = 64 / LPR;              // rows a wave serves at a time
   constexpr int kIds = LPR >= 16 ? 16 : 8;   // neighbour ids a lane group fetches with one load
   __shared__ int claimed[2];
   if (status[0] != 0) return;
+  // the counters of the launch before this one are at rest: cleared for the launch after it
+  if (blockIdx.x == 0) other_ctr[threadIdx.x] = 0;
   const int ntot = node_off[C];
   const int ntiles = (ntot + kBM - 1) / kBM;
   const v4u* __restrict__ h4 = reinterpret_cast<const v4u*>(h);
@@ -892,6 +891,9 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_means_kernel(
   const int r0 = heavy_off[2 * t_begin], r1 = heavy_off[2 * t_end];
   const int per_batch = n_waves * NSG * kHeavyGroups;
   const int n_batches = (r1 - r0 + per_batch - 1) / per_batch;
+  // No more workgroups than batches: each claims at least two, and 224 of them that find nothing on one counter took
+  // most of a launch over a few thousand rows (11.4 -> 6.8 us).
+  if ((int)(blockIdx.x >> 3) >= n_batches) return;
   int* my_ctr = ctr + xcd * 32;
   if (threadIdx.x == 0) {
     claimed[0] = atomicAdd(my_ctr, 1);
@@ -1024,26 +1026,28 @@ hipError_t launch_build_desc_sorted(const GnnArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(build_desc_sorted_kernel, dim3(a.n_cu * 8), dim3(256), 0, s, a.in_rowptr, a.in_col, a.out_rowptr,
                      a.out_col, static_cast<v4i*>(a.desc[0]), static_cast<v4i*>(a.desc[1]), a.heavy[0], a.heavy[1],
                      a.heavy_cnt, a.node_off, a.n_cand, a.status);
-  hipLaunchKernelGGL(heavy_scan_kernel, dim3(1), dim3(1024), 0, s, a.heavy_cnt, a.heavy_off, a.node_off, a.n_cand,
-                     a.status);
+  hipLaunchKernelGGL(heavy_scan_kernel, dim3(1), dim3(1024), 0, s, a.heavy_cnt, a.heavy_off, a.heavy_ctr, a.node_off,
+                     a.n_cand, a.status);
   hipLaunchKernelGGL(heavy_compact_kernel, dim3(a.n_cu * 8), dim3(256), 0, s, a.heavy[0], a.heavy[1], a.heavy_cnt,
                      a.heavy_off, a.heavy_list, a.node_off, a.n_cand, a.status);
   return hipGetLastError();
 }
 
-hipError_t launch_heavy_means(const void* h, int d, const GnnArgs& a, hipStream_t s) {
+hipError_t launch_heavy_means(const void* h, int d, const GnnArgs& a, int turn, hipStream_t s) {
   if (d != 256 && d != 64) return hipErrorInvalidValue;
   const int grid = ((a.n_cu + 7) / 8) * 8 * kHeavyWgs;
   const u16* hh = static_cast<const u16*>(h);
-  hipLaunchKernelGGL(clear_heavy_ctr_kernel, dim3(1), dim3(256), 0, s, a.heavy_ctr);
+  static_assert(kHeavyThreads == kHeavyCtrInts, "one thread of a workgroup clears one counter word");
+  int* ctr = a.heavy_ctr + (turn & 1) * kHeavyCtrInts;
+  int* other = a.heavy_ctr + (~turn & 1) * kHeavyCtrInts;
   if (d == 256)
     hipLaunchKernelGGL(heavy_means_kernel<32>, dim3(grid), dim3(kHeavyThreads), 0, s, hh, a.in_rowptr, a.in_col,
                        a.out_rowptr, a.out_col, a.heavy_list, a.heavy_off, static_cast<u16*>(a.agg[0]),
-                       static_cast<u16*>(a.agg[1]), a.heavy_ctr, a.node_off, a.n_cand, a.status);
+                       static_cast<u16*>(a.agg[1]), ctr, other, a.node_off, a.n_cand, a.status);
   else
     hipLaunchKernelGGL(heavy_means_kernel<8>, dim3(grid), dim3(kHeavyThreads), 0, s, hh, a.in_rowptr, a.in_col,
                        a.out_rowptr, a.out_col, a.heavy_list, a.heavy_off, static_cast<u16*>(a.agg[0]),
-                       static_cast<u16*>(a.agg[1]), a.heavy_ctr, a.node_off, a.n_cand, a.status);
+                       static_cast<u16*>(a.agg[1]), ctr, other, a.node_off, a.n_cand, a.status);
   return hipGetLastError();
 }
 
