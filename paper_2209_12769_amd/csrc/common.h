@@ -154,21 +154,26 @@ hipError_t launch_attention_scores(const GnnArgs& a, const void* z, const float*
 hipError_t launch_attention_aggregate(const GnnArgs& a, const void* z, const float* bias, void* out, hipStream_t s);
 bool gnn_shape_supported(int F, int H, int L);
 // gnn_fused.hip: one layer with both neighbour means folded into the A-tile load (bf16).
-bool fused_layer_supported(int d, int H, int bf16);
+bool fused_layer_supported(int d, int H, int bf16);   // asked after wave_layer_supported and layer256_supported
 hipError_t launch_fused_layer(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
                               hipStream_t s);
+
+// gnn_wave.hip: the same for d in {16, 32, 64, 128} and H in {32, 64, 128} (d = 128: H > 32): all of W in LDS, a wave per 32 rows.
+bool wave_layer_supported(int d, int H, int bf16);
+hipError_t launch_wave_layer(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
+                             hipStream_t s);
 
 // gnn_layer256.hip: wave-specialised fused layer for H = 256, d = 256 or 64 (bf16); uses a.agg[] for rows with long lists.
 bool layer256_supported(int d, int H, int bf16);
 hipError_t launch_build_desc(const GnnArgs& a, hipStream_t s);
 // readout: the layer leaves the readout's chunk sums in a.ro_part instead of its rows in out (needs
 // launch_chunk_first on the same batch before)
+// turn: number of the layer (launches of one pass use the pre-pass's two sets of counters in turn)
 hipError_t launch_layer256(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
                            bool readout, int turn, Profiler* prof, hipStream_t s);
 hipError_t launch_chunk_first(const GnnArgs& a, hipStream_t s);
 // gnn_layer256w.hip: the same layer (five gather slots) with sixteen waves per workgroup; descriptors and
 // pre-pass means as for launch_layer256
-// turn: number of the layer (launches of one pass use the pre-pass's two sets of counters in turn)
 hipError_t launch_build_desc_sorted(const GnnArgs& a, hipStream_t s);
 // Means of the rows with more than five neighbours (listed by launch_build_desc_sorted), written at the rows'
 // own places in a.agg[0] (predecessors) and a.agg[1] (successors); h [rows, d], d = 256 or 64, bf16.

@@ -760,6 +760,11 @@ hipError_t mean_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, const vo
       const bool readout = l == a.L - 1 && readout_in_last_layer(a);   // then hnext is not written
       hipError_t e = launch_layer256(hcur, d, a, Wl, bl, hnext, readout, l, prof, s);
       if (e != hipSuccess) return e;
+    } else if (a.allow_fused && wave_layer_supported(d, a.H, a.bf16)) {
+      if (prof) prof->begin(kFamFused, s);
+      hipError_t e = launch_wave_layer(hcur, d, a, Wl, bl, hnext, s);
+      if (prof) prof->end(s);
+      if (e != hipSuccess) return e;
     } else if (a.allow_fused && fused_layer_supported(d, a.H, a.bf16)) {
       if (prof) prof->begin(kFamFused, s);
       hipError_t e = launch_fused_layer(hcur, d, a, Wl, bl, hnext, s);
