@@ -755,7 +755,6 @@ dc_status dc_contract_graphs(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_gr
   if (n_cand > 0 && (!cand_graph || !cand_off || !group_id)) return fail(ctx, DC_ERR_INVALID_ARG, "null candidate array");
   hipStream_t s = static_cast<hipStream_t>(stream);
   out->n_cand = n_cand;
-  hipLaunchKernelGGL(reset_status_kernel, dim3(1), dim3(1), 0, s, ctx->status);
   BatchView v;
   v.node_off = out->node_off;
   v.edge_off = out->edge_off;
@@ -839,7 +838,6 @@ dc_status dc_eval_candidates(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_gr
   if (n_cand == 0) return DC_OK;
   if (!cand_graph || !cand_off || !group_id || !pred) return fail(ctx, DC_ERR_INVALID_ARG, "null array");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(reset_status_kernel, dim3(1), dim3(1), 0, s, ctx->status);
   dc_status st = do_contract(ctx, n_cand, cand_graph, cand_off, group_id, ctx->ib, s);
   if (st != DC_OK) return st;
   return do_forward(ctx, n_cand, ctx->ib, pred, s);
@@ -957,7 +955,6 @@ dc_status dc_cost_candidates(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_gr
   if (n_cand == 0) return DC_OK;
   if (!cand_graph || !cand_off || !group_id || !cost) return fail(ctx, DC_ERR_INVALID_ARG, "null array");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(reset_status_kernel, dim3(1), dim3(1), 0, s, ctx->status);
   st = do_contract(ctx, n_cand, cand_graph, cand_off, group_id, ctx->ib, s, false);
   if (st != DC_OK) return st;
   st = do_module_times(ctx, n_cand, cand_graph, cand_off, ctx->ib, ctx->m_op_time, ctx->m_ar_size, s);
@@ -1164,7 +1161,6 @@ dc_status dc_fused_op_batch(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_gra
   if (n_cand == 0) return DC_OK;
   if (!cand_graph || !cand_off || !group_id) return fail(ctx, DC_ERR_INVALID_ARG, "null candidate array");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(reset_status_kernel, dim3(1), dim3(1), 0, s, ctx->status);
   st = do_contract(ctx, n_cand, cand_graph, cand_off, group_id, ctx->ib, s, false);
   if (st != DC_OK) return st;
   Profiler* prof = ctx->prof.on ? &ctx->prof : nullptr;

@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kCT) void contract_kernel(BaseGraphs bg, int C, con
   }
 }
 
-// Validates the candidate list and scans the base edge counts (one workgroup).
+// Clears the call's status, validates the candidate list and scans the base edge counts (one workgroup).
 __global__ __launch_bounds__(1024) void prep_kernel(BaseGraphs bg, int C, const int* cand_graph, const int* cand_off,
                                                      int* tmp_eoff, long long max_base_nodes,
                                                      long long max_base_edges, int* status, int* big_order,
@@ -446,6 +446,7 @@ __global__ __launch_bounds__(1024) void prep_kernel(BaseGraphs bg, int C, const 
   __shared__ int wsum[16];
   const int t = threadIdx.x, T = blockDim.x;
   int bad = 0;
+  if (t == 0) status[0] = 0;                  // a call begins here (a launch of its own for this was 4 us)
   for (int c = t; c < C; c += T) {
     const int b = cand_graph[c];
     int e = 0;
@@ -633,7 +634,10 @@ int contract_working_set_bytes(int n_nodes, int n_edges) { return slab_layout(n_
 __global__ void reset_status_kernel(int* status) { status[0] = 0; }
 
 hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t s) {
-  if (a.n_cand <= 0) return hipSuccess;
+  if (a.n_cand <= 0) {
+    hipLaunchKernelGGL(reset_status_kernel, dim3(1), dim3(1), 0, s, a.status);
+    return hipGetLastError();
+  }
   const int C = a.n_cand;
   if (prof) prof->begin(kFamPrep, s);
   const int need = slab_layout(a.max_graph_nodes, a.max_graph_edges).total;
@@ -657,7 +661,7 @@ hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t 
   // One workgroup per candidate fills the chip once there are eight of them per CU.  With fewer candidates several
   // share one, down to one round of 4 x 256 feature items each (7 candidates of 1.4 k groups and F = 64: 111 us with
   // one workgroup each, 9.8 us with 23).
-  const int rounds = ceil_div(a.max_graph_nodes * (a.F >> 2), 4 * 256);
+  const int rounds = ceil_div(a.max_graph_nodes * (a.F > 4 ? a.F >> 2 : 1), 4 * 256);
   const int want = ceil_div(8 * a.n_cu, C);
   const dim3 fgrid(C, want < rounds ? want : (rounds > 0 ? rounds : 1));
   if (a.bf16)
