@@ -241,8 +241,6 @@ dc_status run_search(dc_ctx* ctx, const SearchView& g, int32_t graph, const dc_s
   int* d_opn = mem.take<int>(opn.size(), &e);
   int* pool = mem.take<int>((size_t)slots * N, &e);
   int* children = mem.take<int>((size_t)C * N, &e);
-  int* d_parent = mem.take<int>(P, &e);
-  int* d_pairs = mem.take<int>(2 * (size_t)(C + 1), &e);
   int* cand_graph = mem.take<int>(C, &e);
   int* cand_off = mem.take<int>(C + 1, &e);
   float* d_cost = mem.take<float>(C, &e);
@@ -253,6 +251,7 @@ dc_status run_search(dc_ctx* ctx, const SearchView& g, int32_t graph, const dc_s
     (void)hipGetLastError();
     return e == hipErrorOutOfMemory ? DC_ERR_OOM : DC_ERR_HIP;
   }
+  // pinned memory: the kernels read the few parents and pairs of a step where the host wrote them, without copies
   float* h_cost = static_cast<float*>(mem.pinned);
   int* h_parent = reinterpret_cast<int*>(h_cost + C);
   int* h_pairs = h_parent + P;
@@ -304,8 +303,7 @@ dc_status run_search(dc_ctx* ctx, const SearchView& g, int32_t graph, const dc_s
     }
     const int np = (int)used.size(), nc = 2 * np;
     for (int i = 0; i < np; ++i) h_parent[i] = used[i];
-    if (hipMemcpyAsync(d_parent, h_parent, np * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess) return DC_ERR_HIP;
-    hipLaunchKernelGGL(mutate_kernel, dim3(nc), dim3(kMutateThreads), lds, s, pool, d_parent, N, (int)edges.size(), d_edges,
+    hipLaunchKernelGGL(mutate_kernel, dim3(nc), dim3(kMutateThreads), lds, s, pool, h_parent, N, (int)edges.size(), d_edges,
                        (int)arn.size(), d_arn, (int)opn.size(), d_opn, op_draw, edges_in_lds, (unsigned long long)p.seed,
                        (unsigned long long)step, p.beta, children);
     if (hipGetLastError() != hipSuccess) return DC_ERR_HIP;
@@ -358,12 +356,9 @@ dc_status run_search(dc_ctx* ctx, const SearchView& g, int32_t graph, const dc_s
       ++n_pairs;
     }
     if (n_pairs > 0) {
-      if (hipMemcpyAsync(d_pairs, h_pairs, 2 * (size_t)n_pairs * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess)
-        return DC_ERR_HIP;
-      hipLaunchKernelGGL(keep_kernel, dim3(n_pairs), dim3(256), 0, s, children, pool, N, d_pairs);
+      hipLaunchKernelGGL(keep_kernel, dim3(n_pairs), dim3(256), 0, s, children, pool, N, h_pairs);
       if (hipGetLastError() != hipSuccess) return DC_ERR_HIP;
-      // h_pairs is reused next step: the copy above must have been taken before then; the next
-      // step synchronises on its costs before it writes h_pairs again
+      // h_pairs is reused next step, which synchronises on its costs before it writes it again
     }
     for (int i = 0; i < np; ++i) free_slots.push_back(used[i]);
     while ((long long)queue.size() > (long long)p.max_queue) {
