@@ -342,7 +342,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
 // in memory; MFMA block j of a wave takes columns 2l + j of its 64 (l = lane mod 32), so one 8-byte
 // LDS read feeds both of a lane's B operands and results leave as 8-byte stores.
 template <int BN, int WM>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) void update32_kernel(const float* __restrict__ A0, const float* __restrict__ A1,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(BN == 128 ? 4 : 1, 8))) void update32_kernel(const float* __restrict__ A0, const float* __restrict__ A1,
                                                        const float* __restrict__ A2, int d, int nseg,
                                                        const float* __restrict__ Wf, const float* __restrict__ bias,
                                                        float* __restrict__ out, int H,
@@ -360,9 +360,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   const int wm = wave / (BN / WN), wn = wave % (BN / WN);
   const int l32 = lane & 31, lh = lane >> 5;
   const int ntot = node_off[C];
-  if (few_tiles(ntot, H, few)) {
-    update32_few(A0, A1, A2, d, nseg, Wf, bias, out, H, ntot);
-    return;
+  if constexpr (BN == 128) {               // beside the wider tile's registers it costs that one 5 %
+    if (few_tiles(ntot, H, few)) {
+      update32_few(A0, A1, A2, d, nseg, Wf, bias, out, H, ntot);
+      return;
+    }
   }
   const int nct = H / BN;
   const int ntiles = ((ntot + BM - 1) / BM) * nct;
