@@ -428,6 +428,18 @@ __device__ __forceinline__ int block_exscan_lines(const int* in, int* out, int n
   return carry;
 }
 
+// The part of `items` (each of `unit` work places) that this workgroup's XCD takes: workgroups are dealt round-robin over
+// the eight XCDs, each with its own L2, so one contiguous eighth each keeps the rows that its rows' lists name in one L2
+// (dealt row by row, every XCD fetches nearly every row).  The grid is a multiple of eight workgroups.
+struct XcdRange {
+  long long begin, end, stride;      // this thread's first place, the part's end, and the step
+};
+__device__ __forceinline__ XcdRange xcd_range(long long items, int unit) {
+  const int xcd = blockIdx.x & 7;
+  const long long lo = items * xcd / 8 * unit, hi = items * (xcd + 1) / 8 * unit;
+  return {lo + (long long)(blockIdx.x >> 3) * blockDim.x + threadIdx.x, hi, (long long)(gridDim.x >> 3) * blockDim.x};
+}
+
 static inline __host__ __device__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace dc
