@@ -969,7 +969,7 @@ __global__ __launch_bounds__(kHeavyThreads) void heavy_means_kernel(
       v4u o;
 #pragma unroll
       for (int w = 0; w < 4; ++w) o[w] = pack_bf16x2(a8[2 * w] * sc, a8[2 * w + 1] * sc);
-      reinterpret_cast<v4u*>(cdir ? h_out : h_in)[(size_t)cv * LPR + ll] = o;
+      __builtin_nontemporal_store(o, reinterpret_cast<v4u*>(cdir ? h_out : h_in) + (size_t)cv * LPR + ll);   // L2 is for the neighbours' rows (2 % of the launch)
     }
     if (threadIdx.x == 0) claimed[par] = after;
     __syncthreads();
