@@ -105,20 +105,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kBf16 ? kAt
   const int LPR = H >> 3, LPH = LPR / K;
   const int lane = threadIdx.x & 63, sg = lane / LPR, ll = lane - sg * LPR;
   const int head = ll / LPH, li = ll - head * LPH, hb = lane - li;      // hb: the first of the head's lanes
-  const int rows_per_wave = 64 / LPR, iters = rows_per_wave >= 16 ? 2 : 4, per_claim = rows_per_wave * iters;
+  const int rows_per_wave = 64 / LPR;
   // Workgroups are dealt round-robin to the eight XCDs, each with its own L2: every XCD takes one contiguous eighth of
   // the rows, and its waves claim them in order, a few at a time, through a counter.  Dealt by a fixed stride the waves
   // drift apart, the rows in work span more than the L2, and neighbours' rows come from memory several times.
   const int xcd = blockIdx.x & 7;
   const int r_begin = (int)((long long)ntot * xcd / 8), r_end = (int)((long long)ntot * (xcd + 1) / 8);
-  const int n_claims = (r_end - r_begin + per_claim - 1) / per_claim;
   const int n_waves = (int)((gridDim.x >> 3) * (blockDim.x >> 6));
+  // Claims of four rounds of rows (two where a round has 16) where every wave has sixteen rounds or more; below that
+  // nothing drifts far and coarse claims leave waves idle at the end (80 k rows, H = 256: 269 us a pass with claims, 187
+  // without), so the waves take single rounds in turn.
+  const bool claims = r_end - r_begin >= 16 * n_waves * rows_per_wave;
+  const int iters = !claims ? 1 : (rows_per_wave >= 16 ? 2 : 4);
+  const int per_claim = rows_per_wave * iters;
+  const int n_claims = (r_end - r_begin + per_claim - 1) / per_claim;
   int* my_ctr = ctr + xcd * 32;
   constexpr int U = kBf16 ? kAttRows : 4;        // rows requested together
   int cur = (int)((blockIdx.x >> 3) * (blockDim.x >> 6)) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   while (cur < n_claims) {
-    int after = 0;
-    if (lane == 0) after = n_waves + atomicAdd(my_ctr, 1);       // the first claim of a wave is its own number
+    int after = cur + n_waves;                                   // the first claim of a wave is its own number
+    if (claims && lane == 0) after = n_waves + atomicAdd(my_ctr, 1);
     const int v0 = r_begin + cur * per_claim, nrows = min(per_claim, r_end - v0);
     // bounds of all rows of the claim (lane i: of row v0 + i), then the first 64 neighbour numbers of each direction
     const int rpi = in_rp[min(v0 + min(lane, per_claim), r_end)], rpo = out_rp[min(v0 + min(lane, per_claim), r_end)];
