@@ -119,8 +119,9 @@ __global__ __launch_bounds__(kWT) void wave_layer_kernel(const u16* __restrict__
   };
   auto load_ids = [&](const int* ci, Lists& l) __attribute__((always_inline)) {
     const int e0 = __builtin_amdgcn_readlane(l.rp, 0), e1 = __builtin_amdgcn_readlane(l.rp, kTR);
-    const int* q0 = e1 > e0 ? ci + min(e0 + lane, e1 - 1) : in_rp;             // a tile without neighbours: number 0
-    const int* q1 = e1 > e0 ? ci + min(e0 + 64 + lane, e1 - 1) : in_rp;
+    // a tile without neighbours takes number 0, which node_off begins with (a caller's row pointers may begin anywhere)
+    const int* q0 = e1 > e0 ? ci + min(e0 + lane, e1 - 1) : node_off;
+    const int* q1 = e1 > e0 ? ci + min(e0 + 64 + lane, e1 - 1) : node_off;
     l.id0 = *q0;
     l.id1 = *q1;
   };

@@ -53,3 +53,32 @@ def test_equals_the_separate_kernels_bit_for_bit(B, F, H, L):
         assert np.array_equal(fused, plain), (n, kind, C, np.abs(fused - plain).max())
         want = orc.evaluate_parallel(w, False, 8, np.arange(1))
         assert abs(fused[0] - want[0]) <= TOL * abs(want[0]), (n, kind, fused[0], want[0])
+
+
+@pytest.mark.parametrize("F,H,L", [(16, 32, 2), (32, 128, 2), (64, 64, 2), (128, 128, 1)])
+def test_row_pointers_that_do_not_begin_at_zero(B, F, H, L):
+    """A caller's batch may keep its edges anywhere in the edge arrays.  The first tiles have no neighbours at all: what
+    they request in their place must be a row of the batch, whatever number the row pointers begin with."""
+    import torch
+    sparse = _graph(90, "sparse", F)
+    X = np.random.default_rng(5).random((100, F), dtype=np.float32)
+    lone = wl.BaseGraph(100, 100, np.zeros(101, np.int32), np.zeros(0, np.int32), X)
+    graphs = [lone, sparse, lone]
+    w = wl.with_time_like_head(wl.custom("moved", wl.ModelSpec(F, H, L, "bf16"), graphs,
+                                         [np.arange(g.n, dtype=np.int32)[None] for g in graphs], seed=4))
+    ev = B.evaluator_for(w)
+    nb, eb = sum(g.n for g in graphs), sum(g.e for g in graphs)
+    b = ev.contract_graphs(ev.to_device(w.cand_graph), ev.to_device(w.cand_off), ev.to_device(w.group_id),
+                           ev.alloc_batch(w.n_cand, nb, nb, eb))
+    want = ev.gnn_forward(b).cpu().numpy()
+    assert ev.check() == B.DC_OK
+    for pad in (1, nb + 7, 1 << 20):
+        rps = [x + pad for x in (b.out_rowptr, b.in_rowptr)]
+        cols = [torch.cat([torch.zeros(pad, dtype=torch.int32, device=ev.device), x]) for x in (b.out_col, b.in_col)]
+        c = B.DcBatch(w.n_cand, nb, eb + pad, b.node_off.data_ptr(), b.edge_off.data_ptr(), b.new_id.data_ptr(),
+                      rps[0].data_ptr(), cols[0].data_ptr(), rps[1].data_ptr(), cols[1].data_ptr(), b.Xc.data_ptr())
+        moved = B.DeviceBatch(c, b.node_off, b.edge_off, b.new_id, rps[0], cols[0], rps[1], cols[1], b.Xc)
+        got = ev.gnn_forward(moved).cpu().numpy()
+        assert ev.check() == B.DC_OK
+        assert np.array_equal(got, want), pad
+    ev.close()
