@@ -287,6 +287,12 @@ dc_status dc_last_fused_ops(dc_ctx* ctx, int64_t* n_fused_ops, int64_t* n_rows, 
  * `stream`.                                                                                 */
 dc_status dc_last_fused_op_repeats(dc_ctx* ctx, int64_t* n_repeats, void* stream);
 
+/* How many modules this context has simulated node by node so far, in dc_simulate,
+ * dc_cost_candidates and dc_search: those in which an op waits for an all-reduce or a time is
+ * negative, those of more than 16384 nodes, and those whose order did not settle (the same costs,
+ * but slower; for tests and measurements).  Synchronises `stream`.                          */
+dc_status dc_walked_modules(dc_ctx* ctx, int64_t* n_modules, void* stream);
+
 /* Backtracking search over fusion strategies (Alg. 1, Sec. 4) with dc_cost_candidates as Cost().
  * A strategy is a labelling of the nodes of base graph `graph`; the search starts from the
  * all-singleton labelling H_in with H_opt = H_in.  Per step up to `parents` entries leave the

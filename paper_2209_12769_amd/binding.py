@@ -107,6 +107,7 @@ def lib():
         L.dc_cost_candidates.argtypes = [vp, i32, vp, vp, vp, C.c_float, C.c_float, vp, vp]
         L.dc_last_fused_ops.argtypes = [vp, C.POINTER(C.c_int64), C.POINTER(C.c_int64), C.POINTER(C.c_int64), vp]
         L.dc_last_fused_op_repeats.argtypes = [vp, C.POINTER(C.c_int64), vp]
+        L.dc_walked_modules.argtypes = [vp, C.POINTER(C.c_int64), vp]
         L.dc_search.argtypes = [vp, i32, C.POINTER(DcSearchParams), vp, C.POINTER(DcSearchResult), vp]
         L.dc_num_params.argtypes = [vp]
         L.dc_num_params.restype = C.c_int64
@@ -125,7 +126,7 @@ def lib():
         for n in ("dc_create", "dc_destroy", "dc_set_weights", "dc_set_attention_weights", "dc_set_base_graphs", "dc_contract_graphs",
                   "dc_gnn_forward", "dc_eval_candidates", "dc_simulate", "dc_check", "dc_last_totals", "dc_profile_begin",
                   "dc_profile_end", "dc_set_profile", "dc_module_times", "dc_cost_candidates", "dc_last_fused_ops",
-                  "dc_last_fused_op_repeats", "dc_search",
+                  "dc_last_fused_op_repeats", "dc_walked_modules", "dc_search",
                   "dc_train_begin", "dc_select_kernels", "dc_fused_op_batch", "dc_loss_gradients", "dc_train_step", "dc_get_weights"):
             getattr(L, n).restype = i32
         _lib = L
@@ -204,6 +205,12 @@ def dc_last_fused_ops(ctx, stream: int = 0) -> Tuple[int, int, int, int]:
 def dc_last_fused_op_repeats(ctx, stream: int = 0) -> Tuple[int, int]:
     n = C.c_int64()
     st = lib().dc_last_fused_op_repeats(ctx, C.byref(n), stream)
+    return st, n.value
+
+
+def dc_walked_modules(ctx, stream: int = 0) -> Tuple[int, int]:
+    n = C.c_int64()
+    st = lib().dc_walked_modules(ctx, C.byref(n), stream)
     return st, n.value
 
 
@@ -477,6 +484,11 @@ class Evaluator:
     def last_fused_op_repeats(self) -> int:
         st, n = dc_last_fused_op_repeats(self.ctx, self._stream())
         self._ok(st, "dc_last_fused_op_repeats")
+        return n
+
+    def walked_modules(self) -> int:
+        st, n = dc_walked_modules(self.ctx, self._stream())
+        self._ok(st, "dc_walked_modules")
         return n
 
     def check(self) -> int:

@@ -50,7 +50,7 @@ struct dc_ctx {
   float* ro_part = nullptr; // chunk sums of the readout when the last layer forms them
   int* ro_first = nullptr;
   int* status = nullptr;    // [2]
-  int* totals = nullptr;    // [2]
+  int* totals = nullptr;    // contracted nodes, edges; [2..3] 64-bit count of the modules that were walked
   int* h_pinned = nullptr;  // [4] pinned host mirror for status / totals
   // weights
   void* W = nullptr;
@@ -106,7 +106,7 @@ const char* const kFamilyNames[kFamCount] = {"prep_scan", "contract", "finalize"
 
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
-constexpr int kSimLdsBytes = 80 * 1024;   // two simulator waves per CU
+constexpr int kSimLdsBytes = 80 * 1024;   // larger modules are walked in global memory, by more waves per CU
 
 struct Arena {
   size_t off = 0;
@@ -347,6 +347,7 @@ dc_status do_simulate(dc_ctx* ctx, int32_t n_cand, const BatchView& in, const fl
   a.scratch_stride = ctx->sim_stride;
   a.n_slices = ctx->sim_slices;
   a.n_cu = ctx->n_cu;
+  a.walked = reinterpret_cast<unsigned long long*>(ctx->totals + 2);
   a.status = ctx->status;
   if (ctx->prof.on) ctx->prof.begin(kFamSimulate, s);
   hipError_t e = launch_simulate(a, s);
@@ -1011,6 +1012,16 @@ dc_status dc_last_fused_op_repeats(dc_ctx* ctx, int64_t* n_repeats, void* stream
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(ctx, e, "dc_last_fused_op_repeats");
   *n_repeats = ctx->every_fused_op ? 0 : ctx->h_pinned[8 + 5];
+  return DC_OK;
+}
+
+dc_status dc_walked_modules(dc_ctx* ctx, int64_t* n_modules, void* stream) {
+  if (!ctx || !n_modules) return DC_ERR_INVALID_ARG;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  hipError_t e = hipMemcpyAsync(ctx->h_pinned + 8, ctx->totals + 2, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) return hip_fail(ctx, e, "dc_walked_modules");
+  memcpy(n_modules, ctx->h_pinned + 8, sizeof(int64_t));
   return DC_OK;
 }
 

@@ -196,11 +196,12 @@ struct SimArgs {
   const float* ar_size;     // [Ntot] tensor size of all-reduce nodes, negative for computation nodes
   float ar_c, ar_d;         // T = ar_c * size + ar_d
   float* cost;              // [n_cand]
-  int lds_bytes;            // LDS per wave of the general walk
+  int lds_bytes;            // largest working set of a module that is walked in LDS
   char* scratch;            // slices of global memory for the modules that do not fit it
   size_t scratch_stride;
   int n_slices;
   int n_cu;
+  unsigned long long* walked;   // counts the modules that were walked node by node, or null
   int* status;
 };
 size_t simulate_scratch_bytes(long long max_graph_nodes, long long max_graph_edges, int n_slices);

@@ -15,14 +15,15 @@
 // implementation.
 //
 //   simulate_order_kernel    modules whose execution times are not negative and whose all-reduces
-//                            have no successors, i.e. every module that comes of profiled data: the
-//                            order of the nodes does not depend on the times there and is found by
-//                            all nodes at once; the times are added along it
-//   simulate_general_kernel  the others: one wave walks the module node by node, with its arrays in
-//                            LDS or in a slice of global memory; the lanes release the successors
-//                            of the current node together (lists are duplicate free, so no two
-//                            lanes touch one node) and append the newly ready ones in lane order =
-//                            ascending index
+//                            have no successors: the order of the nodes does not depend on the times
+//                            there and is found by all nodes at once; the times are added along it
+//   simulate_walk_kernel     the others, where an op waits for an all-reduce (a weight update behind
+//                            its tensor) or a time is negative: one wave walks the module node by
+//                            node, with its arrays in LDS; the lanes release the successors of the
+//                            current node together (lists are duplicate free, so no two lanes touch
+//                            one node) and append the newly ready ones in lane order = ascending
+//                            index
+//   simulate_walk_global_kernel  those too large for LDS, in slices of global memory
 #include <math.h>
 
 #include <mutex>
@@ -32,7 +33,7 @@
 namespace dc {
 namespace {
 
-// The arrays of a module of the general kernel in global memory ...
+// The arrays of a module that is walked, in global memory ...
 __host__ __device__ inline size_t sim_bytes(long long G, long long E) {
   // ready[G] f64 | val[G] f32 | dep[G] i32 | queue[G] i32 | rp[G+1] i32 | ci[E] u16 (padded to 8 bytes)
   return (size_t)G * (8 + 4 + 4 + 4) + (size_t)(G + 1) * 4 + (((size_t)E * 2 + 7) & ~(size_t)7) + 8;
@@ -58,7 +59,7 @@ struct SimTypes<true> {           // LDS
   static constexpr int kAr = 1 << 15;
 };
 
-// Modules the first kernel leaves to the second carry this pattern in their cost: a NaN that no arithmetic gives.
+// Modules that the first kernel leaves to the walk carry this pattern in their cost: a NaN that no arithmetic gives.
 constexpr unsigned kLeft = 0x7FC5A11Du;
 
 extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
@@ -82,7 +83,7 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 // four dependent LDS round trips each (about 1000 cycles a node).  The number of iterations is the depth to which
 // neighbouring chains interleave, not the length of the module: from the index order as the first guess 4 to 7 on the
 // contracted modules of a 24-block transformer (1.4 k nodes, 1.3 k of them one after another), 13 on the unfused
-// module (6.6 k nodes), 20 on power-law graphs.  What takes kMostRounds is left to the general kernel.
+// module (6.6 k nodes), 20 on power-law graphs.  What takes kMostRounds is left to the walk.
 //
 // A thread owns NPT nodes and keeps their predecessors (three or four each; what longer lists hold beyond three lies
 // in LDS, or is read from memory again once that is full) and keys in registers; LDS holds the places, the counters of
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(T) void simulate_order_kernel(
     const int* __restrict__ node_off, const int* __restrict__ out_rp, const int* __restrict__ in_rp,
     const int* __restrict__ in_ci, const float* __restrict__ op_time, const float* __restrict__ ar_size, int C,
     float ar_c, float ar_d, float* __restrict__ cost, int fewest, int last, const int* __restrict__ status) {
-  // the modules of `fewest` to T * NPT nodes; the last class to be launched leaves the larger ones to the general kernel
+  // the modules of `fewest` to T * NPT nodes; the last class to be launched leaves the larger ones to the walk
   typedef OrderLds<T, NPT> Lds;
   constexpr int kCap = Lds::kCap, kWaves = T / 64;
   __shared__ int wsum[kWaves], sh_min[2][2], sh_src[NPT][kWaves], n_extra;
@@ -472,132 +473,205 @@ hipError_t launch_order(const SimArgs& a, int fewest, bool last, hipStream_t s) 
   return hipGetLastError();
 }
 
-// The workgroup is one wave.  LDS operations of a wave are carried out in issue order, so
-// between a lane's write and another lane's later read only the compiler has to be kept from
-// reordering; global memory needs the writes to have completed.
+// ---------------------------------------------------------------------------------------------------
+// The walk of a module node by node, by one wave.  A chain of dependent accesses, about 800 cycles a node in LDS, so
+// what counts is how many modules a CU walks at a time.
+// ---------------------------------------------------------------------------------------------------
+// LDS operations of a wave are carried out in issue order, so between a lane's write and another lane's later read only
+// the compiler has to be kept from reordering; global memory needs the writes to have completed (there the workgroup
+// is the one wave).
 template <bool kLds>
 __device__ __forceinline__ void sync_wave() {
   if (kLds) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   else __syncthreads();
 }
 
+// base: the wave's working set, of sim_lds_bytes / sim_bytes of the module's G nodes and E edges
 template <bool kLds>
-__global__ __launch_bounds__(64) void simulate_general_kernel(const int* __restrict__ node_off,
-                                                               const int* __restrict__ out_rp,
-                                                               const int* __restrict__ out_ci,
-                                                               const int* __restrict__ in_rp,
-                                                               const float* __restrict__ op_time,
-                                                               const float* __restrict__ ar_size, int C, float ar_c,
-                                                               float ar_d, float* __restrict__ cost, char* gscratch,
-                                                               size_t gstride, int lds_bytes, int last, int* status) {
-  // The modules that simulate_order_kernel left.  kLds: those whose arrays fit lds_bytes of LDS; !kLds: the others,
-  // in global memory.  The last of the two to be launched reports a module that fits neither.
+__device__ __forceinline__ void walk_module(char* base, int n0, int G, int e0, int E, const int* __restrict__ out_rp,
+                                            const int* __restrict__ out_ci, const int* __restrict__ in_rp,
+                                            const float* __restrict__ op_time, const float* __restrict__ ar_size,
+                                            float ar_c, float ar_d, float* __restrict__ cost) {
   typedef typename SimTypes<kLds>::dep_t dep_t;
   typedef typename SimTypes<kLds>::q_t q_t;
   constexpr int kAr = SimTypes<kLds>::kAr;
+  const int lane = threadIdx.x & 63;
+  double* ready = reinterpret_cast<double*>(base);
+  float* val = reinterpret_cast<float*>(ready + G);      // execution time, or tensor size of an all-reduce
+  dep_t* dep;
+  q_t* qu;                 // every node is queued once: ops fill it from the front, all-reduces from the back
+  int* rp;
+  unsigned short* ci;
+  if (kLds) {
+    rp = reinterpret_cast<int*>(val + G);
+    dep = reinterpret_cast<dep_t*>(rp + G + 1);
+    qu = reinterpret_cast<q_t*>(dep + G);
+    ci = reinterpret_cast<unsigned short*>(qu + G);
+  } else {
+    dep = reinterpret_cast<dep_t*>(val + G);
+    qu = reinterpret_cast<q_t*>(dep + G);
+    rp = reinterpret_cast<int*>(qu + G);
+    ci = reinterpret_cast<unsigned short*>(rp + G + 1);
+  }
+  const double dc = (double)ar_c, dd = (double)ar_d;
+
+  // ---- load the module
+  for (int v = lane; v < G; v += 64) {
+    const float x = ar_size[n0 + v];
+    const bool ar = x >= 0.0f;
+    ready[v] = 0.0;
+    val[v] = ar ? x : op_time[n0 + v];
+    dep[v] = (dep_t)((in_rp[n0 + v + 1] - in_rp[n0 + v]) | (ar ? kAr : 0));
+    rp[v] = out_rp[n0 + v] - e0;
+  }
+  if (lane == 0) rp[G] = E;
+  for (int k = lane; k < E; k += 64) ci[k] = (unsigned short)(out_ci[e0 + k] - n0);
+  sync_wave<kLds>();
+
+  // ---- sources, in ascending index, onto the two queues
+  int qt = 0, at = 0;                   // entries queued so far (wave-uniform)
+  for (int v0 = 0; v0 < G; v0 += 64) {
+    const int v = v0 + lane;
+    const int d = v < G ? dep[v] : 1;
+    const bool src_op = d == 0, src_ar = d == kAr;
+    const unsigned long long mo = __ballot(src_op), ma = __ballot(src_ar);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    if (src_op) qu[qt + __popcll(mo & below)] = (q_t)v;
+    if (src_ar) qu[G - 1 - (at + __popcll(ma & below))] = (q_t)v;
+    qt += __popcll(mo);
+    at += __popcll(ma);
+  }
+  sync_wave<kLds>();
+
+  // ---- the walk
+  int qh = 0, ah = 0, processed = 0;
+  double dev = 0.0, chan = 0.0;
+  while (ah < at || qh < qt) {
+    int u;
+    double done;
+    if (ah < at) {                      // tensors already produced go on the channel first
+      u = qu[G - 1 - ah++];
+      const double r = ready[u];
+      done = (r > chan ? r : chan) + (dc * (double)val[u] + dd);
+      chan = done;
+    } else {
+      u = qu[qh++];
+      const double r = ready[u];
+      done = (r > dev ? r : dev) + (double)val[u];
+      dev = done;
+    }
+    ++processed;
+    const int s = rp[u], e = rp[u + 1];
+    for (int k0 = s; k0 < e; k0 += 64) {
+      const int k = k0 + lane;
+      bool new_op = false, new_ar = false;
+      int w = 0;
+      if (k < e) {
+        w = ci[k];
+        if (done > ready[w]) ready[w] = done;
+        const int d = (int)dep[w] - 1;
+        dep[w] = (dep_t)d;
+        new_op = d == 0;
+        new_ar = d == kAr;
+      }
+      const unsigned long long mo = __ballot(new_op), ma = __ballot(new_ar);
+      const unsigned long long below = (1ull << lane) - 1ull;
+      if (new_op) qu[qt + __popcll(mo & below)] = (q_t)w;
+      if (new_ar) qu[G - 1 - (at + __popcll(ma & below))] = (q_t)w;
+      qt += __popcll(mo);
+      at += __popcll(ma);
+    }
+    sync_wave<kLds>();                  // the releases are visible before the next node is taken
+  }
+  if (lane == 0) *cost = processed == G ? (float)(dev > chan ? dev : chan) : INFINITY;
+  sync_wave<kLds>();
+}
+
+// The modules that simulate_order_kernel left and whose arrays fit LDS: a workgroup has a CU's LDS to itself and deals
+// its modules to as many waves as working sets of their size class fit.  One launch for all classes: in the usual call,
+// where nothing is left, a launch per class would cost as much as a small batch takes.  4096 modules in which ops wait
+// for all-reduces, 2 waves on a CU whatever the size -> by classes: 1.6 k nodes 5.01 -> 2.77 ms, 0.7 k nodes
+// 2.16 -> 0.94, 250 nodes 0.83 -> 0.27.
+constexpr int kWalkClasses = 6;
+constexpr int kWalkWaves = 10, kWalkThreads = 64 * kWalkWaves;
+constexpr int kWalkList = 16;                                  // after the two counters: the modules of a class
+constexpr int kWalkSlots = kWalkList + ((2 * kWalkThreads + 15) & ~15);
+constexpr int kWalkLds = 160 * 1024 - 512;                     // less what __syncthreads_count takes
+__host__ __device__ constexpr int walk_waves(int k) { return k == 0 ? 10 : k == 1 ? 6 : 6 - k; }      // 10, 6, 4, 3, 2, 1
+__host__ __device__ constexpr int walk_slot(int k) { return (kWalkLds - kWalkSlots) / walk_waves(k) & ~15; }
+
+__global__ __launch_bounds__(kWalkThreads) void simulate_walk_kernel(
+    const int* __restrict__ node_off, const int* __restrict__ out_rp, const int* __restrict__ out_ci,
+    const int* __restrict__ in_rp, const float* __restrict__ op_time, const float* __restrict__ ar_size, int C,
+    float ar_c, float ar_d, float* __restrict__ cost, int lds_most, int last,
+    unsigned long long* __restrict__ walked, int* status) {
+  // lds_most: larger working sets are left to the kernel that follows; without one (last) such a module is an error
   if (status[0] != 0) return;
-  const int lane = threadIdx.x;
+  int* ctr = reinterpret_cast<int*>(dc_sim_smem);
+  unsigned short* list = reinterpret_cast<unsigned short*>(dc_sim_smem + kWalkList);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int mine = (C - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;      // modules blockIdx.x + k * gridDim.x
+  for (int k0 = 0; k0 < mine; k0 += kWalkThreads) {
+    int cls = kWalkClasses;
+    const int c = blockIdx.x + (k0 + t) * gridDim.x;
+    const bool left = k0 + t < mine && __float_as_uint(cost[c]) == kLeft;
+    if (left) {
+      const int n0 = node_off[c], G = node_off[c + 1] - n0;
+      const size_t need = sim_lds_bytes(G, out_rp[n0 + G] - out_rp[n0]);
+      if (need <= (size_t)lds_most)
+        for (cls = 0; cls < kWalkClasses && need > (size_t)walk_slot(cls);) ++cls;
+      if (cls == kWalkClasses && last) {                       // larger than any base graph of this context
+        set_error(status, (int)DC_ERR_CAPACITY);
+        cost[c] = INFINITY;
+      }
+    }
+    const int n_left = __syncthreads_count(left);
+    if (n_left == 0) continue;
+    if (walked && t == 0) atomicAdd(walked, (unsigned long long)n_left);
+#pragma unroll 1
+    for (int k = 0; k < kWalkClasses; ++k) {
+      if (t == 0) ctr[0] = ctr[1] = 0;
+      __syncthreads();
+      if (cls == k) list[atomicAdd(&ctr[0], 1)] = (unsigned short)t;
+      __syncthreads();
+      const int n = __builtin_amdgcn_readfirstlane(ctr[0]);
+      if (wave < walk_waves(k)) {
+        char* base = dc_sim_smem + kWalkSlots + __builtin_amdgcn_readfirstlane(wave) * walk_slot(k);
+        for (;;) {
+          int i = 0;
+          if (lane == 0) i = atomicAdd(&ctr[1], 1);
+          i = __builtin_amdgcn_readfirstlane(i);
+          if (i >= n) break;
+          const int cc = blockIdx.x + (k0 + __builtin_amdgcn_readfirstlane(list[i])) * gridDim.x;    // known to be one for the wave
+          const int n0 = node_off[cc], G = node_off[cc + 1] - n0, e0 = out_rp[n0];
+          walk_module<true>(base, n0, G, e0, out_rp[n0 + G] - e0, out_rp, out_ci, in_rp, op_time, ar_size, ar_c, ar_d,
+                            cost + cc);
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// The modules that both kernels before it left, each in a slice of global memory.
+__global__ __launch_bounds__(64) void simulate_walk_global_kernel(
+    const int* __restrict__ node_off, const int* __restrict__ out_rp, const int* __restrict__ out_ci,
+    const int* __restrict__ in_rp, const float* __restrict__ op_time, const float* __restrict__ ar_size, int C,
+    float ar_c, float ar_d, float* __restrict__ cost, char* scratch, size_t stride, int* status) {
+  if (status[0] != 0) return;
   for (int c = blockIdx.x; c < C; c += gridDim.x) {
     if (__float_as_uint(cost[c]) != kLeft) continue;
     const int n0 = node_off[c], G = node_off[c + 1] - n0;
     const int e0 = out_rp[n0], E = out_rp[n0 + G] - e0;
-    if (kLds ? sim_lds_bytes(G, E) > (size_t)lds_bytes : sim_bytes(G, E) > gstride) {
-      if (last && lane == 0) {                      // larger than any base graph of this context
+    if (sim_bytes(G, E) > stride) {                 // larger than any base graph of this context
+      if (threadIdx.x == 0) {
         set_error(status, (int)DC_ERR_CAPACITY);
         cost[c] = INFINITY;
       }
       continue;
     }
-    char* base = kLds ? dc_sim_smem : gscratch + (size_t)blockIdx.x * gstride;
-    double* ready = reinterpret_cast<double*>(base);
-    float* val = reinterpret_cast<float*>(ready + G);      // execution time, or tensor size of an all-reduce
-    dep_t* dep;
-    q_t* qu;                 // every node is queued once: ops fill it from the front, all-reduces from the back
-    int* rp;
-    unsigned short* ci;
-    if (kLds) {
-      rp = reinterpret_cast<int*>(val + G);
-      dep = reinterpret_cast<dep_t*>(rp + G + 1);
-      qu = reinterpret_cast<q_t*>(dep + G);
-      ci = reinterpret_cast<unsigned short*>(qu + G);
-    } else {
-      dep = reinterpret_cast<dep_t*>(val + G);
-      qu = reinterpret_cast<q_t*>(dep + G);
-      rp = reinterpret_cast<int*>(qu + G);
-      ci = reinterpret_cast<unsigned short*>(rp + G + 1);
-    }
-    const double dc = (double)ar_c, dd = (double)ar_d;
-
-    // ---- load the module
-    for (int v = lane; v < G; v += 64) {
-      const float x = ar_size[n0 + v];
-      const bool ar = x >= 0.0f;
-      ready[v] = 0.0;
-      val[v] = ar ? x : op_time[n0 + v];
-      dep[v] = (dep_t)((in_rp[n0 + v + 1] - in_rp[n0 + v]) | (ar ? kAr : 0));
-      rp[v] = out_rp[n0 + v] - e0;
-    }
-    if (lane == 0) rp[G] = E;
-    for (int k = lane; k < E; k += 64) ci[k] = (unsigned short)(out_ci[e0 + k] - n0);
-    sync_wave<kLds>();
-
-    // ---- sources, in ascending index, onto the two queues
-    int qt = 0, at = 0;                   // entries queued so far (wave-uniform)
-    for (int v0 = 0; v0 < G; v0 += 64) {
-      const int v = v0 + lane;
-      const int d = v < G ? dep[v] : 1;
-      const bool src_op = d == 0, src_ar = d == kAr;
-      const unsigned long long mo = __ballot(src_op), ma = __ballot(src_ar);
-      const unsigned long long below = (1ull << lane) - 1ull;
-      if (src_op) qu[qt + __popcll(mo & below)] = (q_t)v;
-      if (src_ar) qu[G - 1 - (at + __popcll(ma & below))] = (q_t)v;
-      qt += __popcll(mo);
-      at += __popcll(ma);
-    }
-    sync_wave<kLds>();
-
-    // ---- the walk
-    int qh = 0, ah = 0, processed = 0;
-    double dev = 0.0, chan = 0.0;
-    while (ah < at || qh < qt) {
-      int u;
-      double done;
-      if (ah < at) {                      // tensors already produced go on the channel first
-        u = qu[G - 1 - ah++];
-        const double r = ready[u];
-        done = (r > chan ? r : chan) + (dc * (double)val[u] + dd);
-        chan = done;
-      } else {
-        u = qu[qh++];
-        const double r = ready[u];
-        done = (r > dev ? r : dev) + (double)val[u];
-        dev = done;
-      }
-      ++processed;
-      const int s = rp[u], e = rp[u + 1];
-      for (int k0 = s; k0 < e; k0 += 64) {
-        const int k = k0 + lane;
-        bool new_op = false, new_ar = false;
-        int w = 0;
-        if (k < e) {
-          w = ci[k];
-          if (done > ready[w]) ready[w] = done;
-          const int d = (int)dep[w] - 1;
-          dep[w] = (dep_t)d;
-          new_op = d == 0;
-          new_ar = d == kAr;
-        }
-        const unsigned long long mo = __ballot(new_op), ma = __ballot(new_ar);
-        const unsigned long long below = (1ull << lane) - 1ull;
-        if (new_op) qu[qt + __popcll(mo & below)] = (q_t)w;
-        if (new_ar) qu[G - 1 - (at + __popcll(ma & below))] = (q_t)w;
-        qt += __popcll(mo);
-        at += __popcll(ma);
-      }
-      sync_wave<kLds>();                  // the releases are visible before the next node is taken
-    }
-    if (lane == 0) cost[c] = processed == G ? (float)(dev > chan ? dev : chan) : INFINITY;
-    sync_wave<kLds>();
+    walk_module<false>(scratch + (size_t)blockIdx.x * stride, n0, G, e0, E, out_rp, out_ci, in_rp, op_time, ar_size, ar_c,
+                       ar_d, cost + c);
   }
 }
 
@@ -611,8 +685,8 @@ hipError_t launch_simulate(const SimArgs& a, hipStream_t s) {
   if (a.n_cand <= 0) return hipSuccess;
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&simulate_general_kernel<true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&simulate_walk_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kWalkLds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
@@ -623,15 +697,14 @@ hipError_t launch_simulate(const SimArgs& a, hipStream_t s) {
   if (e == hipSuccess && n > 2048) e = launch_order<1024, 8>(a, 2049, n <= 8192, s);
   if (e == hipSuccess && n > 8192) e = launch_order<1024, 16>(a, 8193, true, s);
   if (e != hipSuccess) return e;
-  // what it left: two modules per CU in LDS, sixteen in global memory
-  const int lds_grid = 2 * a.n_cu;
-  hipLaunchKernelGGL(simulate_general_kernel<true>, dim3(a.n_cand < lds_grid ? a.n_cand : lds_grid), dim3(64), a.lds_bytes, s,
+  // what it left
+  hipLaunchKernelGGL(simulate_walk_kernel, dim3(a.n_cand < a.n_cu ? a.n_cand : a.n_cu), dim3(kWalkThreads), kWalkLds, s,
                      a.node_off, a.out_rowptr, a.out_col, a.in_rowptr, a.op_time, a.ar_size, a.n_cand, a.ar_c, a.ar_d,
-                     a.cost, nullptr, (size_t)0, a.lds_bytes, a.n_slices == 0, a.status);
+                     a.cost, a.lds_bytes, a.n_slices == 0, a.walked, a.status);
   if (a.n_slices > 0)
-    hipLaunchKernelGGL(simulate_general_kernel<false>, dim3(a.n_slices), dim3(64), 0, s, a.node_off, a.out_rowptr,
+    hipLaunchKernelGGL(simulate_walk_global_kernel, dim3(a.n_slices), dim3(64), 0, s, a.node_off, a.out_rowptr,
                        a.out_col, a.in_rowptr, a.op_time, a.ar_size, a.n_cand, a.ar_c, a.ar_d, a.cost, a.scratch,
-                       a.scratch_stride, a.lds_bytes, 1, a.status);
+                       a.scratch_stride, a.status);
   return hipGetLastError();
 }
 
@@ -734,6 +807,7 @@ extern "C" dc_status dc_simulate_static(const dc_batch* in, int32_t max_module_n
   a.scratch_stride = kStaticSliceBytes;
   a.n_slices = kStaticSlices;
   a.n_cu = n_cu;
+  a.walked = nullptr;
   a.status = status;
   e = launch_simulate(a, s);
   if (e == hipSuccess && dev_status) {

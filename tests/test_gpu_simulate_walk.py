@@ -92,3 +92,68 @@ def test_every_layout_gives_the_oracle_s_costs(B):
         for name, a, b in zip(CASES, got, want):
             assert a == b, (name, c, d, a, b)
     ev.close()
+
+
+def _batch(B, graphs, copies):
+    """`copies` times all the graphs as one contracted batch, unfused."""
+    import torch
+    w = wl.custom("walk", wl.ModelSpec(F, 32, 1, "f32"), graphs, [np.arange(g.n, dtype=np.int32).reshape(1, -1) for g in graphs], seed=1)
+    nb, eb = copies * sum(g.n for g in graphs), copies * sum(g.e for g in graphs)
+    ev = B.Evaluator(F, 32, 1, "f32", copies * len(graphs), nb, max(eb, 1))
+    ev.set_base_graphs(w.g_node_off(), w.g_edge_off(), w.cat_rowptr(), w.cat_col(), w.cat_X())
+    off = np.concatenate([[0], np.cumsum(np.tile([g.n for g in graphs], copies))])
+    batch = ev.contract_graphs(ev.to_device(np.tile(w.cand_graph, copies)), ev.to_device(off),
+                               torch.from_numpy(w.group_id).to(ev.device).repeat(copies),
+                               ev.alloc_batch(copies * len(graphs), nb, nb, max(eb, 1)))
+    return ev, batch, orc.contract(w, False)
+
+
+def _times(ev, graphs, copies, is_ar, seed=3):
+    """Host arrays of one copy, device arrays of all; is_ar: mask of all-reduce nodes by (graph, node number)."""
+    import torch
+    rng = wl.Rng(seed, 2)
+    t = np.concatenate([rng.uniform(g.n) + 0.01 for g in graphs]).astype(np.float32)
+    x = np.concatenate([np.where([is_ar(i, v) for v in range(g.n)], 8 * rng.uniform(g.n), -1.0)
+                        for i, g in enumerate(graphs)]).astype(np.float32)
+    return t, x, torch.from_numpy(np.tile(t, copies)).to(ev.device), torch.from_numpy(np.tile(x, copies)).to(ev.device)
+
+
+def test_walked_modules_of_every_size_class_share_a_cu(B):
+    """Ops wait for all-reduces, so every module is walked; about a dozen modules of six classes and of global memory
+    fall to each workgroup."""
+    graphs = [chain(n, [(1, n - 2), (n // 2, n - 1)]) for n in (5, 600, 680, 700, 1150, 1750, 2350, 3500, 3700, 5000)]
+    copies = 310
+    ev, batch, ref = _batch(B, graphs, copies)
+    t, x, td, xd = _times(ev, graphs, copies, lambda i, v: v % 50 == 2)
+    want = orc.simulate(ref, t, x, 0.25, 0.05)
+    before = ev.walked_modules()
+    got = ev.simulate(batch, td, xd, 0.25, 0.05).cpu().numpy()
+    assert ev.check() == B.DC_OK
+    assert np.array_equal(got.reshape(copies, -1), np.tile(want, (copies, 1)))
+    assert ev.walked_modules() - before == copies * len(graphs)
+    ev.close()
+
+
+def test_small_walked_modules_fill_a_cu(B):
+    """Ten working sets of 16 KB fit a CU's LDS: four times the modules of a batch that gives every CU two take little
+    longer (0.27 and 0.32 ms); two to a CU whatever their size took four times as long."""
+    import torch
+    g = chain(600)
+    took = []
+    for copies in (512, 2048):
+        ev, batch, _ = _batch(B, [g], copies)
+        _, _, td, xd = _times(ev, [g], copies, lambda i, v: v % 50 == 2)
+        cost = ev.simulate(batch, td, xd, 0.25, 0.05)
+        best = np.inf
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            ev.simulate(batch, td, xd, 0.25, 0.05, cost)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        assert ev.walked_modules() == 6 * copies
+        ev.close()
+        took.append(best)
+    print(took, flush=True)
+    assert took[1] < 2.5 * took[0]
