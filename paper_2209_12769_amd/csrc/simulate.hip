@@ -87,9 +87,13 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 //
 // A thread owns NPT nodes and keeps their predecessors (three or four each; what longer lists hold beyond three lies
 // in LDS, or is read from memory again once that is full) and keys in registers; LDS holds the places, the counters of
-// the sort and the order: 8 bytes per node with the longer lists.  The sort is a
-// counting sort by key (16-bit counters, two to a word); equal keys are the few ops that one op releases, and an op
-// finds its rank among them by comparing with each.  Sources keep their places throughout.
+// the sort and the order: 8 bytes per node with the longer lists.  The sort is a counting sort by key (16-bit counters,
+// two to a word); equal keys are the ops that one op releases, and an op finds its rank among them by comparing with
+// each.  Where one op has more than kTies successors (or tensors without predecessors are about), that could take the
+// square of their number: there the nodes of such a key are marked in a bitmap, one key after another, and the bits
+// below a node give its rank.  One op that releases 6 k others, 512 modules: 6.6 ms by comparing, 3.1 now, 5.8 by the
+// walk; 6 k tensors of one op: 5.1, 1.3, 2.7.  Whether a module is so wide is seen when it is loaded: looked for in
+// every round it would cost the others 3 %.  Sources keep their places throughout.
 //
 // The times: the device's clock is a running sum over the ops, the channel's a chain of maximum and sum over the
 // all-reduces, which are sorted by (place of the last predecessor, index) in the same way and taken by one wave.
@@ -101,6 +105,7 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 // threads with sixteen nodes each, two per CU, take the same time as 1024 with eight.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kMostRounds = 256;
+constexpr int kTies = 128;             // up to so many, comparing is cheaper than four barriers for a key
 constexpr int kNone = 0x7FFFFFFF;
 
 __device__ __forceinline__ int lane_of(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
@@ -120,6 +125,8 @@ struct OrderLds {
   static constexpr int kValue = kCount;                              // f32 [kCap]: times along the order, at last
   static_assert(kSums - kValue >= 4 * kCap, "the times take the place of the counters and the longer lists");
   static constexpr int kBytes = kSums + 8 * (T > 128 ? T : 128);
+  static constexpr int kWords = kCap / 32;                           // bitmap of the nodes, while no sums are kept
+  static_assert(kWords * 6 <= 8 * (T > 128 ? T : 128), "u32 [kWords] bits, u16 [kWords] bits set before each word");
 };
 
 // Exclusive scan of the counters of keys 1 .. n (16 bits each, at words [0, words)) in place, starting from `base`;
@@ -152,14 +159,15 @@ __device__ __forceinline__ void scan_counts(unsigned* words_, int words, int bas
 }
 
 template <int T, int NPT>
-__global__ __launch_bounds__(T) void simulate_order_kernel(
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 : 4, 8))) void simulate_order_kernel(
     const int* __restrict__ node_off, const int* __restrict__ out_rp, const int* __restrict__ in_rp,
     const int* __restrict__ in_ci, const float* __restrict__ op_time, const float* __restrict__ ar_size, int C,
     float ar_c, float ar_d, float* __restrict__ cost, int fewest, int last, const int* __restrict__ status) {
   // the modules of `fewest` to T * NPT nodes; the last class to be launched leaves the larger ones to the walk
   typedef OrderLds<T, NPT> Lds;
   constexpr int kCap = Lds::kCap, kWaves = T / 64;
-  __shared__ int wsum[kWaves], sh_min[2][2], sh_src[NPT][kWaves], n_extra;
+  __shared__ int wsum[kWaves], sh_min[2][2], sh_src[NPT][kWaves], n_extra, n_tied, sh_wide;
+  __shared__ unsigned short tied[kCap / kTies];
   unsigned short* place = reinterpret_cast<unsigned short*>(dc_sim_smem + Lds::kPlace);
   unsigned* count2 = reinterpret_cast<unsigned*>(dc_sim_smem + Lds::kCount);
   unsigned short* count = reinterpret_cast<unsigned short*>(dc_sim_smem + Lds::kCount);
@@ -176,12 +184,12 @@ __global__ __launch_bounds__(T) void simulate_order_kernel(
       if (last && t == 0) cost[c] = __uint_as_float(kLeft);
       continue;
     }
-    if (t == 0) n_extra = 0;
+    if (t == 0) n_extra = sh_wide = 0;
     __syncthreads();
     // ---- the thread's nodes t, t + T, ...: predecessors, kind
     unsigned p01[NPT], p23[NPT];
     unsigned is_op = 0, is_ar = 0, is_src = 0, more = 0, far = 0;   // bit i: node t + i * T
-    bool plain = true;
+    bool plain = true, wide = false;                         // wide: more than kTies nodes may share a key
 #pragma unroll
     for (int i = 0; i < NPT; ++i) {
       const int v = t + i * T;
@@ -189,7 +197,9 @@ __global__ __launch_bounds__(T) void simulate_order_kernel(
       if (v < G) {
         const int a = in_rp[n0 + v], d = in_rp[n0 + v + 1] - a;
         const bool ar = ar_size[n0 + v] >= 0.0f;
-        plain &= ar ? out_rp[n0 + v + 1] == out_rp[n0 + v] : op_time[n0 + v] >= 0.0f;      // a NaN is neither
+        const int released = out_rp[n0 + v + 1] - out_rp[n0 + v];
+        plain &= ar ? released == 0 : op_time[n0 + v] >= 0.0f;      // a NaN is neither
+        wide |= released > kTies || (ar && d == 0);
         const unsigned x0 = d > 0 ? in_ci[a] - n0 : kCap, x1 = d > 1 ? in_ci[a + 1] - n0 : kCap;
         const unsigned x2 = d > 2 ? in_ci[a + 2] - n0 : kCap;
         unsigned x3 = d > 3 ? in_ci[a + 3] - n0 : kCap;
@@ -220,10 +230,12 @@ __global__ __launch_bounds__(T) void simulate_order_kernel(
       if (lane == 0) sh_src[i][wave] = __popcll(m);
     }
     if (t == 0) sh_min[0][0] = sh_min[0][1] = kNone;
+    if (__any(wide) && lane == 0) sh_wide = 1;
     if (__syncthreads_or(!plain)) {
       if (t == 0) cost[c] = __uint_as_float(kLeft);
       continue;
     }
+    const bool ties = __builtin_amdgcn_readfirstlane(sh_wide) != 0;
     // sources stand first, in index order
     int n_src = 0;
 #pragma unroll
@@ -282,6 +294,56 @@ __global__ __launch_bounds__(T) void simulate_order_kernel(
         for (int k = s; k < e; ++k) r += (int)order[off + k] < t + i * T;
       return r;
     };
+    // the same for a wide module: f(node, rank, key) for all sorted nodes.  Here a thread takes places of the scratch
+    // order, not its own nodes (which would cost the usual module registers), and looks for the key of each.
+    auto tied_ranks = [&](int base, int off, auto&& f) {
+      if (t == 0) n_tied = 0;
+      __syncthreads();
+      for (int k = base + t; k < (int)count[G + 1]; k += T) {
+        int key = 0;                                         // the last key that starts at or before k
+        for (int hi = G + 1; hi - key > 1;) {
+          const int mid = (key + hi) >> 1;
+          if ((int)count[mid] <= k) key = mid;
+          else hi = mid;
+        }
+        const int s = count[key], e = count[key + 1], v = order[off + k];
+        if (e - s <= kTies) {
+          int r = s;
+          for (int j = s; j < e; ++j) r += (int)order[off + j] < v;
+          f(v, r, key);
+        } else if (k == s) {
+          tied[atomicAdd(&n_tied, 1)] = (unsigned short)key;
+        }
+      }
+      __syncthreads();
+      unsigned* bits = reinterpret_cast<unsigned*>(sums);
+      unsigned short* below = reinterpret_cast<unsigned short*>(bits + Lds::kWords);
+      const int n = n_tied;
+#pragma unroll 1
+      for (int q = 0; q < n; ++q) {
+        const int key = tied[q], s = count[key], e = count[key + 1];
+        for (int w = t; w < Lds::kWords; w += T) bits[w] = 0;
+        __syncthreads();
+        for (int k = s + t; k < e; k += T) atomicOr(&bits[order[off + k] >> 5], 1u << (order[off + k] & 31));
+        __syncthreads();
+        if (wave == 0) {
+          constexpr int kPer = (Lds::kWords + 63) / 64;
+          int c = 0;
+          for (int w = lane * kPer; w < min((lane + 1) * kPer, Lds::kWords); ++w) c += __popc(bits[w]);
+          int run = wave_incl_scan(c) - c;
+          for (int w = lane * kPer; w < min((lane + 1) * kPer, Lds::kWords); ++w) {
+            below[w] = (unsigned short)run;
+            run += __popc(bits[w]);
+          }
+        }
+        __syncthreads();
+        for (int k = s + t; k < e; k += T) {
+          const int v = order[off + k];
+          f(v, s + below[v >> 5] + __popc(bits[v >> 5] & ((1u << (v & 31)) - 1u)), key);
+        }
+        __syncthreads();
+      }
+    };
 
     // ---- the order of the ops
     const unsigned mask = is_op & ~is_src;
@@ -289,16 +351,20 @@ __global__ __launch_bounds__(T) void simulate_order_kernel(
     for (; round < kMostRounds && state == 0; ++round) {
       sort(mask, n_src, 0);
       int changed = kNone, ahead = kNone;
-#pragma unroll
-      for (int i = 0; i < NPT; ++i)
-        if ((mask >> i) & 1u) {
-          const int rank = rank_of(i, 0);
-          if ((int)place[t + i * T] != rank + 1) {
-            changed = min(changed, rank);
-            place[t + i * T] = (unsigned short)(rank + 1);
-          }
-          if ((int)(ka[i] & 0xFFFFu) > rank) ahead = min(ahead, rank);
+      auto settle = [&](int v, int rank, int key) {
+        if ((int)place[v] != rank + 1) {
+          changed = min(changed, rank);
+          place[v] = (unsigned short)(rank + 1);
         }
+        if (key > rank) ahead = min(ahead, rank);
+      };
+      if (!ties) {
+#pragma unroll
+        for (int i = 0; i < NPT; ++i)
+          if ((mask >> i) & 1u) settle(t + i * T, rank_of(i, 0), (int)(ka[i] & 0xFFFFu));
+      } else {
+        tied_ranks(n_src, 0, settle);
+      }
       int* mn = sh_min[round & 1];
       changed = wave_min(changed);
       ahead = wave_min(ahead);
@@ -328,9 +394,16 @@ __global__ __launch_bounds__(T) void simulate_order_kernel(
     __syncthreads();
     if (n_ar > 0) {
       sort(is_ar, 0, n_op);
+      if (!ties) {
 #pragma unroll
-      for (int i = 0; i < NPT; ++i)
-        if ((is_ar >> i) & 1u) ka[i] = (unsigned)rank_of(i, n_op) << 16 | (ka[i] & 0xFFFFu);
+        for (int i = 0; i < NPT; ++i)
+          if ((is_ar >> i) & 1u) ka[i] = (unsigned)rank_of(i, n_op) << 16 | (ka[i] & 0xFFFFu);
+      } else {
+        tied_ranks(0, n_op, [&](int v, int rank, int) { place[v] = (unsigned short)rank; });
+#pragma unroll
+        for (int i = 0; i < NPT; ++i)
+          if ((is_ar >> i) & 1u) ka[i] = (unsigned)place[t + i * T] << 16 | (ka[i] & 0xFFFFu);
+      }
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < NPT; ++i)
