@@ -80,10 +80,19 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 // all its predecessors among them, the module has a cycle.
 //
 // One iteration is parallel over all nodes, where the walk that this replaces took the nodes one after another at
-// four dependent LDS round trips each (about 1000 cycles a node).  The number of iterations is the depth to which
+// four dependent LDS round trips each (about 800 cycles a node).  The number of iterations is the depth to which
 // neighbouring chains interleave, not the length of the module: from the index order as the first guess 4 to 7 on the
 // contracted modules of a 24-block transformer (1.4 k nodes, 1.3 k of them one after another), 13 on the unfused
-// module (6.6 k nodes), 20 on power-law graphs.  What takes kMostRounds is left to the walk.
+// module (6.6 k nodes), 20 to 36 on power-law graphs.
+//
+// Where chains that run side by side are numbered one after the other (two towers, long branches), or the numbering
+// follows no order, that depth is the length of the chains.  So after sixteen rounds, unless at their rate as many more
+// are enough, the depth of every op is found and ranks by (depth, index) are the second guess: an op of smaller depth
+// always comes first.  Depths by iteration too: every op chooses a predecessor, pointer doubling gives the lengths of the
+// paths along the chosen ones, and ops with a deeper predecessor choose that; two to four steps of about a round each.
+// Mostly one round then settles the rest (two chains of 300 ops, 4096 modules: 4.4 ms by rounds, 0.33 now, 0.63 by the
+// walk; two unfused modules of 1.6 k nodes side by side, 1000 times: 6.4, 0.53, 2.5).  What is still slow is left to the
+// walk: branches numbered at random, whose order settles depth by depth (16 and 8 rounds in vain: a quarter of the walk).
 //
 // A thread owns NPT nodes and keeps their predecessors (three or four each; what longer lists hold beyond three lies
 // in LDS, or is read from memory again once that is full) and keys in registers; LDS holds the places, the counters of
@@ -104,7 +113,10 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 // (walked in global memory before) 6.02 -> 0.59 ms, 16 modules of 0.7 k nodes 0.27 -> 0.03 ms.  Workgroups of 512
 // threads with sixteen nodes each, two per CU, take the same time as 1024 with eight.
 // ---------------------------------------------------------------------------------------------------
-constexpr int kMostRounds = 256;
+constexpr int kSecondGuess = 16;       // so many more rounds take longer than a second guess
+constexpr int kGuessRound = 1 << 16;   // the number of the round that takes it
+constexpr int kMostSteps = 4;          // of the second guess
+constexpr int kWalkRounds = 64;        // the walk takes as long as so many rounds, and one more for 32 nodes
 constexpr int kTies = 128;             // up to so many, comparing is cheaper than four barriers for a key
 constexpr int kNone = 0x7FFFFFFF;
 
@@ -125,6 +137,8 @@ struct OrderLds {
   static constexpr int kValue = kCount;                              // f32 [kCap]: times along the order, at last
   static_assert(kSums - kValue >= 4 * kCap, "the times take the place of the counters and the longer lists");
   static constexpr int kBytes = kSums + 8 * (T > 128 ? T : 128);
+  static constexpr int kPath = kOrder;                               // u32 [kCap], between two rounds: see depths
+  static_assert(kExtra - kPath >= 4 * kCap, "the paths take the place of the order and the counters");
   static constexpr int kWords = kCap / 32;                           // bitmap of the nodes, while no sums are kept
   static_assert(kWords * 6 <= 8 * (T > 128 ? T : 128), "u32 [kWords] bits, u16 [kWords] bits set before each word");
 };
@@ -193,7 +207,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
 #pragma unroll
     for (int i = 0; i < NPT; ++i) {
       const int v = t + i * T;
-      p01[i] = p23[i] = (unsigned)kCap * 0x10001u;
+      p01[i] = p23[i] = 2u * kCap * 0x10001u;                // twice the numbers: where their places lie
       if (v < G) {
         const int a = in_rp[n0 + v], d = in_rp[n0 + v + 1] - a;
         const bool ar = ar_size[n0 + v] >= 0.0f;
@@ -215,8 +229,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
             far |= 1u << i;
           }
         }
-        p01[i] = x0 | x1 << 16;
-        p23[i] = x2 | x3 << 16;
+        p01[i] = 2 * x0 | x1 << 17;
+        p23[i] = 2 * x2 | x3 << ((more >> i) & 1u ? 16 : 17);
         is_ar |= (unsigned)ar << i;
         is_op |= (unsigned)!ar << i;
         is_src |= (unsigned)(!ar && d == 0) << i;
@@ -251,21 +265,30 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
     }
     const int words = (G + 3) >> 1;                          // counters of keys 0 .. G and one more start
 
-    // key of node i: the largest place + 1 among its predecessors
-    auto key_of = [&](int i) {
-      // (kept from being taken out of the loop of rounds: unpacked, the predecessors would take four registers a node)
-      asm volatile("" : "+v"(p01[i]), "+v"(p23[i]));
-      int k = max(max((int)place[p01[i] & 0xFFFFu], (int)place[p01[i] >> 16]), (int)place[p23[i] & 0xFFFFu]);
+    // f(twice the predecessor) for those of node i, of kCap where there are fewer than four
+    auto each_before = [&](int i, auto&& f) {
+      // (kept from being taken out of the loop of rounds: unpacked, the predecessors would take four registers a node, and
+      // the bits of all nodes more scalar registers than there are)
+      asm volatile("" : "+v"(p01[i]), "+v"(p23[i]), "+v"(more), "+v"(far));
+      f(p01[i] & 0xFFFFu);
+      f(p01[i] >> 16);
+      f(p23[i] & 0xFFFFu);
       if ((more >> i) & 1u) {
-        for (int at = p23[i] >> 16, u = extra[at]; u != kCap; u = extra[++at]) k = max(k, (int)place[u]);
+        for (int at = p23[i] >> 16, u = extra[at]; u != kCap; u = extra[++at]) f(2u * u);
       } else {
-        k = max(k, (int)place[p23[i] >> 16]);
+        f(p23[i] >> 16);
       }
       if ((far >> i) & 1u) {
         int v = n0 + t + i * T;
         asm volatile("" : "+v"(v));
-        for (int e = in_rp[v] + 4; e < in_rp[v + 1]; ++e) k = max(k, (int)place[in_ci[e] - n0]);
+        for (int e = in_rp[v] + 4; e < in_rp[v + 1]; ++e) f(2u * (in_ci[e] - n0));
       }
+    };
+    auto place_at = [&](unsigned twice) { return *reinterpret_cast<const unsigned short*>(dc_sim_smem + Lds::kPlace + twice); };
+    // key of node i: the largest place + 1 among its predecessors
+    auto key_of = [&](int i) {
+      int k = 0;
+      each_before(i, [&](unsigned twice) { k = max(k, (int)place_at(twice)); });
       return k;
     };
     // Sorts the nodes of the mask by (key, index), ranks counted from `base`; order[off + base] and the places behind
@@ -345,10 +368,49 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
       }
     };
 
-    // ---- the order of the ops
+    // The second guess: the depth of the ops in their places, so that the next round ranks them by (depth, index).
     const unsigned mask = is_op & ~is_src;
-    int round = 0, state = 0;                                // 1: the order is found, 2: a cycle
-    for (; round < kMostRounds && state == 0; ++round) {
+    auto depths = [&]() {
+      unsigned* path = reinterpret_cast<unsigned*>(dc_sim_smem + Lds::kPath);     // a node's ancestor, and its distance above
+#pragma unroll 1
+      for (int step = 0; step < kMostSteps; ++step) {
+        // every op chooses its deepest predecessor (the first time the one that stands last)
+        bool deeper = step == 0;
+#pragma unroll
+        for (int i = 0; i < NPT; ++i) {
+          const int v = t + i * T;
+          unsigned best = (unsigned)v;                       // place + 1 above the node
+          if ((mask >> i) & 1u) {
+            each_before(i, [&](unsigned twice) { best = max(best, (unsigned)place_at(twice) << 16 | twice >> 1); });
+            deeper |= (best >> 16) >= (unsigned)place[v];
+            best = (best & 0xFFFFu) | 0x10000u;
+          }
+          if (v < G) path[v] = best;
+        }
+        if (!__syncthreads_or(deeper)) break;
+        // the lengths of the paths along the chosen ones: a path reaches twice as far in every pass (the two halves of
+        // a word belong together, so that it does not matter whether a pass finds another node's old or new word)
+#pragma unroll 1
+        for (int reach = 1; reach < G; reach <<= 1) {
+#pragma unroll 4
+          for (int i = 0; i < NPT; ++i) {
+            const int v = min(t + i * T, G - 1);
+            const unsigned x = path[v], y = path[x & 0xFFFFu];
+            path[v] = min((x >> 16) + (y >> 16), (unsigned)(G - n_src)) << 16 | (y & 0xFFFFu);     // a cycle's grow on and on
+          }
+          __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < NPT; ++i)
+          if ((mask >> i) & 1u) place[t + i * T] = (unsigned short)(n_src + (path[t + i * T] >> 16));
+        __syncthreads();
+      }
+    };
+
+    // ---- the order of the ops
+    int round = 0, state = 0;                                // 1: the order is found, 2: a cycle, 3: left to the walk
+    int seen = 0;                                            // places that were right at the last look
+    for (; state == 0; ++round) {
       sort(mask, n_src, 0);
       int changed = kNone, ahead = kNone;
       auto settle = [&](int v, int rank, int key) {
@@ -358,7 +420,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
         }
         if (key > rank) ahead = min(ahead, rank);
       };
-      if (!ties) {
+      if (!ties && round != kGuessRound) {                   // depths may be shared by many in any module
 #pragma unroll
         for (int i = 0; i < NPT; ++i)
           if ((mask >> i) & 1u) settle(t + i * T, rank_of(i, 0), (int)(ka[i] & 0xFFFFu));
@@ -373,9 +435,25 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
       if (t == 0) sh_min[(round & 1) ^ 1][0] = sh_min[(round & 1) ^ 1][1] = kNone;
       __syncthreads();
       const int right = min(mn[0], mn[1]);                   // so many places are the queue's
-      if (right == kNone) state = 1;
-      else if ((int)count[right + 1] == right) state = 2;    // no other op has all its predecessors among them
+      bool slow = false;
+      if (round == kGuessRound) {                            // depths are not distinct: nothing follows from them yet
+      } else if (right == kNone) {
+        state = 1;
+      } else if ((int)count[right + 1] == right) {
+        state = 2;                                           // no other op has all its predecessors among them
+      } else if ((round & (round < kGuessRound ? 15 : 7)) == (round < kGuessRound ? 15 : 7)) {
+        // how many more rounds at the rate of the last sixteen or eight?
+        const bool first = round < kGuessRound;
+        slow = ((int)count[G + 1] - right) * (first ? 16 : 8) > (right - seen) * (first ? kSecondGuess : kWalkRounds + (G >> 5));
+        seen = right;
+        if (slow && !first) state = 3;
+      }
       __syncthreads();
+      if (slow && round < kGuessRound) {
+        depths();
+        round = kGuessRound - 1;
+        seen = 0;
+      }
     }
     if (state != 1) {
       if (t == 0) cost[c] = state == 2 ? INFINITY : __uint_as_float(kLeft);

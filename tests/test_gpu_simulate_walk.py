@@ -212,3 +212,119 @@ def test_tensors_of_one_op_take_the_time_of_tensors_of_many(B):
         ev.close()
     print(took, flush=True)
     assert took[0] < 3 * took[1]
+
+
+def chains(k, n):
+    """k chains of n ops, numbered one after the other."""
+    return graph(k * n, [(c * n + i, c * n + i + 1) for c in range(k) for i in range(n - 1)])
+
+
+def renumbered(g, how):
+    p = np.arange(g.n)[::-1] if how == "reversed" else np.random.default_rng(g.n).permutation(g.n)
+    src = np.repeat(np.arange(g.n), np.diff(g.rowptr))
+    return graph(g.n, list(zip(p[src].tolist(), p[g.col].tolist())))
+
+
+def twice(g):
+    src = np.repeat(np.arange(g.n), np.diff(g.rowptr))
+    return graph(2 * g.n, list(zip(src.tolist(), g.col.tolist())) + list(zip((src + g.n).tolist(), (g.col + g.n).tolist())))
+
+
+def blocks(n, lengths, shift=0):
+    """n times: branches of these lengths between two ops, each branch numbered on its own."""
+    e, at, new = [], 0, 1
+    for _ in range(n):
+        ends = []
+        for m in lengths:
+            p = at
+            for _ in range(m):
+                e.append((p, new))
+                p, new = new, new + 1
+            ends.append(p)
+        e += [(p, new) for p in ends]
+        at, new = new, new + 1
+    return graph(new, e)
+
+
+SMALL = wl.make("cfg2", 1).graphs[0]          # 729 nodes
+SLOW = {
+    **{f"chains{k}x{n}": chains(k, n) for k, n in ((2, 30), (2, 120), (2, 254), (2, 300), (8, 100), (3, 1000), (2, 4000), (2, 8000), (300, 40))},
+    "reversed200": renumbered(chain(200), "reversed"),
+    "reversed5000": renumbered(chain(5000, [(3, 4000)]), "reversed"),
+    "permuted": renumbered(SMALL, "at random"),
+    "twice": twice(SMALL),
+    "blocks": twice(blocks(60, (3, 7, 5, 9))),
+    "long_lists": renumbered(twice(wl.random_dag(5, 500, 0.02, F)), "reversed"),
+}
+
+
+def test_orders_far_from_the_numbering(B):
+    """Parallel chains numbered one after the other, and numberings that follow no order: as many rounds from the index
+    order as a chain is long, a handful from the depths."""
+    graphs = list(SLOW.values())
+    ev, batch, ref = _batch(B, graphs, 1)
+    t, x, td, xd = _times(ev, graphs, 1, lambda i, v: graphs[i].rowptr[v] == graphs[i].rowptr[v + 1] and v % 3 == 0)
+    want = orc.simulate(ref, t, x, 0.25, 0.05)
+    got = ev.simulate(batch, td, xd, 0.25, 0.05).cpu().numpy()
+    assert ev.check() == B.DC_OK
+    for name, a, b in zip(SLOW, got, want):
+        assert a == b, (name, a, b)
+    assert ev.walked_modules() == 0
+    ev.close()
+
+
+def test_cycles_where_the_second_guess_is_needed(B):
+    for n in (60, 600, 3000):
+        g = chains(2, n)
+        labs = np.stack([np.arange(2 * n)] * 3).astype(np.int32)
+        labs[1, n - 5] = labs[1, n - 9]                      # late in the first chain
+        labs[2, 2 * n - 1] = labs[2, 3]                      # no cycle: the ends of both
+        w = wl.custom("cycles", wl.ModelSpec(F, 32, 1, "f32"), [g], [labs], seed=1)
+        ref = orc.contract(w, False)
+        t = (wl.Rng(n, 3).uniform(ref.ntot) + 0.01).astype(np.float32)
+        x = np.full(ref.ntot, -1.0, np.float32)
+        want = orc.simulate(ref, t, x, 0.25, 0.05)
+        assert np.isinf(want[1]) and np.isfinite(want[[0, 2]]).all()
+        ev = B.evaluator_for(w)
+        batch = ev.contract_graphs(ev.to_device(w.cand_graph), ev.to_device(w.cand_off), ev.to_device(w.group_id),
+                                   ev.alloc_batch(3, 6 * n, 6 * n, 6 * n))
+        import torch
+        got = ev.simulate(batch, torch.from_numpy(t).to(ev.device), torch.from_numpy(x).to(ev.device), 0.25, 0.05).cpu().numpy()
+        assert ev.check() == B.DC_OK and ev.walked_modules() == 0
+        assert np.array_equal(got, want), (n, got, want)
+        ev.close()
+
+
+def test_which_modules_are_walked(B):
+    """Sizes at the ends of the classes, predecessor lists that overflow LDS, and an order that depths do not settle:
+    every layer of three ops turns the order of the one before, so that a round settles one layer."""
+    graphs = {
+        **{f"chain{n}": chain(n) for n in (256, 257, 2048, 2049, 8192, 8193, 16384, 16385)},
+        **{f"dense{n}": wl.random_dag(77, n, p, F) for n, p in ((256, 0.2), (2048, 0.02), (8192, 0.003), (16384, 0.0015))},
+        "turning": graph(1500, [(3 * a - 1 - i, 3 * a + i) for a in range(1, 500) for i in range(3)]),
+        "permuted_branches": renumbered(twice(SMALL), "at random"),
+    }
+    ev, batch, ref = _batch(B, list(graphs.values()), 1)
+    t, x, td, xd = _times(ev, list(graphs.values()), 1, lambda i, v: False)
+    want = orc.simulate(ref, t, x, 0.25, 0.05)
+    got = ev.simulate(batch, td, xd, 0.25, 0.05).cpu().numpy()
+    assert ev.check() == B.DC_OK
+    for name, a, b in zip(graphs, got, want):
+        assert a == b, (name, a, b)
+    for g in list(graphs.values())[8:12]:                     # what lists longer than four keep in LDS does not fit it
+        d = np.bincount(g.col, minlength=g.n)
+        assert (d[d > 4] - 2).sum() > (256 if g.n <= 256 else 2048 if g.n <= 2048 else 8192 if g.n <= 8192 else 16384)
+    assert ev.walked_modules() == 3                           # chain16385 and the last two
+    ev.close()
+
+
+def test_parallel_chains_do_not_take_a_round_per_op(B):
+    """Two chains of 300 ops, 4096 modules: 4.4 ms with 256 rounds and then the walk, 0.33 now; one chain of 600 0.10."""
+    took = []
+    for g in (chains(2, 300), chain(600)):
+        ev, batch, _ = _batch(B, [g], 4096)
+        _, _, td, xd = _times(ev, [g], 4096, lambda i, v: False)
+        took.append(_milliseconds(ev, batch, td, xd))
+        ev.close()
+    print(took, flush=True)
+    assert took[0] < 6 * took[1]
