@@ -89,7 +89,8 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 // follows no order, that depth is the length of the chains.  So after sixteen rounds, unless at their rate as many more
 // are enough, the depth of every op is found and ranks by (depth, index) are the second guess: an op of smaller depth
 // always comes first.  Depths by iteration too: every op chooses a predecessor, pointer doubling gives the lengths of the
-// paths along the chosen ones, and ops with a deeper predecessor choose that; two to four steps of about a round each.
+// paths along the chosen ones, and ops with a deeper predecessor choose that; two to four steps of a few rounds each.  A
+// path longer than the module has nodes is a cycle.
 // Mostly one round then settles the rest (two chains of 300 ops, 4096 modules: 4.4 ms by rounds, 0.33 now, 0.63 by the
 // walk; two unfused modules of 1.6 k nodes side by side, 1000 times: 6.4, 0.53, 2.5).  What is still slow is left to the
 // walk: branches numbered at random, whose order settles depth by depth (16 and 8 rounds in vain: a quarter of the walk).
@@ -369,6 +370,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
     };
 
     // The second guess: the depth of the ops in their places, so that the next round ranks them by (depth, index).
+    // Returns whether it found a cycle.
     const unsigned mask = is_op & ~is_src;
     auto depths = [&]() {
       unsigned* path = reinterpret_cast<unsigned*>(dc_sim_smem + Lds::kPath);     // a node's ancestor, and its distance above
@@ -387,24 +389,29 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
           }
           if (v < G) path[v] = best;
         }
-        if (!__syncthreads_or(deeper)) break;
+        if (!__syncthreads_or(deeper)) return false;
         // the lengths of the paths along the chosen ones: a path reaches twice as far in every pass (the two halves of
         // a word belong together, so that it does not matter whether a pass finds another node's old or new word)
+        bool on = true;
 #pragma unroll 1
-        for (int reach = 1; reach < G; reach <<= 1) {
+        for (int reach = 1; on; reach <<= 1) {
+          if (reach >= 2 * G) return true;                   // so long a path from no source
+          on = false;
 #pragma unroll 4
           for (int i = 0; i < NPT; ++i) {
             const int v = min(t + i * T, G - 1);
             const unsigned x = path[v], y = path[x & 0xFFFFu];
             path[v] = min((x >> 16) + (y >> 16), (unsigned)(G - n_src)) << 16 | (y & 0xFFFFu);     // a cycle's grow on and on
+            on |= y >> 16 != 0;
           }
-          __syncthreads();
+          on = __syncthreads_or(on) != 0;
         }
 #pragma unroll
         for (int i = 0; i < NPT; ++i)
           if ((mask >> i) & 1u) place[t + i * T] = (unsigned short)(n_src + (path[t + i * T] >> 16));
         __syncthreads();
       }
+      return false;
     };
 
     // ---- the order of the ops
@@ -450,7 +457,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
       }
       __syncthreads();
       if (slow && round < kGuessRound) {
-        depths();
+        if (depths()) state = 2;
         round = kGuessRound - 1;
         seen = 0;
       }
