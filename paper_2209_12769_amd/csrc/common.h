@@ -232,7 +232,7 @@ struct FusedOpsArgs {
   int* fo_cnode;               // contracted node (global) of each fused op
   // Fused ops with the same members in the same base graph have the same subgraph and hence the same
   // estimate: with a table (not null) the estimator runs on the first of each kind only
-  unsigned long long* table;   // [table_mask + 1] open addressing, entry = candidate << 32 | group of that first one, all ones = free
+  unsigned long long* table;   // [table_mask + 1] open addressing, entry = candidate << 32 | 16 bits of the hash << 16 | group of that first one, all ones = free
   unsigned table_mask;
   int* dup_of;                 // slot cand_off[c] + c, per group: the contracted node (global) it repeats, or -1
   long long cap_ops, cap_rows, cap_edges;
