@@ -106,3 +106,42 @@ def test_config_errors(B):
     ev = B.Evaluator(16, 32, 1, "f32", 4, 100, 100, agg="attention", heads=2)
     assert B.dc_set_weights(ev.ctx, z, z, z) == B.DC_ERR_INVALID_ARG
     ev.close()
+
+
+def hub(n, F):
+    """A chain, an op that precedes all others and one that follows all: lists of n - 1."""
+    edges = {(i, i + 1) for i in range(n - 1)} | {(0, i) for i in range(1, n)} | {(i, n - 1) for i in range(n - 1)}
+    src, dst = (np.array(x) for x in zip(*sorted(edges)))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int32)
+    return wl.BaseGraph(n, n, rowptr, dst.astype(np.int32), np.random.default_rng(n).random((n, F), dtype=np.float32))
+
+
+# (H, heads, dtype, waves per SIMD of the kernel, rows per wave and round): four rounds to a claim, two where a round has 16 rows
+@pytest.mark.parametrize("H,K,dtype,waves,rows", [(256, 4, "bf16", 7, 2), (256, 4, "f32", 5, 2), (128, 1, "bf16", 7, 4),
+                                                  (512, 2, "bf16", 7, 1), (64, 2, "f32", 5, 8), (32, 1, "bf16", 7, 16),
+                                                  (32, 1, "f32", 5, 16)])
+def test_rows_claimed_in_order(B, H, K, dtype, waves, rows):
+    """A batch in which every XCD's eighth has sixteen rounds of rows for every wave, from where on the waves claim rows
+    through a counter: every candidate gets the prediction of a batch of three, whose rows are dealt, bit for bit."""
+    import torch
+    F = 16
+    graphs = [hub(150, F), wl.random_dag(901, 700, 0.004, F), wl.random_dag(902, 333, 0.01, F)]
+    model = wl.ModelSpec(F, H, 2, dtype, "attention", K)
+    w = wl.with_time_like_head(wl.custom("claims", model, graphs, [np.arange(g.n, dtype=np.int32)[None] for g in graphs], seed=6))
+    want = run(B, w)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n_waves = (n_cu + 7) // 8 * waves * 4                     # on an XCD
+    per, edges = sum(g.n for g in graphs), sum(g.e for g in graphs)
+    copies = 8 * 16 * n_waves * rows // per + 2
+    assert copies * per // 8 >= 16 * n_waves * rows > 2 * per
+    ev = B.Evaluator(F, H, 2, dtype, 3 * copies, copies * per, copies * edges, agg="attention", heads=K)
+    ev.set_base_graphs(w.g_node_off(), w.g_edge_off(), w.cat_rowptr(), w.cat_col(), w.cat_X())
+    ev.set_weights(w.weights)
+    off = np.concatenate([[0], np.cumsum(np.tile([g.n for g in graphs], copies))])
+    args = (ev.to_device(np.tile(w.cand_graph, copies)), ev.to_device(off), ev.to_device(w.group_id).repeat(copies))
+    print(H, K, dtype, copies, flush=True)
+    for _ in range(2):
+        got = ev.eval_candidates(*args).cpu().numpy().reshape(copies, 3)
+        assert ev.check() == B.DC_OK
+        assert np.array_equal(got, np.tile(want, (copies, 1)))
+    ev.close()

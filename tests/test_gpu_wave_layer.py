@@ -82,3 +82,33 @@ def test_row_pointers_that_do_not_begin_at_zero(B, F, H, L):
         assert ev.check() == B.DC_OK
         assert np.array_equal(got, want), pad
     ev.close()
+
+
+@pytest.mark.parametrize("F,H,L", [(16, 32, 2), (32, 128, 3), (64, 64, 2), (128, 128, 2), (128, 64, 1), (16, 128, 1), (64, 128, 1),
+                                   (32, 64, 2), (64, 32, 1), (16, 64, 1)])
+def test_waves_with_several_tiles(B, F, H, L):
+    """At least two tiles of 32 rows for each of the grid's waves (sixteen of them on a CU, eight for the wider shapes),
+    so that a tile's requests are made in the one before, across graphs with long lists, few and none."""
+    import torch
+    X = np.random.default_rng(6).random((41, F), dtype=np.float32)
+    graphs = [_graph(150, "hub", F), _graph(700, "sparse", F), _graph(90, "dense", F), wl.BaseGraph(41, 41, np.zeros(42, np.int32), np.zeros(0, np.int32), X)]
+    w = wl.with_time_like_head(wl.custom("tiles", wl.ModelSpec(F, H, L, "bf16"), graphs,
+                                         [np.arange(g.n, dtype=np.int32)[None] for g in graphs], seed=8))
+    per, edges = sum(g.n for g in graphs), sum(g.e for g in graphs)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    copies = 2 * 16 * n_cu * 32 // per + 3
+    ev = B.Evaluator(F, H, L, "bf16", 4 * copies, copies * per, copies * edges)
+    ev.set_base_graphs(w.g_node_off(), w.g_edge_off(), w.cat_rowptr(), w.cat_col(), w.cat_X())
+    ev.set_weights(w.weights)
+    off = np.concatenate([[0], np.cumsum(np.tile([g.n for g in graphs], copies))])
+    args = (ev.to_device(np.tile(w.cand_graph, copies)), ev.to_device(off), ev.to_device(w.group_id).repeat(copies))
+    print(F, H, L, copies, flush=True)
+    fused = ev.eval_candidates(*args).cpu().numpy()
+    assert ev.check() == B.DC_OK
+    ev.select_kernels(B.DC_KERNELS_SEPARATE_LAYERS)
+    plain = ev.eval_candidates(*args).cpu().numpy()
+    assert ev.check() == B.DC_OK
+    ev.close()
+    assert np.array_equal(fused, plain)
+    want = orc.evaluate(w)
+    assert np.all(np.abs(fused[:4] - want) <= TOL * np.abs(want))
