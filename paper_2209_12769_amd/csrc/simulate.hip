@@ -210,10 +210,12 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
       const int v = t + i * T;
       p01[i] = p23[i] = 2u * kCap * 0x10001u;                // twice the numbers: where their places lie
       if (v < G) {
+        // (all six requested together, whatever the node: one wait)
         const int a = in_rp[n0 + v], d = in_rp[n0 + v + 1] - a;
-        const bool ar = ar_size[n0 + v] >= 0.0f;
         const int released = out_rp[n0 + v + 1] - out_rp[n0 + v];
-        plain &= ar ? released == 0 : op_time[n0 + v] >= 0.0f;      // a NaN is neither
+        const float size = ar_size[n0 + v], time = op_time[n0 + v];
+        const bool ar = size >= 0.0f;
+        plain &= (ar & (released == 0)) | (!ar & (time >= 0.0f));   // a NaN is neither
         wide |= released > kTies || (ar && d == 0);
         const unsigned x0 = d > 0 ? in_ci[a] - n0 : kCap, x1 = d > 1 ? in_ci[a + 1] - n0 : kCap;
         const unsigned x2 = d > 2 ? in_ci[a + 2] - n0 : kCap;
