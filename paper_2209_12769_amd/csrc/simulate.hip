@@ -110,8 +110,8 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 //
 // What bounds it: LDS round trips between some six barriers a round (about 15 k cycles a round with 1024 threads and
 // 6.6 k nodes, 12 rounds, and 60 k for the times; 64 or 256 threads for small modules: 9 k a round).  Measured, walk
-// before -> now: 4096 contracted modules of 1.4 k nodes 2.48 -> 0.23 ms, 1000 nearly unfused ones of 6.5 k nodes
-// (walked in global memory before) 6.02 -> 0.59 ms, 16 modules of 0.7 k nodes 0.27 -> 0.03 ms.  Workgroups of 512
+// before -> now: 4096 contracted modules of 1.4 k nodes 2.48 -> 0.24 ms, 1000 nearly unfused ones of 6.5 k nodes
+// (walked in global memory before) 6.02 -> 0.46 ms, 16 modules of 0.7 k nodes 0.27 -> 0.03 ms.  Workgroups of 512
 // threads with sixteen nodes each, two per CU, take the same time as 1024 with eight.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kSecondGuess = 16;       // so many more rounds take longer than a second guess
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
         }
         if (key > rank) ahead = min(ahead, rank);
       };
-      if (!ties && round != kGuessRound) {                   // depths may be shared by many in any module
+      if (__builtin_expect(!ties && round != kGuessRound, 1)) {                   // depths may be shared by many in any module
 #pragma unroll
         for (int i = 0; i < NPT; ++i)
           if ((mask >> i) & 1u) settle(t + i * T, rank_of(i, 0), (int)(ka[i] & 0xFFFFu));
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 64 ? 5 :
         if (slow && !first) state = 3;
       }
       __syncthreads();
-      if (slow && round < kGuessRound) {
+      if (__builtin_expect(slow && round < kGuessRound, 0)) {
         if (depths()) state = 2;
         round = kGuessRound - 1;
         seen = 0;
