@@ -51,7 +51,7 @@ struct dc_ctx {
   int* ro_first = nullptr;
   int* status = nullptr;    // [2]
   int* totals = nullptr;    // contracted nodes, edges; [2..3] 64-bit count of the modules that were walked
-  int* h_pinned = nullptr;  // [4] pinned host mirror for status / totals
+  int* h_pinned = nullptr;  // [64] pinned host mirror for status / totals
   // weights
   void* W = nullptr;
   float* b = nullptr;

@@ -295,6 +295,10 @@ hipError_t launch(const u16* h, int d, const GnnArgs& a, const u16* Wp, const fl
 
 }  // namespace
 
+// What the wave and the sixteen-wave kernel leave: first layers of an unusual width.  Measured against aggregate and update
+// as separate kernels (one layer, check and readout included): d = 256, H = 128 647 and 826 us for 639 k rows, 230 and 287
+// for 192 k, 96 and 91 for 19 k, 92 and 73 for 3 k; d = 128, H = 256 526 and 716, 205 and 218, 121 and 126, 109 and 108.
+// The row count is known on the device only, so the shape alone decides.
 bool fused_layer_supported(int d, int H, int bf16) { return bf16 && (H == 256 || H == 128) && d % kBK == 0; }
 
 hipError_t launch_fused_layer(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
