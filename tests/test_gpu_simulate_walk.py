@@ -1,5 +1,6 @@
-"""The two kernels of the simulator at the places where one hands over to the other or changes its layout: costs bit
-for bit equal to the CPU oracle's (both add fp64 times in the order the rules fix)."""
+"""The kernels of the simulator (the order by iteration, the walk in LDS, the walk in global memory) at the places where
+one hands over to the next or changes its layout: costs bit for bit equal to the CPU oracle's (both add fp64 times in
+the order the rules fix)."""
 import numpy as np
 import pytest
 
@@ -60,8 +61,8 @@ CASES = {
     "times_at_the_limit": (chain(255), None, lambda t: np.where(np.arange(t.size) == 9, 2.0 ** -20, 1.0 + t)),
     "times_past_the_limit": (chain(255), None, lambda t: np.where(np.arange(t.size) == 9, 2.0 ** -24 * (1 + t), 1.0 + t)),
     "zero_times": (fan(100), lambda v: v == 99, lambda t: np.zeros_like(t)),
-    "longest_in_lds": (chain(32000), None, None),
-    "too_long_for_lds": (chain(33500), None, None),
+    "walked_in_memory": (chain(32000), None, None),
+    "walked_in_memory_past_32768": (chain(33500), None, None),
     "wide_and_long": (wl.random_dag(31, 3000, 0.002, F), lambda v: v % 9 == 8, None),
 }
 
