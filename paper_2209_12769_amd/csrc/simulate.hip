@@ -111,7 +111,7 @@ extern __shared__ __attribute__((aligned(16))) char dc_sim_smem[];
 // What bounds it: LDS round trips between some six barriers a round (about 15 k cycles a round with 1024 threads and
 // 6.6 k nodes, 12 rounds, and 60 k for the times; 64 or 256 threads for small modules: 9 k a round).  Measured, walk
 // before -> now: 4096 contracted modules of 1.4 k nodes 2.48 -> 0.24 ms, 1000 nearly unfused ones of 6.5 k nodes
-// (walked in global memory before) 6.02 -> 0.46 ms, 16 modules of 0.7 k nodes 0.27 -> 0.03 ms.  Workgroups of 512
+// (walked in global memory before) 6.02 -> 0.47 ms, 16 modules of 0.7 k nodes 0.27 -> 0.03 ms.  Workgroups of 512
 // threads with sixteen nodes each, two per CU, take the same time as 1024 with eight.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kSecondGuess = 16;       // so many more rounds take longer than a second guess
