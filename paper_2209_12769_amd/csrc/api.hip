@@ -54,6 +54,7 @@ struct dc_ctx {
   int* h_pinned = nullptr;  // [64] pinned host mirror for status / totals
   // weights
   void* W = nullptr;
+  unsigned short* Ws = nullptr;       // fp32: pieces of the layer matrices (dense32.hip)
   float* b = nullptr;
   float* head = nullptr;
   float* att = nullptr;     // attention vectors (DC_AGG_ATTENTION only)
@@ -89,6 +90,7 @@ struct dc_ctx {
   long long train_t = 0;         // Adam steps taken
   char* train_mem = nullptr;
   TrainPass tb{};                // the buffers of a pass
+  unsigned short* train_WTs = nullptr;   // pieces of the transposed matrices
   float* adam_m = nullptr;
   float* adam_v = nullptr;
   Profiler prof;
@@ -278,6 +280,7 @@ GnnArgs gnn_args(dc_ctx* ctx, int32_t n_cand, const BatchView& in, float* pred);
 
 dc_status do_forward(dc_ctx* ctx, int32_t n_cand, const BatchView& in, float* pred, hipStream_t s) {
   GnnArgs g = gnn_args(ctx, n_cand, in, pred);
+  g.Ws = ctx->Ws;
   g.fuse_readout = 1;                        // nothing but the readout looks at the last layer's rows here
   hipError_t e = launch_gnn_forward(g, ctx->prof.on ? &ctx->prof : nullptr, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "forward launch");
@@ -517,6 +520,8 @@ dc_status dc_create(dc_ctx** out, const dc_config* cfg) {
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->b), (size_t)cfg->L * cfg->H * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->head), (2 * HH + 3 * cfg->H + 1) * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&ctx->headW, 2 * HH * es);
+  if (e == hipSuccess && cfg->dtype == DC_F32)
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->Ws), packed_weight_elems(cfg->F, cfg->H, cfg->L, 3) * 3 * sizeof(unsigned short));
   if (e != hipSuccess) {
     (void)hipGetLastError();
     dc_destroy(ctx);
@@ -537,6 +542,7 @@ dc_status dc_destroy(dc_ctx* ctx) {
   if (ctx->head) (void)hipFree(ctx->head);
   if (ctx->att) (void)hipFree(ctx->att);
   if (ctx->headW) (void)hipFree(ctx->headW);
+  if (ctx->Ws) (void)hipFree(ctx->Ws);
   if (ctx->cost_mem) (void)hipFree(ctx->cost_mem);
   if (ctx->bg_mem) (void)hipFree(ctx->bg_mem);
   if (ctx->slab) (void)hipFree(ctx->slab);
@@ -544,6 +550,42 @@ dc_status dc_destroy(dc_ctx* ctx) {
   if (ctx->train_mem) (void)hipFree(ctx->train_mem);
   delete ctx;
   return DC_OK;
+}
+
+// The pieces (dense32.hip) of the fp32 matrices as they are now: the layers, and for training the transposes of all.
+static void refresh_pieces(dc_ctx* ctx, hipStream_t s) {
+  const dc_config& c = ctx->cfg;
+  if (c.dtype != DC_F32) return;
+  const int nseg = c.aggregator == DC_AGG_ATTENTION ? 1 : 3;
+  const size_t HH = (size_t)c.H * c.H;
+  const bool reverse = ctx->train_mem != nullptr;
+  SplitJobs jobs;
+  int n = 0;
+  auto add = [&](const float* src, unsigned short* dst, int K, int N, int transposed) {
+    jobs.job[n++] = SplitJob{src, dst, K, N, transposed ? K : N, transposed};
+    if (n == kSplitJobsMost) {
+      launch_pack_split(jobs, n, s);
+      n = 0;
+    }
+  };
+  const float* W = static_cast<const float*>(ctx->W);
+  unsigned short* Ws = ctx->Ws;
+  unsigned short* WTs = ctx->train_WTs;
+  for (int l = 0; l < c.L; ++l) {
+    const int d = l == 0 ? c.F : c.H;
+    add(W, Ws, nseg * d, c.H, 0);
+    if (reverse && l > 0) {
+      add(W, WTs, c.H, 3 * c.H, 1);
+      WTs += 9 * HH;
+    }
+    W += (size_t)nseg * d * c.H;
+    Ws += (size_t)3 * nseg * d * c.H;
+  }
+  for (int i = 0; i < 2; ++i) {
+    const float* Wi = ctx->head + i * (HH + c.H);
+    if (reverse) add(Wi, WTs + i * 3 * HH, c.H, c.H, 1);
+  }
+  launch_pack_split(jobs, n, s);
 }
 
 static dc_status set_weights_common(dc_ctx* ctx, const float* W_layers, const float* att, const float* b_layers,
@@ -582,6 +624,8 @@ static dc_status set_weights_common(dc_ctx* ctx, const float* W_layers, const fl
   if (e == hipSuccess) e = hipMemcpyAsync(ctx->head, hd.data(), hd.size() * sizeof(float), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && att)
     e = hipMemcpyAsync(ctx->att, att, (size_t)c.L * 2 * c.H * sizeof(float), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) refresh_pieces(ctx, s);
+  if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(s);   // host staging buffers die at return
   if (e != hipSuccess) return hip_fail(ctx, e, "weight copy");
   ctx->have_weights = true;
@@ -1123,7 +1167,7 @@ dc_status dc_train_begin(dc_ctx* ctx, const dc_train_params* params, void* strea
     t.lterm = a.take<double>(B);
     t.gid = a.take<int>(R);
     t.cnt = a.take<int>(2);
-    t.WT = a.take<float>(3 * H * H);
+    ctx->train_WTs = a.take<unsigned short>((9 * (size_t)(c.L - 1) + 6) * H * H);
     t.part = a.take<float>((size_t)S * (3 * dmax * H + H));
     t.grad = a.take<float>(P);
     m = a.take<float>(P);
@@ -1146,6 +1190,8 @@ dc_status dc_train_begin(dc_ctx* ctx, const dc_train_params* params, void* strea
   t.max_rows = p.max_rows;
   t.status = ctx->status;
   t.n_cu = ctx->n_cu;
+  t.Ws = ctx->Ws;
+  t.WTs = ctx->train_WTs;
   ctx->tb = t;
   ctx->adam_m = m;
   ctx->adam_v = v;
@@ -1153,6 +1199,7 @@ dc_status dc_train_begin(dc_ctx* ctx, const dc_train_params* params, void* strea
   ctx->train_t = 0;
   hipLaunchKernelGGL(zero_kernel, dim3(256), dim3(256), 0, s, m, (long long)P);
   hipLaunchKernelGGL(zero_kernel, dim3(256), dim3(256), 0, s, v, (long long)P);
+  refresh_pieces(ctx, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e, "training state");
   ctx->training = true;
@@ -1268,6 +1315,10 @@ dc_status dc_train_step(dc_ctx* ctx, const dc_batch* in, const float* target, fl
   if (e == hipSuccess)
     e = hipMemcpyAsync(static_cast<float*>(ctx->headW) + HH, ctx->head + HH + c.H, HH * sizeof(float),
                        hipMemcpyDeviceToDevice, s);
+  if (e == hipSuccess) {
+    refresh_pieces(ctx, s);
+    e = hipGetLastError();
+  }
   return e == hipSuccess ? DC_OK : hip_fail(ctx, e, "optimiser step");
 }
 

@@ -106,6 +106,7 @@ struct GnnArgs {
   const void* Xc;
   int F, H, L, bf16;
   const void* W;        // layer matrices in device layout
+  const unsigned short* Ws = nullptr;   // fp32, products on the bf16 matrix cores (dense32.hip): their pieces, matrix after matrix
   const float* b;       // biases fp32
   const float* head;    // fp32 head (bf16-representable matrices on the bf16 path)
   void* act[2];         // ping/pong activations [max_nodes, H]
@@ -141,7 +142,33 @@ void launch_mean_aggregate(const GnnArgs& a, const void* h, int d, void* h_in, v
 // out [rows, a.H] = [A0 | A1 | A2] Wl (nseg = 3) or A0 Wl (nseg = 1), rows = a.node_off[a.n_cand]; with a bias
 // the result is ReLU(. + bias), without one it is stored as it is.  a.H must be a multiple of 32.
 void launch_dense_update(const GnnArgs& a, const void* A0, const void* A1, const void* A2, int d, int nseg,
-                         const void* Wl, const float* bias, void* out, hipStream_t s);
+                         const void* Wl, const float* bias, void* out, hipStream_t s, const unsigned short* Ws = nullptr);
+// dense32.hip: fp32 products on the bf16 matrix cores.  A matrix W [K, N] has a second form there (three bf16 pieces
+// per element, 3 K N 16-bit values); K a multiple of 16, N of 32.
+struct SplitJob {
+  const float* src;         // element (k, n) at src[k * ld + n], transposed: src[n * ld + k]
+  unsigned short* dst;
+  int K, N, ld, transposed;
+};
+// Layers with fewer rows of W keep the fp32 instructions: their sums are as near to 64 bits or nearer (error over the root
+// mean square of the result, ReLU outputs and normal weights: K = 48 0.9e-7 against 1.2e-7, 96 1.3e-7 both, 128 1.44e-7
+// against 1.36e-7), and there is little to gain (K = 48: 4.5 us of matrix time per 100 k rows and 128 columns).
+constexpr int kSplitLeast = 128;
+constexpr int kSplitJobsMost = 32;
+struct SplitJobs {
+  SplitJob job[kSplitJobsMost];
+};
+void launch_pack_split(const SplitJobs& jobs, int n, hipStream_t s);
+// out [rows, a.H] = [A0 | A1 | A2] Wf (nseg = 3) or A0 Wf (nseg = 1), rows = a.node_off[a.n_cand]; with a bias the result
+// is ReLU(. + bias), without one it is stored as it is.  Ws: the pieces of the matrix; Wf holds it row by row, transposed
+// column by column.  a.H must be a multiple of 32.
+void launch_update_split(const GnnArgs& a, const float* A0, const float* A1, const float* A2, int d, int nseg, const float* Wf,
+                         const unsigned short* Ws, const float* bias, float* out, hipStream_t s, bool transposed = false);
+// Partial sums over S slabs of rows (S a multiple of 8): C [M, N] = [A0 | A1 | A2]^T B with M = nseg * d, then the N column
+// sums of B, at part + slab * part_stride.  d a multiple of 16, N and ldb of 4, rows 16-byte aligned.
+void launch_wgrad_split(const float* A0, const float* A1, const float* A2, int d, int nseg, const float* B, int ldb, int N,
+                        const int* nrows, float* part, long long part_stride, int S, const int* status, hipStream_t s);
+int wgrad_split_tiles(int M, int N);
 // Elements (of the storage dtype) of all layer matrices in device layout; nseg row blocks of
 // d rows per layer (3: self / predecessor mean / successor mean; 1: attention).
 size_t packed_weight_elems(int F, int H, int L, int nseg);
@@ -274,6 +301,8 @@ struct TrainPass {
   const float* W;
   const float* b;
   const float* head;
+  const unsigned short* Ws;    // pieces (dense32.hip) of the layers' matrices
+  const unsigned short* WTs;   // of the transposed matrices: layers 1 .. L - 1, then W1, W2
   int F, H, L;
   float floor;
   // buffers
@@ -292,7 +321,6 @@ struct TrainPass {
   double* lterm;               // [max_samples] per-sample loss terms
   int* gid;                    // [max_rows] sample of each row
   int* cnt;                    // {0, n_samples}
-  float* WT;                   // [H, 3H] transposed matrix of the layer at hand
   float* part;                 // [slabs][3 max(F,H) H + H] partial sums of the weight gradients
   int slabs;
   long long max_rows;

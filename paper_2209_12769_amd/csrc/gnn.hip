@@ -637,9 +637,13 @@ void dispatch_update(const GnnArgs& a, const void* A0, const void* A1, const voi
 }
 
 // [A0 | A1 | A2] W (nseg = 3) or A0 W (nseg = 1) with the chunk width the input width allows
+// (fp32 with the pieces Ws of W at hand: dense32.hip)
 void run_update(const GnnArgs& a, const void* A0, const void* A1, const void* A2, int d, int nseg, const void* Wl,
-                const float* bias, void* out, hipStream_t s) {
-  if (a.bf16) {
+                const unsigned short* Ws, const float* bias, void* out, hipStream_t s) {
+  if (Ws && nseg * d >= kSplitLeast) {
+    launch_update_split(a, static_cast<const float*>(A0), static_cast<const float*>(A1), static_cast<const float*>(A2), d, nseg,
+                        static_cast<const float*>(Wl), Ws, bias, static_cast<float*>(out), s);
+  } else if (a.bf16) {
     // the shapes the sixteen-wave layer kernel serves add their K chunks in its order
     const int interleave = nseg == 3 && layer256_supported(d, a.H, a.bf16);
     if (d % 64 == 0) dispatch_update<true, 64>(a, A0, A1, A2, d, nseg, Wl, bias, out, interleave, s);
@@ -706,6 +710,7 @@ hipError_t attention_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, con
   int d = a.F;
   const size_t esz = a.bf16 ? 2 : 4;
   const char* Wl = static_cast<const char*>(a.W);
+  const unsigned short* Ws = a.Ws;
   const float* bl = a.b;
   const float* al = a.att;
   void* z = a.agg[0];
@@ -716,7 +721,7 @@ hipError_t attention_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, con
       hipError_t e = launch_dense256(hcur, d, a, Wl, nullptr, z, s);
       if (e != hipSuccess) return e;
     } else {
-      run_update(a, hcur, nullptr, nullptr, d, 1, Wl, nullptr, z, s);
+      run_update(a, hcur, nullptr, nullptr, d, 1, Wl, Ws, nullptr, z, s);
     }
     if (prof) prof->end(s);
     if (prof) prof->begin(kFamAttScores, s);
@@ -728,6 +733,7 @@ hipError_t attention_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, con
     if (prof) prof->end(s);
     if (e != hipSuccess) return e;
     Wl += (size_t)d * a.H * esz;
+    if (Ws) Ws += (size_t)3 * d * a.H;
     bl += a.H;
     al += 2 * a.H;
     hcur = hnext;
@@ -752,6 +758,7 @@ hipError_t mean_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, const vo
   int d = a.F;
   const size_t esz = a.bf16 ? 2 : 4;
   const char* Wl = static_cast<const char*>(a.W);
+  const unsigned short* Ws = a.Ws;
   const float* bl = a.b;
   const int agg_grid = ((a.n_cu + 7) / 8) * 64;
   if (a.allow_fused && (layer256_supported(a.F, a.H, a.bf16) || (a.L > 1 && layer256_supported(a.H, a.H, a.bf16)))) {
@@ -788,10 +795,11 @@ hipError_t mean_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, const vo
                            a.out_rowptr, a.out_col, a.agg[0], a.agg[1], a.node_off, a.n_cand, a.status);
       if (prof) prof->end(s);
       if (prof) prof->begin(kFamUpdate, s);
-      run_update(a, hcur, a.agg[0], a.agg[1], d, 3, Wl, bl, hnext, s);
+      run_update(a, hcur, a.agg[0], a.agg[1], d, 3, Wl, Ws, bl, hnext, s);
       if (prof) prof->end(s);
     }
     Wl += (size_t)3 * d * a.H * esz;
+    if (Ws) Ws += (size_t)9 * d * a.H;
     bl += a.H;
     hcur = hnext;
     d = a.H;
@@ -816,15 +824,15 @@ void launch_mean_aggregate(const GnnArgs& a, const void* h, int d, void* h_in, v
 }
 
 void launch_dense_update(const GnnArgs& a, const void* A0, const void* A1, const void* A2, int d, int nseg,
-                         const void* Wl, const float* bias, void* out, hipStream_t s) {
-  run_update(a, A0, A1, A2, d, nseg, Wl, bias, out, s);
+                         const void* Wl, const float* bias, void* out, hipStream_t s, const unsigned short* Ws) {
+  run_update(a, A0, A1, A2, d, nseg, Wl, Ws, bias, out, s);
 }
 
 void launch_dense_bias_relu(const GnnArgs& a, const void* A, int d, const void* Wp, const float* bias, void* out,
                             hipStream_t s) {
   if (a.allow_fused && layer256_supported(d, a.H, a.bf16) && launch_dense256(A, d, a, Wp, bias, out, s) == hipSuccess)
     return;
-  run_update(a, A, nullptr, nullptr, d, 1, Wp, bias, out, s);
+  run_update(a, A, nullptr, nullptr, d, 1, Wp, nullptr, bias, out, s);
 }
 
 hipError_t launch_gnn_forward(const GnnArgs& a, Profiler* prof, hipStream_t s) {
