@@ -4,6 +4,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <string>
 #include <vector>
@@ -63,7 +64,7 @@ struct dc_ctx {
   // base graphs
   BaseGraphs bg{};
   char* bg_mem = nullptr;
-  int max_gn = 0, max_ge = 0, min_need = 0;
+  int max_gn = 0, max_ge = 0, size_classes = 0;
   bool have_graphs = false;
   char* slab = nullptr;
   size_t slab_stride = 0;
@@ -253,7 +254,7 @@ dc_status do_contract(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_graph, co
   a.bg = ctx->bg;
   a.max_graph_nodes = ctx->max_gn;
   a.max_graph_edges = ctx->max_ge;
-  a.min_graph_need = ctx->min_need;
+  a.size_classes = ctx->size_classes;
   a.n_cand = n_cand;
   a.cand_graph = cand_graph;
   a.cand_off = cand_off;
@@ -657,7 +658,8 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
     return fail(ctx, DC_ERR_INVALID_ARG, "null pointer or no graphs");
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (g_node_off[0] != 0 || g_edge_off[0] != 0) return fail(ctx, DC_ERR_BAD_GRAPH, "offsets must start at 0");
-  int max_gn = 0, max_ge = 0, min_need = INT32_MAX;
+  int max_gn = 0, max_ge = 0, size_classes = 0;
+  size_t slab_bytes = 0;          // of the largest graph that does not fit LDS
   bool canonical = true;
   for (int b = 0; b < n_graphs; ++b) {
     const long long n = (long long)g_node_off[b + 1] - g_node_off[b];
@@ -677,8 +679,9 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
         if (ci[k] == v || (k > rp[v] && ci[k] <= ci[k - 1])) canonical = false;
     if (n > max_gn) max_gn = (int)n;
     if (e > max_ge) max_ge = (int)e;
-    const int need = contract_working_set_bytes((int)n, (int)e);
-    if (need < min_need) min_need = need;
+    const int k = contract_size_class((int)n, (int)e, ctx->lds_limit);
+    size_classes |= 1 << k;
+    if (k == kSizeClasses) slab_bytes = std::max(slab_bytes, contract_slab_bytes((int)n, (int)e));
   }
   const long long NT = g_node_off[n_graphs], ET = g_edge_off[n_graphs];
   // predecessor lists (transpose), sources ascending
@@ -696,7 +699,25 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
     for (int u = 0; u < n; ++u)
       for (int k = rp[u]; k < rp[u + 1]; ++k) tci[cur[ci[k]]++] = u;
   }
-  // one device block: gno | geo | rowptr | col | crowptr | ccol | X
+  std::vector<uint32_t> edges((size_t)(ET > 0 ? ET : 1));
+  for (int b = 0; b < n_graphs; ++b) {
+    const int n = g_node_off[b + 1] - g_node_off[b];
+    const int32_t* rp = rowptr + g_node_off[b] + b;
+    const int32_t* ci = col + g_edge_off[b];
+    // 64 runs of the edges in their order, the first `full` of them one edge longer; entry 64 i + r is edge i of run r
+    const int e = rp[n], per = (e + 63) / 64, full = e - 64 * (per - 1);
+    uint32_t* out = edges.data() + g_edge_off[b];
+    int run = 0, i = 0;
+    for (int u = 0; u < n; ++u)
+      for (int k = rp[u]; k < rp[u + 1]; ++k) {
+        out[i * 64 + run] = (uint32_t)u | (uint32_t)ci[k] << 16;
+        if (++i == (run < full ? per : per - 1)) {
+          ++run;
+          i = 0;
+        }
+      }
+  }
+  // one device block: gno | geo | rowptr | col | crowptr | ccol | edge | X
   Arena a;
   a.take<int>(n_graphs + 1);
   a.take<int>(n_graphs + 1);
@@ -704,6 +725,7 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
   a.take<int>(ET + 1);
   a.take<int>(NT + n_graphs);
   a.take<int>(ET + 1);
+  a.take<uint32_t>(ET + 1);
   a.take<float>((size_t)NT * ctx->cfg.F + 4);
   char* mem = nullptr;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&mem), a.off);
@@ -719,6 +741,7 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
   int* d_ci = d.take<int>(ET + 1);
   int* d_crp = d.take<int>(NT + n_graphs);
   int* d_cci = d.take<int>(ET + 1);
+  uint32_t* d_edge = d.take<uint32_t>(ET + 1);
   float* d_X = d.take<float>((size_t)NT * ctx->cfg.F + 4);
   e = hipMemcpyAsync(d_gno, g_node_off, (n_graphs + 1) * sizeof(int), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(d_geo, g_edge_off, (n_graphs + 1) * sizeof(int), hipMemcpyHostToDevice, s);
@@ -726,13 +749,14 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
   if (e == hipSuccess && ET > 0) e = hipMemcpyAsync(d_ci, col, (size_t)ET * sizeof(int), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(d_crp, crp.data(), (size_t)(NT + n_graphs) * sizeof(int), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && ET > 0) e = hipMemcpyAsync(d_cci, cci.data(), (size_t)ET * sizeof(int), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess && ET > 0) e = hipMemcpyAsync(d_edge, edges.data(), (size_t)ET * sizeof(uint32_t), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && NT > 0) e = hipMemcpyAsync(d_X, X, (size_t)NT * ctx->cfg.F * sizeof(float), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   char* slab = nullptr;
   size_t slab_stride = 0;
   int slab_wgs = 0;
-  if (e == hipSuccess && contract_working_set_bytes(max_gn, max_ge) > ctx->lds_limit) {
-    slab_stride = al((size_t)contract_working_set_bytes(max_gn, max_ge));
+  if (e == hipSuccess && slab_bytes > 0) {
+    slab_stride = al(slab_bytes);
     slab_wgs = ctx->n_cu * 2;
     e = hipMalloc(reinterpret_cast<void**>(&slab), slab_stride * slab_wgs);
   }
@@ -773,10 +797,11 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
   ctx->bg.col = d_ci;
   ctx->bg.crowptr = d_crp;
   ctx->bg.ccol = d_cci;
+  ctx->bg.edge = d_edge;
   ctx->bg.X = d_X;
   ctx->max_gn = max_gn;
   ctx->max_ge = max_ge;
-  ctx->min_need = min_need;
+  ctx->size_classes = size_classes;
   ctx->have_graphs = true;
   ctx->bg_canonical = canonical;
   ctx->bg_nodes = NT;

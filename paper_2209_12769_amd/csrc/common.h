@@ -23,6 +23,7 @@ struct BaseGraphs {
   const int* col;      // graph b at geo[b], local node numbers
   const int* crowptr;  // predecessors, same layout
   const int* ccol;
+  const unsigned* edge;   // graph b at geo[b]: source | target << 16 of each edge, neighbouring entries far apart in the graph
   const float* X;      // [sum N_b, F]
 };
 
@@ -72,7 +73,7 @@ struct Profiler {
 struct ContractLaunch {
   BaseGraphs bg;
   int max_graph_nodes, max_graph_edges;   // largest base graph
-  int min_graph_need;                      // smallest per-graph working-set bytes
+  int size_classes;                        // bit contract_size_class() of every base graph
   int n_cand;
   const int* cand_graph;
   const int* cand_off;
@@ -90,7 +91,10 @@ struct ContractLaunch {
   int n_cu;
 };
 hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t s);
-int contract_working_set_bytes(int n_nodes, int n_edges);
+// 0 .. kSizeClasses - 1: working sets in LDS, smallest first; kSizeClasses: in contract_slab_bytes() of global memory
+constexpr int kSizeClasses = 3;
+int contract_size_class(int n_nodes, int n_edges, int lds_limit);
+size_t contract_slab_bytes(int n_nodes, int n_edges);
 hipError_t contract_set_lds_limit(int bytes);
 
 // ints of the pre-pass's work counters: one counter per XCD, each on a cache line of its own

@@ -18,36 +18,77 @@
 // member index and every neighbour list is ascending.
 #include <limits.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace dc {
 namespace {
 
-constexpr int kCT = 1024;       // threads per contraction workgroup
-constexpr int kCW = kCT / 64;   // waves per workgroup
-constexpr int kSmallRow = 16;   // lists up to this length are sorted by one thread in registers, up to 64 by a wave
+constexpr int kTinyRow = 4;     // lists up to this length are sorted where they are met, by one thread in registers,
+constexpr int kSmallRow = 16;   // up to this length by one thread once all such are known, up to 64 by a wave
+constexpr int kBmWaves = 2;     // waves that sort lists of more than 64 entries, through a bitmap each
 constexpr unsigned short kSelf = 0xFFFF;
 
 typedef unsigned short u16;
+typedef unsigned long long u64;
 
-// Byte offsets of the per-candidate working arrays (same on host and device).
+// Working arrays of a candidate (byte offsets, the same on host and device).  Counters and starts are 16-bit in LDS and
+// 32-bit in global memory (`wide`).  nd = 2: successors and predecessors as one array of 2 G rows, nd = 1: one after the
+// other.
+//   ids:    u16 NID[N]: labels, then contracted ids | bitmaps, row numbers set aside, then masks (nd = 2: in the ids' place)
+//   first:  MS[N + 1] group ends, int FIRST[N] (then u16 MEM[N], LST), u64 HM / int HP: heads and their ranks
+//   later:  OFF[nd N + 1] row ends, u16 RAW[nd E] neighbours by row
 struct Slab {
-  int A, MS, UL, BM, NID, MEM, RAW, LST, total;
+  int nid, lst2, longest2, bm, mask, pre, ms, first, hm, hp, off, raw, nd, total;
 };
 __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
-__host__ __device__ inline Slab slab_layout(int N, int E) {
+__host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) {
+  const int os = wide ? 4 : 2, rows = nd * N, slots = nd * E, w = (slots + 63) / 64 + 1, hw = (N + 63) / 64 + 1;
   Slab s;
-  int o = 0;
-  s.A = o;   o = align16(o + 4 * (N + 1));          // int   [N+1] label->first / cursors / raw offsets
-  s.MS = o;  o = align16(o + 4 * (N + 1));          // int   [N+1] group start in MEM
-  s.UL = o;  o = align16(o + 4 * (N + 1));          // int   [N+1] flags / row lengths / local rowptr
-  s.BM = o;  o = align16(o + 4 * kCW * ((N + 31) / 32 + 1));  // per-wave bitmaps
-  s.NID = o; o = align16(o + 2 * (N + 1));          // u16   [N] contracted id per base node
-  s.MEM = o; o = align16(o + 2 * (N + 1));          // u16   [N] base nodes grouped by contracted id
-  s.RAW = o; o = align16(o + 2 * ((E > N ? E : N) + 1));   // u16 [max(E,N)] labels, later remapped neighbours by row
-  s.LST = o; o = align16(o + 2 * (N + 1));          // u16   [N] lists set aside for the second sorting pass
+  s.nd = nd;
+  s.nid = 0;
+  const int ids = align16(2 * (N + 2));
+  const int bm = align16(4 * kBmWaves * ((N + 31) / 32 + 1)), mask = align16(8 * w) + align16(4 * w);
+  const int lst = align16(os * (slots / (kTinyRow + 1) + 2));
+  const int longest = align16(os * (slots / (kSmallRow + 1) + 2));
+  const int aux = bm + (mask > lst + longest ? mask : lst + longest);
+  const int x = nd == 2 && aux > ids ? aux : ids;
+  int o = x;
+  s.ms = o;    o = align16(o + os * (N + 2));
+  s.first = o; o = align16(o + 4 * N + 4 * os);
+  s.hm = o;    o = align16(o + 8 * hw);
+  s.hp = o;    o = align16(o + 4 * hw);
   s.total = o;
+  o = x;
+  s.off = o;   o = align16(o + os * (rows + 2));
+  s.raw = o;   o = align16(o + 2 * (slots + 2));
+  s.bm = nd == 2 ? 0 : o;                  // one after the other: the ids are needed again
+  s.lst2 = s.mask = s.bm + bm;
+  s.longest2 = s.lst2 + lst;
+  s.pre = s.mask + align16(8 * w);
+  if (nd == 1) o += aux;
+  if (o > s.total) s.total = o;
+  if (!wide && slots > 65535) s.total = INT_MAX;
   return s;
+}
+// Both directions at once, in half the phases, where that fits.
+__host__ __device__ inline Slab slab_layout(int N, int E, int lds) {
+  const Slab s = slab_layout_nd(N, E, 2, false);
+  return s.total <= lds ? s : slab_layout_nd(N, E, 1, false);
+}
+__host__ __device__ inline int slab_need(int N, int E) { return slab_layout_nd(N, E, 1, false).total; }
+
+// Classes of base graphs by working set (one direction after the other): four, two and one workgroup per CU, which its 16
+// waves of some 110 registers allow; a workgroup takes its share of the LDS.  1024 candidates of 1.6 k nodes: 131 us with
+// sixteen waves each, 45 us with four; 4096 of 6.6 k nodes: 762 us with eight waves, 584 with sixteen.
+constexpr int kStatic = 256;               // static LDS of the kernel
+struct SizeClass {
+  int most, lds, threads;
+};
+__host__ __device__ inline SizeClass size_class_of(int k, int lds_limit) {
+  const int lds = k == 2 ? lds_limit : (40960 << k) - kStatic, share = lds < lds_limit ? lds : lds_limit;
+  return {k == 2 ? share : share / 2, share, 256 << k};
 }
 
 // Short lists (up to 16 entries) are sorted by one thread each, in registers, with a
@@ -71,86 +112,239 @@ __device__ __forceinline__ void sort_network(unsigned (&v)[NN]) {
           }
 }
 
-// Sorts a[0..n) ascending, drops entries equal to kSelf and repeats; returns the count kept.
+// Sorts a[0..n) ascending, n <= NN; kSelf in the place of a repeat.  The reads are unconditional (a[0] is readable with
+// n = 0 too): behind a condition each would wait for the one before it.
 template <int NN>
-__device__ __forceinline__ int sort_unique_small(u16* a, int n) {
+__device__ __forceinline__ void sort_unique_small(u16* a, int n) {
   unsigned v[NN];
 #pragma unroll
-  for (int k = 0; k < NN; ++k) v[k] = k < n ? (unsigned)a[k] : (unsigned)kSelf;
-  sort_network<NN>(v);
-  int m = 0;
+  for (int k = 0; k < NN; ++k) v[k] = a[min(k, max(n - 1, 0))];
 #pragma unroll
-  for (int k = 0; k < NN; ++k) {
-    const bool keep = v[k] != (unsigned)kSelf && (k == 0 || v[k] != v[k - 1]);
-    if (keep) a[m++] = (u16)v[k];
-  }
-  return m;
+  for (int k = 0; k < NN; ++k) v[k] = k < n ? v[k] : (unsigned)kSelf;
+  sort_network<NN>(v);
+#pragma unroll
+  for (int k = 0; k < NN; ++k)
+    if (k < n) a[k] = (k > 0 && v[k] == v[k - 1]) ? kSelf : (u16)v[k];
 }
 
-// Picks the smallest network that covers every list of the wave (n is 0 for lanes without one).
-__device__ __forceinline__ int sort_unique_by_class(u16* a, int n) {
-  if (__any(n > 8)) return sort_unique_small<16>(a, n);
-  if (__any(n > 4)) return sort_unique_small<8>(a, n);
-  if (__any(n > 1)) return sort_unique_small<4>(a, n);
-  return (n == 1 && a[0] != kSelf) ? 1 : 0;
+// Same for up to 64 entries by a whole wave (lane i holds entry i): an entry's place is the number of smaller ones.
+__device__ __forceinline__ void sort_wave(u16* a, int n, int lane) {
+  const unsigned x = a[min(lane, n - 1)];
+  const int key = (int)(x << 6) | lane;
+  int pos = 0;
+#pragma unroll 4
+  for (int j = 0; j < n; ++j) pos += __builtin_amdgcn_readlane(key, j) < key ? 1 : 0;
+  if (lane < n) a[pos] = (u16)x;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  const u16 y = a[min(lane, n - 1)], before = a[max(min(lane, n - 1) - 1, 0)];
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  if (lane > 0 && lane < n && y == before) a[lane] = kSelf;
 }
 
-// Same for one list of up to 64 entries held by a whole wave (lane i holds entry i).
-__device__ __forceinline__ bool rank64(unsigned x, int lane, int n, int& pos, int& m) {
-  bool first = lane < n && x != kSelf;
-  for (int j = 0; j < n; ++j) {
-    const unsigned y = (unsigned)__shfl((int)x, j, 64);
-    if (j < lane && y == x) first = false;
-  }
-  const unsigned long long kb = __ballot(first);
-  int p = 0;
-  for (int j = 0; j < n; ++j) {
-    const unsigned y = (unsigned)__shfl((int)x, j, 64);
-    if (((kb >> j) & 1ull) && y < x) ++p;
-  }
-  pos = p;
-  m = __popcll(kb);
-  return first;
-}
-
-// The body works on plain pointers; instantiated once with LDS pointers and
-// once with global-memory pointers.
+// A barrier for working arrays in LDS: results on their way to memory, which nobody reads here, are not waited for.
 template <bool kLds>
-__device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b, int N, char* base, const Slab& L,
-                                             const int* cand_off, const int* label, const ContractTmp& tmp,
-                                             int* new_id_out, int* status, int* wsum) {
-  const int t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6;
-  int* A = reinterpret_cast<int*>(base + L.A);
-  int* MS = reinterpret_cast<int*>(base + L.MS);
-  int* UL = reinterpret_cast<int*>(base + L.UL);
-  const int bm_words = (N + 31) / 32 + 1;
-  unsigned* BM = reinterpret_cast<unsigned*>(base + L.BM) + wave * bm_words;
-  u16* NID = reinterpret_cast<u16*>(base + L.NID);
-  u16* MEM = reinterpret_cast<u16*>(base + L.MEM);
-  u16* RAW = reinterpret_cast<u16*>(base + L.RAW);
-  u16* LST = reinterpret_cast<u16*>(base + L.LST);
-  int* lst_cnt = wsum + kCW;       // one more word behind the scan's wave sums
+__device__ __forceinline__ void block_sync() {
+  if (kLds) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  } else {
+    __syncthreads();
+  }
+}
 
-  const int coff = cand_off[c];
+// Counters: one more at place i, returns what was there.  16-bit ones lie in pairs (LDS has no 16-bit atomics); the
+// arrays hold at most 65535 entries, so no counter carries into its neighbour.
+__device__ __forceinline__ int count_one(u16* a, int i) {
+  const int sh = (i & 1) * 16;
+  return (int)((atomicAdd(reinterpret_cast<unsigned*>(a) + (i >> 1), 1u << sh) >> sh) & 0xFFFFu);
+}
+__device__ __forceinline__ int count_one(int* a, int i) { return atomicAdd(&a[i], 1); }
+
+// The sum over the waves in front of this one, and over all of them (`total`), of what each wave's last lane has in `inc`.
+template <bool kLds>
+__device__ __forceinline__ int wave_offsets(int inc, int& total, int* wsum) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, nw = blockDim.x >> 6;
+  if (lane == 63) wsum[wave] = inc;
+  block_sync<kLds>();
+  const int x = wave_incl_scan(lane < nw ? wsum[lane & 15] : 0);
+  total = __builtin_amdgcn_readlane(x, 63);
+  return __builtin_amdgcn_readlane(x, wave) - __builtin_amdgcn_readlane(inc, 63);
+}
+
+// Exclusive scan in place; the entry behind the last is 0 before and may be anything after.  Returns the total.
+__device__ __forceinline__ int exscan(u16* a, int n, int* wsum) {
+  unsigned* w = reinterpret_cast<unsigned*>(a);
+  const int t = threadIdx.x, T = blockDim.x, nw = (n + 1) >> 1;
+  const int K = ((nw + T - 1) / T) | 1;          // an odd run of words per thread: no two lanes of a half wave in one bank
+  const int lo = min(t * K, nw), hi = min(lo + K, nw);
+  int s = 0;
+  for (int i = lo; i < hi; ++i) s += (w[i] & 0xFFFF) + (w[i] >> 16);
+  const int inc = wave_incl_scan(s);
+  int total;
+  int run = wave_offsets<true>(inc, total, wsum) + inc - s;
+  for (int i = lo; i < hi; ++i) {
+    const unsigned x = w[i];
+    const int mid = run + (x & 0xFFFF);
+    w[i] = (unsigned)run | ((unsigned)mid << 16);
+    run = mid + (x >> 16);
+  }
+  block_sync<true>();
+  return total;
+}
+__device__ __forceinline__ int exscan(int* a, int n, int* wsum) { return block_exscan_lines(a, a, n, wsum); }
+
+// pre[w] = bits set in front of word w of m, pre[nw] = all of them (returned); m[nw] = 0
+template <bool kLds>
+__device__ __forceinline__ int scan_bits(u64* m, int* pre, int nw, int* wsum) {
+  const int t = threadIdx.x, T = blockDim.x;
+  int carry = 0;
+  for (int w0 = 0; w0 < nw; w0 += T) {
+    const int w = w0 + t, pc = w < nw ? __popcll(m[w]) : 0;
+    const int inc = wave_incl_scan(pc);
+    int total;
+    const int run = carry + wave_offsets<kLds>(inc, total, wsum) + inc - pc;
+    if (w < nw) pre[w] = run;
+    carry += total;
+    if (w0 + T < nw) block_sync<kLds>();         // wsum is written again
+  }
+  if (t == 0) {
+    m[nw] = 0;
+    pre[nw] = carry;
+  }
+  block_sync<kLds>();
+  return carry;
+}
+// Bit i of m: `set(i)`, i < n.  A wave takes kBatch words of 64 at a time.
+template <int kBatch, typename Set>
+__device__ __forceinline__ void fill_bits(u64* m, int n, Set set) {
+  const int t = threadIdx.x, T = blockDim.x, lane = t & 63;
+  for (int i0 = t & ~63; i0 < n; i0 += kBatch * T) {
+    bool x[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) x[j] = set(min(i0 + j * T + lane, n - 1));
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int i = i0 + j * T;
+      const u64 b = __ballot(x[j] && i + lane < n);
+      if (lane == 0 && i < n) m[i >> 6] = b;
+    }
+  }
+}
+// Four neighbouring entries in one store; p is aligned to an entry only.
+__device__ __forceinline__ void store4(int* p, int a, int b, int c, int d) {
+  struct __attribute__((packed, aligned(4))) Quad { int x[4]; };
+  *reinterpret_cast<Quad*>(p) = Quad{{a, b, c, d}};
+}
+// p[i] = value(i), i < n; a thread takes four neighbouring entries (a store costs a CU some 40 cycles whatever its width)
+template <typename Value>
+__device__ __forceinline__ void store_all(int* p, int n, Value value) {
+  for (int i = 4 * threadIdx.x; i < n; i += 4 * blockDim.x) {
+    if (i + 4 <= n) store4(p + i, value(i), value(i + 1), value(i + 2), value(i + 3));
+    else for (int k = i; k < n; ++k) p[k] = value(k);
+  }
+}
+__device__ __forceinline__ int bits_before(const u64* m, const int* pre, int i) {
+  return pre[i >> 6] + __popcll(m[i >> 6] & ((1ull << (i & 63)) - 1ull));
+}
+
+// Rows r < rows of `a`, row r ending at end[r], each ascending, kSelf in the place of a repeat.  Rows of up to four entries
+// are sorted as they are met; the others are set aside, those of up to eight from the front of `lst`, of up to 16 from
+// its back (`room` entries), so that the waves that sort them are full and take one network each.  More than 16
+// entries (`longest`): `longer(r, begin, n)`, called by whole waves, all of them for up to 64 entries, the first kBmWaves
+// for more.  cnt[0 .. 2] are 0.
+template <bool kLds, typename Off, typename Longer>
+__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, Off* longest, int* cnt, Longer longer) {
+  const int t = threadIdx.x, T = blockDim.x, wave = t >> 6, lane = t & 63;
+  auto begin = [&](int r) { return r ? (int)end[r - 1] : 0; };
+  for (int r = t; r < rows; r += T) {
+    const int s = begin(r), n = (int)end[r] - s;
+    if (n > kSmallRow) longest[atomicAdd(&cnt[2], 1)] = (Off)r;
+    else if (n > 2 * kTinyRow) lst[room - 1 - atomicAdd(&cnt[1], 1)] = (Off)r;
+    else if (n > kTinyRow) lst[atomicAdd(&cnt[0], 1)] = (Off)r;
+    else if (n > 1) sort_unique_small<kTinyRow>(a + s, n);
+  }
+  block_sync<kLds>();
+  const int n8 = cnt[0], n16 = cnt[1], nl = cnt[2], w8 = (n8 + 63) >> 6, w16 = (n16 + 63) >> 6;
+  for (int w = wave; w < w8 + w16; w += T >> 6) {
+    if (w < w16) {                               // the longer network first
+      const int i = w * 64 + lane;
+      if (i < n16) {
+        const int r = lst[room - 1 - i], s = begin(r);
+        sort_unique_small<kSmallRow>(a + s, (int)end[r] - s);
+      }
+    } else {
+      const int i = (w - w16) * 64 + lane;
+      if (i < n8) {
+        const int r = lst[i], s = begin(r);
+        sort_unique_small<2 * kTinyRow>(a + s, (int)end[r] - s);
+      }
+    }
+  }
+  // the last waves first: the first ones have the networks
+  for (int pass = 0; pass < 2; ++pass) {
+    const int step = pass ? kBmWaves : T >> 6, first = pass ? wave : step - 1 - wave;
+    if (wave >= step) break;
+    for (int i = first; i < nl; i += step) {
+      const int r = longest[i], s = begin(r), n = (int)end[r] - s;
+      if ((n > 64) == (pass == 1)) longer(r, s, n);
+    }
+  }
+  block_sync<kLds>();
+}
+
+// One candidate, working arrays in LDS (counters of 16 bits) or in global memory.  Bound by the latency of its phases:
+// about twenty, a barrier each, of a few dependent LDS accesses.  Edges are dealt to the threads as (source, target) pairs
+// and counted, then placed, by group; those inside a group never enter a row.  What is left of the rows after sorting
+// is found through a mask over their places, so that lists and row starts leave in order, whole lines at a time.
+// One candidate of 6.5 k nodes and 10 k edges in 1.4 k groups: 58 us with a scan per direction over all members and lists
+// gathered member by member, 36 us; 4096 of them 866 -> 584 us, 1000 of 6.5 k groups 224 -> 159 us; 8192 candidates of
+// 64 graphs of up to 19 k nodes, the larger ones in global memory before, 4.9 -> 1.4 ms.
+template <bool kLds, int kBatch>
+__device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b, int N, int E, char* base, const Slab& L,
+                                             int coff, int eslot, const int* label, const ContractTmp& tmp,
+                                             int* new_id_out, int* status, int* wsum) {
+  typedef typename std::conditional<kLds, u16, int>::type Off;
+  const int t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6;
+  u16* NID = reinterpret_cast<u16*>(base + L.nid);
+  Off* MS = reinterpret_cast<Off*>(base + L.ms);
+  int* FIRST = reinterpret_cast<int*>(base + L.first);
+  u16* MEM = reinterpret_cast<u16*>(FIRST);                       // once the ids are known
+  Off* LST = reinterpret_cast<Off*>(base + L.first + align16(2 * N));
+  Off* LONGEST = LST + N / (kTinyRow + 1) + 1;
+  u64* HM = reinterpret_cast<u64*>(base + L.hm);
+  int* HP = reinterpret_cast<int*>(base + L.hp);
+  int* cnt = wsum + 16;            // three words behind the scans' wave sums
+
   const int* lab = label + coff;
   int* nid_out = new_id_out + coff;
   const int nslot = coff + c;
-  const int eslot = tmp.tmp_eoff[c];
+  const unsigned* edge = bg.edge + bg.geo[b];
+
+  // The lanes of a wave take nodes far from each other where they count or place by group: neighbours are mostly in one
+  // group, and atomics on one word follow each other (edges lie in memory in such an order).  An odd distance: every
+  // lane in a bank of its own.
+  const int apart = ((N + 63) >> 6) | 1, spread = apart << 6;
+  auto node = [&](int i) { return i < spread ? (i & 63) * apart + (i >> 6) : N; };
 
   // ---- relabel: groups numbered by ascending smallest member -----------------
   int bad = 0;
-  u16* LAB = RAW;                 // labels stay in LDS until the ids are known; RAW is unused until then
-#pragma unroll 4
-  for (int v = t; v < N; v += T) {
-    A[v] = INT_MAX;
-    int l = lab[v];
-    bad |= (l < 0) | (l >= N);
-    LAB[v] = (u16)l;
+  for (int v0 = t; v0 < N; v0 += kBatch * T) {
+    int l[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) l[j] = lab[min(v0 + j * T, N - 1)];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int v = v0 + j * T;
+      bad |= (l[j] < 0) | (l[j] >= N);
+      if (v < N) {
+        NID[v] = (u16)l[j];
+        FIRST[v] = INT_MAX;
+      }
+    }
   }
-  {
-    unsigned* bmall = reinterpret_cast<unsigned*>(base + L.BM);
-    for (int i = t; i < kCW * bm_words; i += T) bmall[i] = 0u;
-  }
+  for (int i = t; i < (int)(sizeof(Off) * (N + 2)) / 4; i += T) reinterpret_cast<int*>(MS)[i] = 0;
+  if (t < 3) cnt[t] = 0;
   if (__syncthreads_or(bad)) {
     if (t == 0) {
       set_error(status, (int)DC_ERR_BAD_PARTITION);
@@ -159,236 +353,175 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
     }
     return;
   }
-  for (int v = t; v < N; v += T) atomicMin(&A[LAB[v]], v);
-  __syncthreads();
-  for (int v = t; v < N; v += T) UL[v] = (A[LAB[v]] == v) ? 1 : 0;
-  __syncthreads();
-  const int G = kLds ? block_exscan(UL, UL, N, wsum) : block_exscan_lines(UL, UL, N, wsum);
-  if (t == 0) UL[N] = G;
-  __syncthreads();
-  for (int v = t; v < N; v += T)
-    if (UL[v + 1] != UL[v]) A[LAB[v]] = UL[v];   // head of its group: rank among heads
-  __syncthreads();
-  for (int v = t; v < N; v += T) {
-    int g = A[LAB[v]];
-    NID[v] = (u16)g;
-    nid_out[v] = g;
+  for (int i = t; i < spread; i += kBatch * T) {
+    int l[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) l[j] = NID[min(node(i + j * T), N - 1)];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (node(i + j * T) < N) atomicMin(&FIRST[l[j]], node(i + j * T));
   }
-  __syncthreads();
+  block_sync<kLds>();
+  fill_bits<kBatch>(HM, N, [&](int v) { return FIRST[NID[v]] == v; });
+  block_sync<kLds>();
+  const int G = scan_bits<kLds>(HM, HP, (N + 63) >> 6, wsum);
+  for (int i = t; i < spread; i += kBatch * T) {
+    int g[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) g[j] = NID[min(node(i + j * T), N - 1)];
+    // a place past the end is another thread's last one, which may hold its id already
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) g[j] = FIRST[node(i + j * T) < N ? g[j] : 0];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) g[j] = bits_before(HM, HP, node(i + j * T) < N ? g[j] : 0);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int v = node(i + j * T);
+      if (v < N) {
+        NID[v] = (u16)g[j];
+        count_one(MS, g[j]);
+      }
+    }
+  }
+  block_sync<kLds>();
 
-  // ---- member lists: counting sort by group, ascending inside a group ---------
-  for (int g = t; g < G; g += T) A[g] = 0;
-  __syncthreads();
-  for (int v = t; v < N; v += T) atomicAdd(&A[NID[v]], 1);
-  __syncthreads();
-  if (kLds) block_exscan(A, MS, G, wsum); else block_exscan_lines(A, MS, G, wsum);
-  if (t == 0) MS[G] = N;
-  __syncthreads();
-  for (int g = t; g < G; g += T) A[g] = MS[g];
-  __syncthreads();
-  for (int v = t; v < N; v += T) {
-    int pos = atomicAdd(&A[NID[v]], 1);
-    MEM[pos] = (u16)v;
+  // ---- member lists: counting sort by group, then ascending inside a group ---------
+  exscan(MS, G, wsum);
+  for (int i = t; i < spread; i += kBatch * T) {
+    int g[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) g[j] = NID[min(node(i + j * T), N - 1)];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (node(i + j * T) < N) g[j] = count_one(MS, g[j]);                 // MS[g] becomes the end of group g
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (node(i + j * T) < N) MEM[g[j]] = (u16)node(i + j * T);
   }
-  __syncthreads();
-  {
-    // ascending order inside each group (the atomics above placed members in arrival order):
-    // groups of up to 16 at once, one thread each; longer ones are set aside and taken
-    // densely packed afterwards (up to 32: one thread; up to 64: one wave; else all nodes)
-    if (t == 0) *lst_cnt = 0;
-    __syncthreads();
-    for (int g0 = 0; g0 < G; g0 += T) {         // uniform trip count: the wave votes on the network size
-      const int g = g0 + t;
-      int s = 0, n = 0;
-      if (g < G) {
-        s = MS[g];
-        n = MS[g + 1] - s;
-      }
-      if (n > kSmallRow) {
-        LST[atomicAdd(lst_cnt, 1)] = (u16)g;
-        n = 0;
-      }
-      sort_unique_by_class(MEM + s, n);          // members are distinct: all are kept
+  block_sync<kLds>();
+  sort_rows<kLds>(MEM, MS, G, LST, N / (kTinyRow + 1) + 1, LONGEST, cnt, [&](int g, int s, int n) {
+    if (n <= 64) {
+      sort_wave(MEM + s, n, lane);
+      return;
     }
-    __syncthreads();
-    const int nl = *lst_cnt;
-    int big = 0;
-    for (int i0 = 0; i0 < nl; i0 += T) {
-      const int i = i0 + t;
-      int s = 0, n = 0;
-      if (i < nl) {
-        const int g = LST[i];
-        s = MS[g];
-        n = MS[g + 1] - s;
-        if (n > 32) {
-          big = 1;
-          n = 0;
-        }
-      }
-      if (__any(n > 0)) sort_unique_small<32>(MEM + s, n);
+    // large groups: ordered compaction over all nodes
+    int cnt = 0;
+    for (int v0 = 0; v0 < N; v0 += 64) {
+      const int v = v0 + lane;
+      const bool f = v < N && NID[v] == g;
+      const u64 m = __ballot(f);
+      if (f) MEM[s + cnt + __popcll(m & ((1ull << lane) - 1ull))] = (u16)v;
+      cnt += __popcll(m);
     }
-    if (__syncthreads_or(big)) {
-      for (int i = wave; i < nl; i += kCW) {
-        const int g = LST[i];
-        const int s = MS[g], n = MS[g + 1] - s;
-        if (n <= 32) continue;
-        if (n <= 64) {
-          const unsigned x = lane < n ? MEM[s + lane] : kSelf;
-          int pos, m;
-          const bool keep = rank64(x, lane, n, pos, m);
-          if (keep) MEM[s + pos] = (u16)x;
-          continue;
-        }
-        // large groups: ordered compaction over all nodes
-        int cnt = 0;
-        for (int v0 = 0; v0 < N; v0 += 64) {
-          int v = v0 + lane;
-          bool f = v < N && NID[v] == g;
-          unsigned long long m = __ballot(f);
-          if (f) MEM[s + cnt + __popcll(m & ((1ull << lane) - 1ull))] = (u16)v;
-          cnt += __popcll(m);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  for (int i = t; i < N; i += T) tmp.members[coff + i] = MEM[i];
-  for (int g = t; g <= G; g += T) tmp.mstart[nslot + g] = MS[g];
+  });
+  store_all(nid_out, N, [&](int v) { return (int)NID[v]; });
+  store_all(tmp.members + coff, N, [&](int i) { return (int)MEM[i]; });
+  store_all(tmp.mstart + nslot, G + 1, [&](int g) { return g ? (int)MS[g - 1] : 0; });
+  block_sync<kLds>();
 
-  // ---- neighbour lists: successors (dir 0), then predecessors (dir 1) ----------
+  // ---- neighbour lists: successors are rows 0 .. G - 1, predecessors the next G (nd = 2), or one after the other ----------
+  const int nd = L.nd, rows = nd * G;
+  Off* OFF = reinterpret_cast<Off*>(base + L.off);
+  u16* RAW = reinterpret_cast<u16*>(base + L.raw);
+  Off* LST2 = reinterpret_cast<Off*>(base + L.lst2);
+  Off* LONGEST2 = reinterpret_cast<Off*>(base + L.longest2);
+  u64* MASK = reinterpret_cast<u64*>(base + L.mask);
+  int* PRE = reinterpret_cast<int*>(base + L.pre);
+  const int bm_words = (N + 31) / 32 + 1;
+  unsigned* BM = reinterpret_cast<unsigned*>(base + L.bm);
   int Ec = 0;
-  for (int dir = 0; dir < 2; ++dir) {
-    const int* rp = (dir == 0 ? bg.rowptr : bg.crowptr) + bg.gno[b] + b;
-    const int* ci = (dir == 0 ? bg.col : bg.ccol) + bg.geo[b];
-    int* t_rp = (dir == 0 ? tmp.orp : tmp.irp) + nslot;
-    int* t_ci = (dir == 0 ? tmp.oc : tmp.ic) + eslot;
-
-#pragma unroll 4
-    for (int i = t; i < N; i += T) {
-      int u = MEM[i];
-      A[i] = rp[u + 1] - rp[u];
-    }
-    __syncthreads();
-    const int Eraw = kLds ? block_exscan(A, A, N, wsum) : block_exscan_lines(A, A, N, wsum);
-    if (t == 0) A[N] = Eraw;
-    __syncthreads();
-    // four member slots per thread and round: their row starts and first neighbours are
-    // requested together so that the global-memory latency is paid once per round
-    for (int i0 = t; i0 < N; i0 += 4 * T) {
-      int uu[4], o[4], dg[4], r0[4], c0[4];
+  for (int dir = 0; dir < 2; dir += nd) {
+    for (int i = t; i < (int)(sizeof(Off) * (rows + 2)) / 4; i += T) reinterpret_cast<int*>(OFF)[i] = 0;
+    if (t < 3) cnt[t] = 0;
+    block_sync<kLds>();
+    // counts the edges between groups, or places them; the others and those past the end are left out
+    auto each_edge = [&](auto place) {
+      for (int e0 = t; e0 < E; e0 += kBatch * T) {
+        unsigned x[kBatch];
+        int gu[kBatch], gw[kBatch];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int i = i0 + j * T;
-        const bool ok = i < N;
-        uu[j] = ok ? MEM[i] : 0;
-        o[j] = ok ? A[i] : 0;
-        dg[j] = ok ? A[i + 1] - A[i] : 0;
-      }
+        for (int j = 0; j < kBatch; ++j) x[j] = edge[min(e0 + j * T, E - 1)];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) r0[j] = dg[j] > 0 ? rp[uu[j]] : 0;
+        for (int j = 0; j < kBatch; ++j) {
+          gu[j] = NID[x[j] & 0xFFFF];
+          gw[j] = NID[x[j] >> 16];
+          if (e0 + j * T >= E) gw[j] = gu[j];
+        }
+        int po[kBatch], pi[kBatch];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) c0[j] = dg[j] > 0 ? ci[r0[j]] : 0;
+        for (int j = 0; j < kBatch; ++j) {
+          if (gu[j] != gw[j] && (nd == 2 || dir == 0)) po[j] = count_one(OFF, gu[j]);
+          if (gu[j] != gw[j] && (nd == 2 || dir == 1)) pi[j] = count_one(OFF, (nd - 1) * G + gw[j]);
+        }
+        if (place.value) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (dg[j] > 0) {
-          const int g = NID[uu[j]];
-          int w = NID[c0[j]];
-          RAW[o[j]] = (w == g) ? kSelf : (u16)w;
-          for (int k = 1; k < dg[j]; ++k) {
-            w = NID[ci[r0[j] + k]];
-            RAW[o[j] + k] = (w == g) ? kSelf : (u16)w;
+          for (int j = 0; j < kBatch; ++j) {
+            if (gu[j] != gw[j] && (nd == 2 || dir == 0)) RAW[po[j]] = (u16)gw[j];
+            if (gu[j] != gw[j] && (nd == 2 || dir == 1)) RAW[pi[j]] = (u16)gu[j];
           }
         }
       }
-    }
-    __syncthreads();
-    // same three passes as for the member lists; here entries equal to kSelf and repeats go
-    if (t == 0) *lst_cnt = 0;
-    __syncthreads();
-    for (int g0 = 0; g0 < G; g0 += T) {         // uniform trip count: the wave votes on the network size
-      const int g = g0 + t;
-      int s = 0, n = 0;
-      if (g < G) {
-        s = A[MS[g]];
-        n = A[MS[g + 1]] - s;
+      block_sync<kLds>();
+    };
+    each_edge(std::false_type{});
+    const int S = exscan(OFF, rows, wsum);
+    each_edge(std::true_type{});
+    for (int i = t; i < kBmWaves * bm_words; i += T) BM[i] = 0u;      // seen by all before the first list of more than 64
+    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (kTinyRow + 1) + 1, LONGEST2, cnt, [&](int, int s, int n) {
+      if (n <= 64) {
+        sort_wave(RAW + s, n, lane);
+        return;
       }
-      const bool here = n <= kSmallRow;
-      if (!here) {
-        LST[atomicAdd(lst_cnt, 1)] = (u16)g;
-        n = 0;
+      // mark neighbours in the wave's bitmap, then list the set bits
+      unsigned* bm = BM + wave * bm_words;
+      for (int i = lane; i < n; i += 64) {
+        const u16 x = RAW[s + i];
+        atomicOr(&bm[x >> 5], 1u << (x & 31));
       }
-      const int m = sort_unique_by_class(RAW + s, n);
-      if (here && g < G) UL[g] = m;
-    }
-    __syncthreads();
-    const int nl = *lst_cnt;
-    int big = 0;
-    for (int i0 = 0; i0 < nl; i0 += T) {
-      const int i = i0 + t;
-      int s = 0, n = 0, g = 0;
-      if (i < nl) {
-        g = LST[i];
-        s = A[MS[g]];
-        n = A[MS[g + 1]] - s;
-        if (n > 32) {
-          big = 1;
-          n = 0;
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      int cnt = 0;
+      for (int w0 = 0; w0 < (G + 31) / 32; w0 += 64) {
+        const int w = w0 + lane;
+        unsigned bits = (w < (G + 31) / 32) ? bm[w] : 0u;
+        if (bits) bm[w] = 0u;
+        const int pc = __popc(bits);
+        const int inc = wave_incl_scan(pc);
+        int o = s + cnt + inc - pc;
+        while (bits) {
+          RAW[o++] = (u16)((w << 5) + __ffs(bits) - 1);
+          bits &= bits - 1;
         }
+        cnt += __shfl(inc, 63, 64);
       }
-      if (__any(n > 0)) {
-        const int m = sort_unique_small<32>(RAW + s, n);
-        if (n > 0) UL[g] = m;
-      }
-    }
-    if (__syncthreads_or(big)) {
-      const int W = (G + 31) / 32;
-      for (int i = wave; i < nl; i += kCW) {
-        const int g = LST[i];
-        const int s = A[MS[g]], n = A[MS[g + 1]] - s;
-        if (n <= 32) continue;
-        if (n <= 64) {
-          const unsigned x = lane < n ? RAW[s + lane] : kSelf;
-          int pos, m;
-          const bool keep = rank64(x, lane, n, pos, m);
-          if (keep) RAW[s + pos] = (u16)x;
-          if (lane == 0) UL[g] = m;
-          continue;
-        }
-        // long rows: mark neighbours in a per-wave bitmap, then list the set bits
-        for (int i2 = lane; i2 < n; i2 += 64) {
-          u16 x = RAW[s + i2];
-          if (x != kSelf) atomicOr(&BM[x >> 5], 1u << (x & 31));
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        int cnt = 0;
-        for (int w0 = 0; w0 < W; w0 += 64) {
-          const int w = w0 + lane;
-          unsigned bits = (w < W) ? BM[w] : 0u;
-          if (bits) BM[w] = 0u;
-          const int pc = __popc(bits);
-          const int inc = wave_incl_scan(pc);
-          int o = s + cnt + inc - pc;
-          while (bits) {
-            int bpos = __ffs(bits) - 1;
-            RAW[o++] = (u16)((w << 5) + bpos);
-            bits &= bits - 1;
+      for (int i = cnt + lane; i < n; i += 64) RAW[s + i] = kSelf;
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    });
+    fill_bits<kBatch>(MASK, S, [&](int i) { return RAW[i] != kSelf; });
+    block_sync<kLds>();
+    const int kept = scan_bits<kLds>(MASK, PRE, (S + 63) >> 6, wsum);
+    Ec = nd == 2 ? kept >> 1 : kept;                   // every kept edge is in one list of either kind
+    int* col0 = (dir == 0 ? tmp.oc : tmp.ic) + eslot;
+    int* col1 = tmp.ic + eslot;
+    // four places per thread: mostly all of them are kept and leave together
+    for (int s = 4 * t; s < S; s += 4 * T) {
+      const u64 m = MASK[s >> 6];
+      const unsigned four = (unsigned)(m >> (s & 63)) & 15u;
+      int k = PRE[s >> 6] + __popcll(m & ((1ull << (s & 63)) - 1ull));
+      if (four == 15u && (k >= Ec || k + 4 <= Ec)) {
+        store4(k < Ec ? col0 + k : col1 + (k - Ec), RAW[s], RAW[s + 1], RAW[s + 2], RAW[s + 3]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if ((four >> j) & 1u) {
+            *(k < Ec ? col0 + k : col1 + (k - Ec)) = RAW[s + j];
+            ++k;
           }
-          cnt += __shfl(inc, 63, 64);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        if (lane == 0) UL[g] = cnt;
       }
     }
-    __syncthreads();
-    Ec = kLds ? block_exscan(UL, UL, G, wsum) : block_exscan_lines(UL, UL, G, wsum);
-    if (t == 0) UL[G] = Ec;
-    __syncthreads();
-    for (int g = t; g <= G; g += T) t_rp[g] = UL[g];
-    for (int g = t; g < G; g += T) {
-      const int s = A[MS[g]], o = UL[g], n = UL[g + 1] - o;
-      for (int k = 0; k < n; ++k) t_ci[o + k] = RAW[s + k];
-    }
-    __syncthreads();
+    auto row_start = [&](int r) { return r ? bits_before(MASK, PRE, (int)OFF[r - 1]) : 0; };
+    store_all((dir == 0 ? tmp.orp : tmp.irp) + nslot, G + 1, row_start);
+    if (nd == 2) store_all(tmp.irp + nslot, G + 1, [&](int g) { return row_start(G + g) - Ec; });
+    block_sync<kLds>();
   }
   if (t == 0) {
     tmp.Gc[c] = G;
@@ -398,21 +531,23 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
 
 extern __shared__ __attribute__((aligned(16))) char dc_smem[];
 
-template <bool kLds>
-__global__ __launch_bounds__(kCT) void contract_kernel(BaseGraphs bg, int C, const int* cand_graph,
-                                                        const int* cand_off, const int* label, ContractTmp tmp,
-                                                        int* new_id_out, int* status, char* gslab,
-                                                        size_t slab_stride, int lds_bytes) {
-  __shared__ int wsum[kCW + 1];
+// kLds: the candidates whose working set is larger than `above` and at most `most`; `lds` bytes are there.  kBatch: places that a thread takes
+// together, so that their latencies overlap.
+template <bool kLds, int kBatch>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) void contract_kernel(
+    BaseGraphs bg, int C, const int* cand_graph, const int* cand_off, const int* label, ContractTmp tmp, int* new_id_out,
+    int* status, char* gslab, size_t slab_stride, int above, int most, int lds) {
+  __shared__ int wsum[19];
   if (status[0] != 0) return;
   if (kLds) {
     for (int c = blockIdx.x; c < C; c += gridDim.x) {
-      const int b = cand_graph[c];
+      const int b = cand_graph[c], coff = cand_off[c], eslot = tmp.tmp_eoff[c];
       const int N = bg.gno[b + 1] - bg.gno[b];
       const int E = bg.geo[b + 1] - bg.geo[b];
-      const Slab L = slab_layout(N, E);
-      if (L.total > lds_bytes) continue;
-      contract_one<true>(bg, c, b, N, dc_smem, L, cand_off, label, tmp, new_id_out, status, wsum);
+      const int need = slab_need(N, E);
+      if (need <= above || need > most) continue;
+      const Slab L = slab_layout(N, E, lds);
+      contract_one<true, kBatch>(bg, c, b, N, E, dc_smem, L, coff, eslot, label, tmp, new_id_out, status, wsum);
       __syncthreads();
     }
   } else {
@@ -430,8 +565,8 @@ __global__ __launch_bounds__(kCT) void contract_kernel(BaseGraphs bg, int C, con
       const int b = cand_graph[c];
       const int N = bg.gno[b + 1] - bg.gno[b];
       const int E = bg.geo[b + 1] - bg.geo[b];
-      const Slab L = slab_layout(N, E);
-      contract_one<false>(bg, c, b, N, gslab + (size_t)blockIdx.x * slab_stride, L, cand_off, label, tmp,
+      const Slab L = slab_layout_nd(N, E, 2, true);
+      contract_one<false, kBatch>(bg, c, b, N, E, gslab + (size_t)blockIdx.x * slab_stride, L, cand_off[c], tmp.tmp_eoff[c], label, tmp,
                           new_id_out, status, wsum);
       __syncthreads();
     }
@@ -489,9 +624,9 @@ __global__ __launch_bounds__(1024) void prep_kernel(BaseGraphs bg, int C, const 
   const int span = need_max > lds_bytes ? need_max - lds_bytes : 1;
   auto size_class = [&](int c) {
     const int b = cand_graph[c];
-    const int need = slab_layout(bg.gno[b + 1] - bg.gno[b], bg.geo[b + 1] - bg.geo[b]).total;
+    const int need = slab_need(bg.gno[b + 1] - bg.gno[b], bg.geo[b + 1] - bg.geo[b]);
     if (need <= lds_bytes) return -1;
-    const long long k = (long long)(need - lds_bytes) * 16 / span;
+    const long long k = ((long long)need - lds_bytes) * 16 / span;
     return (int)(k > 15 ? 15 : k);
   };
   for (int c = t; c < C; c += T) {
@@ -629,7 +764,13 @@ __global__ __launch_bounds__(256) void finalize_kernel(BaseGraphs bg, int C, con
 
 }  // namespace
 
-int contract_working_set_bytes(int n_nodes, int n_edges) { return slab_layout(n_nodes, n_edges).total; }
+int contract_size_class(int n_nodes, int n_edges, int lds_limit) {
+  const int need = slab_need(n_nodes, n_edges);
+  for (int k = 0; k < kSizeClasses; ++k)
+    if (need <= size_class_of(k, lds_limit).most) return k;
+  return kSizeClasses;
+}
+size_t contract_slab_bytes(int n_nodes, int n_edges) { return (size_t)slab_layout_nd(n_nodes, n_edges, 2, true).total; }
 
 __global__ void reset_status_kernel(int* status) { status[0] = 0; }
 
@@ -640,19 +781,26 @@ hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t 
   }
   const int C = a.n_cand;
   if (prof) prof->begin(kFamPrep, s);
-  const int need = slab_layout(a.max_graph_nodes, a.max_graph_edges).total;
-  const int lds_bytes = need <= a.lds_limit ? need : a.lds_limit;
   hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, a.bg, C, a.cand_graph, a.cand_off, a.tmp.tmp_eoff,
-                     a.max_base_nodes, a.max_base_edges, a.status, a.tmp.big_order, a.tmp.big_meta, lds_bytes, need);
+                     a.max_base_nodes, a.max_base_edges, a.status, a.tmp.big_order, a.tmp.big_meta, a.lds_limit,
+                     slab_need(a.max_graph_nodes, a.max_graph_edges));
   if (prof) prof->end(s);
   if (prof) prof->begin(kFamContract, s);
-  if (a.min_graph_need <= a.lds_limit) {   // at least one base graph fits in LDS
-    hipLaunchKernelGGL(contract_kernel<true>, dim3(C), dim3(kCT), lds_bytes, s, a.bg, C, a.cand_graph, a.cand_off,
-                       a.group_id, a.tmp, a.out.new_id, a.status, (char*)nullptr, (size_t)0, lds_bytes);
+  int above = 0;
+  for (int k = 0; k < kSizeClasses; ++k) {
+    const SizeClass z = size_class_of(k, a.lds_limit);
+    if ((a.size_classes >> k) & 1) {
+      // a workgroup that has its CU to itself takes as many waves as there are nodes for
+      const int threads = C <= a.n_cu && a.max_graph_nodes > 512 ? 1024 : z.threads;
+      const bool small = a.max_graph_nodes <= threads;
+      hipLaunchKernelGGL((small ? contract_kernel<true, 2> : contract_kernel<true, 8>), dim3(C), dim3(threads), z.lds, s, a.bg, C,
+                         a.cand_graph, a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, (char*)nullptr, (size_t)0, above, z.most, z.lds);
+    }
+    above = z.most;
   }
-  if (need > a.lds_limit) {                // at least one base graph needs the global slab
-    hipLaunchKernelGGL(contract_kernel<false>, dim3(a.slab_wgs), dim3(kCT), 0, s, a.bg, C, a.cand_graph,
-                       a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, a.slab, a.slab_stride, lds_bytes);
+  if ((a.size_classes >> kSizeClasses) & 1) {        // at least one base graph needs the global slab
+    hipLaunchKernelGGL((contract_kernel<false, 8>), dim3(a.slab_wgs), dim3(1024), 0, s, a.bg, C, a.cand_graph,
+                       a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, a.slab, a.slab_stride, 0, 0, 0);
   }
   if (prof) prof->end(s);
   if (prof) prof->begin(kFamFinalize, s);
@@ -675,8 +823,10 @@ hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t 
 }
 
 hipError_t contract_set_lds_limit(int bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&contract_kernel<true>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&contract_kernel<true, 8>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&contract_kernel<true, 2>),
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 }  // namespace dc

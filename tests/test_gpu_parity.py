@@ -204,6 +204,29 @@ def test_every_list_length_class_of_the_contraction(B):
     ev.close()
 
 
+# nodes and edges at the borders of the contraction's size classes: a quarter of the LDS, a half, all of it with both
+# directions together and one after the other, the most that fits, global memory; few nodes with so many edges that
+# 16-bit row ends hold one direction only, or not even that
+@pytest.mark.parametrize("n,e", [(3000, 2000), (1200, 6500), (2500, 4200), (4000, 9500), (5000, 8000), (12000, 20000), (19100, 31000),
+                                 (19600, 33500), (900, 32768), (700, 66000)])
+def test_size_classes_of_the_contraction(B, n, e):
+    rng = np.random.default_rng(n + e)
+    src = rng.integers(0, n - 1, e)
+    dst = np.minimum(src + 1 + rng.geometric(0.02, e), n - 1)
+    src[:400], dst[200:400] = 3, n - 1                       # a node with hundreds of successors, one of predecessors
+    keep = np.stack([src, dst], 1)
+    if e < 60000 and n > 1000:
+        keep = np.unique(keep[src < dst], axis=0)            # the others have repeats and self loops
+    order = np.argsort(keep[:, 0], kind="stable")
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(keep[:, 0], minlength=n))]).astype(np.int32)
+    g = wl.BaseGraph(n, n, rowptr, keep[order, 1].astype(np.int32), rng.integers(0, 7, (n, 16)).astype(np.float32))   # sums are exact
+    runs = (np.cumsum(rng.random(n) < 0.25) + 5).astype(np.int32) % n
+    labs = np.stack([np.arange(n, dtype=np.int32), runs, rng.integers(0, max(1, n // 40), n).astype(np.int32), np.full(n, n - 1, np.int32)])
+    w = wl.custom(f"{n} nodes {g.e} edges", wl.ModelSpec(16, 32, 1, "f32"), [g], [labs], seed=3)
+    ev, _, _ = check_contraction(B, w)
+    ev.close()
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("name", ["cfg3", "cfg4", "cfg5"])
 def test_full_size_contraction_of_every_candidate(B, name):
