@@ -278,10 +278,10 @@ dc_status do_contract(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_graph, co
 }
 
 GnnArgs gnn_args(dc_ctx* ctx, int32_t n_cand, const BatchView& in, float* pred);
+int nseg_of(const dc_config& c) { return c.aggregator == DC_AGG_ATTENTION ? 1 : 3; }   // row blocks of a layer's matrix
 
 dc_status do_forward(dc_ctx* ctx, int32_t n_cand, const BatchView& in, float* pred, hipStream_t s) {
   GnnArgs g = gnn_args(ctx, n_cand, in, pred);
-  g.Ws = ctx->Ws;
   g.fuse_readout = 1;                        // nothing but the readout looks at the last layer's rows here
   hipError_t e = launch_gnn_forward(g, ctx->prof.on ? &ctx->prof : nullptr, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "forward launch");
@@ -302,6 +302,7 @@ GnnArgs gnn_args(dc_ctx* ctx, int32_t n_cand, const BatchView& in, float* pred) 
   g.L = ctx->cfg.L;
   g.bf16 = ctx->cfg.dtype == DC_BF16;
   g.W = ctx->W;
+  g.Ws = ctx->Ws;
   g.b = ctx->b;
   g.head = ctx->head;
   g.act[0] = ctx->act[0];
@@ -396,8 +397,9 @@ dc_status do_module_times(dc_ctx* ctx, int32_t n_cand, const int32_t* cand_graph
   e = launch_fused_op_readout(a, h_last, R, s);
   GnnArgs gh = g;
   gh.node_off = a.totals + 2;               // rows = fused ops
-  launch_dense_bias_relu(gh, R, H, ctx->headW, ctx->head + HH, Z1, s);
-  launch_dense_bias_relu(gh, Z1, H, static_cast<char*>(ctx->headW) + HH * es, ctx->head + 2 * HH + H, Z2, s);
+  const unsigned short* hs = ctx->Ws ? ctx->Ws + 3 * packed_weight_elems(ctx->cfg.F, H, ctx->cfg.L, nseg_of(ctx->cfg)) : nullptr;
+  launch_dense_bias_relu(gh, R, H, ctx->headW, hs, ctx->head + HH, Z1, s);
+  launch_dense_bias_relu(gh, Z1, H, static_cast<char*>(ctx->headW) + HH * es, hs ? hs + 3 * HH : nullptr, ctx->head + 2 * HH + H, Z2, s);
   if (e == hipSuccess) e = launch_fused_op_times(a, Z2, ctx->head + 2 * HH + 2 * H, ctx->fo_pred, s);
   if (prof) prof->end(s);
   if (e != hipSuccess) return hip_fail(ctx, e, "fused-op head launch");
@@ -522,7 +524,7 @@ dc_status dc_create(dc_ctx** out, const dc_config* cfg) {
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->head), (2 * HH + 3 * cfg->H + 1) * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&ctx->headW, 2 * HH * es);
   if (e == hipSuccess && cfg->dtype == DC_F32)
-    e = hipMalloc(reinterpret_cast<void**>(&ctx->Ws), packed_weight_elems(cfg->F, cfg->H, cfg->L, 3) * 3 * sizeof(unsigned short));
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->Ws), (packed_weight_elems(cfg->F, cfg->H, cfg->L, 3) + 2 * HH) * 3 * sizeof(unsigned short));
   if (e != hipSuccess) {
     (void)hipGetLastError();
     dc_destroy(ctx);
@@ -553,11 +555,11 @@ dc_status dc_destroy(dc_ctx* ctx) {
   return DC_OK;
 }
 
-// The pieces (dense32.hip) of the fp32 matrices as they are now: the layers, and for training the transposes of all.
+// The pieces (dense32.hip) of the fp32 matrices as they are now: layers, W1 and W2, and for training the transposes of all.
 static void refresh_pieces(dc_ctx* ctx, hipStream_t s) {
   const dc_config& c = ctx->cfg;
   if (c.dtype != DC_F32) return;
-  const int nseg = c.aggregator == DC_AGG_ATTENTION ? 1 : 3;
+  const int nseg = nseg_of(c);
   const size_t HH = (size_t)c.H * c.H;
   const bool reverse = ctx->train_mem != nullptr;
   SplitJobs jobs;
@@ -584,6 +586,7 @@ static void refresh_pieces(dc_ctx* ctx, hipStream_t s) {
   }
   for (int i = 0; i < 2; ++i) {
     const float* Wi = ctx->head + i * (HH + c.H);
+    add(Wi, Ws + i * 3 * HH, c.H, c.H, 0);
     if (reverse) add(Wi, WTs + i * 3 * HH, c.H, c.H, 1);
   }
   launch_pack_split(jobs, n, s);
@@ -1215,7 +1218,6 @@ dc_status dc_train_begin(dc_ctx* ctx, const dc_train_params* params, void* strea
   t.max_rows = p.max_rows;
   t.status = ctx->status;
   t.n_cu = ctx->n_cu;
-  t.Ws = ctx->Ws;
   t.WTs = ctx->train_WTs;
   ctx->tb = t;
   ctx->adam_m = m;

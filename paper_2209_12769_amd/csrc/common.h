@@ -138,15 +138,16 @@ struct GnnArgs {
 hipError_t launch_gnn_forward(const GnnArgs& a, Profiler* prof, hipStream_t s);
 // The message-passing layers alone; *h_last receives the final embeddings [node_off[n_cand], H].
 hipError_t launch_gnn_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, const void** h_last);
-// out = ReLU(A Wp + bias) for the node_off[n_cand] rows of A [rows, d]; Wp in the device layout of one layer block.
-void launch_dense_bias_relu(const GnnArgs& a, const void* A, int d, const void* Wp, const float* bias, void* out,
-                            hipStream_t s);
+// out = ReLU(A Wp + bias) for the node_off[n_cand] rows of A [rows, d]; Wp in the device layout of one layer block, Ws its
+// pieces (fp32) or null.
+void launch_dense_bias_relu(const GnnArgs& a, const void* A, int d, const void* Wp, const unsigned short* Ws, const float* bias,
+                            void* out, hipStream_t s);
 // The two neighbour means of every row of h [rows, d] (separate kernel; any d that is a multiple of 16 bytes).
 void launch_mean_aggregate(const GnnArgs& a, const void* h, int d, void* h_in, void* h_out, hipStream_t s);
 // out [rows, a.H] = [A0 | A1 | A2] Wl (nseg = 3) or A0 Wl (nseg = 1), rows = a.node_off[a.n_cand]; with a bias
 // the result is ReLU(. + bias), without one it is stored as it is.  a.H must be a multiple of 32.
 void launch_dense_update(const GnnArgs& a, const void* A0, const void* A1, const void* A2, int d, int nseg,
-                         const void* Wl, const float* bias, void* out, hipStream_t s, const unsigned short* Ws = nullptr);
+                         const void* Wl, const float* bias, void* out, hipStream_t s);
 // dense32.hip: fp32 products on the bf16 matrix cores.  A matrix W [K, N] has a second form there (three bf16 pieces
 // per element, 3 K N 16-bit values); K a multiple of 16, N of 32.
 struct SplitJob {
@@ -305,8 +306,7 @@ struct TrainPass {
   const float* W;
   const float* b;
   const float* head;
-  const unsigned short* Ws;    // pieces (dense32.hip) of the layers' matrices
-  const unsigned short* WTs;   // of the transposed matrices: layers 1 .. L - 1, then W1, W2
+  const unsigned short* WTs;   // pieces (dense32.hip) of the transposed matrices: layers 1 .. L - 1, then W1, W2
   int F, H, L;
   float floor;
   // buffers

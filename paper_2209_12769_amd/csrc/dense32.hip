@@ -14,8 +14,8 @@
 // inputs like those of the layers (ReLU outputs, normal weights), error over the root mean square of the result: K = 48
 // 1.2e-7 (fp32 instructions 0.9e-7), 192 1.4e-7 (1.8e-7), 384 1.4e-7 (2.5e-7), 768 1.5e-7 (3.5e-7); positive operands:
 // 768 0.7e-7 (4.2e-7).
-// Measured: 475 k rows, K = 768, 256 columns: 1.62 ms with the fp32 instructions, 1.2 ms; 96 k rows, K = 384, 128 columns
-// 105 -> 70 us; the same 475 k rows of weight gradients 1.5 -> 1.05 ms; the training pass of those rows 18.1 -> 14.2 ms.
+// Measured: 475 k rows, K = 256, 768 columns: 1.62 ms with the fp32 instructions, 1.22 ms; 96 k rows, K = 384, 128 columns
+// 105 -> 70 us; 475 k rows of weight gradients (768 x 256) 1.5 -> 1.05 ms; the reverse pass of those rows in all 9.6 -> 7.5 ms.
 // The matrix cores are busy 40 % of the time at 2.1 GHz.
 //
 // The pieces of W are made once per set of weights (pack_split_kernel) and lie as the matrix instruction reads them:
@@ -105,18 +105,18 @@ __device__ __forceinline__ const float* chunk_base(const Operands& o, int c) {
 
 // Accumulator register v of lane (l32 = lane & 31, lh = lane >> 5) holds column 8 (v / 4) + 4 lh + v % 4 of its block of
 // 32 (W is the first operand of the instruction), row l32: four consecutive columns per lane and quad.
+__device__ __forceinline__ void store_quad(const Operands& o, f32x4 y, int row, int col) {
+  if (o.bias) {
+    const f32x4 b = *reinterpret_cast<const f32x4*>(o.bias + col);
+    y = f32x4{fmaxf(y.x + b.x, 0.f), fmaxf(y.y + b.y, 0.f), fmaxf(y.z + b.z, 0.f), fmaxf(y.w + b.w, 0.f)};
+  }
+  *reinterpret_cast<f32x4*>(o.out + (size_t)row * o.N + col) = y;
+}
 __device__ __forceinline__ void store_block(const Operands& o, const f32x16& acc, int row, int col0, int lh) {
   if (row >= o.ntot) return;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int col = col0 + 8 * q + 4 * lh;
-    f32x4 y = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-    if (o.bias) {
-      const f32x4 b = *reinterpret_cast<const f32x4*>(o.bias + col);
-      y = f32x4{fmaxf(y.x + b.x, 0.f), fmaxf(y.y + b.y, 0.f), fmaxf(y.z + b.z, 0.f), fmaxf(y.w + b.w, 0.f)};
-    }
-    *reinterpret_cast<f32x4*>(o.out + (size_t)row * o.N + col) = y;
-  }
+  for (int q = 0; q < 4; ++q)
+    store_quad(o, f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]}, row, col0 + 8 * q + 4 * lh);
 }
 // 0 where every value of the block is finite, else NaN
 __device__ __forceinline__ float finite_probe(const f32x16& acc, float t) {
@@ -191,6 +191,58 @@ __device__ __forceinline__ void few_step(const Operands& o, f32x16& total, f32x1
   if (kInSection == kSection - 1 || c == nk - 1) add_section(total, acc, section_sign(c));
   __builtin_amdgcn_sched_barrier(0);
 }
+// Fewer tiles still, at most one per workgroup of the grid: the four waves of a workgroup share a tile.  Wave w has sections
+// w, w + 4 .. of W and leaves their sums in LDS; wave w then adds quad w of all sections in their order, which gives the
+// bits that one wave gives.  `sums`: a section's 1024 sums each.  A search step's layers of some hundred rows, K = 384 and
+// 128: 16.6 and 9.8 us with the fp32 instructions and one wave per tile, 5.9 us on average; the search 5.6 -> 4.9 ms.
+__device__ __forceinline__ void update_fewer(const Operands& o, float* sums) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int nct = o.N >> 5, ntiles = ((o.ntot + 31) >> 5) * nct, nk = o.nseg * o.d / 16, nsec = (nk + kSection - 1) / kSection;
+  const int tile = blockIdx.x;
+  if (tile >= ntiles) return;
+  const int m0 = (tile / nct) * 32, n0 = (tile % nct) * 32, row = m0 + l32;
+  const size_t aoff = (size_t)min(row, o.ntot - 1) * o.d + 8 * lh;
+  const u32x4* wp = o.Ws + (size_t)lh * o.N + n0 + l32;
+  if (wave < nsec) {
+    FewChunk x[kSection];
+#pragma unroll
+    for (int i = 0; i < kSection; ++i) few_fetch(o, x[i], min(wave * kSection + i, nk - 1), aoff, wp);
+    for (int sec = wave; sec < nsec; sec += 4) {
+      f32x16 acc = zero16();
+#pragma unroll
+      for (int i = 0; i < kSection; ++i) {
+        const int c = sec * kSection + i;
+        const Pieces s = split8(x[i].a[0], x[i].a[1]);
+        const u32x4 w0 = x[i].w[0], w1 = x[i].w[1], w2 = x[i].w[2];
+        few_fetch(o, x[i], min(c + 4 * kSection, nk - 1), aoff, wp);
+        if (c < nk) {
+          acc = product(w0, s.p[0], acc);
+          acc = product(w0, s.p[1], acc);
+          acc = product(w0, s.p[2], acc);
+          acc = product(w1, s.p[0], acc);
+          acc = product(w1, s.p[1], acc);
+          acc = product(w2, s.p[0], acc);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sums[(sec * 16 + v) * 64 + lane] = acc[v];
+    }
+  }
+  __syncthreads();
+  float y[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int sec = 0; sec < nsec; ++sec)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) y[u] = fmaf(sums[(sec * 16 + wave * 4 + u) * 64 + lane], section_sign(sec * kSection), y[u]);
+  float probe = 0.f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) probe = fmaf(y[u], 0.f, probe);
+  if (__syncthreads_or(!(probe == 0.f))) {
+    if (wave == 0) redo_block(o, m0, n0);
+  } else if (row < o.ntot) {
+    store_quad(o, f32x4{y[0], y[1], y[2], y[3]}, row, n0 + 8 * wave + 4 * lh);
+  }
+}
 __device__ __forceinline__ void update_few(const Operands& o) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int l32 = lane & 31, lh = lane >> 5;
@@ -246,6 +298,10 @@ __global__ __launch_bounds__(256, 2) void update_split_kernel(Operands o, const 
   constexpr int kAhead = 4;                                      // chunks that rows are requested ahead of their splitting
   __shared__ u32x4 Wl[2][6 * CH * BN];
   o.ntot = node_off[C];
+  if (few_tiles(o.ntot, o.N, gridDim.x) && (o.nseg * o.d + 16 * kSection - 1) / (16 * kSection) * 4096 <= (int)sizeof(Wl)) {
+    update_fewer(o, reinterpret_cast<float*>(&Wl[0][0]));
+    return;
+  }
   if (few_tiles(o.ntot, o.N, few)) {
     update_few(o);
     return;

@@ -824,15 +824,15 @@ void launch_mean_aggregate(const GnnArgs& a, const void* h, int d, void* h_in, v
 }
 
 void launch_dense_update(const GnnArgs& a, const void* A0, const void* A1, const void* A2, int d, int nseg,
-                         const void* Wl, const float* bias, void* out, hipStream_t s, const unsigned short* Ws) {
-  run_update(a, A0, A1, A2, d, nseg, Wl, Ws, bias, out, s);
+                         const void* Wl, const float* bias, void* out, hipStream_t s) {
+  run_update(a, A0, A1, A2, d, nseg, Wl, nullptr, bias, out, s);
 }
 
-void launch_dense_bias_relu(const GnnArgs& a, const void* A, int d, const void* Wp, const float* bias, void* out,
-                            hipStream_t s) {
+void launch_dense_bias_relu(const GnnArgs& a, const void* A, int d, const void* Wp, const unsigned short* Ws, const float* bias,
+                            void* out, hipStream_t s) {
   if (a.allow_fused && layer256_supported(d, a.H, a.bf16) && launch_dense256(A, d, a, Wp, bias, out, s) == hipSuccess)
     return;
-  run_update(a, A, nullptr, nullptr, d, 1, Wp, nullptr, bias, out, s);
+  run_update(a, A, nullptr, nullptr, d, 1, Wp, Ws, bias, out, s);
 }
 
 hipError_t launch_gnn_forward(const GnnArgs& a, Profiler* prof, hipStream_t s) {

@@ -349,10 +349,11 @@ hipError_t launch_train_pass(const TrainPass& t, Profiler* prof, hipStream_t s) 
   hipLaunchKernelGGL(gid_kernel, dim3(grid_for(rows_cap, t.n_cu)), dim3(256), 0, s, t.node_off, B, t.gid, t.status);
 
   // ---- forward, every layer's output kept ----
+  // In fp32 instructions: a sum that rounds differently about zero passes or stops a row's whole gradient at its ReLU, and in
+  // 475 k rows some do (gradients of either form 4e-6 to 9e-6 apart, each as far from 64 bits; the reverse pass alone: 1.4e-7).
   const float* hcur = t.X;
   int d = F;
   const float* Wl = t.W;
-  const unsigned short* Ws = t.Ws;
   const float* bl = t.b;
   for (int l = 0; l < L; ++l) {
     float* hn = t.hs + (size_t)l * rows_cap * H;
@@ -362,10 +363,9 @@ hipError_t launch_train_pass(const TrainPass& t, Profiler* prof, hipStream_t s) 
     launch_mean_aggregate(g, hcur, d, mp, ms, s);
     end();
     begin(kFamTrainUpdate);
-    launch_dense_update(g, hcur, mp, ms, d, 3, Wl, bl, hn, s, Ws);
+    launch_dense_update(g, hcur, mp, ms, d, 3, Wl, bl, hn, s);
     end();
     Wl += (size_t)3 * d * H;
-    Ws += (size_t)9 * d * H;
     bl += H;
     hcur = hn;
     d = H;
