@@ -56,6 +56,8 @@ struct dc_ctx {
   // weights
   void* W = nullptr;
   unsigned short* Ws = nullptr;       // fp32: pieces of the layer matrices (dense32.hip)
+  unsigned short* Wx = nullptr;       // attention, H = 256, bf16, up to eight heads: score columns (gnn_layer256.hip)
+  bool have_wx = false;
   float* b = nullptr;
   float* head = nullptr;
   float* att = nullptr;     // attention vectors (DC_AGG_ATTENTION only)
@@ -326,6 +328,7 @@ GnnArgs gnn_args(dc_ctx* ctx, int32_t n_cand, const BatchView& in, float* pred) 
   if (ctx->cfg.aggregator == DC_AGG_ATTENTION) {
     g.heads = ctx->cfg.heads;
     g.att = ctx->att;
+    if (ctx->have_wx) g.Wx = ctx->Wx;
     g.score[0] = ctx->score[0];
     g.score[1] = ctx->score[1];
   }
@@ -523,6 +526,8 @@ dc_status dc_create(dc_ctx** out, const dc_config* cfg) {
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->b), (size_t)cfg->L * cfg->H * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->head), (2 * HH + 3 * cfg->H + 1) * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&ctx->headW, 2 * HH * es);
+  if (e == hipSuccess && cfg->aggregator == DC_AGG_ATTENTION && cfg->heads <= 8 && layer256_supported(cfg->H, cfg->H, cfg->dtype == DC_BF16))
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->Wx), ((size_t)cfg->F + (size_t)(cfg->L - 1) * cfg->H) * 32 * sizeof(unsigned short));
   if (e == hipSuccess && cfg->dtype == DC_F32)
     e = hipMalloc(reinterpret_cast<void**>(&ctx->Ws), (packed_weight_elems(cfg->F, cfg->H, cfg->L, 3) + 2 * HH) * 3 * sizeof(unsigned short));
   if (e != hipSuccess) {
@@ -546,6 +551,7 @@ dc_status dc_destroy(dc_ctx* ctx) {
   if (ctx->att) (void)hipFree(ctx->att);
   if (ctx->headW) (void)hipFree(ctx->headW);
   if (ctx->Ws) (void)hipFree(ctx->Ws);
+  if (ctx->Wx) (void)hipFree(ctx->Wx);
   if (ctx->cost_mem) (void)hipFree(ctx->cost_mem);
   if (ctx->bg_mem) (void)hipFree(ctx->bg_mem);
   if (ctx->slab) (void)hipFree(ctx->slab);
@@ -628,6 +634,13 @@ static dc_status set_weights_common(dc_ctx* ctx, const float* W_layers, const fl
   if (e == hipSuccess) e = hipMemcpyAsync(ctx->head, hd.data(), hd.size() * sizeof(float), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && att)
     e = hipMemcpyAsync(ctx->att, att, (size_t)c.L * 2 * c.H * sizeof(float), hipMemcpyHostToDevice, s);
+  std::vector<unsigned short> wx;
+  ctx->have_wx = false;
+  if (e == hipSuccess && ctx->Wx && att) {
+    wx.resize(((size_t)c.F + (size_t)(c.L - 1) * c.H) * 32);
+    ctx->have_wx = pack_score_columns(W_layers, att, c.F, c.L, c.heads, wx.data());
+    e = hipMemcpyAsync(ctx->Wx, wx.data(), wx.size() * sizeof(unsigned short), hipMemcpyHostToDevice, s);
+  }
   if (e == hipSuccess) refresh_pieces(ctx, s);
   if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(s);   // host staging buffers die at return

@@ -111,6 +111,7 @@ struct GnnArgs {
   int F, H, L, bf16;
   const void* W;        // layer matrices in device layout
   const unsigned short* Ws = nullptr;   // fp32, products on the bf16 matrix cores (dense32.hip): their pieces, matrix after matrix
+  const unsigned short* Wx = nullptr;   // attention, H = 256, bf16: score columns (gnn_layer256.hip), or null
   const float* b;       // biases fp32
   const float* head;    // fp32 head (bf16-representable matrices on the bf16 path)
   void* act[2];         // ping/pong activations [max_nodes, H]
@@ -214,6 +215,11 @@ hipError_t launch_layer256w(const void* h, int d, const GnnArgs& a, const void* 
                             bool readout, hipStream_t s);
 hipError_t launch_dense256(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
                            hipStream_t s);
+// The same with the score terms of the attention variant (up to eight heads) in a.score; Wx: the layer's part of what
+// pack_score_columns() leaves, 32 d values.
+hipError_t launch_dense256_scores(const void* h, int d, const GnnArgs& a, const void* Wl, const unsigned short* Wx, void* z,
+                                  hipStream_t s);
+bool pack_score_columns(const float* W_layers, const float* att, int F, int L, int heads, unsigned short* dst);
 
 // simulate.hip: list-scheduling estimate of the end-to-end time of each candidate module
 struct SimArgs {

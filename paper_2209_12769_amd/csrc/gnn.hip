@@ -713,21 +713,24 @@ hipError_t attention_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, con
   const unsigned short* Ws = a.Ws;
   const float* bl = a.b;
   const float* al = a.att;
+  const unsigned short* Wx = a.Wx;
   void* z = a.agg[0];
   for (int l = 0; l < a.L; ++l) {
     void* hnext = a.act[l & 1];
     if (prof) prof->begin(kFamAttProject, s);
-    if (a.allow_fused && layer256_supported(d, a.H, a.bf16)) {
-      hipError_t e = launch_dense256(hcur, d, a, Wl, nullptr, z, s);
-      if (e != hipSuccess) return e;
-    } else {
-      run_update(a, hcur, nullptr, nullptr, d, 1, Wl, Ws, nullptr, z, s);
-    }
-    if (prof) prof->end(s);
-    if (prof) prof->begin(kFamAttScores, s);
-    hipError_t e = launch_attention_scores(a, z, al, s);
+    const bool dense256 = a.allow_fused && layer256_supported(d, a.H, a.bf16), scores = dense256 && Wx;
+    hipError_t e = hipSuccess;
+    if (scores) e = launch_dense256_scores(hcur, d, a, Wl, Wx, z, s);
+    else if (dense256) e = launch_dense256(hcur, d, a, Wl, nullptr, z, s);
+    else run_update(a, hcur, nullptr, nullptr, d, 1, Wl, Ws, nullptr, z, s);
     if (prof) prof->end(s);
     if (e != hipSuccess) return e;
+    if (!scores) {
+      if (prof) prof->begin(kFamAttScores, s);
+      e = launch_attention_scores(a, z, al, s);
+      if (prof) prof->end(s);
+      if (e != hipSuccess) return e;
+    }
     if (prof) prof->begin(kFamAttAggregate, s);
     e = launch_attention_aggregate(a, z, bl, hnext, s);
     if (prof) prof->end(s);
@@ -736,6 +739,7 @@ hipError_t attention_layers(const GnnArgs& a, Profiler* prof, hipStream_t s, con
     if (Ws) Ws += (size_t)3 * d * a.H;
     bl += a.H;
     al += 2 * a.H;
+    if (Wx) Wx += (size_t)32 * d;
     hcur = hnext;
     d = a.H;
   }

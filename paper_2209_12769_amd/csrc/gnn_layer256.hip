@@ -1,9 +1,12 @@
 // The plain product out = h W (or ReLU(h W + b)) for output width H = 256 and input width d = 256 or
-// 64, bf16 (gfx950): z = W e' of the attention variant, the hidden layers of the regression network over
-// many fused ops.  Four waves each own a 64 x 128 block of a 128 x 256 output tile and read their
+// 64, bf16 (gfx950): z = W e' of the attention variant with its score terms, the hidden layers of the regression network
+// over many fused ops.  Four waves each own a 64 x 128 block of a 128 x 256 output tile and read their
 // fragments from LDS rings that are filled from global memory by direct copies (no registers), with one
 // barrier per K chunk of 64 columns (mfma_step).  The message-passing layer for these shapes is the
 // sixteen-wave kernel of gnn_layer256w.hip; this file also holds the launchers of both.
+#include <math.h>
+#include <string.h>
+
 #include <type_traits>
 
 #include "common.h"
@@ -19,7 +22,7 @@ typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int kBM = 128, kBN = 256, kBK = 64;
-constexpr int kNT = 512;
+constexpr int kNT = 256;                    // one wave per SIMD: 512 registers each
 // Shape constants for input width D = 64 * DCH: K = D in DCH chunks of 64 columns, every one the
 // row's own columns (DENSE; the flag is kept so that the step below reads like the layer's).
 template <int DCH, bool DENSE = true>
@@ -105,8 +108,22 @@ struct MfmaConst {
   int ntot, tile0, per, wm, wn, l32, lh, lane, wave, sw;
 };
 
-template <int DCH, bool DENSE>
-__device__ __forceinline__ void mfma_step(int s, int S, f32x16 (&acc)[2][4], const MfmaConst c) {
+// The score terms of the attention variant: s_i = a . z_i per head and kind = h_i (W a), so they are eight (K = 8: sixteen)
+// more columns of the product, kept in two bf16 pieces each (column 8 q + 4 kind + v: head v; the second pieces two or
+// four quads on), 32 with the unused ones.  Their part of W stays in registers; a wave multiplies the half of its rows
+// that no other wave has.  Bound by memory like the product, which hides them: 1.39 M rows, d = 256, 298 us the product and
+// 173 us a kernel that read z again, 321 us together.  Nearer to 64 bits than terms from the rounded z: predictions of 43 k
+// rows 1.6e-4 off instead of 1.9e-4, of 25 k rows 1.9e-4 instead of 1.5e-3.
+template <int DCH>
+struct ScoreColumns {
+  bf16x8 w[DCH * 4];
+  f32x16 acc;
+  float *src, *dst;
+  int heads;
+};
+// KC: which chunk of the tile step s multiplies (none before step 0)
+template <int DCH, bool DENSE, int KC, bool kScores>
+__device__ __forceinline__ void mfma_step(int s, int S, f32x16 (&acc)[2][4], ScoreColumns<DCH>& sc, const MfmaConst c) {
   constexpr int NK = Shape<DCH, DENSE>::NK;
   int n_req = 0;                            // requests of this step, in fours
   if (s + 2 >= 0) {
@@ -145,9 +162,9 @@ __device__ __forceinline__ void mfma_step(int s, int S, f32x16 (&acc)[2][4], con
       }
     }
   }
-  if (s >= 0) {
+  if constexpr (KC >= 0) {
     const char* As = c.smem + (s % 3) * kABytes;
-    const u16* Bs = reinterpret_cast<const u16*>(c.smem + kBOff + (NK > 3 ? s % 3 : s % NK) * kBBytes);
+    const u16* Bs = reinterpret_cast<const u16*>(c.smem + kBOff + (NK > 3 ? s % 3 : KC) * kBBytes);
 #pragma unroll
     for (int ks = 0; ks < kBK / 16; ++ks) {
       bf16x8 a[2], b[4];
@@ -165,6 +182,8 @@ __device__ __forceinline__ void mfma_step(int s, int S, f32x16 (&acc)[2][4], con
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+      if constexpr (kScores)
+        sc.acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sc.w[KC * 4 + ks], c.wn ? a[1] : a[0], sc.acc, 0, 0, 0);
     }
   }
   // All but this step's requests (eight W pieces and/or, for one of the node's own chunks, four
@@ -172,8 +191,7 @@ __device__ __forceinline__ void mfma_step(int s, int S, f32x16 (&acc)[2][4], con
   // complete in issue order, so this holds whatever stores of an earlier tile are still
   // on their way; placed before the tile's stores so that it never waits for those.
   wait_vm_times4(__builtin_amdgcn_readfirstlane(n_req));
-  const bool tile_end = s >= 0 && (s % NK) == NK - 1;
-  if (tile_end) {
+  if constexpr (KC == NK - 1) {
     // ---- tile finished.  First bias and ReLU in place, one group of 32 columns at a time,
     // with the next group's bias in flight; no load follows a store, so nothing here waits
     // for a store to be acknowledged.
@@ -248,18 +266,38 @@ __device__ __forceinline__ void mfma_step(int s, int S, f32x16 (&acc)[2][4], con
         __builtin_amdgcn_wave_barrier();
       }
     }
+    if constexpr (kScores) {
+      const int row = m0 + c.wm * 64 + c.wn * 32 + c.l32;
+      const int lo = sc.heads > 4 ? 8 : 4;
+      float x[8];
+#pragma unroll
+      for (int v = 0; v < 8; ++v) x[v] = sc.acc[v] + (lo == 8 ? sc.acc[8 + v] : sc.acc[4 + v]);   // four heads or fewer: the first four
+      if (row < c.ntot) {
+        float* p = (c.lh ? sc.dst : sc.src) + (size_t)row * sc.heads;
+        if (sc.heads == 4) {
+          *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
+        } else {
+#pragma unroll
+          for (int v = 0; v < 8; ++v)
+            if (v < sc.heads) p[v] = x[v];
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sc.acc[v] = 0.f;
+    }
   }
 }
 
 // The plain product out = h W (bias == nullptr) or ReLU(h W + bias): K = d, every chunk comes from global
-// memory by direct copy.  Waves 0-3 run the multiplying steps; waves 4-7 have nothing to move and only
-// keep step with the barriers (the workgroup keeps the shape of the layer kernel, whose LDS plan it shares).
-template <int DCH>
-__global__ __launch_bounds__(kNT) void layer256_dense_kernel(
+// memory by direct copy.
+template <int DCH, bool kScores>
+__global__ __launch_bounds__(kNT, 1) void layer256_dense_kernel(
     const u16* __restrict__ h, const u16* __restrict__ Wp, const float* __restrict__ bias, u16* __restrict__ out,
+    const u16* __restrict__ Wx, float* __restrict__ sc_src, float* __restrict__ sc_dst, int heads, int* __restrict__ ctr,
     const int* __restrict__ node_off, int C, const int* __restrict__ status) {
   constexpr int NK = Shape<DCH, true>::NK;
   if (status[0] != 0) return;
+  if (kScores && blockIdx.x == 0) ctr[threadIdx.x] = 0;     // the counters of the kernel that follows
   char* smem = dc_l256_smem;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int ntot = node_off[C];
@@ -271,41 +309,59 @@ __global__ __launch_bounds__(kNT) void layer256_dense_kernel(
   const int nt_wg = lim > slot ? (lim - slot + per - 1) / per : 0;
   const int S = nt_wg * NK;                 // steps of this workgroup
   if (S == 0) return;                       // no tile for this workgroup (uniform)
-  // All waves pass S + 3 barriers (steps -3 .. S-1).
-  const int role_wave = wave & 3;
-  if (wave < 4) {
-    f32x16 acc[2][4];
+  f32x16 acc[2][4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    MfmaConst mc;
-    mc.Wp = Wp;
-    mc.bias = bias;
-    mc.out = out;
-    mc.smem = smem;
-    mc.h = reinterpret_cast<const char*>(h);
-    mc.stage = smem + kStageOff + role_wave * kStageBytes;
-    mc.lds0 = (unsigned)(size_t)((lds_char*)dc_l256_smem);
-    mc.ntot = ntot;
-    mc.tile0 = xcd * tpx + slot;
-    mc.per = per;
-    mc.wm = role_wave >> 1;
-    mc.wn = role_wave & 1;
-    mc.l32 = lane & 31;
-    mc.lh = lane >> 5;
-    mc.lane = lane;
-    mc.sw = ((lane & 31) >> 1) & 7;
-    mc.wave = __builtin_amdgcn_readfirstlane(role_wave);   // scalar: the LDS base of a direct copy must be uniform
-    __syncthreads();                          // step -3
-    for (int s = -2; s < S; ++s) {
-      mfma_step<DCH, true>(s, S, acc, mc);
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  MfmaConst mc;
+  mc.Wp = Wp;
+  mc.bias = bias;
+  mc.out = out;
+  mc.smem = smem;
+  mc.h = reinterpret_cast<const char*>(h);
+  mc.stage = smem + kStageOff + wave * kStageBytes;
+  mc.lds0 = (unsigned)(size_t)((lds_char*)dc_l256_smem);
+  mc.ntot = ntot;
+  mc.tile0 = xcd * tpx + slot;
+  mc.per = per;
+  mc.wm = wave >> 1;
+  mc.wn = wave & 1;
+  mc.l32 = lane & 31;
+  mc.lh = lane >> 5;
+  mc.lane = lane;
+  mc.sw = ((lane & 31) >> 1) & 7;
+  mc.wave = __builtin_amdgcn_readfirstlane(wave);   // scalar: the LDS base of a direct copy must be uniform
+  ScoreColumns<DCH> sc;
+  if constexpr (kScores) {
+    sc.src = sc_src;
+    sc.dst = sc_dst;
+    sc.heads = heads;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sc.acc[v] = 0.f;
+#pragma unroll
+    for (int k = 0; k < DCH * 4; ++k) sc.w[k] = *reinterpret_cast<const bf16x8*>(Wx + (size_t)((k * 2 + mc.lh) * 32 + mc.l32) * 8);
+    // here they are waited for, before the first copy that the compiler does not know of
+#pragma unroll
+    for (int k = 0; k < DCH * 4; ++k) asm volatile("" : "+v"(sc.w[k]));
+  }
+  mfma_step<DCH, true, -1, kScores>(-2, S, acc, sc, mc);
+  __syncthreads();
+  mfma_step<DCH, true, -1, kScores>(-1, S, acc, sc, mc);
+  __syncthreads();
+  for (int s = 0; s < S; s += NK) {
+    mfma_step<DCH, true, 0, kScores>(s, S, acc, sc, mc);
+    __syncthreads();
+    if constexpr (NK == 4) {
+      mfma_step<DCH, true, 1, kScores>(s + 1, S, acc, sc, mc);
+      __syncthreads();
+      mfma_step<DCH, true, 2, kScores>(s + 2, S, acc, sc, mc);
+      __syncthreads();
+      mfma_step<DCH, true, 3, kScores>(s + 3, S, acc, sc, mc);
       __syncthreads();
     }
-  } else {
-    for (int s = -3; s < S; ++s) __syncthreads();
   }
 }
 
@@ -318,11 +374,11 @@ hipError_t launch_build_desc(const GnnArgs& a, hipStream_t s) { return launch_bu
 
 namespace {
 
-template <int DCH>
+template <int DCH, bool kScores>
 hipError_t launch_dense_shape(const void* h, const GnnArgs& a, const void* Wl, const float* bias, void* out,
-                              hipStream_t s) {
+                              const unsigned short* Wx, hipStream_t s) {
   static bool attr_done = false;
-  auto kern = layer256_dense_kernel<DCH>;
+  auto kern = layer256_dense_kernel<DCH, kScores>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsTotal);
@@ -330,8 +386,10 @@ hipError_t launch_dense_shape(const void* h, const GnnArgs& a, const void* Wl, c
     attr_done = true;
   }
   const int grid = ((a.n_cu + 7) / 8) * 8;
+  static_assert(kHeavyCtrInts == kNT, "the kernel clears one counter word per thread");
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kNT), kLdsTotal, s, static_cast<const u16*>(h),
-                     static_cast<const u16*>(Wl), bias, static_cast<u16*>(out), a.node_off, a.n_cand, a.status);
+                     static_cast<const u16*>(Wl), bias, static_cast<u16*>(out), Wx, a.score[0], a.score[1], a.heads, a.heavy_ctr,
+                     a.node_off, a.n_cand, a.status);
   return hipGetLastError();
 }
 
@@ -340,9 +398,55 @@ hipError_t launch_dense_shape(const void* h, const GnnArgs& a, const void* Wl, c
 // out = h W (bias == nullptr) or ReLU(h W + bias) for H = 256, d = 256 or 64, bf16
 hipError_t launch_dense256(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
                            hipStream_t s) {
-  if (d == 256) return launch_dense_shape<4>(h, a, Wl, bias, out, s);
-  if (d == 64) return launch_dense_shape<1>(h, a, Wl, bias, out, s);
+  if (d == 256) return launch_dense_shape<4, false>(h, a, Wl, bias, out, nullptr, s);
+  if (d == 64) return launch_dense_shape<1, false>(h, a, Wl, bias, out, nullptr, s);
   return hipErrorInvalidValue;
+}
+
+// z = h W and the score terms of its rows
+hipError_t launch_dense256_scores(const void* h, int d, const GnnArgs& a, const void* Wl, const unsigned short* Wx, void* z,
+                                  hipStream_t s) {
+  if (d == 256) return launch_dense_shape<4, true>(h, a, Wl, nullptr, z, Wx, s);
+  if (d == 64) return launch_dense_shape<1, true>(h, a, Wl, nullptr, z, Wx, s);
+  return hipErrorInvalidValue;
+}
+
+// Wx of all layers for W (bf16) and the attention vectors: W a per head and kind in 64 bits, as two bf16 numbers, in the order
+// the product reads them (unit of eight rows of a column; 32 columns).  False where one is no finite number.
+bool pack_score_columns(const float* W_layers, const float* att, int F, int L, int heads, unsigned short* dst) {
+  const int H = kBN, Dh = H / heads;
+  auto to_bf16 = [](float x) {
+    unsigned u;
+    memcpy(&u, &x, 4);
+    u += 0x7FFFu + ((u >> 16) & 1u);
+    return (unsigned short)(u >> 16);
+  };
+  auto from_bf16 = [](unsigned short b) {
+    const unsigned u = (unsigned)b << 16;
+    float x;
+    memcpy(&x, &u, 4);
+    return x;
+  };
+  for (int l = 0; l < L; ++l) {
+    const int d = l == 0 ? F : H;
+    memset(dst, 0, (size_t)d * 32 * sizeof(unsigned short));
+    for (int k = 0; k < d; ++k)
+      for (int kind = 0; kind < 2; ++kind)
+        for (int n = 0; n < heads; ++n) {
+          double x = 0.0;
+          for (int j = n * Dh; j < (n + 1) * Dh; ++j)
+            x += (double)from_bf16(to_bf16(W_layers[(size_t)k * H + j])) * (double)att[kind * H + j];
+          if (!(fabs(x) < 1e38)) return false;
+          const unsigned short hi = to_bf16((float)x), lo = to_bf16((float)(x - (double)from_bf16(hi)));
+          const int col = 8 * (n >> 2) + 4 * kind + (n & 3);
+          dst[(size_t)(k / 8 * 32 + col) * 8 + k % 8] = hi;
+          dst[(size_t)(k / 8 * 32 + col + (heads > 4 ? 16 : 8)) * 8 + k % 8] = lo;
+        }
+    dst += (size_t)d * 32;
+    W_layers += (size_t)d * H;
+    att += 2 * H;
+  }
+  return true;
 }
 
 // One layer for H = 256, d = 256 or 64, bf16, after launch_build_desc: the pre-pass over the listed long rows,

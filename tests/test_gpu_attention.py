@@ -145,3 +145,17 @@ def test_rows_claimed_in_order(B, H, K, dtype, waves, rows):
         assert ev.check() == B.DC_OK
         assert np.array_equal(got, np.tile(want, (copies, 1)))
     ev.close()
+
+
+# the score terms as columns of the product (up to eight heads) and in a kernel of their own (sixteen, thirty-two); one row,
+# the edges of its tiles of 128 rows, several tiles per workgroup
+@pytest.mark.parametrize("F,K", [(64, 1), (64, 2), (256, 4), (64, 8), (64, 16), (64, 32)])
+@pytest.mark.parametrize("n,C", [(1, 1), (43, 3), (127, 1), (129, 1), (640, 64)])
+def test_score_columns(B, F, K, n, C):
+    g = wl.random_dag(40 + n, n, min(1.0, 3.0 / n), F)
+    w = wl.custom(f"att-columns-{F}-{K}", wl.ModelSpec(F, 256, 2, "bf16", "attention", K), [g],
+                  [np.tile(np.arange(n, dtype=np.int32), (C, 1))], seed=K)
+    w = wl.with_time_like_head(w)
+    got = run(B, w)
+    assert np.all(got == got[0])
+    check(got[:1], w.subset([0]), w.name)
