@@ -307,6 +307,7 @@ GnnArgs gnn_args(dc_ctx* ctx, int32_t n_cand, const BatchView& in, float* pred) 
   g.Ws = ctx->Ws;
   g.b = ctx->b;
   g.head = ctx->head;
+  g.headW = ctx->headW;
   g.act[0] = ctx->act[0];
   g.act[1] = ctx->act[1];
   g.agg[0] = ctx->agg[0];

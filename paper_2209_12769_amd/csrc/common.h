@@ -114,6 +114,7 @@ struct GnnArgs {
   const unsigned short* Wx = nullptr;   // attention, H = 256, bf16: score columns (gnn_layer256.hip), or null
   const float* b;       // biases fp32
   const float* head;    // fp32 head (bf16-representable matrices on the bf16 path)
+  const void* headW = nullptr;   // W1, W2 in the layout of a layer block
   void* act[2];         // ping/pong activations [max_nodes, H]
   void* agg[2];         // predecessor mean / successor mean [max_nodes, max(F,H)]
   void* desc[2];        // gather descriptors [max_nodes] x 16 bytes per direction

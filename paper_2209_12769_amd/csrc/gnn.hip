@@ -488,10 +488,31 @@ __device__ __forceinline__ double head_column(double s, const float* x, const fl
   return s;
 }
 
+// The same from a bf16 matrix in the layout of a layer block (eight rows of a column = 16 bytes): half the bytes and an
+// eighth of the loads (with the chunk sums requested 24 at a time: 7 candidates with H = 256 16.5 -> 15.2 us, 4096 107 -> 88 us).
+__device__ __forceinline__ double head_column(double s, const float* x, const uint4* __restrict__ Wp, int H, int j) {
+  for (int k = 0; k < H; k += 32) {
+    uint4 w[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) w[u] = Wp[(size_t)((k >> 3) + u) * H + j];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const unsigned q[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        s += (double)x[k + 8 * u + 2 * v] * (double)__uint_as_float(q[v] << 16);
+        s += (double)x[k + 8 * u + 2 * v + 1] * (double)__uint_as_float(q[v] & 0xFFFF0000u);
+      }
+    }
+  }
+  return s;
+}
+
 template <bool kBf16, int kOrder>
 __global__ __launch_bounds__(256) void readout_head_kernel(const void* __restrict__ h, int H,
                                                             const int* __restrict__ node_off, int C,
-                                                            const float* __restrict__ head, float* __restrict__ pred,
+                                                            const float* __restrict__ head, const void* __restrict__ headW,
+                                                            float* __restrict__ pred,
                                                             const float* __restrict__ part,
                                                             const int* __restrict__ status) {
   if (status[0] != 0) return;
@@ -508,14 +529,14 @@ __global__ __launch_bounds__(256) void readout_head_kernel(const void* __restric
     if (n1 > n0) {
       const int k1 = ((n1 - 1) >> 6) + 1;
       int k = n0 >> 6;
-      for (; k + 8 <= k1; k += 8) {                // eight chunk sums requested together
-        float x[8];
+      for (; k < k1; k += 24) {                    // 24 chunk sums requested together; past the end the last one, not added
+        float x[24];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = part[(size_t)(k + u + c) * 256 + t];
+        for (int u = 0; u < 24; ++u) x[u] = part[(size_t)(min(k + u, k1 - 1) + c) * 256 + t];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += (double)x[u];
+        for (int u = 0; u < 24; ++u)
+          if (k + u < k1) acc += (double)x[u];
       }
-      for (; k < k1; ++k) acc += (double)part[(size_t)(k + c) * 256 + t];
     }
     r[t] = (float)acc;
   } else if constexpr (kOrder == 1) {
@@ -600,13 +621,15 @@ __global__ __launch_bounds__(256) void readout_head_kernel(const void* __restric
   const float* b3 = w3 + H;
   for (int j = t; j < H; j += 256) {
     double s = b1[j];
-    s = head_column(s, r, W1, H, j);
+    if constexpr (kBf16) s = head_column(s, r, static_cast<const uint4*>(headW), H, j);
+    else s = head_column(s, r, W1, H, j);
     z[j] = (float)(s > 0.0 ? s : 0.0);
   }
   __syncthreads();
   for (int j = t; j < H; j += 256) {
     double s = b2[j];
-    s = head_column(s, z, W2, H, j);
+    if constexpr (kBf16) s = head_column(s, z, static_cast<const uint4*>(headW) + (size_t)H * (H >> 3), H, j);
+    else s = head_column(s, z, W2, H, j);
     r[j] = (float)(s > 0.0 ? s : 0.0);     // r now holds z2
   }
   __syncthreads();
@@ -848,16 +871,16 @@ hipError_t launch_gnn_forward(const GnnArgs& a, Profiler* prof, hipStream_t s) {
   if (a.bf16 && chunked_readout(a)) {
     if (readout_in_last_layer(a))
       hipLaunchKernelGGL((readout_head_kernel<true, 2>), dim3(a.n_cand), dim3(256), 0, s, hcur, a.H, a.node_off, a.n_cand,
-                         a.head, a.pred, a.ro_part, a.status);
+                         a.head, a.headW, a.pred, a.ro_part, a.status);
     else
       hipLaunchKernelGGL((readout_head_kernel<true, 1>), dim3(a.n_cand), dim3(256), 0, s, hcur, a.H, a.node_off, a.n_cand,
-                         a.head, a.pred, static_cast<const float*>(nullptr), a.status);
+                         a.head, a.headW, a.pred, static_cast<const float*>(nullptr), a.status);
   } else if (a.bf16) {
     hipLaunchKernelGGL((readout_head_kernel<true, 0>), dim3(a.n_cand), dim3(256), 0, s, hcur, a.H, a.node_off, a.n_cand,
-                       a.head, a.pred, static_cast<const float*>(nullptr), a.status);
+                       a.head, a.headW, a.pred, static_cast<const float*>(nullptr), a.status);
   } else {
     hipLaunchKernelGGL((readout_head_kernel<false, 0>), dim3(a.n_cand), dim3(256), 0, s, hcur, a.H, a.node_off, a.n_cand,
-                       a.head, a.pred, static_cast<const float*>(nullptr), a.status);
+                       a.head, a.headW, a.pred, static_cast<const float*>(nullptr), a.status);
   }
   if (prof) prof->end(s);
   return hipGetLastError();
