@@ -467,6 +467,8 @@ __global__ __launch_bounds__(256) void fo_time_kernel(const void* __restrict__ Z
   const bool active = sg < per_wave;
   const long long wave0 = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const long long nwaves = ((long long)gridDim.x * blockDim.x) >> 6;
+  // a wave without fused ops leaves before it loads w3 (a search step has some ten of them, the grid 8192 waves: 9.5 -> 3.8 us)
+  if (wave0 * per_wave >= K) return;
   float w[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) w[i] = active ? w3b3[ll * 8 + i] : 0.0f;
