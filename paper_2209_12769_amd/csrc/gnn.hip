@@ -21,6 +21,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16;
 
 __device__ __forceinline__ float bf2f(u16 x) { return __uint_as_float((unsigned)x << 16); }
@@ -159,6 +160,76 @@ __device__ __forceinline__ void step16(const Operands32& o, f32x16& acc, const C
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Fewer still: 16 x 16 tiles.  The chain of K / 4 instructions of 32 cycles that a tile is takes a quarter of the time of
+// K / 2 of 64 cycles, and there are waves enough for all SIMDs with half the rows per wave.  Either instruction adds its
+// columns of K one after the other, each with one rounding (measured: the bits of a sequential fma), so the results
+// are the same.  Twice the bytes from L2 are read: up to two tiles per SIMD.  2115 rows, 128 columns, K = 96 and 384: 13.4 us with
+// 32 x 32 tiles on average, 8.7 us; 45 rows, 32 columns, K = 48 and 96: 6.5 and 5.0 us.
+struct Chunk4 {
+  float4 a;         // columns 4 g .. 4 g + 3 of the lane's row
+  float b[4];       // the lane's column of W, rows 4 i + g
+};
+__device__ __forceinline__ void fetch4(const Operands32& o, Chunk4& x, int c) {
+  const int per = o.d >> 4, seg = (c >= per ? 1 : 0) + (c >= 2 * per ? 1 : 0);
+  x.a = *reinterpret_cast<const float4*>((seg == 0 ? o.A0 : (seg == 1 ? o.A1 : o.A2)) + (c - seg * per) * 16 + o.arow);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x.b[i] = (o.W + (size_t)(c * 16 + 4 * i) * o.H)[o.wcol];
+}
+__device__ __forceinline__ void swap32(float& p, float& q) {      // upper half of p with the lower half of q
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+  p = __uint_as_float(r[0]);
+  q = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float& p, float& q) {      // rows 1 and 3 of p with rows 0 and 2 of q, 16 lanes each
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+  p = __uint_as_float(r[0]);
+  q = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ bool fewer_tiles(int ntot, int H, int few) { return ((ntot + 15) >> 4) * (H >> 4) <= 2 * few; }
+__device__ __forceinline__ void update32_fewer(const float* __restrict__ A0, const float* __restrict__ A1,
+                                               const float* __restrict__ A2, int d, int nseg, const float* __restrict__ Wf,
+                                               const float* __restrict__ bias, float* __restrict__ out, int H, int ntot) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, nw = blockDim.x >> 6;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int nct = H >> 4, ntiles = ((ntot + 15) >> 4) * nct;
+  constexpr int kSets = 8;                              // chunks in registers, seven of them on their way
+  for (int tile = blockIdx.x + wave * gridDim.x; tile < ntiles; tile += nw * gridDim.x) {
+    const int m0 = (tile / nct) * 16, n0 = (tile % nct) * 16;
+    const Operands32 o{A0, A1, A2, Wf, (unsigned)(min(m0 + l16, ntot - 1) * d + 4 * g), (unsigned)(n0 + l16 + g * H), d, H, nseg * d / 16};
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    Chunk4 s[kSets];
+#pragma unroll
+    for (int i = 0; i < kSets - 1; ++i) fetch4(o, s[i], min(i, o.nk - 1));
+    for (int c0 = 0; c0 < o.nk; c0 += kSets) {
+#pragma unroll
+      for (int i = 0; i < kSets; ++i) {
+        const int c = c0 + i;
+        if (c < o.nk) {
+          fetch4(o, s[(i + kSets - 1) % kSets], min(c + kSets - 1, o.nk - 1));
+          __builtin_amdgcn_sched_barrier(0);            // the requests stay ahead of the products
+          // four columns per lane to the operands of four instructions: lane group g holds column 4 i + g of instruction i
+          float x = s[i].a.x, y = s[i].a.y, z = s[i].a.z, w = s[i].a.w;
+          swap32(x, z);
+          swap32(y, w);
+          swap16(x, y);
+          swap16(z, w);
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, s[i].b[0], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(y, s[i].b[1], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(z, s[i].b[2], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w, s[i].b[3], acc, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    const float bj = bias ? bias[n0 + l16] : 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = m0 + 4 * g + v;
+      if (row < ntot) out[(size_t)row * H + n0 + l16] = bias ? fmaxf(acc[v] + bj, 0.f) : acc[v];
+    }
+  }
+}
+
 __device__ __forceinline__ void update32_few(const float* __restrict__ A0, const float* __restrict__ A1,
                                              const float* __restrict__ A2, int d, int nseg, const float* __restrict__ Wf,
                                              const float* __restrict__ bias, float* __restrict__ out, int H, int ntot) {
@@ -226,6 +297,11 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
   const int l32 = lane & 31, lh = lane >> 5;
   const int ntot = node_off[C];
   if constexpr (!kBf16 && BN == 32) {      // the wider tiles of this kernel need the registers for more waves
+    if (fewer_tiles(ntot, H, few)) {
+      update32_fewer(static_cast<const float*>(A0), static_cast<const float*>(A1), static_cast<const float*>(A2), d, nseg,
+                     static_cast<const float*>(Wl), bias, static_cast<float*>(out), H, ntot);
+      return;
+    }
     if (few_tiles(ntot, H, few)) {
       update32_few(static_cast<const float*>(A0), static_cast<const float*>(A1), static_cast<const float*>(A2), d, nseg,
                    static_cast<const float*>(Wl), bias, static_cast<float*>(out), H, ntot);
@@ -367,6 +443,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(BN == 128 ?
   const int l32 = lane & 31, lh = lane >> 5;
   const int ntot = node_off[C];
   if constexpr (BN == 128) {               // beside the wider tile's registers it costs that one 5 %
+    if (fewer_tiles(ntot, H, few)) {
+      update32_fewer(A0, A1, A2, d, nseg, Wf, bias, out, H, ntot);
+      return;
+    }
     if (few_tiles(ntot, H, few)) {
       update32_few(A0, A1, A2, d, nseg, Wf, bias, out, H, ntot);
       return;
