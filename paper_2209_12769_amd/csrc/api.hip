@@ -56,7 +56,7 @@ struct dc_ctx {
   // weights
   void* W = nullptr;
   unsigned short* Ws = nullptr;       // fp32: pieces of the layer matrices (dense32.hip)
-  unsigned short* Wx = nullptr;       // attention, H = 256, bf16, up to eight heads: score columns (gnn_layer256.hip)
+  unsigned short* Wx = nullptr;       // attention, H = 256, bf16, up to four heads: score columns (gnn_layer256.hip)
   bool have_wx = false;
   float* b = nullptr;
   float* head = nullptr;
@@ -527,7 +527,7 @@ dc_status dc_create(dc_ctx** out, const dc_config* cfg) {
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->b), (size_t)cfg->L * cfg->H * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->head), (2 * HH + 3 * cfg->H + 1) * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&ctx->headW, 2 * HH * es);
-  if (e == hipSuccess && cfg->aggregator == DC_AGG_ATTENTION && cfg->heads <= 8 && layer256_supported(cfg->H, cfg->H, cfg->dtype == DC_BF16))
+  if (e == hipSuccess && cfg->aggregator == DC_AGG_ATTENTION && cfg->heads <= 4 && layer256_supported(cfg->H, cfg->H, cfg->dtype == DC_BF16))
     e = hipMalloc(reinterpret_cast<void**>(&ctx->Wx), ((size_t)cfg->F + (size_t)(cfg->L - 1) * cfg->H) * 32 * sizeof(unsigned short));
   if (e == hipSuccess && cfg->dtype == DC_F32)
     e = hipMalloc(reinterpret_cast<void**>(&ctx->Ws), (packed_weight_elems(cfg->F, cfg->H, cfg->L, 3) + 2 * HH) * 3 * sizeof(unsigned short));

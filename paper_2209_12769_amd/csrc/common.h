@@ -216,7 +216,7 @@ hipError_t launch_layer256w(const void* h, int d, const GnnArgs& a, const void* 
                             bool readout, hipStream_t s);
 hipError_t launch_dense256(const void* h, int d, const GnnArgs& a, const void* Wl, const float* bias, void* out,
                            hipStream_t s);
-// The same with the score terms of the attention variant (up to eight heads) in a.score; Wx: the layer's part of what
+// The same with the score terms of the attention variant (up to four heads) in a.score; Wx: the layer's part of what
 // pack_score_columns() leaves, 32 d values.
 hipError_t launch_dense256_scores(const void* h, int d, const GnnArgs& a, const void* Wl, const unsigned short* Wx, void* z,
                                   hipStream_t s);

@@ -108,9 +108,9 @@ struct MfmaConst {
   int ntot, tile0, per, wm, wn, l32, lh, lane, wave, sw;
 };
 
-// The score terms of the attention variant: s_i = a . z_i per head and kind = h_i (W a), so they are eight (K = 8: sixteen)
-// more columns of the product, kept in two bf16 pieces each (column 8 q + 4 kind + v: head v; the second pieces two or
-// four quads on), 32 with the unused ones.  Their part of W stays in registers; a wave multiplies the half of its rows
+// The score terms of the attention variant, up to four heads: s_i = a . z_i per head and kind = h_i (W a), so they are
+// eight more columns of the product, kept in three bf16 pieces each, which together are fp32 (column 8 q + 4 kind + v:
+// piece q of head v), 32 with the unused ones.  Their part of W stays in registers; a wave multiplies the half of its rows
 // that no other wave has.  Bound by memory like the product, which hides them: 1.39 M rows, d = 256, 298 us the product and
 // 173 us a kernel that read z again, 321 us together.  Nearer to 64 bits than terms from the rounded z: predictions of 43 k
 // rows 1.6e-4 off instead of 1.9e-4, of 25 k rows 1.9e-4 instead of 1.5e-3.
@@ -268,17 +268,16 @@ __device__ __forceinline__ void mfma_step(int s, int S, f32x16 (&acc)[2][4], Sco
     }
     if constexpr (kScores) {
       const int row = m0 + c.wm * 64 + c.wn * 32 + c.l32;
-      const int lo = sc.heads > 4 ? 8 : 4;
-      float x[8];
+      float x[4];
 #pragma unroll
-      for (int v = 0; v < 8; ++v) x[v] = sc.acc[v] + (lo == 8 ? sc.acc[8 + v] : sc.acc[4 + v]);   // four heads or fewer: the first four
+      for (int v = 0; v < 4; ++v) x[v] = sc.acc[v] + (sc.acc[4 + v] + sc.acc[8 + v]);
       if (row < c.ntot) {
         float* p = (c.lh ? sc.dst : sc.src) + (size_t)row * sc.heads;
         if (sc.heads == 4) {
           *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
         } else {
 #pragma unroll
-          for (int v = 0; v < 8; ++v)
+          for (int v = 0; v < 3; ++v)
             if (v < sc.heads) p[v] = x[v];
         }
       }
@@ -411,7 +410,7 @@ hipError_t launch_dense256_scores(const void* h, int d, const GnnArgs& a, const 
   return hipErrorInvalidValue;
 }
 
-// Wx of all layers for W (bf16) and the attention vectors: W a per head and kind in 64 bits, as two bf16 numbers, in the order
+// Wx of all layers for W (bf16) and the attention vectors: W a per head and kind in 64 bits, as three bf16 numbers, in the order
 // the product reads them (unit of eight rows of a column; 32 columns).  False where one is no finite number.
 bool pack_score_columns(const float* W_layers, const float* att, int F, int L, int heads, unsigned short* dst) {
   const int H = kBN, Dh = H / heads;
@@ -437,10 +436,11 @@ bool pack_score_columns(const float* W_layers, const float* att, int F, int L, i
           for (int j = n * Dh; j < (n + 1) * Dh; ++j)
             x += (double)from_bf16(to_bf16(W_layers[(size_t)k * H + j])) * (double)att[kind * H + j];
           if (!(fabs(x) < 1e38)) return false;
-          const unsigned short hi = to_bf16((float)x), lo = to_bf16((float)(x - (double)from_bf16(hi)));
-          const int col = 8 * (n >> 2) + 4 * kind + (n & 3);
-          dst[(size_t)(k / 8 * 32 + col) * 8 + k % 8] = hi;
-          dst[(size_t)(k / 8 * 32 + col + (heads > 4 ? 16 : 8)) * 8 + k % 8] = lo;
+          for (int q = 0; q < 3; ++q) {
+            const unsigned short piece = to_bf16((float)x);
+            x -= (double)from_bf16(piece);
+            dst[(size_t)(k / 8 * 32 + 8 * q + 4 * kind + n) * 8 + k % 8] = piece;
+          }
         }
     dst += (size_t)d * 32;
     W_layers += (size_t)d * H;
