@@ -135,9 +135,9 @@ __device__ __forceinline__ void fetch16(const Operands32& o, Chunk16& x, int c) 
 #pragma unroll
   for (int i = 0; i < 8; ++i) x.b[i] = (o.W + (size_t)(k0 + 2 * i) * o.H)[o.wcol];
 }
-// Lanes 0-31 hold column k in p and k + 1 in q, lanes 32-63 k + 4 and k + 5: afterwards p is the operand of columns
-// (k, k + 1), q that of (k + 4, k + 5).
-__device__ __forceinline__ void halves_to_pairs(float& p, float& q) {
+// The upper half of p's lanes changes with the lower half of q's.  Lanes 0-31 hold column k in p and k + 1 in q, lanes 32-63
+// k + 4 and k + 5: afterwards p is the operand of columns (k, k + 1), q that of (k + 4, k + 5).
+__device__ __forceinline__ void swap32(float& p, float& q) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
   p = __uint_as_float(r[0]);
   q = __uint_as_float(r[1]);
@@ -150,8 +150,8 @@ __device__ __forceinline__ void step16(const Operands32& o, f32x16& acc, const C
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     float x = cur.a[i].x, y = cur.a[i].y, z = cur.a[i].z, w = cur.a[i].w;
-    halves_to_pairs(x, y);
-    halves_to_pairs(z, w);
+    swap32(x, y);
+    swap32(z, w);
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, cur.b[4 * i], acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(z, cur.b[4 * i + 1], acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y, cur.b[4 * i + 2], acc, 0, 0, 0);
@@ -174,11 +174,6 @@ __device__ __forceinline__ void fetch4(const Operands32& o, Chunk4& x, int c) {
   x.a = *reinterpret_cast<const float4*>((seg == 0 ? o.A0 : (seg == 1 ? o.A1 : o.A2)) + (c - seg * per) * 16 + o.arow);
 #pragma unroll
   for (int i = 0; i < 4; ++i) x.b[i] = (o.W + (size_t)(c * 16 + 4 * i) * o.H)[o.wcol];
-}
-__device__ __forceinline__ void swap32(float& p, float& q) {      // upper half of p with the lower half of q
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
-  p = __uint_as_float(r[0]);
-  q = __uint_as_float(r[1]);
 }
 __device__ __forceinline__ void swap16(float& p, float& q) {      // rows 1 and 3 of p with rows 0 and 2 of q, 16 lanes each
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);

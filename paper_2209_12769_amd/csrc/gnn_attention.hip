@@ -7,7 +7,8 @@
 //     gamma_ij = softmax over j in N_i,   e_i = ReLU(sum_j gamma_ij z_j + b),
 // with N_i = (i, predecessors ascending, successors ascending) and heads being contiguous
 // blocks of H / K columns.  z = h W is a dense contraction (update_kernel); here are the
-// two kernels that follow it: the score terms per node and head, and the weighted sums.
+// two kernels that follow it: the score terms per node and head (with H = 256, bf16 and up to four heads the product
+// forms them itself, gnn_layer256.hip), and the weighted sums.
 //
 // A row of z is served by LPR = H / 8 lanes, eight columns each (16 bytes in bf16, 32 in
 // fp32); a head's Dh = H / K columns sit in Dh / 8 adjacent lanes, so the reductions over a

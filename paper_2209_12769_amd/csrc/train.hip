@@ -5,8 +5,8 @@
 //     y = z2.w3 + b3,  z2 = ReLU(z1 W2 + b2),  z1 = ReLU(r W1 + b1),  r = sum of h_L over the
 //     ops of the fused op (Secs. 3.3.1, 3.3.2),
 //     h_{l+1} = ReLU([h_l | mean over predecessors | mean over successors] W_l + b_l).
-// Dense products run on the fp32 matrix cores (32x32x2): forward and the data gradients through the
-// layer update kernel, the weight gradients through wgrad_kernel below, whose contraction
+// Dense products: forward on the fp32 matrix cores (32x32x2) through the layer update kernel; the reverse pass
+// on the bf16 ones in three pieces (dense32.hip): data gradients, and weight gradients, whose contraction
 // index is the row of the batch (transposed-A product, split over slabs of rows, partial
 // results reduced in a fixed order, so a pass is bit-reproducible).  Everything else is
 // bandwidth-bound and done by plain grid-stride kernels.  Adam as published by Kingma & Ba.
@@ -14,8 +14,6 @@
 
 namespace dc {
 namespace {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ---- sample of each row: largest g with node_off[g] <= v (graphs may be empty) ----
 __global__ __launch_bounds__(256) void gid_kernel(const int* __restrict__ node_off, int B, int* __restrict__ gid,
