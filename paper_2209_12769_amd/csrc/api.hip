@@ -502,7 +502,7 @@ dc_status dc_create(dc_ctx** out, const dc_config* cfg) {
     if (prop.sharedMemPerBlockOptin > lds) lds = prop.sharedMemPerBlockOptin;
     if (lds > 160 * 1024) lds = 160 * 1024;
     // keep room for the kernel's static LDS
-    ctx->lds_limit = (int)lds - 1024;
+    ctx->lds_limit = (int)lds - 512;
     if (ctx->lds_limit > 48 * 1024 && contract_set_lds_limit(ctx->lds_limit) != hipSuccess) {
       (void)hipGetLastError();
       ctx->lds_limit = 48 * 1024;

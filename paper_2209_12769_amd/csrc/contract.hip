@@ -37,12 +37,14 @@ typedef unsigned long long u64;
 // 32-bit in global memory (`wide`).  nd = 2: successors and predecessors as one array of 2 G rows, nd = 1: one after the
 // other.
 //   ids:    u16 NID[N]: labels, then contracted ids | bitmaps, row numbers set aside, then masks (nd = 2: in the ids' place)
-//   first:  MS[N + 1] group ends, int FIRST[N] (then u16 MEM[N], LST), u64 HM / int HP: heads and their ranks
+//   first:  MS[N + 1] group ends, int FIRST[N] (then u16 MEM[N], LST), u64 HM / u16 HP: heads and their ranks
 //   later:  OFF[nd N + 1] row ends, u16 RAW[nd E] neighbours by row
 struct Slab {
   int nid, lst2, longest2, bm, mask, pre, ms, first, hm, hp, off, raw, nd, total;
 };
 __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
+// Lists sorted where they are met: with one direction after the other LDS is short, and fewer numbers are set aside
+__host__ __device__ inline int first_pass(int nd) { return nd == 2 ? kTinyRow : 2 * kTinyRow; }
 __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) {
   const int os = wide ? 4 : 2, rows = nd * N, slots = nd * E, w = (slots + 63) / 64 + 1, hw = (N + 63) / 64 + 1;
   Slab s;
@@ -50,7 +52,7 @@ __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) 
   s.nid = 0;
   const int ids = align16(2 * (N + 2));
   const int bm = align16(4 * kBmWaves * ((N + 31) / 32 + 1)), mask = align16(8 * w) + align16(4 * w);
-  const int lst = align16(os * (slots / (kTinyRow + 1) + 2));
+  const int lst = align16(os * (slots / (first_pass(nd) + 1) + 2));
   const int longest = align16(os * (slots / (kSmallRow + 1) + 2));
   const int aux = bm + (mask > lst + longest ? mask : lst + longest);
   const int x = nd == 2 && aux > ids ? aux : ids;
@@ -58,7 +60,7 @@ __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) 
   s.ms = o;    o = align16(o + os * (N + 2));
   s.first = o; o = align16(o + 4 * N + 4 * os);
   s.hm = o;    o = align16(o + 8 * hw);
-  s.hp = o;    o = align16(o + 4 * hw);
+  s.hp = o;    o = align16(o + 2 * hw);
   s.total = o;
   o = x;
   s.off = o;   o = align16(o + os * (rows + 2));
@@ -195,8 +197,8 @@ __device__ __forceinline__ int exscan(u16* a, int n, int* wsum) {
 __device__ __forceinline__ int exscan(int* a, int n, int* wsum) { return block_exscan_lines(a, a, n, wsum); }
 
 // pre[w] = bits set in front of word w of m, pre[nw] = all of them (returned); m[nw] = 0
-template <bool kLds>
-__device__ __forceinline__ int scan_bits(u64* m, int* pre, int nw, int* wsum) {
+template <bool kLds, typename Pre>
+__device__ __forceinline__ int scan_bits(u64* m, Pre* pre, int nw, int* wsum) {
   const int t = threadIdx.x, T = blockDim.x;
   int carry = 0;
   for (int w0 = 0; w0 < nw; w0 += T) {
@@ -204,13 +206,13 @@ __device__ __forceinline__ int scan_bits(u64* m, int* pre, int nw, int* wsum) {
     const int inc = wave_incl_scan(pc);
     int total;
     const int run = carry + wave_offsets<kLds>(inc, total, wsum) + inc - pc;
-    if (w < nw) pre[w] = run;
+    if (w < nw) pre[w] = (Pre)run;
     carry += total;
     if (w0 + T < nw) block_sync<kLds>();         // wsum is written again
   }
   if (t == 0) {
     m[nw] = 0;
-    pre[nw] = carry;
+    pre[nw] = (Pre)carry;
   }
   block_sync<kLds>();
   return carry;
@@ -244,24 +246,26 @@ __device__ __forceinline__ void store_all(int* p, int n, Value value) {
     else for (int k = i; k < n; ++k) p[k] = value(k);
   }
 }
-__device__ __forceinline__ int bits_before(const u64* m, const int* pre, int i) {
+template <typename Pre>
+__device__ __forceinline__ int bits_before(const u64* m, const Pre* pre, int i) {
   return pre[i >> 6] + __popcll(m[i >> 6] & ((1ull << (i & 63)) - 1ull));
 }
 
-// Rows r < rows of `a`, row r ending at end[r], each ascending, kSelf in the place of a repeat.  Rows of up to four entries
-// are sorted as they are met; the others are set aside, those of up to eight from the front of `lst`, of up to 16 from
+// Rows r < rows of `a`, row r ending at end[r], each ascending, kSelf in the place of a repeat.  Rows of up to `at_once`
+// (four or eight) entries are sorted as they are met; the others are set aside, those of up to eight from the front of `lst`, of up to 16 from
 // its back (`room` entries), so that the waves that sort them are full and take one network each.  More than 16
 // entries (`longest`): `longer(r, begin, n)`, called by whole waves, all of them for up to 64 entries, the first kBmWaves
 // for more.  cnt[0 .. 2] are 0.
 template <bool kLds, typename Off, typename Longer>
-__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, Off* longest, int* cnt, Longer longer) {
+__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, int at_once, Off* longest, int* cnt, Longer longer) {
   const int t = threadIdx.x, T = blockDim.x, wave = t >> 6, lane = t & 63;
   auto begin = [&](int r) { return r ? (int)end[r - 1] : 0; };
   for (int r = t; r < rows; r += T) {
     const int s = begin(r), n = (int)end[r] - s;
     if (n > kSmallRow) longest[atomicAdd(&cnt[2], 1)] = (Off)r;
     else if (n > 2 * kTinyRow) lst[room - 1 - atomicAdd(&cnt[1], 1)] = (Off)r;
-    else if (n > kTinyRow) lst[atomicAdd(&cnt[0], 1)] = (Off)r;
+    else if (n > at_once) lst[atomicAdd(&cnt[0], 1)] = (Off)r;
+    else if (n > kTinyRow) sort_unique_small<2 * kTinyRow>(a + s, n);
     else if (n > 1) sort_unique_small<kTinyRow>(a + s, n);
   }
   block_sync<kLds>();
@@ -313,7 +317,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   Off* LST = reinterpret_cast<Off*>(base + L.first + align16(2 * N));
   Off* LONGEST = LST + N / (kTinyRow + 1) + 1;
   u64* HM = reinterpret_cast<u64*>(base + L.hm);
-  int* HP = reinterpret_cast<int*>(base + L.hp);
+  u16* HP = reinterpret_cast<u16*>(base + L.hp);
   int* cnt = wsum + 16;            // three words behind the scans' wave sums
 
   const int* lab = label + coff;
@@ -399,7 +403,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
       if (node(i + j * T) < N) MEM[g[j]] = (u16)node(i + j * T);
   }
   block_sync<kLds>();
-  sort_rows<kLds>(MEM, MS, G, LST, N / (kTinyRow + 1) + 1, LONGEST, cnt, [&](int g, int s, int n) {
+  sort_rows<kLds>(MEM, MS, G, LST, N / (kTinyRow + 1) + 1, kTinyRow, LONGEST, cnt, [&](int g, int s, int n) {
     if (n <= 64) {
       sort_wave(MEM + s, n, lane);
       return;
@@ -467,7 +471,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
     const int S = exscan(OFF, rows, wsum);
     each_edge(std::true_type{});
     for (int i = t; i < kBmWaves * bm_words; i += T) BM[i] = 0u;      // seen by all before the first list of more than 64
-    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (kTinyRow + 1) + 1, LONGEST2, cnt, [&](int, int s, int n) {
+    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (first_pass(nd) + 1) + 1, first_pass(nd), LONGEST2, cnt, [&](int, int s, int n) {
       if (n <= 64) {
         sort_wave(RAW + s, n, lane);
         return;

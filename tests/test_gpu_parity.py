@@ -208,7 +208,7 @@ def test_every_list_length_class_of_the_contraction(B):
 # directions together and one after the other, the most that fits, global memory; few nodes with so many edges that
 # 16-bit row ends hold one direction only, or not even that
 @pytest.mark.parametrize("n,e", [(3000, 2000), (1200, 6500), (2500, 4200), (4000, 9500), (5000, 8000), (12000, 20000), (19100, 31000),
-                                 (19600, 33500), (900, 32768), (700, 66000)])
+                                 (19990, 33500), (21000, 33500), (900, 32768), (700, 66000)])
 def test_size_classes_of_the_contraction(B, n, e):
     rng = np.random.default_rng(n + e)
     src = rng.integers(0, n - 1, e)
