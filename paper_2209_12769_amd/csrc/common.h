@@ -14,6 +14,16 @@ __device__ __forceinline__ void set_error(int* status, int code) {
   atomicCAS(&status[1], 0, code);
 }
 
+// Whether the call has failed by now, one answer for the whole workgroup.  Where a kernel sets an error itself and its waves
+// meet at barriers, waves that read the word one by one could see it change in between: those that left would be missing in
+// what the others sum and share.
+__device__ __forceinline__ bool call_failed(const int* status) {
+  __shared__ int word;
+  if (threadIdx.x == 0) word = status[0];
+  __syncthreads();
+  return word != 0;
+}
+
 // Base graphs as the kernels see them (device pointers).
 struct BaseGraphs {
   int n_graphs;

@@ -542,7 +542,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     BaseGraphs bg, int C, const int* cand_graph, const int* cand_off, const int* label, ContractTmp tmp, int* new_id_out,
     int* status, char* gslab, size_t slab_stride, int above, int most, int lds) {
   __shared__ int wsum[19];
-  if (status[0] != 0) return;
+  if (call_failed(status)) return;
   if (kLds) {
     for (int c = blockIdx.x; c < C; c += gridDim.x) {
       const int b = cand_graph[c], coff = cand_off[c], eslot = tmp.tmp_eoff[c];
@@ -694,7 +694,7 @@ template <bool kBf16>
 __global__ __launch_bounds__(256) void finalize_kernel(BaseGraphs bg, int C, const int* cand_graph,
                                                         const int* cand_off, ContractTmp tmp, BatchView out, int F,
                                                         int* status, int* totals) {
-  if (status[0] != 0) return;
+  if (C > kOwnScan && status[0] != 0) return;        // set by an earlier launch only
   const int c = blockIdx.x, t = blockIdx.y * blockDim.x + threadIdx.x, T = gridDim.y * blockDim.x;
   const int b = cand_graph[c];
   const int coff = cand_off[c];
@@ -702,7 +702,8 @@ __global__ __launch_bounds__(256) void finalize_kernel(BaseGraphs bg, int C, con
   const int G = tmp.Gc[c], E = tmp.Ec[c];
   int n0, e0;
   if (C <= kOwnScan) {
-    __shared__ int wn[4], we[4], own[2];
+    __shared__ int wn[4], we[4], own[2], failed;
+    if (threadIdx.x == 0) failed = status[0];        // read once: workgroup 0 of this launch may set it
     const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
     const int xn = i < C ? tmp.Gc[i] : 0, xe = i < C ? tmp.Ec[i] : 0;
     int sn = wave_incl_scan(xn), se = wave_incl_scan(xe);
@@ -711,6 +712,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(BaseGraphs bg, int C, con
       we[wave] = se;
     }
     __syncthreads();
+    if (failed) return;
     int nt = 0, et = 0;
     for (int w = 0; w < 4; ++w) {
       if (w < wave) {

@@ -153,7 +153,7 @@ __device__ __forceinline__ int find_or_enter(const FusedOpsArgs& a, int b, const
 // 126 us; 1000 candidates of 6.5 k groups: 256 -> 157 and 58 -> 18 us).
 __global__ __launch_bounds__(1024) void fo_count_kernel(FusedOpsArgs a) {
   __shared__ int wsum[2][2][16];
-  if (a.status[0] != 0) return;
+  if (call_failed(a.status)) return;
   const int c = blockIdx.x, t = threadIdx.x, T = blockDim.x;
   const int b = a.cand_graph[c];
   const int coff = a.cand_off[c], nslot = coff + c;

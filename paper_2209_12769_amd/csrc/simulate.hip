@@ -766,7 +766,7 @@ __global__ __launch_bounds__(kWalkThreads) void simulate_walk_kernel(
     float ar_c, float ar_d, float* __restrict__ cost, int lds_most, int last,
     unsigned long long* __restrict__ walked, int* status) {
   // lds_most: larger working sets are left to the kernel that follows; without one (last) such a module is an error
-  if (status[0] != 0) return;
+  if (call_failed(status)) return;
   int* ctr = reinterpret_cast<int*>(dc_sim_smem);
   unsigned short* list = reinterpret_cast<unsigned short*>(dc_sim_smem + kWalkList);
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;

@@ -227,6 +227,32 @@ def test_size_classes_of_the_contraction(B, n, e):
     ev.close()
 
 
+# A capacity error is found by the launch that would place the results: no workgroup of it, of which many share a candidate, may
+# write past what fits (all of it is refused), and a batch that fits is complete.
+@pytest.mark.parametrize("C", [1, 7, 256, 257])
+def test_capacity_error_writes_nothing(B, C):
+    import torch
+    w = wl.make("cfg2", C)
+    ev = B.evaluator_for(w)
+    cg, co, gid = ev.to_device(w.cand_graph), ev.to_device(w.cand_off), ev.to_device(w.group_id)
+    nb = int(w.cand_off[-1])
+    geo = w.g_edge_off()
+    eb = int(sum(int(geo[b + 1] - geo[b]) for b in w.cand_graph))
+    ref = orc.contract(w, False)
+    for cn, ce in ((ref.ntot - 1, eb), (nb, ref.etot - 1), (1, 1)):
+        batch = ev.alloc_batch(C, nb, nb, eb)
+        names = ("out_rowptr", "out_col", "in_rowptr", "in_col", "Xc")
+        for k in names:
+            getattr(batch, k).fill_(-77)
+        batch.c.cap_nodes, batch.c.cap_edges = cn, ce
+        ev.contract_graphs(cg, co, gid, batch)
+        assert ev.check() == B.DC_ERR_CAPACITY
+        for k in names:
+            assert bool(torch.all(getattr(batch, k) == -77)), (k, cn, ce)
+    ev.close()
+    check_contraction(B, w)[0].close()
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("name", ["cfg3", "cfg4", "cfg5"])
 def test_full_size_contraction_of_every_candidate(B, name):
