@@ -328,7 +328,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   // The lanes of a wave take nodes far from each other where they count or place by group: neighbours are mostly in one
   // group, and atomics on one word follow each other (edges lie in memory in such an order).  An odd distance: every
   // lane in a bank of its own.
-  const int apart = ((N + 63) >> 6) | 1, spread = apart << 6;
+  const int apart = ((N + 63) >> 6) | 1, spread = N > 0 ? apart << 6 : 0;
   auto node = [&](int i) { return i < spread ? (i & 63) * apart + (i >> 6) : N; };
 
   // ---- relabel: groups numbered by ascending smallest member -----------------

@@ -366,9 +366,10 @@ def test_edgeless_and_tiny_graphs(B):
                       wl.Rng(1, 1).uniform(n * 16).reshape(n, 16).astype(np.float32))
     g1 = wl.BaseGraph(1, 1, np.zeros(2, np.int32), np.zeros(0, np.int32), np.ones((1, 16), np.float32))
     g2 = wl.random_dag(3, 9, 0.5, 16)
-    labs = [np.array([[0, 1, 2, 3, 4], [4, 4, 2, 2, 0]], np.int32), np.zeros((2, 1), np.int32),
-            wl.random_labels(4, 9, 4, C=2)]
-    w = wl.custom("tiny", wl.ModelSpec(16, 32, 3, "f32"), [g0, g1, g2], labs, seed=7)
+    none = wl.BaseGraph(0, 0, np.zeros(1, np.int32), np.zeros(0, np.int32), np.zeros((0, 16), np.float32))
+    labs = [np.array([[0, 1, 2, 3, 4], [4, 4, 2, 2, 0]], np.int32), np.zeros((2, 0), np.int32), np.zeros((2, 1), np.int32),
+            wl.random_labels(4, 9, 4, C=2), np.zeros((1, 0), np.int32)]
+    w = wl.custom("tiny", wl.ModelSpec(16, 32, 3, "f32"), [g0, none, g1, g2, none], labs, seed=7)
     ev, batch, ref = check_contraction(B, w)
     check_forward(B, w, ev, batch, ref)
     ev.close()
