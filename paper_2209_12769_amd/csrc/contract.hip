@@ -27,7 +27,7 @@ namespace {
 
 constexpr int kTinyRow = 4;     // lists up to this length are sorted where they are met, by one thread in registers,
 constexpr int kSmallRow = 16;   // up to this length by one thread once all such are known, up to 64 by a wave
-constexpr int kBmWaves = 2;     // waves that sort lists of more than 64 entries, through a bitmap each
+constexpr int kBmWaves = 2;     // waves that can always sort neighbour lists of more than 64 entries, through a bitmap each
 constexpr unsigned short kSelf = 0xFFFF;
 
 typedef unsigned short u16;
@@ -41,6 +41,7 @@ typedef unsigned long long u64;
 //   later:  OFF[nd N + 1] row ends, u16 RAW[nd E] neighbours by row
 struct Slab {
   int nid, lst2, longest2, bm, mask, pre, ms, first, hm, hp, off, raw, nd, total;
+  int bm_more, bm_waves;          // LDS: bitmaps of the waves behind the first kBmWaves, and how many waves have one
 };
 __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 // Lists sorted where they are met: with one direction after the other LDS is short, and fewer numbers are set aside
@@ -51,7 +52,7 @@ __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) 
   s.nd = nd;
   s.nid = 0;
   const int ids = align16(2 * (N + 2));
-  const int bm = align16(4 * kBmWaves * ((N + 31) / 32 + 1)), mask = align16(8 * w) + align16(4 * w);
+  const int bm = align16(4 * (wide ? 16 : kBmWaves) * ((N + 31) / 32 + 1)), mask = align16(8 * w) + align16(4 * w);
   const int lst = align16(os * (slots / (first_pass(nd) + 1) + 2));
   const int longest = align16(os * (slots / (kSmallRow + 1) + 2));
   const int aux = bm + (mask > lst + longest ? mask : lst + longest);
@@ -71,13 +72,19 @@ __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) 
   s.pre = s.mask + align16(8 * w);
   if (nd == 1) o += aux;
   if (o > s.total) s.total = o;
+  s.bm_more = s.bm + 4 * kBmWaves * ((N + 31) / 32 + 1);
+  s.bm_waves = wide ? 16 : kBmWaves;
   if (!wide && slots > 65535) s.total = INT_MAX;
   return s;
 }
 // Both directions at once, in half the phases, where that fits.
 __host__ __device__ inline Slab slab_layout(int N, int E, int lds) {
-  const Slab s = slab_layout_nd(N, E, 2, false);
-  return s.total <= lds ? s : slab_layout_nd(N, E, 1, false);
+  Slab s = slab_layout_nd(N, E, 2, false);
+  if (s.total > lds) s = slab_layout_nd(N, E, 1, false);
+  s.bm_more = s.total;                     // the LDS that is left, up to a bitmap for each of sixteen waves
+  const int more = (lds - s.total) / (4 * ((N + 31) / 32 + 1));
+  s.bm_waves = kBmWaves + (more < 16 - kBmWaves ? more : 16 - kBmWaves);
+  return s;
 }
 __host__ __device__ inline int slab_need(int N, int E) { return slab_layout_nd(N, E, 1, false).total; }
 
@@ -254,10 +261,12 @@ __device__ __forceinline__ int bits_before(const u64* m, const Pre* pre, int i) 
 // Rows r < rows of `a`, row r ending at end[r], each ascending, kSelf in the place of a repeat.  Rows of up to `at_once`
 // (four or eight) entries are sorted as they are met; the others are set aside, those of up to eight from the front of `lst`, of up to 16 from
 // its back (`room` entries), so that the waves that sort them are full and take one network each.  More than 16
-// entries (`longest`): `longer(r, begin, n)`, called by whole waves, all of them for up to 64 entries, the first kBmWaves
-// for more.  cnt[0 .. 2] are 0.
+// entries (`longest`): `longer(r, begin, n)`, called by whole waves, all of them for up to 64 entries, the first `most` for
+// more.  Member lists need no bitmap: one candidate with 50 groups of 100 of its 6.6 k nodes 328 us with two waves for them, 117 us
+// with sixteen; one of 900 nodes with 33 k edges, nearly all lists longer than 64: 488 us with two bitmaps, 186 us with sixteen.
+// cnt[0 .. 2] are 0.
 template <bool kLds, typename Off, typename Longer>
-__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, int at_once, Off* longest, int* cnt, Longer longer) {
+__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, int at_once, Off* longest, int most, int* cnt, Longer longer) {
   const int t = threadIdx.x, T = blockDim.x, wave = t >> 6, lane = t & 63;
   auto begin = [&](int r) { return r ? (int)end[r - 1] : 0; };
   for (int r = t; r < rows; r += T) {
@@ -286,14 +295,16 @@ __device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off*
     }
   }
   // the last waves first: the first ones have the networks
-  for (int pass = 0; pass < 2; ++pass) {
-    const int step = pass ? kBmWaves : T >> 6, first = pass ? wave : step - 1 - wave;
-    if (wave >= step) break;
-    for (int i = first; i < nl; i += step) {
-      const int r = longest[i], s = begin(r), n = (int)end[r] - s;
-      if ((n > 64) == (pass == 1)) longer(r, s, n);
-    }
+  const int all = T >> 6;
+  for (int i = all - 1 - wave; i < nl; i += all) {
+    const int r = longest[i], s = begin(r), n = (int)end[r] - s;
+    if (n <= 64 || most >= all) longer(r, s, n);
   }
+  if (most < all && wave < most)
+    for (int i = wave; i < nl; i += most) {
+      const int r = longest[i], s = begin(r), n = (int)end[r] - s;
+      if (n > 64) longer(r, s, n);
+    }
   block_sync<kLds>();
 }
 
@@ -403,7 +414,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
       if (node(i + j * T) < N) MEM[g[j]] = (u16)node(i + j * T);
   }
   block_sync<kLds>();
-  sort_rows<kLds>(MEM, MS, G, LST, N / (kTinyRow + 1) + 1, kTinyRow, LONGEST, cnt, [&](int g, int s, int n) {
+  sort_rows<kLds>(MEM, MS, G, LST, N / (kTinyRow + 1) + 1, kTinyRow, LONGEST, T >> 6, cnt, [&](int g, int s, int n) {
     if (n <= 64) {
       sort_wave(MEM + s, n, lane);
       return;
@@ -432,7 +443,8 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   u64* MASK = reinterpret_cast<u64*>(base + L.mask);
   int* PRE = reinterpret_cast<int*>(base + L.pre);
   const int bm_words = (N + 31) / 32 + 1;
-  unsigned* BM = reinterpret_cast<unsigned*>(base + L.bm);
+  unsigned* BM = reinterpret_cast<unsigned*>(wave < kBmWaves ? base + L.bm + 4 * wave * bm_words
+                                                             : base + L.bm_more + 4 * (wave - kBmWaves) * bm_words);
   int Ec = 0;
   for (int dir = 0; dir < 2; dir += nd) {
     for (int i = t; i < (int)(sizeof(Off) * (rows + 2)) / 4; i += T) reinterpret_cast<int*>(OFF)[i] = 0;
@@ -470,24 +482,28 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
     each_edge(std::false_type{});
     const int S = exscan(OFF, rows, wsum);
     each_edge(std::true_type{});
-    for (int i = t; i < kBmWaves * bm_words; i += T) BM[i] = 0u;      // seen by all before the first list of more than 64
-    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (first_pass(nd) + 1) + 1, first_pass(nd), LONGEST2, cnt, [&](int, int s, int n) {
+    bool clean = false;                                // the wave's bitmap is zero
+    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (first_pass(nd) + 1) + 1, first_pass(nd), LONGEST2, L.bm_waves, cnt, [&](int, int s, int n) {
       if (n <= 64) {
         sort_wave(RAW + s, n, lane);
         return;
       }
       // mark neighbours in the wave's bitmap, then list the set bits
-      unsigned* bm = BM + wave * bm_words;
+      if (!clean) {
+        for (int i = lane; i < bm_words; i += 64) BM[i] = 0u;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        clean = true;
+      }
       for (int i = lane; i < n; i += 64) {
         const u16 x = RAW[s + i];
-        atomicOr(&bm[x >> 5], 1u << (x & 31));
+        atomicOr(&BM[x >> 5], 1u << (x & 31));
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       int cnt = 0;
       for (int w0 = 0; w0 < (G + 31) / 32; w0 += 64) {
         const int w = w0 + lane;
-        unsigned bits = (w < (G + 31) / 32) ? bm[w] : 0u;
-        if (bits) bm[w] = 0u;
+        unsigned bits = (w < (G + 31) / 32) ? BM[w] : 0u;
+        if (bits) BM[w] = 0u;
         const int pc = __popc(bits);
         const int inc = wave_incl_scan(pc);
         int o = s + cnt + inc - pc;

@@ -227,6 +227,29 @@ def test_size_classes_of_the_contraction(B, n, e):
     ev.close()
 
 
+# Many groups of 64 and more members and many lists of 64 and more neighbours: workgroups of four, eight and sixteen waves, with
+# a bitmap for each wave, for some of them and for two; in global memory
+@pytest.mark.parametrize("n,e,C", [(600, 9000, 300), (1500, 9500, 300), (1500, 9500, 1), (900, 32768, 1), (2000, 62000, 2), (16000, 42000, 1),
+                                   (18000, 37000, 1), (3000, 90000, 2)])
+def test_long_lists_of_the_contraction(B, n, e, C):
+    rng = np.random.default_rng(n + e)
+    src = np.sort(rng.integers(0, n - 1, e))
+    dst = src + 1 + rng.integers(0, 1 << 30, e) % (n - 1 - src)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int32)
+    g = wl.BaseGraph(n, n, rowptr, dst.astype(np.int32), rng.integers(0, 7, (n, 16)).astype(np.float32))   # sums are exact
+    labs = np.empty((C, n), np.int32)
+    for c in range(C):
+        # a third of the nodes in groups of 63, 64, 65 and some hundred members, the others in pairs or alone
+        sizes = rng.choice([63, 64, 65, 128, 300], n) if c % 2 == 0 else rng.integers(1, 3, n)
+        lab = np.repeat(np.arange(n), sizes)[:n]
+        if c % 2 == 0:
+            alone = rng.random(n) < 0.6
+            lab = np.where(alone, np.arange(n), lab)
+        labs[c] = rng.permutation(n)[lab] if c % 3 else lab
+    w = wl.custom(f"{n} nodes {e} edges", wl.ModelSpec(16, 32, 1, "f32"), [g], [labs], seed=3)
+    check_contraction(B, w)[0].close()
+
+
 # A capacity error is found by the launch that would place the results: no workgroup of it, of which many share a candidate, may
 # write past what fits (all of it is refused), and a batch that fits is complete.
 @pytest.mark.parametrize("C", [1, 7, 256, 257])
