@@ -26,7 +26,8 @@ namespace dc {
 namespace {
 
 constexpr int kTinyRow = 4;     // lists up to this length are sorted where they are met, by one thread in registers,
-constexpr int kSmallRow = 16;   // up to this length by one thread once all such are known, up to 64 by a wave
+constexpr int kSmallRow = 16;   // up to this length by one thread once all such are known, up to twice this by one thread where
+                                // there are many, up to 64 by a wave
 constexpr int kBmWaves = 2;     // waves that can always sort neighbour lists of more than 64 entries, through a bitmap each
 constexpr unsigned short kSelf = 0xFFFF;
 
@@ -38,7 +39,7 @@ typedef unsigned long long u64;
 // other.
 //   ids:    u16 NID[N]: labels, then contracted ids | bitmaps, row numbers set aside, then masks (nd = 2: in the ids' place)
 //   first:  MS[N + 1] group ends, int FIRST[N] (then u16 MEM[N], LST), u64 HM / u16 HP: heads and their ranks
-//   later:  OFF[nd N + 1] row ends, u16 RAW[nd E] neighbours by row
+//   later:  OFF[nd N + 1] row ends, u16 RAW[nd E] neighbours by row, then what sort_unique_32 may read
 struct Slab {
   int nid, lst2, longest2, bm, mask, pre, ms, first, hm, hp, off, raw, nd, total;
   int bm_more, bm_waves;          // LDS: bitmaps of the waves behind the first kBmWaves, and how many waves have one
@@ -65,7 +66,7 @@ __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) 
   s.total = o;
   o = x;
   s.off = o;   o = align16(o + os * (rows + 2));
-  s.raw = o;   o = align16(o + 2 * (slots + 2));
+  s.raw = o;   o = align16(o + 2 * (slots + kSmallRow));
   s.bm = nd == 2 ? 0 : o;                  // one after the other: the ids are needed again
   s.lst2 = s.mask = s.bm + bm;
   s.longest2 = s.lst2 + lst;
@@ -104,8 +105,14 @@ __host__ __device__ inline SizeClass size_class_of(int k, int lds_limit) {
 // fixed compare-exchange network (Batcher's odd-even merge sort): no dependent chain
 // through memory, and the same instruction stream for every lane.  Unused places hold
 // kSelf (0xFFFF), which sorts to the end.
-template <int NN>
-__device__ __forceinline__ void sort_network(unsigned (&v)[NN]) {
+template <int NN, typename T>
+__device__ __forceinline__ void compare_exchange(T (&v)[NN], int i, int j) {
+  const T lo = __builtin_elementwise_min(v[i], v[j]), hi = __builtin_elementwise_max(v[i], v[j]);
+  v[i] = lo;
+  v[j] = hi;
+}
+template <int NN, typename T>
+__device__ __forceinline__ void sort_network(T (&v)[NN]) {
 #pragma unroll
   for (int p = 1; p < NN; p <<= 1)
 #pragma unroll
@@ -114,11 +121,7 @@ __device__ __forceinline__ void sort_network(unsigned (&v)[NN]) {
       for (int j = k % p; j + k < NN; j += 2 * k)
 #pragma unroll
         for (int i = 0; i < k; ++i)
-          if (i + j + k < NN && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
-            const unsigned lo = min(v[i + j], v[i + j + k]), hi = max(v[i + j], v[i + j + k]);
-            v[i + j] = lo;
-            v[i + j + k] = hi;
-          }
+          if (i + j + k < NN && (i + j) / (2 * p) == (i + j + k) / (2 * p)) compare_exchange<NN>(v, i + j, i + j + k);
 }
 
 // Sorts a[0..n) ascending, n <= NN; kSelf in the place of a repeat.  The reads are unconditional (a[0] is readable with
@@ -134,6 +137,39 @@ __device__ __forceinline__ void sort_unique_small(u16* a, int n) {
 #pragma unroll
   for (int k = 0; k < NN; ++k)
     if (k < n) a[k] = (k > 0 && v[k] == v[k - 1]) ? kSelf : (u16)v[k];
+}
+
+// Same for 17 to 32 entries, two to a register (a register each leaves the kernel none to work with): entries i and i + 16 are
+// sorted side by side, and what is left is the merge of a bitonic sequence.  The 15 places behind a list's end are readable.
+typedef u16 u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void sort_unique_32(u16* a, int n) {
+  u16x2 w[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) w[k] = u16x2{a[k], a[k + 16]};
+#pragma unroll
+  for (int k = 0; k < 16; ++k) w[k].y = k + 16 < n ? w[k].y : kSelf;
+  sort_network<16>(w);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {              // the upper half downwards
+    const u16 y = w[k].y;
+    w[k].y = w[15 - k].y;
+    w[15 - k].y = y;
+  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const u16x2 s = w[k].yx;
+    w[k] = u16x2{__builtin_elementwise_min(w[k], s).x, __builtin_elementwise_max(w[k], s).y};
+  }
+#pragma unroll
+  for (int d = 8; d >= 1; d >>= 1)
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if ((k & d) == 0) compare_exchange<16>(w, k, k + d);
+#pragma unroll
+  for (int k = 0; k < 32; ++k) {
+    const u16 x = k < 16 ? w[k & 15].x : w[k & 15].y, before = k == 0 ? kSelf : (k <= 16 ? w[(k - 1) & 15].x : w[(k - 1) & 15].y);
+    if (k < n) a[k] = k > 0 && x == before ? kSelf : x;
+  }
 }
 
 // Same for up to 64 entries by a whole wave (lane i holds entry i): an entry's place is the number of smaller ones.
@@ -261,33 +297,51 @@ __device__ __forceinline__ int bits_before(const u64* m, const Pre* pre, int i) 
 // Rows r < rows of `a`, row r ending at end[r], each ascending, kSelf in the place of a repeat.  Rows of up to `at_once`
 // (four or eight) entries are sorted as they are met; the others are set aside, those of up to eight from the front of `lst`, of up to 16 from
 // its back (`room` entries), so that the waves that sort them are full and take one network each.  More than 16
-// entries (`longest`): `longer(r, begin, n)`, called by whole waves, all of them for up to 64 entries, the first `most` for
-// more.  Member lists need no bitmap: one candidate with 50 groups of 100 of its 6.6 k nodes 328 us with two waves for them, 117 us
+// entries: up to 32 from the front of `longest`, more from its back (`long_room` entries).  Those of up to 32 take a network too
+// where there are more of them than waves (one candidate of 2.5 k nodes and 25 k edges: 225 us with a wave each, 96 us; 8192
+// of 64 power-law graphs of up to 20 k nodes 2.01 -> 1.69 ms); the others `longer(r, begin, n)`, called by whole waves, all of
+// them for up to 64 entries, the first `most` for more.  Member lists need no bitmap: one candidate with 50 groups of 100 of its 6.6 k nodes 328 us with two waves for them, 117 us
 // with sixteen; one of 900 nodes with 33 k edges, nearly all lists longer than 64: 488 us with two bitmaps, 186 us with sixteen.
-// cnt[0 .. 2] are 0.
+// cnt[0 .. 3] are 0.
 template <bool kLds, typename Off, typename Longer>
-__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, int at_once, Off* longest, int most, int* cnt, Longer longer) {
+__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, int at_once, Off* longest,
+                                          int long_room, int most, int* cnt, Longer longer) {
   const int t = threadIdx.x, T = blockDim.x, wave = t >> 6, lane = t & 63;
   auto begin = [&](int r) { return r ? (int)end[r - 1] : 0; };
   for (int r = t; r < rows; r += T) {
     const int s = begin(r), n = (int)end[r] - s;
-    if (n > kSmallRow) longest[atomicAdd(&cnt[2], 1)] = (Off)r;
-    else if (n > 2 * kTinyRow) lst[room - 1 - atomicAdd(&cnt[1], 1)] = (Off)r;
-    else if (n > at_once) lst[atomicAdd(&cnt[0], 1)] = (Off)r;
-    else if (n > kTinyRow) sort_unique_small<2 * kTinyRow>(a + s, n);
-    else if (n > 1) sort_unique_small<kTinyRow>(a + s, n);
+    if (n <= kTinyRow) {
+      if (n > 1) sort_unique_small<kTinyRow>(a + s, n);
+    } else if (n <= at_once) {
+      sort_unique_small<2 * kTinyRow>(a + s, n);
+    } else if (n <= 2 * kTinyRow) {
+      lst[atomicAdd(&cnt[0], 1)] = (Off)r;
+    } else if (n <= kSmallRow) {
+      lst[room - 1 - atomicAdd(&cnt[1], 1)] = (Off)r;
+    } else if (n <= 2 * kSmallRow) {
+      longest[atomicAdd(&cnt[2], 1)] = (Off)r;
+    } else {
+      longest[long_room - 1 - atomicAdd(&cnt[3], 1)] = (Off)r;
+    }
   }
   block_sync<kLds>();
-  const int n8 = cnt[0], n16 = cnt[1], nl = cnt[2], w8 = (n8 + 63) >> 6, w16 = (n16 + 63) >> 6;
-  for (int w = wave; w < w8 + w16; w += T >> 6) {
-    if (w < w16) {                               // the longer network first
+  const int all = T >> 6, n8 = cnt[0], n16 = cnt[1], n64 = cnt[2] > all ? 0 : cnt[2], n32 = cnt[2] - n64, nl = n64 + cnt[3];
+  const int w8 = (n8 + 63) >> 6, w16 = (n16 + 63) >> 6, w32 = (n32 + 63) >> 6;
+  for (int w = wave; w < w8 + w16 + w32; w += all) {
+    if (w < w32) {                               // the longer network first
       const int i = w * 64 + lane;
+      if (i < n32) {
+        const int r = longest[i], s = begin(r);
+        sort_unique_32(a + s, (int)end[r] - s);
+      }
+    } else if (w < w32 + w16) {
+      const int i = (w - w32) * 64 + lane;
       if (i < n16) {
         const int r = lst[room - 1 - i], s = begin(r);
         sort_unique_small<kSmallRow>(a + s, (int)end[r] - s);
       }
     } else {
-      const int i = (w - w16) * 64 + lane;
+      const int i = (w - w32 - w16) * 64 + lane;
       if (i < n8) {
         const int r = lst[i], s = begin(r);
         sort_unique_small<2 * kTinyRow>(a + s, (int)end[r] - s);
@@ -295,14 +349,14 @@ __device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off*
     }
   }
   // the last waves first: the first ones have the networks
-  const int all = T >> 6;
+  auto by_wave = [&](int i) { return (int)(i < n64 ? longest[i] : longest[long_room - 1 - (i - n64)]); };
   for (int i = all - 1 - wave; i < nl; i += all) {
-    const int r = longest[i], s = begin(r), n = (int)end[r] - s;
+    const int r = by_wave(i), s = begin(r), n = (int)end[r] - s;
     if (n <= 64 || most >= all) longer(r, s, n);
   }
   if (most < all && wave < most)
-    for (int i = wave; i < nl; i += most) {
-      const int r = longest[i], s = begin(r), n = (int)end[r] - s;
+    for (int i = n64 + wave; i < nl; i += most) {
+      const int r = by_wave(i), s = begin(r), n = (int)end[r] - s;
       if (n > 64) longer(r, s, n);
     }
   block_sync<kLds>();
@@ -329,7 +383,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   Off* LONGEST = LST + N / (kTinyRow + 1) + 1;
   u64* HM = reinterpret_cast<u64*>(base + L.hm);
   u16* HP = reinterpret_cast<u16*>(base + L.hp);
-  int* cnt = wsum + 16;            // three words behind the scans' wave sums
+  int* cnt = wsum + 16;            // four words behind the scans' wave sums
 
   const int* lab = label + coff;
   int* nid_out = new_id_out + coff;
@@ -359,7 +413,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
     }
   }
   for (int i = t; i < (int)(sizeof(Off) * (N + 2)) / 4; i += T) reinterpret_cast<int*>(MS)[i] = 0;
-  if (t < 3) cnt[t] = 0;
+  if (t < 4) cnt[t] = 0;
   if (__syncthreads_or(bad)) {
     if (t == 0) {
       set_error(status, (int)DC_ERR_BAD_PARTITION);
@@ -414,7 +468,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
       if (node(i + j * T) < N) MEM[g[j]] = (u16)node(i + j * T);
   }
   block_sync<kLds>();
-  sort_rows<kLds>(MEM, MS, G, LST, N / (kTinyRow + 1) + 1, kTinyRow, LONGEST, T >> 6, cnt, [&](int g, int s, int n) {
+  sort_rows<kLds>(MEM, MS, G, LST, N / (kTinyRow + 1) + 1, kTinyRow, LONGEST, N / (kSmallRow + 1) + 1, T >> 6, cnt, [&](int g, int s, int n) {
     if (n <= 64) {
       sort_wave(MEM + s, n, lane);
       return;
@@ -448,7 +502,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   int Ec = 0;
   for (int dir = 0; dir < 2; dir += nd) {
     for (int i = t; i < (int)(sizeof(Off) * (rows + 2)) / 4; i += T) reinterpret_cast<int*>(OFF)[i] = 0;
-    if (t < 3) cnt[t] = 0;
+    if (t < 4) cnt[t] = 0;
     block_sync<kLds>();
     // counts the edges between groups, or places them; the others and those past the end are left out
     auto each_edge = [&](auto place) {
@@ -483,7 +537,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
     const int S = exscan(OFF, rows, wsum);
     each_edge(std::true_type{});
     bool clean = false;                                // the wave's bitmap is zero
-    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (first_pass(nd) + 1) + 1, first_pass(nd), LONGEST2, L.bm_waves, cnt, [&](int, int s, int n) {
+    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (first_pass(nd) + 1) + 1, first_pass(nd), LONGEST2, S / (kSmallRow + 1) + 1, L.bm_waves, cnt, [&](int, int s, int n) {
       if (n <= 64) {
         sort_wave(RAW + s, n, lane);
         return;
@@ -557,7 +611,7 @@ template <bool kLds, int kBatch>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) void contract_kernel(
     BaseGraphs bg, int C, const int* cand_graph, const int* cand_off, const int* label, ContractTmp tmp, int* new_id_out,
     int* status, char* gslab, size_t slab_stride, int above, int most, int lds) {
-  __shared__ int wsum[19];
+  __shared__ int wsum[20];
   if (call_failed(status)) return;
   if (kLds) {
     for (int c = blockIdx.x; c < C; c += gridDim.x) {

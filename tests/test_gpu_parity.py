@@ -250,6 +250,26 @@ def test_long_lists_of_the_contraction(B, n, e, C):
     check_contraction(B, w)[0].close()
 
 
+# Lists at the borders of the networks (16, 32 and 64 entries), with and without repeats, as many as there are waves and more:
+# hubs with `size` neighbours each, in one direction and then in the other, and groups of `size` members
+@pytest.mark.parametrize("size", [15, 16, 17, 18, 31, 32, 33, 48, 64, 65])
+@pytest.mark.parametrize("hubs,C", [(1, 1), (16, 1), (17, 1), (70, 1), (5, 300), (70, 300)])
+def test_borders_of_the_list_networks(B, size, hubs, C):
+    rng = np.random.default_rng(size * hubs)
+    n = 2 * hubs + 200
+    pool = np.arange(hubs, hubs + 200)
+    src = np.concatenate([np.full(size, h) for h in range(hubs)] + [rng.choice(pool, size, replace=False) for _ in range(hubs)])
+    dst = np.concatenate([rng.choice(pool, size, replace=False) for _ in range(hubs)] + [np.full(size, hubs + 200 + h) for h in range(hubs)])
+    order = np.argsort(src, kind="stable")
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int32)
+    g = wl.BaseGraph(n, n, rowptr, dst[order].astype(np.int32), rng.integers(0, 7, (n, 16)).astype(np.float32))   # sums are exact
+    pairs = np.arange(n)
+    pairs[pool] -= (pairs[pool] - hubs) % 2                          # the hubs' neighbours in pairs: repeats in their lists
+    labs = np.stack([np.arange(n), pairs, rng.permutation(n)[np.arange(n) // size], rng.permutation(n)[pairs]]).astype(np.int32)
+    w = wl.custom(f"{hubs} hubs of {size}", wl.ModelSpec(16, 32, 1, "f32"), [g], [np.tile(labs, ((C + 3) // 4, 1))], seed=3)
+    check_contraction(B, w)[0].close()
+
+
 # A capacity error is found by the launch that would place the results: no workgroup of it, of which many share a candidate, may
 # write past what fits (all of it is refused), and a batch that fits is complete.
 @pytest.mark.parametrize("C", [1, 7, 256, 257])
