@@ -774,7 +774,7 @@ dc_status dc_set_base_graphs(dc_ctx* ctx, int32_t n_graphs, const int32_t* g_nod
   int slab_wgs = 0;
   if (e == hipSuccess && slab_bytes > 0) {
     slab_stride = al(slab_bytes);
-    slab_wgs = ctx->n_cu * 2;
+    slab_wgs = ctx->n_cu;                // a workgroup takes all of its CU's LDS
     e = hipMalloc(reinterpret_cast<void**>(&slab), slab_stride * slab_wgs);
   }
   // the simulator keeps a module in LDS if it fits kSimLdsBytes; a contracted graph is never

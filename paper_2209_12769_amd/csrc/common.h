@@ -94,14 +94,14 @@ struct ContractLaunch {
   long long max_base_nodes, max_base_edges;
   int* status;
   int* totals;       // [2] contracted nodes, edges of this call
-  char* slab;        // global working sets for graphs that do not fit in LDS
+  char* slab;        // global memory for the working sets that do not fit in LDS, contract_slab_bytes() per workgroup
   size_t slab_stride;
   int slab_wgs;
   int lds_limit;
   int n_cu;
 };
 hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t s);
-// 0 .. kSizeClasses - 1: working sets in LDS, smallest first; kSizeClasses: in contract_slab_bytes() of global memory
+// 0 .. kSizeClasses - 1: working sets in LDS, smallest first; kSizeClasses: partly in contract_slab_bytes() of global memory
 constexpr int kSizeClasses = 3;
 int contract_size_class(int n_nodes, int n_edges, int lds_limit);
 size_t contract_slab_bytes(int n_nodes, int n_edges);
@@ -449,7 +449,8 @@ __device__ __forceinline__ int block_exscan(const int* in, int* out, int n, int*
 
 // The same scan for arrays in global memory: rounds of four neighbouring entries per thread, so that a wave reads
 // and writes whole cache lines (a contiguous run per thread touches a line per entry).  blockDim.x <= 1024.
-__device__ __forceinline__ int block_exscan_lines(const int* in, int* out, int n, int* wsum) {
+template <typename In, typename Out>
+__device__ __forceinline__ int block_exscan_lines(In in, Out out, int n, int* wsum) {
   const int t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6, nw = T >> 6;
   int carry = 0;
   for (int i0 = 0; i0 < n; i0 += 4 * T) {

@@ -9,8 +9,8 @@
 // tensor is the sum of its members' sizes).
 //
 // One workgroup contracts one candidate entirely in LDS (or, for base graphs
-// that do not fit, in a per-workgroup slab of global memory with the same
-// layout).  Results go to per-candidate scratch slots; after a scan of the
+// that do not fit, in what LDS takes of its working arrays and a per-workgroup
+// slab of global memory for the others).  Results go to per-candidate scratch slots; after a scan of the
 // contracted sizes over the batch a second kernel places them block-diagonally
 // and reduces the features.
 //
@@ -34,26 +34,26 @@ constexpr unsigned short kSelf = 0xFFFF;
 typedef unsigned short u16;
 typedef unsigned long long u64;
 
-// Working arrays of a candidate (byte offsets, the same on host and device).  Counters and starts are 16-bit in LDS and
-// 32-bit in global memory (`wide`).  nd = 2: successors and predecessors as one array of 2 G rows, nd = 1: one after the
-// other.
+// Working arrays of a candidate that fits LDS (byte offsets, the same on host and device).  nd = 2: successors and
+// predecessors as one array of 2 G rows, nd = 1: one after the other.
 //   ids:    u16 NID[N]: labels, then contracted ids | bitmaps, row numbers set aside, then masks (nd = 2: in the ids' place)
 //   first:  MS[N + 1] group ends, int FIRST[N] (then u16 MEM[N], LST), u64 HM / u16 HP: heads and their ranks
 //   later:  OFF[nd N + 1] row ends, u16 RAW[nd E] neighbours by row, then what sort_unique_32 may read
 struct Slab {
   int nid, lst2, longest2, bm, mask, pre, ms, first, hm, hp, off, raw, nd, total;
-  int bm_more, bm_waves;          // LDS: bitmaps of the waves behind the first kBmWaves, and how many waves have one
+  int bm_more, bm_waves;          // bitmaps of the waves behind the first kBmWaves, and how many waves have one
 };
 __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 // Lists sorted where they are met: with one direction after the other LDS is short, and fewer numbers are set aside
 __host__ __device__ inline int first_pass(int nd) { return nd == 2 ? kTinyRow : 2 * kTinyRow; }
-__host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) {
-  const int os = wide ? 4 : 2, rows = nd * N, slots = nd * E, w = (slots + 63) / 64 + 1, hw = (N + 63) / 64 + 1;
+__host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd) {
+  constexpr int os = 2;                    // counters and ends of rows are 16-bit
+  const int rows = nd * N, slots = nd * E, w = (slots + 63) / 64 + 1, hw = (N + 63) / 64 + 1;
   Slab s;
   s.nd = nd;
   s.nid = 0;
   const int ids = align16(2 * (N + 2));
-  const int bm = align16(4 * (wide ? 16 : kBmWaves) * ((N + 31) / 32 + 1)), mask = align16(8 * w) + align16(4 * w);
+  const int bm = align16(4 * kBmWaves * ((N + 31) / 32 + 1)), mask = align16(8 * w) + align16(4 * w);
   const int lst = align16(os * (slots / (first_pass(nd) + 1) + 2));
   const int longest = align16(os * (slots / (kSmallRow + 1) + 2));
   const int aux = bm + (mask > lst + longest ? mask : lst + longest);
@@ -73,21 +73,68 @@ __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd, bool wide) 
   s.pre = s.mask + align16(8 * w);
   if (nd == 1) o += aux;
   if (o > s.total) s.total = o;
-  s.bm_more = s.bm + 4 * kBmWaves * ((N + 31) / 32 + 1);
-  s.bm_waves = wide ? 16 : kBmWaves;
-  if (!wide && slots > 65535) s.total = INT_MAX;
+  s.bm_more = s.total;
+  s.bm_waves = kBmWaves;
+  if (slots > 65535) s.total = INT_MAX;
   return s;
 }
 // Both directions at once, in half the phases, where that fits.
 __host__ __device__ inline Slab slab_layout(int N, int E, int lds) {
-  Slab s = slab_layout_nd(N, E, 2, false);
-  if (s.total > lds) s = slab_layout_nd(N, E, 1, false);
+  Slab s = slab_layout_nd(N, E, 2);
+  if (s.total > lds) s = slab_layout_nd(N, E, 1);
   s.bm_more = s.total;                     // the LDS that is left, up to a bitmap for each of sixteen waves
   const int more = (lds - s.total) / (4 * ((N + 31) / 32 + 1));
   s.bm_waves = kBmWaves + (more < 16 - kBmWaves ? more : 16 - kBmWaves);
   return s;
 }
-__host__ __device__ inline int slab_need(int N, int E) { return slab_layout_nd(N, E, 1, false).total; }
+__host__ __device__ inline int slab_need(int N, int E) { return slab_layout_nd(N, E, 1).total; }
+
+// The working arrays of a candidate that does not fit LDS: one direction after the other, counters of 16 bits up to 65535 edges
+// and of 32 beyond.  An array goes to LDS while there is room, in the order in which they are asked for, which is how
+// much their accesses are dependent on each other; sizes that are only known as the candidate is contracted (groups, edges
+// between groups) are asked for as they are.  One candidate of 21 k nodes and 34 k edges 660 us with all arrays in global memory,
+// 213 us; of 65 k nodes and 107 k edges 2.03 and 1.18 ms; 256 of 700 nodes and 66 k edges 4.06 and 0.31 ms.
+template <typename T>
+struct Split {                             // an array whose first `cap` entries (a multiple of sixteen) lie apart from the others
+  T *near, *far;
+  int cap;
+  __device__ __forceinline__ T* of(int i) const { return i < cap ? near : far; }
+  __device__ __forceinline__ T& operator[](int i) const { return of(i)[i]; }
+};
+template <typename T>
+__device__ __forceinline__ T* part_of(const Split<T>& a, int i) { return a.of(i); }
+template <typename T>
+__device__ __forceinline__ T* part_of(T* a, int) { return a; }
+struct Places {
+  char *lds, *lds_end, *slab;
+  __device__ __forceinline__ char* take(size_t bytes, size_t spare = 0) {      // spare: of the LDS, for a later array
+    bytes = (bytes + 15) & ~(size_t)15;
+    char* p;
+    if (bytes + spare <= (size_t)(lds_end - lds)) {
+      p = lds;
+      lds += bytes;
+    } else {
+      p = slab;
+      slab += bytes;
+    }
+    return p;
+  }
+  // n entries, as many of them in LDS as there is room for
+  template <typename T>
+  __device__ __forceinline__ Split<T> take_split(int n) {
+    const int cap = min((n + 15) & ~15, (int)((lds_end - lds) / sizeof(T)) & ~15);
+    Split<T> s{reinterpret_cast<T*>(lds), reinterpret_cast<T*>(slab) - cap, cap};
+    lds += cap * sizeof(T);
+    if (n > cap) slab += ((size_t)(n - cap) * sizeof(T) + 15) & ~(size_t)15;
+    return s;
+  }
+};
+inline size_t slab_bytes(int N, int E) {                  // of Places without any LDS
+  const size_t n = N, e = E, mask = 12 * ((e + 63) / 64 + 1), lst = 2 * (e / (2 * kTinyRow + 1) + e / (kSmallRow + 1) + 4);
+  const size_t relabel = 10 * ((n + 63) / 64 + 1) + 4 * n + 8 + 2 * (n + 2);
+  const size_t lists = 4 * (n + 2) + 2 * (e + kSmallRow) + (mask > lst ? mask : lst) + 64 * ((n + 31) / 32);
+  return 2 * (n + 2) + (relabel > lists ? relabel : lists) + 16 * 16;
+}
 
 // Classes of base graphs by working set (one direction after the other): four, two and one workgroup per CU, which its 16
 // waves of some 110 registers allow; a workgroup takes its share of the LDS.  1024 candidates of 1.6 k nodes: 131 us with
@@ -205,6 +252,14 @@ __device__ __forceinline__ int count_one(u16* a, int i) {
   return (int)((atomicAdd(reinterpret_cast<unsigned*>(a) + (i >> 1), 1u << sh) >> sh) & 0xFFFFu);
 }
 __device__ __forceinline__ int count_one(int* a, int i) { return atomicAdd(&a[i], 1); }
+template <typename T>
+__device__ __forceinline__ int count_one(const Split<T>& a, int i) { return count_one(a.of(i), i); }
+// The 32-bit word w of an array: two counters of 16 bits or one of 32
+template <typename A>
+__device__ __forceinline__ int* word_of(const A& a, int w) {
+  const int i = w * (int)(4 / sizeof(a[0]));
+  return reinterpret_cast<int*>(part_of(a, i) + i);
+}
 
 // The sum over the waves in front of this one, and over all of them (`total`), of what each wave's last lane has in `inc`.
 template <bool kLds>
@@ -218,26 +273,33 @@ __device__ __forceinline__ int wave_offsets(int inc, int& total, int* wsum) {
 }
 
 // Exclusive scan in place; the entry behind the last is 0 before and may be anything after.  Returns the total.
-__device__ __forceinline__ int exscan(u16* a, int n, int* wsum) {
-  unsigned* w = reinterpret_cast<unsigned*>(a);
+template <bool kLds, typename A>
+__device__ __forceinline__ int exscan16(const A& a, int n, int* wsum) {
   const int t = threadIdx.x, T = blockDim.x, nw = (n + 1) >> 1;
   const int K = ((nw + T - 1) / T) | 1;          // an odd run of words per thread: no two lanes of a half wave in one bank
   const int lo = min(t * K, nw), hi = min(lo + K, nw);
   int s = 0;
-  for (int i = lo; i < hi; ++i) s += (w[i] & 0xFFFF) + (w[i] >> 16);
+  for (int i = lo; i < hi; ++i) {
+    const unsigned x = *word_of(a, i);
+    s += (x & 0xFFFF) + (x >> 16);
+  }
   const int inc = wave_incl_scan(s);
   int total;
-  int run = wave_offsets<true>(inc, total, wsum) + inc - s;
+  int run = wave_offsets<kLds>(inc, total, wsum) + inc - s;
   for (int i = lo; i < hi; ++i) {
-    const unsigned x = w[i];
+    const unsigned x = *word_of(a, i);
     const int mid = run + (x & 0xFFFF);
-    w[i] = (unsigned)run | ((unsigned)mid << 16);
+    *word_of(a, i) = (int)((unsigned)run | ((unsigned)mid << 16));
     run = mid + (x >> 16);
   }
-  block_sync<true>();
+  block_sync<kLds>();
   return total;
 }
-__device__ __forceinline__ int exscan(int* a, int n, int* wsum) { return block_exscan_lines(a, a, n, wsum); }
+template <bool kLds, typename A>
+__device__ __forceinline__ int exscan(const A& a, int n, int* wsum) {
+  if constexpr (sizeof(a[0]) == 2) return exscan16<kLds>(a, n, wsum);
+  else return block_exscan_lines(a, a, n, wsum);
+}
 
 // pre[w] = bits set in front of word w of m, pre[nw] = all of them (returned); m[nw] = 0
 template <bool kLds, typename Pre>
@@ -303,8 +365,8 @@ __device__ __forceinline__ int bits_before(const u64* m, const Pre* pre, int i) 
 // them for up to 64 entries, the first `most` for more.  Member lists need no bitmap: one candidate with 50 groups of 100 of its 6.6 k nodes 328 us with two waves for them, 117 us
 // with sixteen; one of 900 nodes with 33 k edges, nearly all lists longer than 64: 488 us with two bitmaps, 186 us with sixteen.
 // cnt[0 .. 3] are 0.
-template <bool kLds, typename Off, typename Longer>
-__device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off* lst, int room, int at_once, Off* longest,
+template <bool kLds, typename End, typename Longer>
+__device__ __forceinline__ void sort_rows(u16* a, const End& end, int rows, u16* lst, int room, int at_once, u16* longest,
                                           int long_room, int most, int* cnt, Longer longer) {
   const int t = threadIdx.x, T = blockDim.x, wave = t >> 6, lane = t & 63;
   auto begin = [&](int r) { return r ? (int)end[r - 1] : 0; };
@@ -315,13 +377,13 @@ __device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off*
     } else if (n <= at_once) {
       sort_unique_small<2 * kTinyRow>(a + s, n);
     } else if (n <= 2 * kTinyRow) {
-      lst[atomicAdd(&cnt[0], 1)] = (Off)r;
+      lst[atomicAdd(&cnt[0], 1)] = (u16)r;
     } else if (n <= kSmallRow) {
-      lst[room - 1 - atomicAdd(&cnt[1], 1)] = (Off)r;
+      lst[room - 1 - atomicAdd(&cnt[1], 1)] = (u16)r;
     } else if (n <= 2 * kSmallRow) {
-      longest[atomicAdd(&cnt[2], 1)] = (Off)r;
+      longest[atomicAdd(&cnt[2], 1)] = (u16)r;
     } else {
-      longest[long_room - 1 - atomicAdd(&cnt[3], 1)] = (Off)r;
+      longest[long_room - 1 - atomicAdd(&cnt[3], 1)] = (u16)r;
     }
   }
   block_sync<kLds>();
@@ -362,27 +424,33 @@ __device__ __forceinline__ void sort_rows(u16* a, const Off* end, int rows, Off*
   block_sync<kLds>();
 }
 
-// One candidate, working arrays in LDS (counters of 16 bits) or in global memory.  Bound by the latency of its phases:
+// One candidate, working arrays in LDS (kLds, where `L` says) or in `places`.  Bound by the latency of its phases:
 // about twenty, a barrier each, of a few dependent LDS accesses.  Edges are dealt to the threads as (source, target) pairs
 // and counted, then placed, by group; those inside a group never enter a row.  What is left of the rows after sorting
 // is found through a mask over their places, so that lists and row starts leave in order, whole lines at a time.
 // One candidate of 6.5 k nodes and 10 k edges in 1.4 k groups: 58 us with a scan per direction over all members and lists
 // gathered member by member, 36 us; 4096 of them 866 -> 584 us, 1000 of 6.5 k groups 224 -> 159 us; 8192 candidates of
-// 64 graphs of up to 19 k nodes, the larger ones in global memory before, 4.9 -> 1.4 ms.
-template <bool kLds, int kBatch>
-__device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b, int N, int E, char* base, const Slab& L,
-                                             int coff, int eslot, const int* label, const ContractTmp& tmp,
+// 64 graphs of up to 19 k nodes, the larger ones in global memory before, 4.9 -> 1.2 ms.
+template <bool kLds, typename Off, int kBatch>
+__device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b, int N, int E, char* base, const Slab& L, Places places,
+                                             int lds_bytes, int coff, int eslot, const int* label, const ContractTmp& tmp,
                                              int* new_id_out, int* status, int* wsum) {
-  typedef typename std::conditional<kLds, u16, int>::type Off;
   const int t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6;
-  u16* NID = reinterpret_cast<u16*>(base + L.nid);
-  Off* MS = reinterpret_cast<Off*>(base + L.ms);
-  int* FIRST = reinterpret_cast<int*>(base + L.first);
+  // the array at byte `at` of the LDS layout, or the next place for `bytes`
+  auto array = [&](int at, size_t bytes, size_t spare = 0) { return kLds ? base + at : places.take(bytes, spare); };
+  u16* NID = reinterpret_cast<u16*>(array(L.nid, 2 * ((size_t)N + 2)));
+  Places behind_ids = places;
+  const int hw = ((N + 63) >> 6) + 1;
+  u64* HM = reinterpret_cast<u64*>(array(L.hm, 8 * (size_t)hw));
+  u16* HP = reinterpret_cast<u16*>(array(L.hp, 2 * (size_t)hw));
+  int* FIRST = reinterpret_cast<int*>(array(L.first, 4 * (size_t)N + 8, 2 * (size_t)N));
+  typedef typename std::conditional<kLds, u16*, Split<u16>>::type Groups;
+  typedef typename std::conditional<kLds, Off*, Split<Off>>::type Ends;
+  Groups MS;
+  if constexpr (kLds) MS = reinterpret_cast<u16*>(base + L.ms);
   u16* MEM = reinterpret_cast<u16*>(FIRST);                       // once the ids are known
-  Off* LST = reinterpret_cast<Off*>(base + L.first + align16(2 * N));
-  Off* LONGEST = LST + N / (kTinyRow + 1) + 1;
-  u64* HM = reinterpret_cast<u64*>(base + L.hm);
-  u16* HP = reinterpret_cast<u16*>(base + L.hp);
+  u16* LST = reinterpret_cast<u16*>(reinterpret_cast<char*>(FIRST) + align16(2 * N));
+  u16* LONGEST = LST + N / (kTinyRow + 1) + 1;
   int* cnt = wsum + 16;            // four words behind the scans' wave sums
 
   const int* lab = label + coff;
@@ -412,7 +480,8 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
       }
     }
   }
-  for (int i = t; i < (int)(sizeof(Off) * (N + 2)) / 4; i += T) reinterpret_cast<int*>(MS)[i] = 0;
+  if constexpr (kLds)
+    for (int i = t; i < (N + 2) / 2; i += T) *word_of(MS, i) = 0;
   if (t < 4) cnt[t] = 0;
   if (__syncthreads_or(bad)) {
     if (t == 0) {
@@ -434,6 +503,11 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   fill_bits<kBatch>(HM, N, [&](int v) { return FIRST[NID[v]] == v; });
   block_sync<kLds>();
   const int G = scan_bits<kLds>(HM, HP, (N + 63) >> 6, wsum);
+  if constexpr (!kLds) {
+    MS = places.take_split<u16>(G + 2);
+    for (int i = t; i < (G + 2) / 2; i += T) *word_of(MS, i) = 0;
+    __syncthreads();
+  }
   for (int i = t; i < spread; i += kBatch * T) {
     int g[kBatch];
 #pragma unroll
@@ -455,7 +529,7 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   block_sync<kLds>();
 
   // ---- member lists: counting sort by group, then ascending inside a group ---------
-  exscan(MS, G, wsum);
+  exscan<kLds>(MS, G, wsum);
   for (int i = t; i < spread; i += kBatch * T) {
     int g[kBatch];
 #pragma unroll
@@ -489,19 +563,31 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
   block_sync<kLds>();
 
   // ---- neighbour lists: successors are rows 0 .. G - 1, predecessors the next G (nd = 2), or one after the other ----------
-  const int nd = L.nd, rows = nd * G;
-  Off* OFF = reinterpret_cast<Off*>(base + L.off);
-  u16* RAW = reinterpret_cast<u16*>(base + L.raw);
-  Off* LST2 = reinterpret_cast<Off*>(base + L.lst2);
-  Off* LONGEST2 = reinterpret_cast<Off*>(base + L.longest2);
-  u64* MASK = reinterpret_cast<u64*>(base + L.mask);
-  int* PRE = reinterpret_cast<int*>(base + L.pre);
-  const int bm_words = (N + 31) / 32 + 1;
-  unsigned* BM = reinterpret_cast<unsigned*>(wave < kBmWaves ? base + L.bm + 4 * wave * bm_words
-                                                             : base + L.bm_more + 4 * (wave - kBmWaves) * bm_words);
+  const int nd = kLds ? L.nd : 1;
+  const int bm_words = kLds ? (N + 31) / 32 + 1 : (G + 31) / 32;
+  if constexpr (!kLds) {
+    // An edge costs 1.8 times as much with the ids in global memory, 3.3 times with the ends of rows there (atomics), so the
+    // ids make room where that brings more than 36 % of the ends into LDS.
+    auto in_lds = [&](const char* from) { return min((long long)G, (long long)((places.lds_end - from) / (long long)sizeof(Off))); };
+    char* const all = places.lds_end - lds_bytes;
+    if (reinterpret_cast<char*>(NID) == all && in_lds(all) - in_lds(behind_ids.lds) > (long long)G * 36 / 100) {
+      u16* moved = reinterpret_cast<u16*>(behind_ids.slab);
+      for (int v = t; v < N; v += T) moved[v] = NID[v];
+      NID = moved;
+      behind_ids.slab += (2 * ((size_t)N + 2) + 15) & ~(size_t)15;
+      behind_ids.lds = all;
+      __syncthreads();
+    }
+  }
   int Ec = 0;
   for (int dir = 0; dir < 2; dir += nd) {
-    for (int i = t; i < (int)(sizeof(Off) * (rows + 2)) / 4; i += T) reinterpret_cast<int*>(OFF)[i] = 0;
+    const int rows = nd * G;
+    places = behind_ids;
+    Ends OFF;
+    if constexpr (kLds) OFF = reinterpret_cast<Off*>(base + L.off);
+    else OFF = places.take_split<Off>(rows + 2);
+    u16* RAW = nullptr;                                // its size is known after the counts
+    for (int i = t; i < (int)(sizeof(Off) * (rows + 2)) / 4; i += T) *word_of(OFF, i) = 0;
     if (t < 4) cnt[t] = 0;
     block_sync<kLds>();
     // counts the edges between groups, or places them; the others and those past the end are left out
@@ -534,10 +620,21 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
       block_sync<kLds>();
     };
     each_edge(std::false_type{});
-    const int S = exscan(OFF, rows, wsum);
+    const int S = exscan<kLds>(OFF, rows, wsum);
+    RAW = reinterpret_cast<u16*>(array(L.raw, 2 * ((size_t)S + kSmallRow)));
     each_edge(std::true_type{});
+    // the rows set aside, and when they are sorted the mask over the places
+    const size_t n_mask = ((size_t)S + 63) / 64 + 1, n_lst = (size_t)S / (first_pass(nd) + 1) + 1, n_longest = (size_t)S / (kSmallRow + 1) + 1;
+    char* aux = array(L.lst2, n_mask * 12 > 2 * (n_lst + n_longest) ? n_mask * 12 : 2 * (n_lst + n_longest));
+    u16* LST2 = reinterpret_cast<u16*>(aux);
+    u16* LONGEST2 = kLds ? reinterpret_cast<u16*>(base + L.longest2) : LST2 + n_lst;
+    u64* MASK = reinterpret_cast<u64*>(kLds ? base + L.mask : aux);
+    int* PRE = reinterpret_cast<int*>(kLds ? base + L.pre : aux + 8 * n_mask);
+    char* bitmaps = array(L.bm, 64 * (size_t)bm_words);
+    unsigned* BM = reinterpret_cast<unsigned*>(kLds && wave >= kBmWaves ? base + L.bm_more + 4 * (wave - kBmWaves) * bm_words
+                                                                       : bitmaps + 4 * wave * bm_words);
     bool clean = false;                                // the wave's bitmap is zero
-    sort_rows<kLds>(RAW, OFF, rows, LST2, S / (first_pass(nd) + 1) + 1, first_pass(nd), LONGEST2, S / (kSmallRow + 1) + 1, L.bm_waves, cnt, [&](int, int s, int n) {
+    sort_rows<kLds>(RAW, OFF, rows, LST2, (int)n_lst, first_pass(nd), LONGEST2, (int)n_longest, kLds ? L.bm_waves : 16, cnt, [&](int, int s, int n) {
       if (n <= 64) {
         sort_wave(RAW + s, n, lane);
         return;
@@ -605,45 +702,49 @@ __device__ __forceinline__ void contract_one(const BaseGraphs& bg, int c, int b,
 
 extern __shared__ __attribute__((aligned(16))) char dc_smem[];
 
-// kLds: the candidates whose working set is larger than `above` and at most `most`; `lds` bytes are there.  kBatch: places that a thread takes
-// together, so that their latencies overlap.
-template <bool kLds, int kBatch>
+// The candidates whose working set is larger than `above` and at most `most`; `lds` bytes are there.  kBatch: places that a
+// thread takes together, so that their latencies overlap.
+template <int kBatch>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) void contract_kernel(
     BaseGraphs bg, int C, const int* cand_graph, const int* cand_off, const int* label, ContractTmp tmp, int* new_id_out,
-    int* status, char* gslab, size_t slab_stride, int above, int most, int lds) {
+    int* status, int above, int most, int lds) {
   __shared__ int wsum[20];
   if (call_failed(status)) return;
-  if (kLds) {
-    for (int c = blockIdx.x; c < C; c += gridDim.x) {
-      const int b = cand_graph[c], coff = cand_off[c], eslot = tmp.tmp_eoff[c];
-      const int N = bg.gno[b + 1] - bg.gno[b];
-      const int E = bg.geo[b + 1] - bg.geo[b];
-      const int need = slab_need(N, E);
-      if (need <= above || need > most) continue;
-      const Slab L = slab_layout(N, E, lds);
-      contract_one<true, kBatch>(bg, c, b, N, E, dc_smem, L, coff, eslot, label, tmp, new_id_out, status, wsum);
-      __syncthreads();
-    }
-  } else {
-    // The candidates that work in global memory are few and long and differ several times in size: they
-    // are handed out one at a time, largest first (the order prep_kernel leaves), through a counter.
-    __shared__ int next_item;
-    const int n_big = tmp.big_meta[0];
-    for (;;) {
-      if (threadIdx.x == 0) next_item = atomicAdd(&tmp.big_meta[1], 1);
-      __syncthreads();
-      const int i = next_item;
-      __syncthreads();                          // everyone has read it before thread 0 writes the next one
-      if (i >= n_big) break;
-      const int c = tmp.big_order[i];
-      const int b = cand_graph[c];
-      const int N = bg.gno[b + 1] - bg.gno[b];
-      const int E = bg.geo[b + 1] - bg.geo[b];
-      const Slab L = slab_layout_nd(N, E, 2, true);
-      contract_one<false, kBatch>(bg, c, b, N, E, gslab + (size_t)blockIdx.x * slab_stride, L, cand_off[c], tmp.tmp_eoff[c], label, tmp,
-                          new_id_out, status, wsum);
-      __syncthreads();
-    }
+  for (int c = blockIdx.x; c < C; c += gridDim.x) {
+    const int b = cand_graph[c], coff = cand_off[c], eslot = tmp.tmp_eoff[c];
+    const int N = bg.gno[b + 1] - bg.gno[b];
+    const int E = bg.geo[b + 1] - bg.geo[b];
+    const int need = slab_need(N, E);
+    if (need <= above || need > most) continue;
+    const Slab L = slab_layout(N, E, lds);
+    contract_one<true, u16, kBatch>(bg, c, b, N, E, dc_smem, L, Places{}, 0, coff, eslot, label, tmp, new_id_out, status, wsum);
+    __syncthreads();
+  }
+}
+
+// The candidates that do not fit LDS are few and long and differ several times in size: they are handed out one at a
+// time, largest first (the order prep_kernel leaves), through a counter.
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) void contract_large_kernel(
+    BaseGraphs bg, const int* cand_graph, const int* cand_off, const int* label, ContractTmp tmp, int* new_id_out, int* status,
+    char* gslab, size_t slab_stride, int lds) {
+  __shared__ int wsum[20];
+  __shared__ int next_item;
+  if (call_failed(status)) return;
+  const int n_big = tmp.big_meta[0];
+  for (;;) {
+    if (threadIdx.x == 0) next_item = atomicAdd(&tmp.big_meta[1], 1);
+    __syncthreads();
+    const int i = next_item;
+    __syncthreads();                          // everyone has read it before thread 0 writes the next one
+    if (i >= n_big) break;
+    const int c = tmp.big_order[i];
+    const int b = cand_graph[c], coff = cand_off[c], eslot = tmp.tmp_eoff[c];
+    const int N = bg.gno[b + 1] - bg.gno[b];
+    const int E = bg.geo[b + 1] - bg.geo[b];
+    const Places places{dc_smem, dc_smem + lds, gslab + (size_t)blockIdx.x * slab_stride};
+    if (E <= 65535) contract_one<false, u16, 8>(bg, c, b, N, E, nullptr, Slab{}, places, lds, coff, eslot, label, tmp, new_id_out, status, wsum);
+    else contract_one<false, int, 8>(bg, c, b, N, E, nullptr, Slab{}, places, lds, coff, eslot, label, tmp, new_id_out, status, wsum);
+    __syncthreads();
   }
 }
 
@@ -903,7 +1004,7 @@ int contract_size_class(int n_nodes, int n_edges, int lds_limit) {
     if (need <= size_class_of(k, lds_limit).most) return k;
   return kSizeClasses;
 }
-size_t contract_slab_bytes(int n_nodes, int n_edges) { return (size_t)slab_layout_nd(n_nodes, n_edges, 2, true).total; }
+size_t contract_slab_bytes(int n_nodes, int n_edges) { return slab_bytes(n_nodes, n_edges); }
 
 __global__ void reset_status_kernel(int* status) { status[0] = 0; }
 
@@ -926,14 +1027,14 @@ hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t 
       // a workgroup that has its CU to itself takes as many waves as there are nodes for
       const int threads = C <= a.n_cu && a.max_graph_nodes > 512 ? 1024 : z.threads;
       const bool small = a.max_graph_nodes <= threads;
-      hipLaunchKernelGGL((small ? contract_kernel<true, 2> : contract_kernel<true, 8>), dim3(C), dim3(threads), z.lds, s, a.bg, C,
-                         a.cand_graph, a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, (char*)nullptr, (size_t)0, above, z.most, z.lds);
+      hipLaunchKernelGGL((small ? contract_kernel<2> : contract_kernel<8>), dim3(C), dim3(threads), z.lds, s, a.bg, C,
+                         a.cand_graph, a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, above, z.most, z.lds);
     }
     above = z.most;
   }
   if ((a.size_classes >> kSizeClasses) & 1) {        // at least one base graph needs the global slab
-    hipLaunchKernelGGL((contract_kernel<false, 8>), dim3(a.slab_wgs), dim3(1024), 0, s, a.bg, C, a.cand_graph,
-                       a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, a.slab, a.slab_stride, 0, 0, 0);
+    hipLaunchKernelGGL(contract_large_kernel, dim3(C < a.slab_wgs ? C : a.slab_wgs), dim3(1024), a.lds_limit, s, a.bg, a.cand_graph,
+                       a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, a.slab, a.slab_stride, a.lds_limit);
   }
   if (prof) prof->end(s);
   if (prof) prof->begin(kFamFinalize, s);
@@ -956,10 +1057,12 @@ hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t 
 }
 
 hipError_t contract_set_lds_limit(int bytes) {
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&contract_kernel<true, 8>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&contract_kernel<true, 2>),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  for (const void* k : {reinterpret_cast<const void*>(&contract_kernel<8>), reinterpret_cast<const void*>(&contract_kernel<2>),
+                        reinterpret_cast<const void*>(&contract_large_kernel)}) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace dc

@@ -270,6 +270,22 @@ def test_borders_of_the_list_networks(B, size, hubs, C):
     check_contraction(B, w)[0].close()
 
 
+# Graphs beyond LDS: counters of 16 and of 32 bits, the ids in LDS and beside it, the rows of a direction in one round and in
+# several, everything down to a single group; more candidates than there are workgroups
+@pytest.mark.parametrize("n,e,C", [(21000, 34000, 5), (33000, 65535, 5), (33000, 65536, 5), (45000, 75000, 5), (65535, 108000, 5), (65535, 0, 3),
+                                   (1, 70000, 2), (40, 70000, 300), (12000, 210000, 5), (65535, 300000, 5)])
+def test_graphs_beyond_lds(B, n, e, C):
+    rng = np.random.default_rng(n + e)
+    src = np.sort(rng.integers(0, max(1, n - 1), e))
+    far = rng.random(e) < 0.1
+    dst = np.minimum(np.where(far, src + 1 + rng.integers(0, n, e), src + 1 + rng.geometric(0.05, e)), n - 1)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int32)
+    g = wl.BaseGraph(n, n, rowptr, dst.astype(np.int32), rng.integers(0, 7, (n, 16)).astype(np.float32))   # sums are exact
+    labs = [np.arange(n), np.cumsum(rng.random(n) < 0.3) % n, rng.permutation(n)[np.arange(n) // 2], rng.integers(0, max(1, n // 90), n), np.full(n, n - 1)]
+    w = wl.custom(f"{n} nodes {e} edges", wl.ModelSpec(16, 32, 1, "f32"), [g], [np.tile(np.stack(labs), ((C + 4) // 5, 1))[:C].astype(np.int32)], seed=3)
+    check_contraction(B, w)[0].close()
+
+
 # A capacity error is found by the launch that would place the results: no workgroup of it, of which many share a candidate, may
 # write past what fits (all of it is refused), and a batch that fits is complete.
 @pytest.mark.parametrize("C", [1, 7, 256, 257])
