@@ -18,6 +18,7 @@
 // member index and every neighbour list is ascending.
 #include <limits.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -48,8 +49,10 @@ __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 __host__ __device__ inline int first_pass(int nd) { return nd == 2 ? kTinyRow : 2 * kTinyRow; }
 __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd) {
   constexpr int os = 2;                    // counters and ends of rows are 16-bit
-  const int rows = nd * N, slots = nd * E, w = (slots + 63) / 64 + 1, hw = (N + 63) / 64 + 1;
   Slab s;
+  s.total = INT_MAX;
+  if ((long long)nd * E > 65535) return s;
+  const int rows = nd * N, slots = nd * E, w = (slots + 63) / 64 + 1, hw = (N + 63) / 64 + 1;
   s.nd = nd;
   s.nid = 0;
   const int ids = align16(2 * (N + 2));
@@ -75,7 +78,6 @@ __host__ __device__ inline Slab slab_layout_nd(int N, int E, int nd) {
   if (o > s.total) s.total = o;
   s.bm_more = s.total;
   s.bm_waves = kBmWaves;
-  if (slots > 65535) s.total = INT_MAX;
   return s;
 }
 // Both directions at once, in half the phases, where that fits.
@@ -722,11 +724,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
   }
 }
 
-// The candidates that do not fit LDS are few and long and differ several times in size: they are handed out one at a
-// time, largest first (the order prep_kernel leaves), through a counter.
+// Where a base graph does not fit LDS, its candidates and those that need a CU's LDS to themselves (all of them where there
+// are few): they are few and long and differ several times in size, and are handed out one at a time, largest
+// first (the order prep_kernel leaves), through a counter.  55 candidates of 55 graphs of 2 to 21 k nodes, four of which do not fit: 417 us in
+// launches of their own after the others, 244 us.
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) void contract_large_kernel(
     BaseGraphs bg, const int* cand_graph, const int* cand_off, const int* label, ContractTmp tmp, int* new_id_out, int* status,
-    char* gslab, size_t slab_stride, int lds) {
+    char* gslab, size_t slab_stride, int most, int lds) {
   __shared__ int wsum[20];
   __shared__ int next_item;
   if (call_failed(status)) return;
@@ -742,7 +746,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     const int N = bg.gno[b + 1] - bg.gno[b];
     const int E = bg.geo[b + 1] - bg.geo[b];
     const Places places{dc_smem, dc_smem + lds, gslab + (size_t)blockIdx.x * slab_stride};
-    if (E <= 65535) contract_one<false, u16, 8>(bg, c, b, N, E, nullptr, Slab{}, places, lds, coff, eslot, label, tmp, new_id_out, status, wsum);
+    if (slab_need(N, E) <= most)
+      contract_one<true, u16, 8>(bg, c, b, N, E, dc_smem, slab_layout(N, E, lds), Places{}, 0, coff, eslot, label, tmp, new_id_out, status, wsum);
+    else if (E <= 65535) contract_one<false, u16, 8>(bg, c, b, N, E, nullptr, Slab{}, places, lds, coff, eslot, label, tmp, new_id_out, status, wsum);
     else contract_one<false, int, 8>(bg, c, b, N, E, nullptr, Slab{}, places, lds, coff, eslot, label, tmp, new_id_out, status, wsum);
     __syncthreads();
   }
@@ -752,7 +758,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
 __global__ __launch_bounds__(1024) void prep_kernel(BaseGraphs bg, int C, const int* cand_graph, const int* cand_off,
                                                      int* tmp_eoff, long long max_base_nodes,
                                                      long long max_base_edges, int* status, int* big_order,
-                                                     int* big_meta, int lds_bytes, int need_max) {
+                                                     int* big_meta, int order_above, int max_weight) {
   __shared__ int wsum[16];
   const int t = threadIdx.x, T = blockDim.x;
   int bad = 0;
@@ -790,20 +796,16 @@ __global__ __launch_bounds__(1024) void prep_kernel(BaseGraphs bg, int C, const 
   }
   const int total = block_exscan(tmp_eoff, tmp_eoff, C, wsum);
   if (t == 0) tmp_eoff[C] = total;
-  if (need_max <= lds_bytes) return;          // every base graph fits
-  // The candidates whose base graph does not fit LDS, in sixteen classes of working-set size, largest class
-  // first (the order inside a class is whatever the atomics give: it decides which workgroup contracts a
+  if (order_above == INT_MAX) return;         // every base graph fits LDS
+  // The candidates whose base graph needs more LDS than `order_above`, in sixteen classes of size (nodes and edges), largest
+  // class first (the order inside a class is whatever the atomics give: it decides which workgroup contracts a
   // candidate, not what is written).
   __shared__ int hist[16], base[16];
   if (t < 16) hist[t] = 0;
   __syncthreads();
-  const int span = need_max > lds_bytes ? need_max - lds_bytes : 1;
   auto size_class = [&](int c) {
-    const int b = cand_graph[c];
-    const int need = slab_need(bg.gno[b + 1] - bg.gno[b], bg.geo[b + 1] - bg.geo[b]);
-    if (need <= lds_bytes) return -1;
-    const long long k = ((long long)need - lds_bytes) * 16 / span;
-    return (int)(k > 15 ? 15 : k);
+    const int b = cand_graph[c], N = bg.gno[b + 1] - bg.gno[b], E = bg.geo[b + 1] - bg.geo[b];
+    return slab_need(N, E) <= order_above ? -1 : (int)(((long long)N + E) * 15 / max_weight);
   };
   for (int c = t; c < C; c += T) {
     const int k = size_class(c);
@@ -1014,27 +1016,33 @@ hipError_t launch_contract(const ContractLaunch& a, Profiler* prof, hipStream_t 
     return hipGetLastError();
   }
   const int C = a.n_cand;
+  // Classes of few candidates need not follow each other: with a CU for every candidate, or every two where there are several
+  // classes, one launch takes all (25 candidates of 25 graphs of 0.2 to 3.2 k nodes: 73 us in two launches, 45 us; 280 of 40
+  // of 0.3 to 6 k 162 and 82 us; 512 of 64 of 0.5 to 3.5 k 122 and 107 us).
+  const bool beyond = (a.size_classes >> kSizeClasses) & 1, several = a.size_classes & (a.size_classes - 1);
+  const bool alone = C <= (several ? 2 : 1) * a.n_cu;
+  const int order_above = !beyond ? INT_MAX : alone ? 0 : size_class_of(kSizeClasses - 2, a.lds_limit).most;
   if (prof) prof->begin(kFamPrep, s);
   hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(1024), 0, s, a.bg, C, a.cand_graph, a.cand_off, a.tmp.tmp_eoff,
-                     a.max_base_nodes, a.max_base_edges, a.status, a.tmp.big_order, a.tmp.big_meta, a.lds_limit,
-                     slab_need(a.max_graph_nodes, a.max_graph_edges));
+                     a.max_base_nodes, a.max_base_edges, a.status, a.tmp.big_order, a.tmp.big_meta, order_above,
+                     (int)std::min<long long>((long long)a.max_graph_nodes + a.max_graph_edges, INT_MAX));
   if (prof) prof->end(s);
   if (prof) prof->begin(kFamContract, s);
+  if (beyond)
+    hipLaunchKernelGGL(contract_large_kernel, dim3(C < a.slab_wgs ? C : a.slab_wgs), dim3(1024), a.lds_limit, s, a.bg, a.cand_graph,
+                       a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, a.slab, a.slab_stride,
+                       size_class_of(kSizeClasses - 1, a.lds_limit).most, a.lds_limit);
   int above = 0;
   for (int k = 0; k < kSizeClasses; ++k) {
     const SizeClass z = size_class_of(k, a.lds_limit);
-    if ((a.size_classes >> k) & 1) {
+    if (alone ? !beyond && (a.size_classes >> k) == 1 : ((a.size_classes >> k) & 1) && !(beyond && k == kSizeClasses - 1)) {
       // a workgroup that has its CU to itself takes as many waves as there are nodes for
       const int threads = C <= a.n_cu && a.max_graph_nodes > 512 ? 1024 : z.threads;
       const bool small = a.max_graph_nodes <= threads;
       hipLaunchKernelGGL((small ? contract_kernel<2> : contract_kernel<8>), dim3(C), dim3(threads), z.lds, s, a.bg, C,
                          a.cand_graph, a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, above, z.most, z.lds);
     }
-    above = z.most;
-  }
-  if ((a.size_classes >> kSizeClasses) & 1) {        // at least one base graph needs the global slab
-    hipLaunchKernelGGL(contract_large_kernel, dim3(C < a.slab_wgs ? C : a.slab_wgs), dim3(1024), a.lds_limit, s, a.bg, a.cand_graph,
-                       a.cand_off, a.group_id, a.tmp, a.out.new_id, a.status, a.slab, a.slab_stride, a.lds_limit);
+    if (!alone) above = z.most;
   }
   if (prof) prof->end(s);
   if (prof) prof->begin(kFamFinalize, s);

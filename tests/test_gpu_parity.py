@@ -286,6 +286,28 @@ def test_graphs_beyond_lds(B, n, e, C):
     check_contraction(B, w)[0].close()
 
 
+# Candidates of several size classes in one launch and in one each (256 CUs), with graphs beyond LDS among them or not
+@pytest.mark.parametrize("C", [5, 256, 257, 512, 513])
+@pytest.mark.parametrize("sizes", [(40, 700), (40, 3500), (40, 700, 3500, 6000), (40, 3500, 6000, 21000), (40, 21000), (6000, 21000)])
+def test_batches_of_several_size_classes(B, C, sizes):
+    graphs, labs = [], []
+    few = [max(1, C // 100)] * (len(sizes) - 1)
+    for k, n in enumerate(sizes):
+        rng = np.random.default_rng(n)
+        src = np.sort(rng.integers(0, n - 1, 2 * n if n < 6000 else n + n // 2))
+        dst = np.minimum(src + 1 + rng.geometric(0.05, src.size), n - 1)
+        rowptr = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int32)
+        graphs.append(wl.BaseGraph(n, n, rowptr, dst.astype(np.int32), rng.integers(0, 7, (n, 16)).astype(np.float32)))   # sums are exact
+        count = C - sum(few) if k == 0 else few[k - 1]
+        if n * count > 2000000:                                     # of the larger graphs only some distinct candidates
+            labs.append(np.tile((np.cumsum(rng.random((4, n)) < 0.4, axis=1) % n).astype(np.int32), ((count + 3) // 4, 1))[:count])
+        else:
+            labs.append((np.cumsum(rng.random((count, n)) < 0.4, axis=1) % n).astype(np.int32))
+    w = wl.custom(f"{C} of {sizes}", wl.ModelSpec(16, 32, 1, "f32"), graphs, labs, seed=3)
+    assert w.n_cand == C
+    check_contraction(B, w)[0].close()
+
+
 # A capacity error is found by the launch that would place the results: no workgroup of it, of which many share a candidate, may
 # write past what fits (all of it is refused), and a batch that fits is complete.
 @pytest.mark.parametrize("C", [1, 7, 256, 257])
