@@ -23,7 +23,8 @@
 // are made in registers.
 //
 // Numbers that are not finite, or so close to the largest fp32 number that their first piece rounds to infinity, give
-// an output that is not finite; a wave that sees one computes its tile again with the fp32 instructions.
+// an output that is not finite; a wave that sees one computes its tile again with the fp32 instructions and takes
+// from there the outputs that are not finite, so that one row's numbers do not change another's bits.
 #include <type_traits>
 
 #include "common.h"
@@ -125,10 +126,9 @@ __device__ __forceinline__ float finite_probe(const f32x16& acc, float t) {
   return t;
 }
 // 32 rows from m0, 32 columns from n0, in fp32 instructions straight from memory
-__device__ __forceinline__ void redo_block(const Operands& o, int m0, int n0) {
+__device__ __forceinline__ f32x16 fp32_block(const Operands& o, int m0, int n0) {
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-  const int row = m0 + l32;
-  const size_t off = (size_t)min(row, o.ntot - 1) * o.d + lh;
+  const size_t off = (size_t)min(m0 + l32, o.ntot - 1) * o.d + lh;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -137,7 +137,15 @@ __device__ __forceinline__ void redo_block(const Operands& o, int m0, int n0) {
     const float* a = (seg == 0 ? o.A0 : (seg == 1 ? o.A1 : o.A2)) + off;
     for (int k = 0; k < o.d; k += 2, w += 2 * (size_t)o.wk) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[0], a[k], acc, 0, 0, 0);
   }
-  store_block(o, acc, row, n0, lh);
+  return acc;
+}
+// The block with the outputs that are not finite from fp32 instructions, the others as they are: rows of other candidates that
+// share its tile keep the bits that they have without it.
+__device__ __forceinline__ f32x16 mended(const f32x16& split, const f32x16& fp32) {
+  f32x16 y;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) y[v] = __builtin_isfinite(split[v]) ? split[v] : fp32[v];
+  return y;
 }
 
 // The six products of a chunk and a block of 32 columns; sections and order are the same in every kernel of this file, so
@@ -238,10 +246,14 @@ __device__ __forceinline__ void update_fewer(const Operands& o, float* sums) {
 #pragma unroll
   for (int u = 0; u < 4; ++u) probe = fmaf(y[u], 0.f, probe);
   if (__syncthreads_or(!(probe == 0.f))) {
-    if (wave == 0) redo_block(o, m0, n0);
-  } else if (row < o.ntot) {
-    store_quad(o, f32x4{y[0], y[1], y[2], y[3]}, row, n0 + 8 * wave + 4 * lh);
+    const f32x16 acc = fp32_block(o, m0, n0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (wave == q && !__builtin_isfinite(y[u])) y[u] = acc[4 * q + u];
   }
+  if (row < o.ntot) store_quad(o, f32x4{y[0], y[1], y[2], y[3]}, row, n0 + 8 * wave + 4 * lh);
 }
 __device__ __forceinline__ void update_few(const Operands& o) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -262,8 +274,8 @@ __device__ __forceinline__ void update_few(const Operands& o) {
       few_step<2>(o, total, acc, s2, s1, c + 2, nk, aoff, wp);
       few_step<3>(o, total, acc, s3, s2, c + 3, nk, aoff, wp);
     }
-    if (__any(!(finite_probe(total, 0.f) == 0.f))) redo_block(o, m0, n0);
-    else store_block(o, total, row, n0, lh);
+    if (__any(!(finite_probe(total, 0.f) == 0.f))) total = mended(total, fp32_block(o, m0, n0));
+    store_block(o, total, row, n0, lh);
   }
 }
 
@@ -396,7 +408,8 @@ __global__ __launch_bounds__(256, 2) void update_split_kernel(Operands o, const 
     for (int j = 0; j < NB; ++j) probe = finite_probe(total[j], probe);
     if (__any(!(probe == 0.f))) {
       if (m0 < o.ntot)
-        for (int j = 0; j < NB; ++j) redo_block(o, m0, n0 + 32 * j);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) store_block(o, mended(total[j], fp32_block(o, m0, n0 + 32 * j)), row, n0 + 32 * j, lh);
     } else {
 #pragma unroll
       for (int j = 0; j < NB; ++j) store_block(o, total[j], row, n0 + 32 * j, lh);
@@ -564,12 +577,13 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradOperands
       const int nb = n0 + wn * 64 + 32 * j;
       if (redo) {                                      // in fp32 instructions, straight from memory
         const float* bn = o.B + min(nb + l32, N - 1);
-        total[i][j] = zero16();
+        f32x16 fp32 = zero16();
         for (int r = r0; r < r1; r += 2) {
           const int rr = min(r + lh, r1 - 1);
           const float x = r + lh < r1 ? am[(size_t)rr * o.d] : 0.f, y = r + lh < r1 ? bn[(size_t)rr * o.ldb] : 0.f;
-          total[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, total[i][j], 0, 0, 0);
+          fp32 = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, fp32, 0, 0, 0);
         }
+        total[i][j] = mended(total[i][j], fp32);
       }
       if (m < M) {
 #pragma unroll
