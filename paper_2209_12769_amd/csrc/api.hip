@@ -93,7 +93,7 @@ struct dc_ctx {
   long long train_t = 0;         // Adam steps taken
   char* train_mem = nullptr;
   TrainPass tb{};                // the buffers of a pass
-  unsigned short* train_WTs = nullptr;   // pieces of the transposed matrices
+  unsigned short* train_WTs = nullptr;   // pieces of the transposed matrices (TrainPass::WTs)
   float* adam_m = nullptr;
   float* adam_v = nullptr;
   Profiler prof;
@@ -572,7 +572,7 @@ static void refresh_pieces(dc_ctx* ctx, hipStream_t s) {
   SplitJobs jobs;
   int n = 0;
   auto add = [&](const float* src, unsigned short* dst, int K, int N, int transposed) {
-    jobs.job[n++] = SplitJob{src, dst, K, N, transposed ? K : N, transposed};
+    jobs.job[n++] = SplitJob{src, dst, K, N, transposed ? K : N, transposed, transposed && c.H < kSplitLeastReverse};
     if (n == kSplitJobsMost) {
       launch_pack_split(jobs, n, s);
       n = 0;

@@ -166,11 +166,17 @@ struct SplitJob {
   const float* src;         // element (k, n) at src[k * ld + n], transposed: src[n * ld + k]
   unsigned short* dst;
   int K, N, ld, transposed;
+  int plain;                // dst receives the matrix in fp32, row by row, instead of its pieces
 };
-// Layers with fewer rows of W keep the fp32 instructions: their sums are as near to 64 bits or nearer (error over the root
-// mean square of the result, ReLU outputs and normal weights: K = 48 0.9e-7 against 1.2e-7, 96 1.3e-7 both, 128 1.44e-7
-// against 1.36e-7), and there is little to gain (K = 48: 4.5 us of matrix time per 100 k rows and 128 columns).
+// Forward products with fewer rows of W keep the fp32 instructions: there is little to gain (K = 48: 4.5 us of matrix time per
+// 100 k rows and 128 columns), and at K = 48 their sums are as near to 64 bits (error over the root mean square of the result,
+// ReLU outputs and normal weights: 0.98e-7 against 0.99e-7; 96 1.40e-7 against 1.04e-7).
 constexpr int kSplitLeast = 128;
+// The same for the data gradients, whose operands have both signs: with K = 32 there is one broken section, so that what the
+// matrix cores drop does not cancel and adds up in the sums over rows (gradient of the first layer's biases, 5280 rows: 2.3e-7 off
+// with pieces, 1.9e-7 with fp32 instructions); from K = 64 on the pieces are nearer (all tensors, 15 to 5280 rows: K = 64 0.74 to 1.04
+// times the error, 128 0.57 to 1.0).
+constexpr int kSplitLeastReverse = 64;
 constexpr int kSplitJobsMost = 32;
 struct SplitJobs {
   SplitJob job[kSplitJobsMost];
@@ -323,7 +329,8 @@ struct TrainPass {
   const float* W;
   const float* b;
   const float* head;
-  const unsigned short* WTs;   // pieces (dense32.hip) of the transposed matrices: layers 1 .. L - 1, then W1, W2
+  const unsigned short* WTs;   // pieces (dense32.hip) of the transposed matrices: layers 1 .. L - 1, then W1, W2; H < kSplitLeastReverse:
+                               // the transposed matrices in fp32 in the same places
   int F, H, L;
   float floor;
   // buffers

@@ -10,10 +10,11 @@
 // bits below it, downwards (towards minus infinity), then add to the accumulator with one rounding to nearest (measured).  Two
 // things follow.  The rows of W are taken in sections of 64, each into an accumulator of its own that is added to the
 // total by the vector ALU: the total is rounded 12 times at K = 768 instead of 288 (384 with the fp32 instructions).  And
-// every other section's W is stored negated and its sum subtracted: what is dropped cancels.  Against 64-bit sums of
+// every other section's W is stored negated and its sum subtracted: what is dropped cancels.  The small partial products
+// of a chunk come first, so that a section's first chunk is rounded once at its full size.  Against 64-bit sums of
 // inputs like those of the layers (ReLU outputs, normal weights), error over the root mean square of the result: K = 48
-// 1.2e-7 (fp32 instructions 0.9e-7), 192 1.4e-7 (1.8e-7), 384 1.4e-7 (2.5e-7), 768 1.5e-7 (3.5e-7); positive operands:
-// 768 0.7e-7 (4.2e-7).
+// 0.99e-7 (fp32 instructions 0.98e-7), 96 1.04e-7 (1.40e-7), 192 1.16e-7 (1.76e-7), 384 1.23e-7 (2.64e-7), 768 1.26e-7 (3.39e-7);
+// positive operands: 48 0.72e-7 (1.03e-7), 768 0.62e-7 (4.04e-7).
 // Measured: 475 k rows, K = 256, 768 columns: 1.62 ms with the fp32 instructions, 1.22 ms; 96 k rows, K = 384, 128 columns
 // 105 -> 70 us; 475 k rows of weight gradients (768 x 256) 1.5 -> 1.05 ms; the reverse pass of those rows in all 9.6 -> 7.5 ms.
 // The matrix cores are busy 40 % of the time at 2.1 GHz.
@@ -63,7 +64,7 @@ constexpr int kSection = 4;          // chunks of 16 rows of W
 __device__ __forceinline__ float section_sign(int chunk) { return (chunk / kSection) & 1 ? -1.f : 1.f; }
 
 // ---- the pieces of W, in the order the products read them ----
-// element (k, n) of the matrix is src[k * ld + n], or src[n * ld + k] (transposed)
+// element (k, n) of the matrix is src[k * ld + n], or src[n * ld + k] (transposed); plain: the matrix itself, row by row
 __global__ __launch_bounds__(256) void pack_split_kernel(SplitJobs jobs) {
   const SplitJob j = jobs.job[blockIdx.y];
   const int units = j.K / 8 * j.N;                       // 8 rows of one column each
@@ -74,6 +75,12 @@ __global__ __launch_bounds__(256) void pack_split_kernel(SplitJobs jobs) {
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       x[u] = j.transposed ? j.src[(size_t)n * j.ld + k8 * 8 + u] : j.src[(size_t)(k8 * 8 + u) * j.ld + n];
+    if (j.plain) {
+      float* out = reinterpret_cast<float*>(j.dst) + (size_t)k8 * 8 * j.N + n;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) out[(size_t)u * j.N] = x[u];
+      continue;
+    }
     const float sign = section_sign(k8 >> 1);
 #pragma unroll
     for (int u = 0; u < 8; ++u) x[u] *= sign;
@@ -190,12 +197,12 @@ __device__ __forceinline__ void few_step(const Operands& o, f32x16& total, f32x1
   few_fetch(o, free, min(c + 3, nk - 1), aoff, wp);
   __builtin_amdgcn_sched_barrier(0);                  // the requests stay ahead of the products
   const Pieces s = split8(cur.a[0], cur.a[1]);
-  acc = product(cur.w[0], s.p[0], kInSection == 0 ? zero16() : acc);
-  acc = product(cur.w[0], s.p[1], acc);
-  acc = product(cur.w[0], s.p[2], acc);
-  acc = product(cur.w[1], s.p[0], acc);
+  acc = product(cur.w[2], s.p[0], kInSection == 0 ? zero16() : acc);
   acc = product(cur.w[1], s.p[1], acc);
-  acc = product(cur.w[2], s.p[0], acc);
+  acc = product(cur.w[1], s.p[0], acc);
+  acc = product(cur.w[0], s.p[2], acc);
+  acc = product(cur.w[0], s.p[1], acc);
+  acc = product(cur.w[0], s.p[0], acc);
   if (kInSection == kSection - 1 || c == nk - 1) add_section(total, acc, section_sign(c));
   __builtin_amdgcn_sched_barrier(0);
 }
@@ -225,12 +232,12 @@ __device__ __forceinline__ void update_fewer(const Operands& o, float* sums) {
         const u32x4 w0 = x[i].w[0], w1 = x[i].w[1], w2 = x[i].w[2];
         few_fetch(o, x[i], min(c + 4 * kSection, nk - 1), aoff, wp);
         if (c < nk) {
-          acc = product(w0, s.p[0], acc);
-          acc = product(w0, s.p[1], acc);
-          acc = product(w0, s.p[2], acc);
-          acc = product(w1, s.p[0], acc);
-          acc = product(w1, s.p[1], acc);
           acc = product(w2, s.p[0], acc);
+          acc = product(w1, s.p[1], acc);
+          acc = product(w1, s.p[0], acc);
+          acc = product(w0, s.p[2], acc);
+          acc = product(w0, s.p[1], acc);
+          acc = product(w0, s.p[0], acc);
         }
       }
 #pragma unroll
@@ -287,17 +294,17 @@ __device__ __forceinline__ void update_few(const Operands& o) {
 // NB = 4 a wave has 48 products of 32 cycles per step and reads 24 KB of W from LDS: 64 of the 128 bytes that LDS
 // gives per cycle, so the matrix cores are the bound.  128 columns are the most that totals and sections leave
 // registers for at two waves per SIMD.
-// Order of a chunk's instructions: the reads of the first piece of W, then two vector instructions (of the splitting)
+// Order of a chunk's instructions: the reads of the third piece of W, then two vector instructions (of the splitting)
 // behind every product, and the next piece's reads behind the first products of a piece.
 template <int NB>
 __device__ __forceinline__ void interleave() {
   __builtin_amdgcn_sched_group_barrier(0x100, NB, 0);                // LDS reads
 #pragma unroll
-  for (int p = 0; p < 3; ++p)
+  for (int p = 2; p >= 0; --p)
 #pragma unroll
     for (int k = 0; k < (3 - p) * NB; ++k) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // product
-      if (p < 2 && k < NB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (p > 0 && k < NB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x002, 8 / NB, 0);        // vector instructions
     }
 }
@@ -376,14 +383,14 @@ __global__ __launch_bounds__(256, 2) void update_split_kernel(Operands o, const 
           const u32x4* wl = &Wl[buf][(i % CH * 6 + lh) * BN + l32];
           u32x4 b[3][NB];
 #pragma unroll
-          for (int p = 0; p < 3; ++p) {
+          for (int p = 2; p >= 0; --p) {
 #pragma unroll
             for (int j = 0; j < NB; ++j) b[p][j] = wl[p * 2 * BN + j * 32];
 #pragma unroll
-            for (int q = 0; q < 3 - p; ++q)
+            for (int q = 2 - p; q >= 0; --q)
 #pragma unroll
               for (int j = 0; j < NB; ++j)
-                acc[j] = product(b[p][j], a.p[q], i % kSection == 0 && p == 0 && q == 0 ? zero16() : acc[j]);
+                acc[j] = product(b[p][j], a.p[q], i % kSection == 0 && p == 2 ? zero16() : acc[j]);
           }
           // the next chunk is split between this one's products
           a = split8(x[(i + 1) % kAhead][0], x[(i + 1) % kAhead][1]);
@@ -425,7 +432,10 @@ __global__ __launch_bounds__(256, 2) void update_split_kernel(Operands o, const 
 // the way the products read them (eight rows of a column = 16 bytes), 16 rows a step, double-buffered; rows are requested two
 // steps ahead.  Sections are 64 rows here; the pieces of B are negated in every other one.  Per step a wave has 24 products
 // (768 cycles) and 110 vector instructions of splitting and adding sections, which other waves' products cover.
-// The column sums of B (bias gradients) ride along in the first row of tiles.  Partial results of the slabs are summed in
+// A slab of few rows is one broken section, so every other slab begins with the negated sign: what is dropped cancels between
+// them (160 rows in ten slabs, gradients of H = 256: 1.9e-7 off without, 1.42e-7 with, 1.45e-7 in fp32 instructions).
+// The column sums of B (bias gradients) ride along in the first row of tiles, in 64 bits: slabs are sixteen rows or more,
+// which sums in fp32 would show (1.45e-7 against 1.17e-7; the pass takes the same time).  Partial results of the slabs are summed in
 // a fixed order afterwards, so a pass is bit-reproducible.
 constexpr int kWgT = 128;
 struct WgradOperands {
@@ -470,8 +480,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradOperands
 #pragma unroll
     for (int k = 0; k < 8; ++k) x.r[k] = *reinterpret_cast<const float2*>(src + (size_t)min(rb + k, r1 - 1) * ld);
   };
-  float bsum[2] = {0.f, 0.f};
-  // kOdd: the chunk belongs to a section whose pieces of B are negated
+  double bsum[2] = {0.0, 0.0};
+  const bool flip = slab & 1;
+  // odd: the chunk belongs to an odd section
   auto stash = [&](RowPairs& x, int c, auto odd) {
     if (!whole || r0 + c * 16 + 16 > r1) {
       const int rb = r0 + c * 16 + 8 * half;
@@ -482,15 +493,15 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradOperands
         x.r[k].y = keep ? x.r[k].y : 0.f;
       }
     }
-    if (m0 == 0) {
+    if (m0 == 0 && is_b) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        bsum[0] += x.r[k].x;
-        bsum[1] += x.r[k].y;
+        bsum[0] += (double)x.r[k].x;
+        bsum[1] += (double)x.r[k].y;
       }
     }
     u32x4* dst = &L[c & 1][half * 2 * kWgT + 2 * cp];
-    if (odd.value && is_b) {
+    if ((odd.value != 0) != flip && is_b) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         x.r[k].x = -x.r[k].x;
@@ -522,22 +533,22 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradOperands
     if (c + 1 < nchunk) stash(x, c + 1, next_odd);
     if (c + 3 < nchunk) fetch(x, c + 3);
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
+    for (int p = 2; p >= 0; --p) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) b[j] = lb[p * 4 * kWgT + 32 * j];
 #pragma unroll
-      for (int q = 0; q < 3 - p; ++q)
+      for (int q = 2 - p; q >= 0; --q)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j)
-            acc[i][j] = product(b[j], a[q][i], in_section.value == 0 && p == 0 && q == 0 ? zero16() : acc[i][j]);
+            acc[i][j] = product(b[j], a[q][i], in_section.value == 0 && p == 2 ? zero16() : acc[i][j]);
     }
     if (in_section.value == kSection - 1 || c == nchunk - 1)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) add_section(total[i][j], acc[i][j], odd.value ? -1.f : 1.f);
+        for (int j = 0; j < 2; ++j) add_section(total[i][j], acc[i][j], (odd.value != 0) != flip ? -1.f : 1.f);
     __syncthreads();
   };
 #define DC_INT(v_) std::integral_constant<int, v_>{}
@@ -597,14 +608,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradOperands
     }
   }
   if (m0 == 0) {                                       // the same for the whole workgroup
-    float* sum = reinterpret_cast<float*>(&L[0][0]);   // [2][128]
+    double* sum = reinterpret_cast<double*>(&L[0][0]); // [2][128]
     __syncthreads();
     if (is_b) {
       sum[half * kWgT + 2 * cp - kWgT] = bsum[0];
       sum[half * kWgT + 2 * cp - kWgT + 1] = bsum[1];
     }
     __syncthreads();
-    if (t < kWgT && n0 + t < N) P[(size_t)M * N + n0 + t] = sum[t] + sum[kWgT + t];
+    if (t < kWgT && n0 + t < N) P[(size_t)M * N + n0 + t] = (float)(sum[t] + sum[kWgT + t]);
   }
 }
 

@@ -294,6 +294,12 @@ void weight_gradient(const TrainPass& t, const float* A0, const float* A1, const
   reduce_slabs(t, S, M * N, N, gW, gb, s);
 }
 
+// out = dZ W^T for W [N, K] with N = g.H, K = H; WTs: its place in TrainPass::WTs
+void data_gradient(const GnnArgs& g, const float* dZ, int H, const float* W, const unsigned short* WTs, float* out, hipStream_t s) {
+  if (H >= kSplitLeastReverse) launch_update_split(g, dZ, nullptr, nullptr, H, 1, W, WTs, nullptr, out, s, true);
+  else launch_dense_update(g, dZ, nullptr, nullptr, H, 1, WTs, nullptr, out, s);
+}
+
 }  // namespace
 
 int train_slabs(int n_cu, int F, int H) {
@@ -389,11 +395,11 @@ hipError_t launch_train_pass(const TrainPass& t, Profiler* prof, hipStream_t s) 
   hipLaunchKernelGGL(dz2_kernel, dim3(grid_for((long long)B * H, t.n_cu)), dim3(256), 0, s, t.Z2, t.dy, w3, H, B,
                      t.dZ2, t.status);
   weight_gradient(t, t.Z1, nullptr, nullptr, H, 1, t.dZ2, H, nB, gW2, gb2, s);
-  launch_update_split(gh, t.dZ2, nullptr, nullptr, H, 1, W2, WTs + 3 * HH, nullptr, t.dZ1, s, true);
+  data_gradient(gh, t.dZ2, H, W2, WTs + 3 * HH, t.dZ1, s);
   hipLaunchKernelGGL(relu_mask_kernel, dim3(grid_for((long long)B * H, t.n_cu)), dim3(256), 0, s, t.dZ1, t.Z1, nB, H,
                      t.status);
   weight_gradient(t, t.R, nullptr, nullptr, H, 1, t.dZ1, H, nB, gW1, gb1, s);
-  launch_update_split(gh, t.dZ1, nullptr, nullptr, H, 1, W1, WTs, nullptr, t.dR, s, true);
+  data_gradient(gh, t.dZ1, H, W1, WTs, t.dR, s);
 
   // ---- graph layers, reverse ----
   float* dZ = t.dZ[0];
@@ -415,7 +421,7 @@ hipError_t launch_train_pass(const TrainPass& t, Profiler* prof, hipStream_t s) 
     end();
     if (l == 0) break;
     begin(kFamTrainDgrad);
-    launch_update_split(g3, dZ, nullptr, nullptr, H, 1, t.W + woff, t.WTs + (size_t)(l - 1) * 9 * HH, nullptr, t.dA, s, true);
+    data_gradient(g3, dZ, H, t.W + woff, t.WTs + (size_t)(l - 1) * 9 * HH, t.dA, s);
     end();
     begin(kFamTrainGatherBack);
     hipLaunchKernelGGL(gather_back_kernel, dim3(grid_for(rows_cap * (H / 4), t.n_cu)), dim3(256), 0, s, t.dA, H,
