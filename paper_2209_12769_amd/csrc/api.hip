@@ -55,7 +55,7 @@ struct dc_ctx {
   int* h_pinned = nullptr;  // [64] pinned host mirror for status / totals
   // weights
   void* W = nullptr;
-  unsigned short* Ws = nullptr;       // fp32: pieces of the layer matrices (dense32.hip)
+  unsigned short* Ws = nullptr;       // fp32: pieces of the layer matrices (dense32.hip), where a product reads any
   unsigned short* Wx = nullptr;       // attention, H = 256, bf16, up to four heads: score columns (gnn_layer256.hip)
   bool have_wx = false;
   float* b = nullptr;
@@ -529,7 +529,7 @@ dc_status dc_create(dc_ctx** out, const dc_config* cfg) {
   if (e == hipSuccess) e = hipMalloc(&ctx->headW, 2 * HH * es);
   if (e == hipSuccess && cfg->aggregator == DC_AGG_ATTENTION && cfg->heads <= 4 && layer256_supported(cfg->H, cfg->H, cfg->dtype == DC_BF16))
     e = hipMalloc(reinterpret_cast<void**>(&ctx->Wx), ((size_t)cfg->F + (size_t)(cfg->L - 1) * cfg->H) * 32 * sizeof(unsigned short));
-  if (e == hipSuccess && cfg->dtype == DC_F32)
+  if (e == hipSuccess && cfg->dtype == DC_F32 && std::max(nseg_of(*cfg) * std::max(cfg->F, cfg->L > 1 ? cfg->H : 0), cfg->H) >= kSplitLeast)
     e = hipMalloc(reinterpret_cast<void**>(&ctx->Ws), (packed_weight_elems(cfg->F, cfg->H, cfg->L, 3) + 2 * HH) * 3 * sizeof(unsigned short));
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -562,7 +562,8 @@ dc_status dc_destroy(dc_ctx* ctx) {
   return DC_OK;
 }
 
-// The pieces (dense32.hip) of the fp32 matrices as they are now: layers, W1 and W2, and for training the transposes of all.
+// The pieces (dense32.hip) of the fp32 matrices as they are now: layers, W1 and W2, where products read them (kSplitLeast), and
+// for training the transposes of all.
 static void refresh_pieces(dc_ctx* ctx, hipStream_t s) {
   const dc_config& c = ctx->cfg;
   if (c.dtype != DC_F32) return;
@@ -583,17 +584,17 @@ static void refresh_pieces(dc_ctx* ctx, hipStream_t s) {
   unsigned short* WTs = ctx->train_WTs;
   for (int l = 0; l < c.L; ++l) {
     const int d = l == 0 ? c.F : c.H;
-    add(W, Ws, nseg * d, c.H, 0);
+    if (Ws && nseg * d >= kSplitLeast) add(W, Ws, nseg * d, c.H, 0);
     if (reverse && l > 0) {
       add(W, WTs, c.H, 3 * c.H, 1);
       WTs += 9 * HH;
     }
     W += (size_t)nseg * d * c.H;
-    Ws += (size_t)3 * nseg * d * c.H;
+    if (Ws) Ws += (size_t)3 * nseg * d * c.H;
   }
   for (int i = 0; i < 2; ++i) {
     const float* Wi = ctx->head + i * (HH + c.H);
-    add(Wi, Ws + i * 3 * HH, c.H, c.H, 0);
+    if (Ws && c.H >= kSplitLeast) add(Wi, Ws + i * 3 * HH, c.H, c.H, 0);
     if (reverse) add(Wi, WTs + i * 3 * HH, c.H, c.H, 1);
   }
   launch_pack_split(jobs, n, s);
