@@ -172,11 +172,10 @@ struct SplitJob {
 // 100 k rows and 128 columns), and at K = 48 their sums are as near to 64 bits (error over the root mean square of the result,
 // ReLU outputs and normal weights: 0.98e-7 against 0.99e-7; 96 1.40e-7 against 1.04e-7).
 constexpr int kSplitLeast = 128;
-// The same for the data gradients, whose operands have both signs: with K = 32 there is one broken section, so that what the
-// matrix cores drop does not cancel and adds up in the sums over rows (gradient of the first layer's biases, 5280 rows: 2.3e-7 off
-// with pieces, 1.9e-7 with fp32 instructions); from K = 64 on the pieces are nearer (all tensors, 15 to 5280 rows: K = 64 0.74 to 1.04
-// times the error, 128 0.57 to 1.0).
-constexpr int kSplitLeastReverse = 64;
+// The same for the data gradients: up to K = 64 there is one section, so that what the matrix cores drop does not cancel and adds
+// up in the sums over rows (gradient of the first layer's biases, 5280 rows, H = 64: 4.2e-8 off with pieces, 3.4e-8 with fp32
+// instructions); from K = 96 on the pieces are nearer (15 to 5280 rows, all tensors: K = 96 0.6 to 1.0 times the error, 256 0.4 to 1.0).
+constexpr int kSplitLeastReverse = 96;
 constexpr int kSplitJobsMost = 32;
 struct SplitJobs {
   SplitJob job[kSplitJobsMost];

@@ -1,8 +1,9 @@
-// Products of fp32 matrices on the bf16 matrix cores, without loss: out = [A0 | A1 | A2] W (+ bias, ReLU), gfx950.
+// Products of fp32 matrices on the bf16 matrix cores: out = [A0 | A1 | A2] W (+ bias, ReLU), gfx950.
 //
-// An fp32 number is exactly the sum of three bf16 numbers (8 + 8 + 8 bits of its significand: x1 = bf16(x),
-// x2 = bf16(x - x1), x3 = x - x1 - x2; both differences are exact).  Of the nine partial products the six with
-// i + j <= 4 are formed; each is exact in fp32, and what is left out (x2 w3, x3 w2, x3 w3) is below 2^-25 of |x w|, less
+// An fp32 number of 2^-110 to 3.39e38 is exactly the sum of three bf16 numbers (8 + 8 + 8 bits of its significand: x1 = bf16(x),
+// x2 = bf16(x - x1), x3 = x - x1 - x2; both differences are exact).  Below, the third piece falls under bf16's smallest number,
+// 2^-133, and what is lost is at most that.  Of the nine partial products the six with i + j <= 4 are formed; each is exact in
+// fp32 unless it lies below fp32's smallest numbers, and what is left out (x2 w3, x3 w2, x3 w3) is below 2^-25 of |x w|, less
 // than the rounding of one fp32 addition.
 // Why: mfma_f32_32x32x2f32 takes 64 cycles for 2 rows of W, mfma_f32_32x32x16_bf16 32 cycles for 16: six of the latter
 // do in 192 cycles what eight of the former do in 512.
@@ -17,7 +18,7 @@
 // positive operands: 48 0.72e-7 (1.03e-7), 768 0.62e-7 (4.04e-7).
 // Measured: 475 k rows, K = 256, 768 columns: 1.62 ms with the fp32 instructions, 1.22 ms; 96 k rows, K = 384, 128 columns
 // 105 -> 70 us; 475 k rows of weight gradients (768 x 256) 1.5 -> 1.05 ms; the reverse pass of those rows in all 9.6 -> 7.5 ms.
-// The matrix cores are busy 40 % of the time at 2.1 GHz.
+// The matrix cores are busy 43 % of the time at 2.1 GHz, 45 % in the weight gradients.
 //
 // The pieces of W are made once per set of weights (pack_split_kernel) and lie as the matrix instruction reads them:
 // unit (chunk c of 16 rows, piece p, half h of the chunk, column n) = 8 consecutive rows = 16 bytes.  The pieces of A
@@ -433,10 +434,14 @@ __global__ __launch_bounds__(256, 2) void update_split_kernel(Operands o, const 
 // steps ahead.  Sections are 64 rows here; the pieces of B are negated in every other one.  Per step a wave has 24 products
 // (768 cycles) and 110 vector instructions of splitting and adding sections, which other waves' products cover.
 // A slab of few rows is one broken section, so every other slab begins with the negated sign: what is dropped cancels between
-// them (160 rows in ten slabs, gradients of H = 256: 1.9e-7 off without, 1.42e-7 with, 1.45e-7 in fp32 instructions).
+// them (160 rows in ten slabs, gradients of H = 256: 1.9e-7 off without, 1.42e-7 with).
 // The column sums of B (bias gradients) ride along in the first row of tiles, in 64 bits: slabs are sixteen rows or more,
 // which sums in fp32 would show (1.45e-7 against 1.17e-7; the pass takes the same time).  Partial results of the slabs are summed in
 // a fixed order afterwards, so a pass is bit-reproducible.
+// Up to kDirectRows rows a slab (a chunk) the rows are dealt as evenly as they go and the products are fp32 instructions on operands
+// straight from memory: most of a chunk would be zeros, and with a row or two per slab a sum in 64 bits over the slabs follows,
+// which six roundings per product would spoil (gradient of W2, 60 samples, H = 128: 5.0e-8 off in pieces, 2.8e-8 now).
+constexpr int kDirectRows = 16;
 constexpr int kWgT = 128;
 struct WgradOperands {
   const float *A0, *A1, *A2, *B;
@@ -459,9 +464,11 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradOperands
   const int tile = item % ntile, slab = item / ntile;
   const int m0 = (tile / tiles_n) * kWgT, n0 = (tile % tiles_n) * kWgT;
   const int rows = nrows[0];
-  const int per = ((rows + o.S - 1) / o.S + 15) & ~15;
+  const int even = (rows + o.S - 1) / o.S;
+  const bool direct = even <= kDirectRows;
+  const int per = direct ? even : (even + 15) & ~15;
   const int r0 = (int)min((long long)slab * per, (long long)rows), r1 = min(r0 + per, rows);
-  const int nchunk = (r1 - r0 + 15) >> 4;
+  const int nchunk = direct ? 0 : (r1 - r0 + 15) >> 4;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
 
@@ -577,6 +584,40 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(const WgradOperands
 #pragma unroll
     for (int j = 0; j < 2; ++j) probe = finite_probe(total[i][j], probe);
   const bool redo = __any(!(probe == 0.f));
+  if (direct && r0 < r1) {
+    // columns of A and B of the wave's two blocks each; pair k of rows, lanes 32-63 the second row of it
+    float x[2][kDirectRows / 2], y[2][kDirectRows / 2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int mc = min(m0 + wm * 64 + 32 * i + l32, M - 1), mseg = mc / o.d;
+      const float* am = (mseg == 0 ? o.A0 : (mseg == 1 ? o.A1 : o.A2)) + (mc - mseg * o.d);
+      const float* bn = o.B + min(n0 + wn * 64 + 32 * i + l32, N - 1);
+#pragma unroll
+      for (int k = 0; k < kDirectRows / 2; ++k) {
+        const int r = r0 + 2 * k + lh, rr = min(r, r1 - 1);
+        const float a = am[(size_t)rr * o.d], b = bn[(size_t)rr * o.ldb];
+        x[i][k] = r < r1 ? a : 0.f;
+        y[i][k] = r < r1 ? b : 0.f;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kDirectRows / 2; ++k)
+      if (2 * k < r1 - r0)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) total[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(y[j][k], x[i][k], total[i][j], 0, 0, 0);
+    if (m0 == 0 && is_b) {
+      RowPairs b;
+      fetch(b, 0);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const bool keep = r0 + 8 * half + k < r1;
+        bsum[0] += keep ? (double)b.r[k].x : 0.0;
+        bsum[1] += keep ? (double)b.r[k].y : 0.0;
+      }
+    }
+  }
   float* P = o.part + (size_t)slab * (size_t)o.part_stride;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
