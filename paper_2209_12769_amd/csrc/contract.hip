@@ -224,10 +224,11 @@ __device__ __forceinline__ void sort_unique_32(u16* a, int n) {
 // Same for up to 64 entries by a whole wave (lane i holds entry i): an entry's place is the number of smaller ones.
 __device__ __forceinline__ void sort_wave(u16* a, int n, int lane) {
   const unsigned x = a[min(lane, n - 1)];
-  const int key = (int)(x << 6) | lane;
+  const int key = lane < n ? (int)(x << 6) | lane : INT_MAX;
   int pos = 0;
-#pragma unroll 4
-  for (int j = 0; j < n; ++j) pos += __builtin_amdgcn_readlane(key, j) < key ? 1 : 0;
+  for (int j = 0; j < n; j += 4)             // four at a time: the compiler does not unroll a loop over lanes by itself
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pos += __builtin_amdgcn_readlane(key, j + u) < key ? 1 : 0;
   if (lane < n) a[pos] = (u16)x;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   const u16 y = a[min(lane, n - 1)], before = a[max(min(lane, n - 1) - 1, 0)];
